@@ -204,7 +204,7 @@ int mhd25_init(const mhd25_mesh_desc* mesh, const mhd25_options* opt, void* stre
   r = r ? r : alloc((void**)&c->snapU, n5 * 8);
   r = r ? r : alloc((void**)&c->red, (K + 1024) * 8 * 8);
   // velocity-OE basis: allocated here so that no allocation happens inside a captured step
-  r = r ? r : alloc((void**)&c->psi, (size_t)K * psi_stride(c->nn) * 8);
+  r = r ? r : alloc((void**)&c->psi, (size_t)K * psi_stride(c->p) * 8);
   r = r ? r : alloc((void**)&c->dfac, (size_t)K * (c->p + 1) * 8);
   r = r ? r : alloc((void**)&c->artr, (size_t)K * (8 * (c->m + 2) + 2) * 8);
   if (!r && hipHostMalloc((void**)&c->h_pinned, 4096) != hipSuccess) r = fail(c, -3, "hipHostMalloc");

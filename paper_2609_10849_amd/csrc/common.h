@@ -48,10 +48,12 @@ struct MagTab {
   double rjw[3][MHD_MAXN][MHD_MAXN];
 };
 
-// velocity-OE basis table per element: nn rows (one per node) of nn values, each row padded to
-// an even length so that every row starts 16-byte aligned
-inline constexpr long psi_row(int nn) { return ((long)nn + 1) & ~1L; }
-inline constexpr long psi_stride(int nn) { return (long)nn * psi_row(nn); }
+// velocity-OE basis table per element of degree p: (p+1)^2 rows (one per node) of the p^2 modes of the
+// shells below the last one (the last shell's part of a field is what the others leave of it), each
+// row padded to an even length so that every row starts 16-byte aligned
+inline constexpr int psi_modes(int p) { return p * p; }
+inline constexpr long psi_row(int p) { return ((long)psi_modes(p) + 1) & ~1L; }
+inline constexpr long psi_stride(int p) { return (long)(p + 1) * (p + 1) * psi_row(p); }
 
 struct MeshP {
   int nx, ny;
@@ -166,7 +168,7 @@ struct mhd25_ctx {
   double *saveU, *saveB, *snapU;
   double* red;  // scratch for small reductions
   double* vjp_scratch;  // allocated on the first magnetic VJP
-  double* psi;          // rho-weighted orthonormal basis values [K][nn][psi_row(nn)] (velocity OE)
+  double* psi;          // rho-weighted orthonormal basis values [K][nn][psi_row(p)] (velocity OE)
   double* dfac;         // velocity-OE damping factors D_l of the current stage [K][p+1]
   double* artr;         // A.R. face traces and wave-speed maxima [K][8(m+2)+2]
   double* h_pinned;

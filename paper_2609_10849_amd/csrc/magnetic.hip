@@ -760,147 +760,158 @@ __host__ __device__ constexpr int mode_b(int k) {
   return r < l ? l : r - l;
 }
 
-// threads per block of the velocity-OE preparation (EB = MHD_PREP_BS / (N+1)^2 elements a block).
-// Measured on the 1024^2, N = 4 workload: 128 threads (5 elements, 98 % of the lanes busy) take
-// 2.67 ms against 3.16 ms for one-wave blocks (2 elements, 78 %), although the Cholesky barriers
-// then span two waves; 256 threads measure the same as 128.
+// threads per block of the velocity-OE preparation (EB = MHD_PREP_BS / (N+1)^2 elements a block)
 #ifndef MHD_PREP_BS
-#define MHD_PREP_BS 128
+#define MHD_PREP_BS 256
 #endif
 template <int P>
 struct VP {
-  static constexpr int NP = P + 1, NN = NP * NP, EB = MHD_PREP_BS / NN > 0 ? MHD_PREP_BS / NN : 1;
+  static constexpr int NP = P + 1, NN = NP * NP, NK = psi_modes(P), EB = MHD_PREP_BS / NN;
 };
 
-// EB elements per block, one thread per node.  The Gram matrix is formed by sum factorisation and packed in
-// LDS; a left-looking Cholesky (thread q owns row q, one barrier per column) overwrites it with L,
-// and row q of Psi = Phi L^{-T} follows by forward substitution with L read from LDS.  Mode indices
-// are compile-time constants in the unrolled loops, and masked arithmetic replaces branches, so
-// the steps stay branch-free; the Cholesky dot products run on two accumulators to halve their FMA
-// chains (a second accumulator in the substitution as well would cost 50 more VGPRs).
+// The basis is needed for the shells 0..p-1 only: they span Q^{p-1}, and since the projection onto all
+// of Q^p is the identity, the last shell's part of a field is the field minus the others' parts.  So
+// the Gram matrix, its Cholesky factor and the table hold NK = p^2 modes instead of (p+1)^2.
+//
+// EB elements per block.  The node weights and the substitution run with one thread per node, the
+// factorisation with one thread per (element, row), packed onto the block's first EB NK threads, so
+// that its lanes are full and the other waves only pass the barriers.  The Gram matrix is formed by
+// sum factorisation and packed in LDS; a left-looking Cholesky (one barrier per column) overwrites it
+// with L, and row q of Psi = Phi L^{-T} follows by forward substitution with L read from LDS.  Mode
+// indices are compile-time constants in the unrolled loops, and masked arithmetic replaces branches;
+// the Cholesky dot products run on two accumulators to halve their FMA chains.
 template <int P>
 __device__ __forceinline__ void vel_prep_body(const double* __restrict__ rho, double* __restrict__ Psi,
                                                  const HydroTab* __restrict__ H, MeshP mp, long blk) {
-  constexpr int NP = P + 1, NN = NP * NP, EB = VP<P>::EB, NL = NN * (NN + 1) / 2;
-  constexpr int NPS = NP * (NP + 1) / 2;  // pairs a <= a'
-  // LDS (16 KB per 128-thread block at N = 4, so LDS is not what limits the blocks per CU):
-  // - sL holds the packed Gram matrix and then L.  Until the Gram rows are written, its first
-  //   EB NN entries hold the node weights sw, whose last reads come before the barrier that
-  //   precedes the Gram rows.
-  // - sH holds the line partials Hm[qj][a][a'] for a <= a', and then the pivot reciprocals srd,
-  //   which are first written after the barrier that follows the last reads of the partials.
-  // - Masked lanes store to one of eight dummy slots.
-  __shared__ double sL[EB][NL], sH[EB][NP][NPS], sV[NP][NP], sdum[8];
-  double(*const sw)[NN] = reinterpret_cast<double(*)[NN]>(&sL[0][0]);
-  double(*const srd)[NN] = reinterpret_cast<double(*)[NN]>(&sH[0][0][0]);
-  const int tid = threadIdx.x, el0 = tid / NN;
-  const bool act0 = el0 < EB && blk * EB + el0 < mp.K;
-  const int el = act0 ? el0 : 0, q = act0 ? tid - el0 * NN : 0;  // idle lanes shadow lane 0
-  const int qi = q % NP, qj = q / NP;
-  const long e = blk * EB + el;
+  using C = VP<P>;
+  constexpr int NP = C::NP, NN = C::NN, NK = C::NK, EB = C::EB;
+  // packed triangle, padded to an odd stride: the elements of a wave read the same entry of their own
+  // triangles from different banks
+  constexpr int NL = (NK * (NK + 1) / 2) | 1;
+  constexpr int NPS = P * (P + 1) / 2;  // pairs a <= a' of the x modes 0..p-1
+  // sH holds the line partials Hm[qj][a][a'] for a <= a', and then the pivot reciprocals srd (first
+  // written after the barrier that follows the last reads of the partials).  Masked lanes store to
+  // one of eight dummy slots.
+  constexpr int NH = NP * NPS > NK ? NP * NPS : NK;
+  __shared__ double sL[EB * NL], sH[EB * NH], sw[EB * NN], sV[NP][NP], sdum[8];
+  const int tid = threadIdx.x;
+  const long e0 = blk * EB;
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;  // elements of this block
   for (int t = tid; t < NP * NP; t += MHD_PREP_BS) sV[t / NP][t % NP] = H->V[t / NP][t % NP];
-  if (act0) sw[el][q] = mp.J * H->w[qi] * H->w[qj] * rho[e * NN + q];
+  if (tid < nel * NN) {
+    const int q = tid % NN;
+    sw[tid] = mp.J * H->w[q % NP] * H->w[q / NP] * rho[e0 * NN + tid];
+  }
   __syncthreads();
   // sum factorisation: Hm[qj][a][a'] = sum_qi W[qj][qi] V[qi][a] V[qi][a'], symmetric in (a, a'),
-  // kept for a <= a' (entry p of a line runs over (0, 0..NP-1), (1, 1..NP-1), ...)
-  if (act0)
-    for (int t = q; t < NP * NPS; t += NN) {
-      const int jj = t / NPS;
-      int p = t - jj * NPS, a = 0;
-      while (p >= NP - a) { p -= NP - a; ++a; }
-      const int a2 = a + p;
-      double s = 0.0;
+  // kept for a <= a' (entry p of a line runs over (0, 0..P-1), (1, 1..P-1), ...)
+  for (int t = tid; t < nel * NP * NPS; t += MHD_PREP_BS) {
+    const int line = t / NPS;  // element * NP + qj
+    int p = t - line * NPS, a = 0;
+    while (p >= P - a) { p -= P - a; ++a; }
+    const int a2 = a + p;
+    double s = 0.0;
 #pragma unroll
-      for (int ii = 0; ii < NP; ++ii) s += sw[el][jj * NP + ii] * sV[ii][a] * sV[ii][a2];
-      sH[el][jj][t - jj * NPS] = s;
-    }
-  __syncthreads();
-  // (LDS stores below go through address selects, not branches: a lane that must not write
-  // targets its own dummy slot)
-  // Gram row q (shell order): G[q][k'] = sum_qj V[qj][b'] (V[qj][b] Hm[qj][a][a']), k' <= q,
-  // packed; row q starts at rq = q (q + 1) / 2, so rq + k <= NL - 1 for every q, k < NN
-  const int rq = q * (q + 1) / 2;
-  {
-    const int ka = mode_a(q), kb = mode_b(q);
-    int hx[NP];  // position of the pair (min(a_q, a'), max(a_q, a')) in a line of sH
-#pragma unroll
-    for (int a2 = 0; a2 < NP; ++a2) {
-      const int lo = ka < a2 ? ka : a2, hi = ka < a2 ? a2 : ka;
-      hx[a2] = lo * NP - lo * (lo - 1) / 2 + (hi - lo);
-    }
-    double w[NP][NP];
-#pragma unroll
-    for (int jj = 0; jj < NP; ++jj)
-#pragma unroll
-      for (int a2 = 0; a2 < NP; ++a2) w[jj][a2] = sV[jj][kb] * sH[el][jj][hx[a2]];
-#pragma unroll
-    for (int k2 = 0; k2 < NN; ++k2) {
-      double s = 0.0;
-#pragma unroll
-      for (int jj = 0; jj < NP; ++jj) s += H->V[jj][mode_b(k2)] * w[jj][mode_a(k2)];  // uniform: scalar loads
-      *((act0 && k2 <= q) ? &sL[el][rq + k2] : &sdum[tid & 7]) = s;
-    }
+    for (int ii = 0; ii < NP; ++ii) s += sw[line * NP + ii] * sV[ii][a] * sV[ii][a2];
+    sH[(line / NP) * NH + (line % NP) * NPS + (t - line * NPS)] = s;
   }
   __syncthreads();
-  // Left-looking Cholesky G = L L^T, one column per step, L written in place over the packed Gram
-  // matrix.  Thread q keeps its row of L in registers.  At step k the threads q > k form
-  // L[q][k] = (G[q][k] - sum_{m<k} L[q][m] L[k][m]) / L[k][k] with row k read from LDS, and the
-  // thread of row k + 1, whose row is then complete up to the diagonal, forms its pivot from its
-  // running G[q][q] - sum_m L[q][m]^2.  srd[k] = 1 / L[k][k].
-  double Lr[NN];
-  double piv = sL[el][rq + q];  // G[q][q]
   {
-    const double rk = rsqrt_refined(piv);  // used by row 0 only
-    *((act0 && q == 0) ? &sL[el][0] : &sdum[tid & 7]) = piv * rk;
-    *((act0 && q == 0) ? &srd[el][0] : &sdum[tid & 7]) = rk;
-  }
-  __syncthreads();
-  // Only the rows q > k read row k; the lanes at or above the diagonal stay masked (measured
-  // faster than letting them read and discard; their Lr[k] = 0 is never used).
+    const bool row = tid < nel * NK;  // this thread owns row q of element el
+    const int el = row ? tid / NK : 0, q = row ? tid - el * NK : 0;  // the others shadow row 0
+    double* const L = sL + el * NL;
+    double* const srd = sH + el * NH;
+    // (LDS stores below go through address selects, not branches: a lane that must not write
+    // targets its own dummy slot)
+    // Gram row q (shell order): G[q][k'] = sum_qj V[qj][b'] (V[qj][b] Hm[qj][a][a']), k' <= q,
+    // packed; row q starts at rq = q (q + 1) / 2
+    const int rq = q * (q + 1) / 2;
+    double Lr[NK];
+    double piv = 1.0;
+    if (tid < EB * NK) {  // whole waves past the rows skip the arithmetic
+      const int l = [&] { int s = 0; while ((s + 1) * (s + 1) <= q) ++s; return s; }();
+      const int ka = q - l * l < l ? q - l * l : l, kb = q - l * l < l ? l : q - l * l - l;
+      int hx[P];  // position of the pair (min(a_q, a'), max(a_q, a')) in a line of sH
 #pragma unroll
-  for (int k = 0; k + 1 < NN; ++k) {
-    Lr[k] = 0.0;
-    if (q > k) {
-      double s0 = sL[el][rq + k], s1 = 0.0;  // G[q][k]
-#pragma unroll
-      for (int m = 0; m < k; ++m) {
-        if (m & 1) s1 -= Lr[m] * sL[el][k * (k + 1) / 2 + m];
-        else s0 -= Lr[m] * sL[el][k * (k + 1) / 2 + m];
+      for (int a2 = 0; a2 < P; ++a2) {
+        const int lo = ka < a2 ? ka : a2, hi = ka < a2 ? a2 : ka;
+        hx[a2] = lo * P - lo * (lo - 1) / 2 + (hi - lo);
       }
-      Lr[k] = (s0 + s1) * srd[el][k];  // L[q][k]
+      double w[NP][P];
+#pragma unroll
+      for (int jj = 0; jj < NP; ++jj)
+#pragma unroll
+        for (int a2 = 0; a2 < P; ++a2) w[jj][a2] = sV[jj][kb] * sH[el * NH + jj * NPS + hx[a2]];
+#pragma unroll
+      for (int k2 = 0; k2 < NK; ++k2) {
+        double s = 0.0;
+#pragma unroll
+        for (int jj = 0; jj < NP; ++jj) s += H->V[jj][mode_b(k2)] * w[jj][mode_a(k2)];  // uniform: scalar loads
+        Lr[k2] = s;              // the row of G, kept in registers
+        if (k2 == q) piv = s;    // G[q][q]
+      }
     }
-    *((act0 && q > k) ? &sL[el][rq + k] : &sdum[tid & 7]) = Lr[k];
-    piv -= Lr[k] * Lr[k];
-    const double rk = rsqrt_refined(piv);  // pivot of row k + 1 (used by that row only)
-    *((act0 && q == k + 1) ? &sL[el][rq + q] : &sdum[tid & 7]) = piv * rk;
-    *((act0 && q == k + 1) ? &srd[el][k + 1] : &sdum[tid & 7]) = rk;
+    __syncthreads();  // every lane has read the partials, whose space the pivot reciprocals take
+    // Left-looking Cholesky G = L L^T, one column per step.  Thread q keeps its row of L in registers.
+    // At step k the threads q > k form L[q][k] = (G[q][k] - sum_{m<k} L[q][m] L[k][m]) / L[k][k] with
+    // row k read from LDS, and the thread of row k + 1, whose row is then complete up to the diagonal,
+    // forms its pivot from its running G[q][q] - sum_m L[q][m]^2.  srd[k] = 1 / L[k][k].
+    {
+      const double rk = rsqrt_refined(piv);  // used by row 0 only
+      *((row && q == 0) ? &L[0] : &sdum[tid & 7]) = piv * rk;
+      *((row && q == 0) ? &srd[0] : &sdum[tid & 7]) = rk;
+    }
     __syncthreads();
+    // Only the rows q > k read row k; the lanes at or above the diagonal stay masked (measured
+    // faster than letting them read and discard).
+#pragma unroll
+    for (int k = 0; k + 1 < NK; ++k) {
+      if (tid < EB * NK) {
+        if (q > k) {
+          double s0 = Lr[k], s1 = 0.0;  // G[q][k]
+#pragma unroll
+          for (int m = 0; m < k; ++m) {
+            if (m & 1) s1 -= Lr[m] * L[k * (k + 1) / 2 + m];
+            else s0 -= Lr[m] * L[k * (k + 1) / 2 + m];
+          }
+          Lr[k] = (s0 + s1) * srd[k];  // L[q][k]
+        }
+        *((row && q > k) ? &L[rq + k] : &sdum[tid & 7]) = Lr[k];
+        piv -= Lr[k] * Lr[k];
+        const double rk = rsqrt_refined(piv);  // pivot of row k + 1 (used by that row only)
+        *((row && q == k + 1) ? &L[rq + q] : &sdum[tid & 7]) = piv * rk;
+        *((row && q == k + 1) ? &srd[k + 1] : &sdum[tid & 7]) = rk;
+      }
+      __syncthreads();
+    }
   }
   // row q of Psi = Phi L^{-T}: forward substitution over the modes with the row in registers
   // (L is read from LDS as broadcasts); Phi[q][k] = V[qi][a_k] V[qj][b_k]
-  double vi[NP], vj[NP];
+  if (tid >= nel * NN) return;
+  const int el = tid / NN, q = tid - el * NN, qi = q % NP, qj = q / NP;
+  const double* const L = sL + el * NL;
+  const double* const srd = sH + el * NH;
+  double vi[P], vj[P];
 #pragma unroll
-  for (int a = 0; a < NP; ++a) { vi[a] = sV[qi][a]; vj[a] = sV[qj][a]; }
+  for (int a = 0; a < P; ++a) { vi[a] = sV[qi][a]; vj[a] = sV[qj][a]; }
   // Right-looking order: once psi[k] is final, L[j][k] psi[k] is subtracted from every later
   // entry j.  Each entry receives the same subtractions in the same order as in the row-by-row
-  // form (so the results are identical), but the 25 entries are independent chains.
-  double psi[NN];
+  // form, but the entries are independent chains.
+  double psi[NK];
 #pragma unroll
-  for (int k = 0; k < NN; ++k) psi[k] = vi[mode_a(k)] * vj[mode_b(k)];
+  for (int k = 0; k < NK; ++k) psi[k] = vi[mode_a(k)] * vj[mode_b(k)];
 #pragma unroll
-  for (int k = 0; k < NN; ++k) {
-    psi[k] *= srd[el][k];
+  for (int k = 0; k < NK; ++k) {
+    psi[k] *= srd[k];
 #pragma unroll
-    for (int j = k + 1; j < NN; ++j) psi[j] -= sL[el][j * (j + 1) / 2 + k] * psi[k];
+    for (int j = k + 1; j < NK; ++j) psi[j] -= L[j * (j + 1) / 2 + k] * psi[k];
   }
   // row q of the element's table, stored directly (rows are 16-byte aligned: psi_row is even)
-  if (act0) {
-    constexpr long PS = psi_stride(NN), RS = psi_row(NN);
-    double2* out = reinterpret_cast<double2*>(Psi + e * PS + q * RS);
+  constexpr long PS = psi_stride(P), RS = psi_row(P);
+  double2* out = reinterpret_cast<double2*>(Psi + (e0 + el) * PS + q * RS);
 #pragma unroll
-    for (int k2 = 0; k2 < NN / 2; ++k2) out[k2] = double2{psi[2 * k2], psi[2 * k2 + 1]};
-    if (NN % 2) Psi[e * PS + q * RS + NN - 1] = psi[NN - 1];
-  }
+  for (int k2 = 0; k2 < NK / 2; ++k2) out[k2] = double2{psi[2 * k2], psi[2 * k2 + 1]};
+  if (NK % 2) out[NK / 2] = double2{psi[NK - 1], 0.0};
 }
 
 template <int P>
@@ -1168,15 +1179,16 @@ __global__ __launch_bounds__(256, (P == 4 && M == 3) ? 6 : 1) void k_vel_sensor_
   vel_sensor_body<P, M, R2>(gl(a.rho), gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.H), gl(a.T), a.mp, a.tau, a.sM, (long)blockIdx.x - boff[r]);
 }
 
-// Velocity-OE map (eq. magnetic-oe-map) with the prepared basis: one thread per node, EB elements
-// per block.  The block's basis tables are copied to LDS first (all of a thread's
-// 16-byte loads are issued before the first store; rows keep an odd LDS stride), so the basis is
-// read from HBM once; then the coefficients c_k = (u_d, psi_k)_rho (thread = mode) and the shell
-// increments at the nodes (thread = node) are formed, and u and e are updated in place.
+// Velocity-OE map (eq. magnetic-oe-map) with the prepared basis, EB elements per block.  The block's
+// basis tables (the p^2 modes of the shells 0..p-1) are copied to LDS first (all of a thread's 16-byte
+// loads are issued before the first store; rows keep an odd LDS stride), so the basis is read from
+// HBM once (5.1 GB at 1024^2, N = 4 in 0.985 ms: 5.2 TB/s, a large copy's rate).  Then the coefficients c_k = (u_d, psi_k)_rho (task = element and mode) and the shells'
+// parts at the nodes (thread = node) are formed, the last shell's part as what the others leave of
+// u, and u and e are updated in place.
 template <int P, int BS>
 struct VPJ {
-  static constexpr int NP = P + 1, NN = NP * NP, EB = BS / NN, NNP = NN | 1;
-  static constexpr long PS = psi_stride(NN), RS = psi_row(NN);
+  static constexpr int NP = P + 1, NN = NP * NP, NK = psi_modes(P), EB = BS / NN, NKP = NK | 1;
+  static constexpr long PS = psi_stride(P), RS = psi_row(P);
 };
 
 template <int P, int BS, bool R2>
@@ -1185,77 +1197,84 @@ __device__ __forceinline__ void vel_proj_body(const double* __restrict__ rho, do
                                                   const double* __restrict__ Dfac, const HydroTab* __restrict__ H,
                                                   MeshP mp, double* __restrict__ Uc, long blk) {
   using C = VPJ<P, BS>;
-  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, NNP = C::NNP;
-  constexpr long PS = C::PS, RS = C::RS;
-  __shared__ double sP[EB * NN * NNP];
-  __shared__ double sv[EB][3][NN], sc[EB][3][NN], sD[EB][NP];
+  constexpr int NP = C::NP, NN = C::NN, NK = C::NK, EB = C::EB, NKP = C::NKP, NU = R2 ? 2 : 3;
+  constexpr int PS = (int)C::PS, RS = (int)C::RS;
+  __shared__ double sP[EB * NN * NKP];
+  __shared__ double sv[EB][NU][NN], sc[EB][NU][NK], sD[EB][NP];
   const int tid = threadIdx.x, el = tid / NN, q = tid - el * NN;
   const int qi = q % NP, qj = q / NP;
   const long e0 = blk * EB, e = e0 + el;
-  const bool act = el < EB && e < mp.K;
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;
+  const bool act = el < nel;
   const long KN = mp.K * NN;
   {
-    constexpr int NL = (int)((EB * PS / 2 + BS - 1) / BS);
-    const long nel = mp.K - e0 < EB ? mp.K - e0 : EB;
-    const long n2 = nel * PS / 2;
+    constexpr int NL = (EB * PS / 2 + BS - 1) / BS;
+    const int n2 = nel * PS / 2;
     const double2* src = reinterpret_cast<const double2*>(Psi + e0 * PS);
     double2 v[NL];
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const long t = tid + (long)BS * k;
+      const int t = tid + BS * k;
       v[k] = t < n2 ? src[t] : double2{0.0, 0.0};
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const long t = tid + (long)BS * k;
+      const int t = tid + BS * k;
       if (t < n2) {
-        // RS even: both values lie in one row (ee, r), columns c0 and c0 + 1 (padding skipped)
-        const int ee = (int)((2 * t) / PS), rem = (int)(2 * t - ee * PS), r = rem / (int)RS, c0 = rem % (int)RS;
-        double* d = sP + ee * NN * NNP + r * NNP;
-        if (c0 < NN) d[c0] = v[k].x;
-        if (c0 + 1 < NN) d[c0 + 1] = v[k].y;
+        // RS even: both values lie in one row (element and node), columns c0 and c0 + 1 (padding skipped)
+        const int r = 2 * t / RS, c0 = 2 * t - r * RS;
+        double* d = sP + r * NKP + c0;
+        d[0] = v[k].x;
+        if (NK % 2 == 0 || c0 + 1 < NK) d[1] = v[k].y;
       }
     }
   }
-  double rq = 0.0;
+  double rq = 0.0, uo[3] = {0.0, 0.0, 0.0};
   if (act) {
     rq = rho[e * NN + q];
     const double wq = mp.J * H->w[qi] * H->w[qj] * rq;
 #pragma unroll
-    for (int d = 0; d < (R2 ? 2 : 3); ++d) sv[el][d][q] = wq * u[d * KN + e * NN + q];  // u_z = 0 in 2D2V
+    for (int d = 0; d < NU; ++d) {  // u_z = 0 in 2D2V
+      uo[d] = u[d * KN + e * NN + q];
+      sv[el][d][q] = wq * uo[d];
+    }
     if (q < NP) sD[el][q] = Dfac[e * NP + q];
   }
   __syncthreads();
-  const double* Pe = sP + (act ? el : 0) * NN * NNP;  // Pe[n * NNP + k] = psi_k(x_n)
-  if (act) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+  for (int t = tid; t < nel * NK; t += BS) {
+    const int ee = t / NK, k = t - ee * NK;
+    const double* Pe = sP + ee * NN * NKP + k;  // Pe[n * NKP] = psi_k(x_n)
+    double s[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int n = 0; n < NN; ++n) {
-      const double pn = Pe[n * NNP + q];
-      s0 += sv[el][0][n] * pn;
-      s1 += sv[el][1][n] * pn;
-      if (!R2) s2 += sv[el][2][n] * pn;
+      const double pn = Pe[n * NKP];
+#pragma unroll
+      for (int d = 0; d < NU; ++d) s[d] += sv[ee][d][n] * pn;
     }
-    sc[el][0][q] = s0; sc[el][1][q] = s1; sc[el][2][q] = s2;
+#pragma unroll
+    for (int d = 0; d < NU; ++d) sc[ee][d][k] = s[d];
   }
   __syncthreads();
   if (!act) return;
   double wl[3][NP];
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int d = 0; d < NU; ++d)
 #pragma unroll
-    for (int l = 0; l < NP; ++l) wl[d][l] = 0.0;
+    for (int l = 0; l < P; ++l) wl[d][l] = 0.0;
+  const double* Pq = sP + tid * NKP;
 #pragma unroll
-  for (int k = 0; k < NN; ++k) {
-    const double pk = Pe[q * NNP + k];
-    wl[0][shell_of(k)] += sc[el][0][k] * pk;
-    wl[1][shell_of(k)] += sc[el][1][k] * pk;
-    if (!R2) wl[2][shell_of(k)] += sc[el][2][k] * pk;
+  for (int k = 0; k < NK; ++k) {
+    const double pk = Pq[k];
+#pragma unroll
+    for (int d = 0; d < NU; ++d) wl[d][shell_of(k)] += sc[el][d][k] * pk;
   }
   double heat = 0.0, un[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-  for (int d = 0; d < (R2 ? 2 : 3); ++d) {
-    double v = wl[d][0];
+  for (int d = 0; d < NU; ++d) {
+    double v = wl[d][0], rest = uo[d] - v;
+#pragma unroll
+    for (int l = 1; l < P; ++l) rest -= wl[d][l];
+    wl[d][P] = rest;
 #pragma unroll
     for (int l = 1; l < NP; ++l) {
       const double Dl = sD[el][l];
@@ -1267,7 +1286,7 @@ __device__ __forceinline__ void vel_proj_body(const double* __restrict__ rho, do
   const long n = e * NN + q;
   if (!Uc) {
 #pragma unroll
-    for (int d = 0; d < (R2 ? 2 : 3); ++d) u[d * KN + n] = un[d];
+    for (int d = 0; d < NU; ++d) u[d * KN + n] = un[d];
     en[n] += heat;
   } else {
     // last stage of a Strang step's magnetic substep: the exchange back to the conserved state

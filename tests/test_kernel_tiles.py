@@ -1,0 +1,82 @@
+"""Each kernel family at the edges of its block and tile sizes, against the oracle: every degree, meshes
+of one element, meshes whose last block is partly filled, and meshes wider than a block's element
+range.  The same checks run on the CPU emulation of the kernel sources (small meshes) and on the GPU.
+
+Tolerance: 1e-12 of the largest value of each output, the parity bar of the other tests (the outputs
+are sums of a few hundred terms of the size of the inputs, each within a few 2^-53 of its value)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2609_10849_amd import workloads as W
+from tests.test_hipemu_kernels import context, emu, omesh, ptr  # noqa: F401
+
+PM = [(1, 0), (2, 2), (3, 2), (4, 3), (4, 4), (5, 5), (6, 5)]
+SMALL = [(1, 1), (3, 2), (5, 4)]
+LARGE = [(67, 31), (9, 130)]
+
+
+def state(p, m, nx, ny, amp=0.3):
+    L, U, Bx, By, Bz = W.random_state(nx, ny, p, m, seed=11 * p + m, domain=(0, 1.5, 0, 1.0), amp=amp)
+    M = omesh(L)
+    return (L, M) + tuple(O.to_primitive(M, U)) + (U, Bx, By, Bz)
+
+
+def close(got, want, what):
+    scale = np.abs(want).max()
+    assert np.abs(got - want).max() <= 1e-12 * scale, "%s: %.2e of %.2e" % (what, np.abs(got - want).max(), scale)
+
+
+def run_emulated(emu, L, opts, name, args):  # noqa: F811
+    """Call an entry point of the emulated library on copies of numpy arguments; returns the copies."""
+    lib, pk = emu
+    h = context(lib, pk, L, opts)
+    args = [np.ascontiguousarray(a).copy() if isinstance(a, np.ndarray) else a for a in args]
+    r = getattr(lib, name)(h, *[ptr(a) if isinstance(a, np.ndarray) else a for a in args])
+    lib.mhd25_destroy(h)
+    assert r == 0, (name, r)
+    return args
+
+
+def run_gpu(L, opts, name, args):
+    from tests._gpu import dev, host
+    import paper_2609_10849_amd as pk
+    S = pk.Solver.from_layout(L, opts)
+    args = [dev(a) if isinstance(a, np.ndarray) else a for a in args]
+    r = getattr(S.lib, name)(S.h, *[ctypes.c_void_p(a.data_ptr()) if hasattr(a, "data_ptr") else a for a in args])
+    out = [host(a) if hasattr(a, "data_ptr") else a for a in args]
+    S.close()
+    assert r == 0, (name, r)
+    return out
+
+
+def check_velocity_oe(run, p, m, nx, ny):
+    import paper_2609_10849_amd as pk
+    L, M, rho, e, u, _, Bx, By, Bz = state(p, m, nx, ny)
+    tau = 0.05  # damping factors well away from 0 and 1
+    ru, re, _ = O.velocity_oe(M, O.Options.full(), tau, rho, u, e, Bx, By, Bz)
+    out = run(L, pk.Options.full(), "mhd25_velocity_oe", [tau, rho, u, e, Bx, By, Bz])
+    close(out[2], ru, "u")
+    close(out[3], re, "e")
+
+
+CHECKS = [check_velocity_oe]
+
+
+@pytest.mark.parametrize("nx,ny", SMALL)
+@pytest.mark.parametrize("p,m", PM)
+@pytest.mark.parametrize("check", CHECKS)
+def test_emulated(emu, check, p, m, nx, ny):  # noqa: F811
+    check(lambda *a: run_emulated(emu, *a), p, m, nx, ny)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", SMALL + LARGE)
+@pytest.mark.parametrize("p,m", PM)
+@pytest.mark.parametrize("check", CHECKS)
+def test_gpu(check, p, m, nx, ny):
+    from tests._gpu import announce
+    announce("%s p=%d m=%d %dx%d" % (check.__name__, p, m, nx, ny))
+    check(run_gpu, p, m, nx, ny)
