@@ -11,6 +11,9 @@
 #define MHD_MAXP 6
 #define MHD_MAXN 8  // max points of any 1D node set used (p+1 <= 7, m+2 <= 8)
 
+// terms of the logarithmic mean's series beyond the constant one
+constexpr int LM_N = 7;
+
 // 1D tables of the DGSEM degree p (section "Nodal bases, quadrature, and mass matrices").
 struct HydroTab {
   double xi[MHD_MAXN], w[MHD_MAXN];    // GLL_p nodes / weights
@@ -20,6 +23,7 @@ struct HydroTab {
   double Dr0[MHD_MAXN][MHD_MAXN];      // r-th derivative of l_i at -1 (reference coordinate)
   double Drp[MHD_MAXN][MHD_MAXN];      // r-th derivative of l_i at +1
   double fr[MHD_MAXN];                 // OE sensor factor (2r+1) 2^r / (2 r!)
+  double lmG[LM_N], lmH[LM_N];         // coefficients of z^1.. of f / atanh f and of atanh f / f, z = f^2
   int ka[MHD_MAXN * MHD_MAXN];         // shell-ordered tensor Legendre basis: k -> (a, b)
   int kb[MHD_MAXN * MHD_MAXN];
   int ksh[MHD_MAXN * MHD_MAXN];        // shell index max(a, b)

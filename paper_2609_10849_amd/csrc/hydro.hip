@@ -1,13 +1,11 @@
 // Hydrodynamic-subflow kernels for gfx950 (section "Hydrodynamic subflow: entropy-stable DGSEM").
 //
-// Mapping: one thread per GLL node, EB = 256 / (p+1)^2 elements per 256-thread block
-// (wave64-friendly for every p).  The flux-differencing volume term uses the skew form
-// sum_{r != i} S_ir F(U_i, U_r) (S = Q - Q^T), which equals eq. euler-volume-residual
-// combined with the boundary corrections of eq. euler-nodal-index; each unordered pair of a
-// line is evaluated once: the p(p+1)/2 pairs of a line are distributed cyclically over its
-// p+1 nodes (node i owns pairs (i, i+d mod (p+1))), the owner accumulates its half in
-// registers and hands the partner's half through LDS.  Reductions are in fixed order, so
-// results are deterministic run to run.
+// The flux-differencing volume term uses the skew form sum_{r != i} S_ir F(U_i, U_r) (S = Q - Q^T),
+// which equals eq. euler-volume-residual combined with the boundary corrections of
+// eq. euler-nodal-index; each unordered pair of a line is evaluated once.  The stage kernel gives a
+// thread a whole grid line of an element, so that the pairs' operands, both halves of each flux
+// and the coefficients stay in registers.  Reductions are in fixed order, so results are
+// deterministic run to run.
 #include <cfloat>
 
 #include "common.h"
@@ -24,27 +22,31 @@ struct Cfg {
   static constexpr int NP = P + 1, NN = NP * NP, EB = BS / NN, NT = EB * NN, ND = NP / 2;
 };
 
+// node values of the EC flux: density, half velocities (normal to the line's direction first) and the
+// ratio rho / p (twice the inverse temperature beta)
 struct Prim {
-  double r, ux, uy, uz, b, lr, lb;
+  double r, hn, ht, hz, b;
 };
 
-__device__ __forceinline__ Prim make_prim(const double U[5], double g) {
-  Prim q;
-  q.r = U[0];
-  const double ir = rcp_refined(U[0]);  // rho > 0 on admissible states
-  q.ux = U[1] * ir; q.uy = U[2] * ir; q.uz = U[3] * ir;
-  const double p = (g - 1.0) * (U[4] - 0.5 * (U[1] * q.ux + U[2] * q.uy + U[3] * q.uz));
-  q.b = 0.5 * q.r * rcp_refined(p);  // p > 0 on admissible states
-  q.lr = log_ec(q.r); q.lb = log_ec(q.b);
-  return q;
+// Logarithmic means (eq. euler-chandrashekar-flux) of near values without logarithms: with
+// f = (aR - aL) / (aR + aL) and z = f^2 the mean is (aL + aR)/2 G(z), G(z) = f / atanh f, and its reciprocal
+// 2/(aL + aR) H(z), H(z) = atanh f / f = 1 + z/3 + z^2/5 + ...; G's coefficients are those of 1/H.  Both
+// series are summed to z^7: for |f| <= LM_NEAR = 0.1 (values within 22 % of each other) the first omitted
+// term is below 2e-18 relative.  The coefficients come from the tables, as scalars (as literals each
+// costs two register moves).
+constexpr double LM_NEAR = 0.1;
+__device__ __forceinline__ double lm_series(const double* __restrict__ c, double z) {
+  double s = c[LM_N - 1];
+#pragma unroll
+  for (int k = LM_N - 2; k >= 0; --k) s = fma(s, z, c[k]);
+  return fma(s, z, 1.0);
 }
 
-// Logarithmic mean (eq. euler-chandrashekar-flux) as a fraction num/den from the node values
-// a and their logarithms l.  Well separated (f^2 >= 1e-4 with f = (aR-aL)/(aR+aL)): (aR-aL)/(lR-lL).
-// Near-equal: with x = (lR-lL)/2 = atanh f, the mean is (aL+aR) tanh(x) / (2x) = (aL+aR) / (2 x coth x),
-// and 2 x coth x = 2 + y/6 - y^2/360 + y^3/15120 - ... in y = (lR-lL)^2 (the Laurent series of coth);
-// there y < 4.1e-4, so the first omitted term is below 1e-19 relative.  The quotient is taken by the
-// caller, which folds the three divisions of the flux into one reciprocal.
+// Logarithmic mean of any two values as a fraction num/den, from the values a and their logarithms l.
+// Well separated (f^2 >= 1e-4): (aR-aL)/(lR-lL).  Near-equal: with x = (lR-lL)/2 = atanh f, the mean is
+// (aL+aR) tanh(x) / (2x) = (aL+aR) / (2 x coth x), and 2 x coth x = 2 + y/6 - y^2/360 + y^3/15120 - ...
+// in y = (lR-lL)^2 (the Laurent series of coth); there y < 4.1e-4, so the first omitted term is below
+// 1e-19 relative.
 struct Frac {
   double n, d;
 };
@@ -56,63 +58,67 @@ __device__ __forceinline__ Frac lmean_frac(double aL, double aR, double lL, doub
   return Frac{near ? s : d, near ? pu : dl};
 }
 
-// Chandrashekar flux (eq. euler-chandrashekar-flux), energy in the form
-// rho_log ud (gk/beta_log - |u|^2avg/2 + |avg u|^2) + p_hat ud with gk = 1/(2(g-1)).  rho_log = nR/dR,
-// 1/beta_log = dB/nB and p_hat = (rhoL+rhoR)/(2(betaL+betaR)) share one reciprocal.
-template <int D>
-__device__ __forceinline__ void ecflux(const Prim& L, const Prim& R, double gk, double F[5]) {
-  const Frac fr = lmean_frac(L.r, R.r, L.lr, R.lr);
-  const Frac fb = lmean_frac(L.b, R.b, L.lb, R.lb);
+// Chandrashekar flux (eq. euler-chandrashekar-flux) in the line's frame (mass, normal, tangential and
+// z momentum, energy) from the logarithmic mean rl of rho, the reciprocal one ibl of b = rho / p and
+// ph = (rhoL + rhoR) / (bL + bR).  With half velocities h = u / 2 the averages are plain sums, and
+// |avg u|^2 - avg |u|^2 / 2 = u_L . u_R / 2 = 2 h_L . h_R; 1 / (2 (g-1) beta_log) = cg / b_log, cg = 1/(g-1).
+__device__ __forceinline__ void ec_form(const Prim& L, const Prim& R, double rl, double ibl, double ph, double cg,
+                                        double F[5]) {
+  const double un = L.hn + R.hn, ut = L.ht + R.ht, uz = L.hz + R.hz;
+  const double f0 = rl * un;
+  const double dot = L.hn * R.hn + L.ht * R.ht + L.hz * R.hz;
+  F[0] = f0;
+  F[1] = fma(f0, un, ph);
+  F[2] = f0 * ut;
+  F[3] = f0 * uz;
+  F[4] = fma(f0, fma(ibl, cg, 2.0 * dot), ph * un);
+}
+// near values: one reciprocal for the three quotients
+__device__ __forceinline__ void ecflux_near(const Prim& L, const Prim& R, double cg, const HydroTab* __restrict__ T,
+                                            double F[5]) {
+  const double sr = L.r + R.r, sb = L.b + R.b;
+  const double is = rcp_refined(sr * sb), isb = sr * is;
+  const double fr = (R.r - L.r) * (sb * is), fb = (R.b - L.b) * isb;
+  const double G = lm_series(T->lmG, fr * fr), H = lm_series(T->lmH, fb * fb);
+  ec_form(L, R, 0.5 * sr * G, (isb + isb) * H, sr * isb, cg, F);
+}
+// any values, with their logarithms (lr of rho, lb of b)
+__device__ __forceinline__ void ecflux_log(const Prim& L, double lrL, double lbL, const Prim& R, double lrR, double lbR,
+                                           double cg, double F[5]) {
+  const Frac fr = lmean_frac(L.r, R.r, lrL, lrR);
+  const Frac fb = lmean_frac(L.b, R.b, lbL, lbR);
   const double sb = L.b + R.b;
   const double t1 = fr.d * fb.n;
   const double Q = rcp_refined(t1 * sb);  // nonzero: each factor is a positive sum or a nonzero difference
-  const double rl = fr.n * fb.n * sb * Q;
-  const double ibl = fb.d * fr.d * sb * Q;
-  const double ph = 0.5 * (L.r + R.r) * t1 * Q;
-  const double uxa = 0.5 * (L.ux + R.ux), uya = 0.5 * (L.uy + R.uy), uza = 0.5 * (L.uz + R.uz);
-  const double u2a = 0.5 * ((L.ux * L.ux + L.uy * L.uy + L.uz * L.uz) + (R.ux * R.ux + R.uy * R.uy + R.uz * R.uz));
-  const double ud = D == 0 ? uxa : uya;
-  const double f0 = rl * ud;
-  F[0] = f0;
-  F[1] = f0 * uxa + (D == 0 ? ph : 0.0);
-  F[2] = f0 * uya + (D == 1 ? ph : 0.0);
-  F[3] = f0 * uza;
-  F[4] = f0 * (ibl * gk - 0.5 * u2a + (uxa * uxa + uya * uya + uza * uza)) + ph * ud;
+  const double sq = sb * Q;
+  ec_form(L, R, fr.n * fb.n * sq, fb.d * fr.d * sq, (L.r + R.r) * (t1 * Q), cg, F);
 }
 
-// physical flux in direction D (0: x, 1: y, a run-time value so that x and y faces can share one
-// code path), with the normal velocity and the sound speed
-__device__ __forceinline__ void physflux(const double U[5], double g, int D, double F[5], double& ud, double& c) {
-  const double ir = rcp_refined(U[0]);
-  const double ux = U[1] * ir, uy = U[2] * ir, uz = U[3] * ir;
-  const double p = (g - 1.0) * (U[4] - 0.5 * (U[1] * ux + U[2] * uy + U[3] * uz));
-  ud = D == 0 ? ux : uy;
-  F[0] = D == 0 ? U[1] : U[2];
-  F[1] = U[1] * ud + (D == 0 ? p : 0.0);
-  F[2] = U[2] * ud + (D == 1 ? p : 0.0);
-  F[3] = U[3] * ud;
-  F[4] = (U[4] + p) * ud;
-  c = sqrt(g * p * ir);
+// pressure of a conserved state whose reciprocal density is ir
+__device__ __forceinline__ double pressure_of(const double U[5], double ir, double g) {
+  return (g - 1.0) * (U[4] - 0.5 * ir * (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]));
 }
 
-// numerical interface flux in direction D between the element's own face value uo and the
-// neighbour's un: LLF (eq. euler-lf-flux) or, for tests, the EC flux.  Both are symmetric in their
-// two states except for the LLF jump U_R - U_L = sgn (un - uo) (sgn = +1 when the neighbour is the
-// plus side), so no left/right copies are formed.
-__device__ __forceinline__ void face_flux(const double uo[5], const double un[5], double sgn, double g, double gk,
-                                          int D, int iface, double F[5]) {
-  if (iface == 1) {
-    Prim a = make_prim(uo, g), b = make_prim(un, g);
-    if (D == 0) ecflux<0>(a, b, gk, F);
-    else ecflux<1>(a, b, gk, F);
-    return;
-  }
-  double Fo[5], Fn[5], udo, co, udn, cn;
-  physflux(uo, g, D, Fo, udo, co);
-  physflux(un, g, D, Fn, udn, cn);
-  const double lam = fmax(fabs(udo) + co, fabs(udn) + cn);
-#pragma unroll
-  for (int c = 0; c < 5; ++c) F[c] = 0.5 * (Fo[c] + Fn[c]) - 0.5 * lam * (sgn * (un[c] - uo[c]));
+// One side of an LLF interface flux (eq. euler-lf-flux) in the line's frame from density, half
+// velocities and pressure: conserved values, physical flux and wave speed |u_n| + c.
+struct FaceSide {
+  double U[5], F[5], s;
+};
+__device__ __forceinline__ FaceSide face_side(double r, double hn, double ht, double hz, double p, double g,
+                                              double cg) {
+  FaceSide a;
+  const double un = hn + hn, x = g * p * rcp_refined(r);  // squared sound speed, positive
+  const double y = rsqrt_refined(x), c0 = x * y;
+  const double c = fma(0.5 * y, fma(-c0, c0, x), c0);  // sqrt(x)
+  a.U[0] = r; a.U[1] = r * un; a.U[2] = r * (ht + ht); a.U[3] = r * (hz + hz);
+  a.U[4] = fma(cg, p, 2.0 * r * (hn * hn + ht * ht + hz * hz));
+  a.F[0] = a.U[1];
+  a.F[1] = fma(a.U[1], un, p);
+  a.F[2] = a.U[2] * un;
+  a.F[3] = a.U[3] * un;
+  a.F[4] = (a.U[4] + p) * un;
+  a.s = fabs(un) + c;
+  return a;
 }
 
 // Face f = 2 D + side of element (ex, ey) (D 0: the x-normal faces, D 1: the y-normal faces; side 0
@@ -126,113 +132,6 @@ __device__ __forceinline__ void face_match(const MeshP& mp, int ex, int ey, int 
   qo = D == 0 ? line * NP + pos : pos * NP + line;
   qn = D == 0 ? line * NP + (P - pos) : (P - pos) * NP + line;
   en = D == 0 ? ey * mp.nx + wrap32(ex + (side ? 1 : -1), mp.nx) : wrap32(ey + (side ? 1 : -1), mp.ny) * mp.nx + ex;
-}
-
-// One direction of the volume part of L_E for the thread's node: owned pairs, incoming halves.
-template <int P, int D, int BS>
-__device__ __forceinline__ void volume_dir(const Prim& me, double acc[5], bool act, int el, int i, int j,
-                                           double (*sp)[Cfg<P, BS>::EB * Cfg<P, BS>::NN], double* sb,
-                                           const double* tS, const MeshP& mp) {
-  using C = Cfg<P, BS>;
-  constexpr int NP = C::NP, NN = C::NN, ND = C::ND;
-  const int pos = D == 0 ? i : j, line = D == 0 ? j : i;
-  const double sc = 2.0 * (D == 0 ? mp.rhx : mp.rhy);
-  const double gk = mp.gk;
-  // sb layout: [el][line][owner pos][dslot][5]
-  double* sbl = sb + ((long)(el * NP + line) * NP) * ND * 5;
-  if (act) {
-#pragma unroll
-    for (int d = 1; d <= ND; ++d) {
-      if (2 * d == NP && pos >= NP / 2) continue;
-      int r = pos + d;
-      if (r >= NP) r -= NP;
-      const int nr = el * NN + (D == 0 ? line * NP + r : r * NP + line);
-      Prim o;
-      o.r = sp[0][nr]; o.ux = sp[1][nr]; o.uy = sp[2][nr]; o.uz = sp[3][nr];
-      o.b = sp[4][nr]; o.lr = sp[5][nr]; o.lb = sp[6][nr];
-      double F[5];
-      ecflux<D>(me, o, gk, F);
-      const double ci = -sc * tS[pos * NP + r], cr = -sc * tS[r * NP + pos];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        acc[c] += ci * F[c];
-        sbl[(pos * ND + (d - 1)) * 5 + c] = cr * F[c];
-      }
-    }
-  }
-  __syncthreads();
-  if (act) {
-#pragma unroll
-    for (int d = 1; d <= ND; ++d) {
-      int o = pos - d;
-      if (o < 0) o += NP;
-      if (2 * d == NP && o >= NP / 2) continue;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] += sbl[(o * ND + (d - 1)) * 5 + c];
-    }
-  }
-  __syncthreads();
-}
-
-// Surface part of L_E: the element's 4 (p+1) interface fluxes as tasks f = (direction, side, line)
-// with the direction a run-time value (x and y faces share one code path, so a wave runs the flux
-// once), stored in sf = scr + el * 20 (p+1); then added at the face nodes.  The minus side of a face
-// is the neighbour for side 0.  Every thread of the block must call this.
-template <int P, int BS>
-__device__ __forceinline__ void surface_terms(double acc[5], bool act, int el, int q, int i, int j, long e,
-                                              const double* __restrict__ Us, long KN, double* scr,
-                                              double (*sp)[Cfg<P, BS>::EB * Cfg<P, BS>::NN],
-                                              const HydroTab* __restrict__ T, const MeshP& mp, int iface) {
-  using C = Cfg<P, BS>;
-  constexpr int NP = C::NP, NN = C::NN;
-  double* sf = scr + el * 20 * NP;  // [f][5]
-  const int tid = el * NN + q;
-  if (act) {
-    // the volume accumulators wait in the (now free) primitive rows, to keep registers for the fluxes
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sp[c][tid] = acc[c];
-    int ex, ey;
-    elem_xy32(mp, (int)e, ex, ey);
-    for (int f = q; f < 4 * NP; f += NN) {
-      const int D = f / (2 * NP), side = (f / NP) & 1, line = f % NP;
-      int en, qo, qn;
-      face_match<P>(mp, ex, ey, D, side, line, en, qo, qn);
-      const unsigned oo = ((unsigned)e * NN + qo) * 8u, on = ((unsigned)en * NN + qn) * 8u;
-      double uo[5], un[5], F[5];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        const auto r = node_rsrc(Us + c * KN, KN);
-        uo[c] = bld(r, oo); un[c] = bld(r, on);
-      }
-      face_flux(uo, un, side ? 1.0 : -1.0, mp.gamma, mp.gk, D, iface, F);
-      const double sc = 2.0 * (D == 0 ? mp.rhx : mp.rhy);
-      const double s = side ? -(sc * rcp_refined(T->w[P])) : sc * rcp_refined(T->w[0]);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sf[f * 5 + c] = s * F[c];
-    }
-  }
-  __syncthreads();
-  if (act) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) acc[c] = sp[c][tid];
-    // face f = (D * 2 + side) * NP + line; x faces carry line j, y faces line i
-    if (i == 0) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] += sf[(0 * NP + j) * 5 + c];
-    }
-    if (i == P) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] += sf[(1 * NP + j) * 5 + c];
-    }
-    if (j == 0) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] += sf[(2 * NP + i) * 5 + c];
-    }
-    if (j == P) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] += sf[(3 * NP + i) * 5 + c];
-    }
-  }
 }
 
 // Per-element sums (GLL weights, without |J_K|), minima and maxima of 5 fields held in LDS rows
@@ -283,89 +182,279 @@ __device__ __forceinline__ void element_stats(double* svf, double* sst, bool act
   }
 }
 
+// Tile of the stage kernel: the x lines of EB elements on the block's first half, their y lines on
+// the second (so a wave has one direction), EB = (BS / 2) / (p+1).  An element's node arrays in LDS keep
+// rows of odd stride RS, so that both the row and the column reads spread over the banks.
+template <int P, int BS>
+struct SC {
+  static constexpr int NP = P + 1, NN = NP * NP, EB = BS / 2 / NP, RS = NP | 1, ES = NP * RS;
+};
+
 // MODE 0: out = L_E(Us).  MODE 1: out = ca*Un + cb*(Us + tau*L_E(Us)) plus element statistics.
+//
+// Phases: (1) per node, the values of the EC flux into LDS, and whether the block needs logarithms; (2) per
+// line, its two interface fluxes and its p(p+1)/2 pair fluxes, the coefficients as scalars and the
+// residual of the line in registers; (3) the x lines' residuals into LDS over the node values, the y
+// lines' added; (4) per node, the SSP combine; (5) per element and component, the statistics.
+// A thread per node instead (each pair's second half through LDS, coefficients and partners by run-time
+// index, two logarithms per node) issued 4.3e8 VALU instructions a launch at 1024^2, N = 4 and was bound
+// by that: 1.02 ms.  This form issues 2.2e8, takes 0.82 ms and moves 4.1 GB (5 TB/s, a large copy's
+// rate); at 512^2, N = 3 0.160 -> 0.131 ms, at 256^2, N = 2 31.5 -> 21.8 us.  Four waves per SIMD: at three
+// it takes 0.87 ms.
 template <int P, int MODE, int BS>
 __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, const double* __restrict__ Un,
                                                     double* __restrict__ out, double* __restrict__ stats,
                                                     int* __restrict__ flag, const HydroTab* __restrict__ T, MeshP mp,
                                                     double ca, double cb, double tau, int iface, long blk) {
-  using C = Cfg<P, BS>;
-  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, ND = C::ND;
-  __shared__ double sp[7][EB * NN];
-  __shared__ double sb[EB * NP * NP * (ND > 0 ? ND : 1) * 5];
-  __shared__ double tS[NP * NP];
-  // scratch for the interface fluxes and the statistics' row partials (20 (p+1) values per
-  // element): the flux hand-off buffer sb when it is large enough, else an array of its own
-  constexpr bool SB_BIG = NP * (ND > 0 ? ND : 1) >= 4;
-  __shared__ double sxt[SB_BIG ? 1 : EB * 20 * NP];
+  using C = SC<P, BS>;
+  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, RS = C::RS, ES = C::ES;
+  __shared__ double sp[8][EB * ES];  // rho, h_x, h_y, h_z, b, p, log rho, log b; rows 0..4 later the residual
   __shared__ int sflag;
   const int tid = threadIdx.x;
-  if (tid < NP * NP) tS[tid] = T->Shat[tid / NP][tid % NP];
-  if (MODE == 1) {  // skip stages after a rejected one; read once per block (other blocks may set it)
-    if (tid == 0) sflag = __atomic_load_n(flag, __ATOMIC_RELAXED);
-    __syncthreads();
-    if (sflag) return;
-  }
-  const int el = tid / NN, q = tid - el * NN;
-  const int i = q % NP, j = q / NP;
-  const long e = blk * EB + el;
-  const bool act = tid < C::NT && e < mp.K;
+  const int e0 = (int)(blk * EB);
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;
   const long KN = mp.K * NN;
-  const unsigned no = ((unsigned)e * NN + q) * 8u;  // the node's byte offset in a component array
-  double U[5], UNo[5], acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  Prim me{};
+  const double cg = 2.0 * mp.gk;
+  auto slot = [](int n) {  // LDS slot of the block's n-th node
+    const int el = n / NN, q = n - el * NN, j = q / NP;
+    return el * ES + j * RS + (q - j * NP);
+  };
+  // every global load of the line phase is issued before the first wait (the reject word's too: read
+  // once per block, because other blocks may set it)
+  constexpr int NR = (EB * NN + BS - 1) / BS;  // nodes per thread
+  double U[NR][5];
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int n = tid + m * BS;
+    const unsigned no = ((unsigned)e0 * NN + n) * 8u;  // the node's byte offset in a component array
+    if (n < nel * NN) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) U[m][c] = bld(node_rsrc(Us + c * KN, KN), no);
+    }
+  }
+  // the thread's line: direction D (0: x, 1: y, the same for a wave), element el, line ln
+  const int D = __builtin_amdgcn_readfirstlane(tid >= BS / 2 ? 1 : 0);
+  const int lt = tid - D * (BS / 2), el = lt / NP, ln = lt - el * NP;
+  const bool act = lt < nel * NP;
+  const int base = el * ES + (D ? ln : ln * RS), step = D ? RS : 1;  // LDS slots of the line's nodes
+  // the neighbours' face nodes (index 0: the face at -1, 1: at +1)
+  double nb[2][5];
   if (act) {
+    int ex, ey;
+    elem_xy32(mp, e0 + el, ex, ey);
 #pragma unroll
-    for (int c = 0; c < 5; ++c) U[c] = bld(node_rsrc(Us + c * KN, KN), no);
-    // U^n is issued early (it is only used at the end); the first stage (ca = 0) has no U^n term
-    if (MODE == 1 && ca != 0.0) {
+    for (int side = 0; side < 2; ++side) {
+      int en, qo, qn;
+      face_match<P>(mp, ex, ey, D, side, ln, en, qo, qn);
+      const unsigned on = ((unsigned)en * NN + qn) * 8u;
 #pragma unroll
-      for (int c = 0; c < 5; ++c) UNo[c] = bld(node_rsrc(Un + c * KN, KN), no);
+      for (int c = 0; c < 5; ++c) nb[side][c] = bld(node_rsrc(Us + c * KN, KN), on);
+    }
+  }
+  if (MODE == 1 && tid == 0) sflag = __atomic_load_n(flag, __ATOMIC_RELAXED);
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int n = tid + m * BS;
+    if (n < nel * NN) {
+      const double* u = U[m];
+      const double ir = rcp_refined(u[0]), hi = 0.5 * ir;  // rho > 0 on admissible states
+      const double p = pressure_of(u, ir, mp.gamma);
+      const int k = slot(n);
+      sp[0][k] = u[0]; sp[1][k] = u[1] * hi; sp[2][k] = u[2] * hi; sp[3][k] = u[3] * hi;
+      sp[4][k] = u[0] * rcp_refined(p); sp[5][k] = p;  // p > 0 on admissible states
+    }
+  }
+  __syncthreads();
+  if (MODE == 1 && sflag) return;  // skip stages after a rejected one
+  double acc[NP][5];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int c = 0; c < 5; ++c) acc[i][c] = 0.0;
+  const int rn = 1 + D, rt = 2 - D;  // LDS rows of the normal and the tangential velocity / momentum
+  auto node = [&](int i) {
+    const int k = base + i * step;
+    return Prim{sp[0][k], sp[rn][k], sp[rt][k], sp[3][k], sp[4][k]};
+  };
+  // does any line of the block hold values too far apart for the series of the logarithmic mean?
+  bool lfar = false;
+  if (act) {
+    double r0 = sp[0][base], r1 = r0, b0 = sp[4][base], b1 = b0;
+#pragma unroll
+    for (int i = 1; i < NP; ++i) {
+      const double r = sp[0][base + i * step], b = sp[4][base + i * step];
+      r0 = r < r0 ? r : r0; r1 = r > r1 ? r : r1;
+      b0 = b < b0 ? b : b0; b1 = b > b1 ? b : b1;
+    }
+    lfar = !(r1 - r0 <= LM_NEAR * (r1 + r0)) || !(b1 - b0 <= LM_NEAR * (b1 + b0));
+  }
+  const bool far = __syncthreads_or(lfar);
+  if (far) {  // then every node's logarithms
+    for (int n = tid; n < nel * NN; n += BS) {
+      const int k = slot(n);
+      sp[6][k] = log_ec(sp[0][k]);
+      sp[7][k] = log_ec(sp[4][k]);
+    }
+    __syncthreads();
+  }
+  if (act) {
+    // interface fluxes: the neighbour is the minus side at -1 and the plus side at +1
+    const double rw = rcp_refined(T->w[0]);
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const double* n = nb[side];
+      const int i = side ? P : 0;
+      const double ir = rcp_refined(n[0]), hi = 0.5 * ir, pn = pressure_of(n, ir, mp.gamma);
+      const double hn = (D ? n[2] : n[1]) * hi, ht = (D ? n[1] : n[2]) * hi, hz = n[3] * hi;
+      const Prim q = node(i);
+      double F[5];
+      if (iface == 1) {
+        const Prim o{n[0], hn, ht, hz, n[0] * rcp_refined(pn)};
+        ecflux_log(q, log_ec(q.r), log_ec(q.b), o, log_ec(o.r), log_ec(o.b), cg, F);
+      } else {
+        const FaceSide a = face_side(q.r, q.hn, q.ht, q.hz, sp[5][base + i * step], mp.gamma, cg);
+        const FaceSide b = face_side(n[0], hn, ht, hz, pn, mp.gamma, cg);
+        const double hl = (side ? -0.5 : 0.5) * fmax(a.s, b.s);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) F[c] = fma(0.5, a.F[c] + b.F[c], hl * (b.U[c] - a.U[c]));
+      }
+#pragma unroll
+      for (int c = 0; c < 5; ++c) acc[i][c] = side ? acc[i][c] + rw * F[c] : acc[i][c] - rw * F[c];
+    }
+    // S_ir by its exact symmetry S_{p-i,p-r} = -S_ir (the tables hold it bit for bit), which halves the
+    // scalars that the pairs keep
+    auto S = [&](int i, int r) {
+      return i * NP + r <= (P - i) * NP + (P - r) ? T->Shat[i][r] : -T->Shat[P - i][P - r];
+    };
+    // the partner is read again for every pair: LDS reads are cheap here, and with a whole line's values
+    // in registers the kernel fits one wave per SIMD less
+    auto pairs = [&](auto flux) {
+#pragma unroll
+      for (int i = 0; i + 1 < NP; ++i) {
+#pragma unroll
+        for (int r = i + 1; r < NP; ++r) {
+          double F[5];
+          flux(i, r, F);
+          const double si = S(i, r), sr = S(r, i);
+#pragma unroll
+          for (int c = 0; c < 5; ++c) {
+            acc[i][c] = fma(si, F[c], acc[i][c]);
+            acc[r][c] = fma(sr, F[c], acc[r][c]);
+          }
+          SCHED_FENCE();
+        }
+      }
+    };
+    if (__builtin_expect(far, 0)) {
+      pairs([&](int i, int r, double* F) {
+        const int ki = base + i * step, kr = base + r * step;
+        ecflux_log(node(i), sp[6][ki], sp[7][ki], node(r), sp[6][kr], sp[7][kr], cg, F);
+      });
     } else {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) UNo[c] = 0.0;
+      pairs([&](int i, int r, double* F) { ecflux_near(node(i), node(r), cg, T, F); });
     }
-    me = make_prim(U, mp.gamma);
-    sp[0][tid] = me.r; sp[1][tid] = me.ux; sp[2][tid] = me.uy; sp[3][tid] = me.uz;
-    sp[4][tid] = me.b; sp[5][tid] = me.lr; sp[6][tid] = me.lb;
-    // the SSP combine ca U^n + cb (U_s + tau L) is carried as (ca U^n + cb U_s) + cb tau L, so
-    // that one state instead of two stays live through the flux phases
-    if (MODE == 1) {
+    const double sc = -2.0 * (D ? mp.rhy : mp.rhx);
 #pragma unroll
-      for (int c = 0; c < 5; ++c) U[c] = ca * UNo[c] + cb * U[c];
-    }
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) acc[i][c] *= sc;
   }
-  __syncthreads();
-  volume_dir<P, 0, BS>(me, acc, act, el, i, j, sp, sb, tS, mp);
-  volume_dir<P, 1, BS>(me, acc, act, el, i, j, sp, sb, tS, mp);
-  double* scr = SB_BIG ? sb : sxt;
-  surface_terms<P, BS>(acc, act, el, q, i, j, e, Us, KN, scr, sp, T, mp, iface);
-  if (MODE == 0) {
-    if (act) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) bst(node_rsrc(out + c * KN, KN), no, acc[c]);
-    }
-    return;
-  }
-  double Y[5];
+  __syncthreads();  // every line has read its values; the residual overwrites rows 0..4
   if (act) {
+    if (D == 0) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      Y[c] = U[c] + (cb * tau) * acc[c];
-      bst(node_rsrc(out + c * KN, KN), no, Y[c]);
-      sp[c][tid] = Y[c];
+      for (int i = 0; i < NP; ++i) {
+        const int k = base + i * step;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sp[c][k] = acc[i][c];
+      }
+    }
+  }
+  // the node values of the combine are loaded before the barrier, so that their latency overlaps it; it
+  // is carried as (ca U^n + cb U_s) + cb tau L; the first stage (ca = 0) has no U^n term
+  double Y[NR][5];
+  if (MODE == 1) {
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const int n = tid + m * BS;
+      const unsigned no = ((unsigned)e0 * NN + n) * 8u;
+      if (n < nel * NN) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) Y[m][c] = cb * bld(node_rsrc(Us + c * KN, KN), no);
+        if (ca != 0.0) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) Y[m][c] = fma(ca, bld(node_rsrc(Un + c * KN, KN), no), Y[m][c]);
+        }
+      }
     }
   }
   __syncthreads();
-  element_stats<C>(&sp[0][0], scr, act, el, q, e, stats, flag, T, mp.gamma);
+  if (act && D == 1) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int k = base + i * step;
+      sp[0][k] += acc[i][0]; sp[2][k] += acc[i][1]; sp[1][k] += acc[i][2];
+      sp[3][k] += acc[i][3]; sp[4][k] += acc[i][4];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int n = tid + m * BS;
+    if (n < nel * NN) {
+      const unsigned no = ((unsigned)e0 * NN + n) * 8u;
+      const int k = slot(n);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        if (MODE == 0) {
+          bst(node_rsrc(out + c * KN, KN), no, sp[c][k]);
+        } else {
+          const double v = fma(cb * tau, sp[c][k], Y[m][c]);
+          bst(node_rsrc(out + c * KN, KN), no, v);
+          sp[c][k] = v;
+        }
+      }
+    }
+  }
+  if (MODE == 0) return;
+  __syncthreads();
+  // element statistics: weighted sum (without |J_K|), minimum and maximum of each component
+  double* const ssum = sp[5];
+  for (int t = tid; t < nel * 5; t += BS) {
+    const int es = t / 5, c = t - es * 5;
+    const double* v = sp[c] + es * ES;
+    double s = 0.0, mn = v[0], mx = v[0];
+#pragma unroll 1
+    for (int j = 0; j < NP; ++j) {
+      double sr = 0.0;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const double x = v[j * RS + i];
+        sr = fma(T->w[i], x, sr);
+        mn = fmin(mn, x); mx = fmax(mx, x);
+      }
+      s = fma(T->w[j], sr, s);
+    }
+    double* o = stats + ((long)(e0 + es) * 5 + c) * 3;
+    o[0] = s; o[1] = mn; o[2] = mx;
+    ssum[t] = s;
+  }
+  __syncthreads();
+  if (tid < nel) {  // raw-average admissibility (NaN-safe)
+    double a[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) a[c] = 0.25 * ssum[tid * 5 + c];
+    const double pb = (mp.gamma - 1.0) * (a[4] - (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * a[0]));
+    if (!(a[0] > 0.0) || !(pb > 0.0)) atomicOr(flag, 1);
+  }
 }
 
 template <int P, int MODE, int BS>
-__global__ __launch_bounds__(BS, P == 4 ? 4 : 1) void k_hydro_stage(const double* __restrict__ Us, const double* __restrict__ Un,
+__global__ __launch_bounds__(BS, 4) void k_hydro_stage(const double* __restrict__ Us, const double* __restrict__ Un,
                                                     double* __restrict__ out, double* __restrict__ stats,
                                                     int* __restrict__ flag, const HydroTab* __restrict__ T, MeshP mp,
                                                     double ca, double cb, double tau, int iface) {
-  hydro_stage_body<P, MODE, BS>(Us, Un, out, stats, flag, T, mp, ca, cb, tau, iface, (long)blockIdx.x);
+  hydro_stage_body<P, MODE, BS>(Us, Un, out, stats, flag, T, mp, ca, cb, tau, iface, xcd_block());
 }
 
 struct hydro_stage_args {
@@ -383,7 +472,7 @@ struct hydro_stage_args {
 };
 
 template <int P, int MODE, int BS>
-__global__ __launch_bounds__(BS, P == 4 ? 4 : 1) void k_hydro_stage_rt(const hydro_stage_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+__global__ __launch_bounds__(BS, 4) void k_hydro_stage_rt(const hydro_stage_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const hydro_stage_args& a = A[r];
   hydro_stage_body<P, MODE, BS>(gl(a.Us), gl(a.Un), gl(a.out), gl(a.stats), gl(a.flag), gl(a.T), a.mp, a.ca, a.cb, a.tau, a.iface, (long)blockIdx.x - boff[r]);
@@ -1007,13 +1096,9 @@ __global__ void k_copy(const double* __restrict__ a, double* __restrict__ b, lon
 
 hipEvent_t* timing_slot(mhd25_ctx* c, int kid);
 static int eb_of(int p) { return 256 / ((p + 1) * (p + 1)); }
-// threads per block of the hydro stage kernel: the tuned value if set, else 128 up to N = 4 (all
-// lanes but three carry nodes, and the kernel fits 128 VGPRs without spills) and 256 above (fewer
-// idle lanes for (N+1)^2 = 36, 49)
-static int stage_block(const mhd25_ctx* c) {
-  if (c->hydro_bs == 128 || c->hydro_bs == 256) return c->hydro_bs;
-  return c->p <= 4 ? 128 : 256;
-}
+// threads per block of the hydro stage kernel: the tuned value if set, else 128 (the halves of a
+// 256-thread block wait for each other longer: 2 to 6 % more time for every degree)
+static int stage_block(const mhd25_ctx* c) { return c->hydro_bs == 256 ? 256 : 128; }
 
 static int check(mhd25_ctx* c, hipError_t e, const char* what) {
   if (e != hipSuccess) { c->err = std::string(what) + ": " + hipGetErrorString(e); return -2; }
@@ -1041,7 +1126,7 @@ static int launch_reductions(mhd25_ctx* c, const double* stats, int nc, const in
 
 int hydro_rhs(mhd25_ctx* c, const double* U, double* dU) {
   const int bs = stage_block(c);
-  const int eb = bs / ((c->p + 1) * (c->p + 1));
+  const int eb = bs / 2 / (c->p + 1);
   const long blocks = (c->mp.K + eb - 1) / eb;
 #define L0(P)                                                                                                      \
   if (bs == 128) hipLaunchKernelGGL((k_hydro_stage<P, 0, 128>), dim3(blocks), dim3(128), 0, c->stream, U, U, dU,  \
@@ -1056,7 +1141,7 @@ int hydro_rhs(mhd25_ctx* c, const double* U, double* dU) {
 // raw stage + statistics + line/global reductions
 int hydro_stage_a(mhd25_ctx* c, const double* Us, const double* Un, double* Ust, double ca, double cb, double tau) {
   const int bs = stage_block(c);
-  const int eb = bs / ((c->p + 1) * (c->p + 1));
+  const int eb = bs / 2 / (c->p + 1);
   const long blocks = (c->mp.K + eb - 1) / eb;
   if (c->rec) {
     rt_record(c, RT_HYDRO_STAGE, c->p * 1000 + bs, blocks,

@@ -123,6 +123,14 @@ void build_hydro_tables(int p, HydroTab* T) {
     if (r > 0) f *= r;
     T->fr[r] = (double)((2 * r + 1) * std::pow((ld)2, r) / (2 * f));
   }
+  // atanh f / f = sum z^k / (2k+1); the other series is its reciprocal
+  ld h[LM_N + 1], g[LM_N + 1];
+  for (int q = 0; q <= LM_N; ++q) {
+    h[q] = (ld)1 / (2 * q + 1);
+    g[q] = q == 0 ? 1 : 0;
+    for (int j = 1; j <= q; ++j) g[q] -= h[j] * g[q - j];
+    if (q > 0) { T->lmG[q - 1] = (double)g[q]; T->lmH[q - 1] = (double)h[q]; }
+  }
 }
 
 void build_mag_tables(int p, int m, MagTab* T) {

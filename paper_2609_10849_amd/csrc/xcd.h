@@ -47,3 +47,11 @@ template <class T>
 __device__ __forceinline__ const T& gl(const T& field) {
   return field;
 }
+
+// The instruction scheduler moves nothing across this point.  Unrolled blocks of independent work
+// otherwise get interleaved until their operands no longer fit the registers.
+#if __has_builtin(__builtin_amdgcn_sched_barrier)
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#else
+#define SCHED_FENCE()
+#endif
