@@ -142,7 +142,7 @@ struct MagIO {
 enum RtKind {
   RT_HYDRO_STAGE, RT_OE_PP, RT_LINE_REDUCE, RT_GLOBAL_REDUCE, RT_RESET, RT_COPY, RT_SNAP_U, RT_COPY_CHECK,
   RT_TO_PRIM, RT_TO_CONS, RT_J_LOADS, RT_E_LOADS, RT_GATHER, RT_MAG_UPDATE, RT_VEL_PREP, RT_VEL_SENSOR,
-  RT_VEL_PROJ, RT_B_STATS, RT_AR_TRACES, RT_AR_ETA, RT_MAX, RT_BATCH_ZERO, RT_BATCH_FOLD, RT_NKIND
+  RT_VEL_PROJ, RT_B_STATS, RT_AR_TRACES, RT_AR_ETA, RT_MAX, RT_BATCH_ZERO, RT_BATCH_FOLD, RT_HYDRO_SENSOR, RT_NKIND
 };
 struct RtRecord {
   int kind;
@@ -173,7 +173,7 @@ struct mhd25_ctx {
   double* red;  // scratch for small reductions
   double* vjp_scratch;  // allocated on the first magnetic VJP
   double* psi;          // rho-weighted orthonormal basis values [K][nn][psi_row(p)] (velocity OE)
-  double* dfac;         // velocity-OE damping factors D_l of the current stage [K][p+1]
+  double* dfac;         // OE damping factors D_l of the current (hydro or magnetic) stage [K][p+1]
   double* artr;         // A.R. face traces and wave-speed maxima [K][8(m+2)+2]
   double* h_pinned;
   std::string err;

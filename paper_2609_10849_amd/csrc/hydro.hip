@@ -504,337 +504,462 @@ __device__ __forceinline__ double Sp(const double* a, double eps_r) {
   return fabs(a[4]) + (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * fmax(a[0], eps_r));
 }
 
-// P = P_PP o P_OE on a raw stage (eq. euler-oe-map, eq. euler-pp-density, eq. euler-pp-pressure).
-// The derivative jumps and the modal transforms run as line tasks: task (c, line) holds one grid
-// line of component c in registers (five tasks per line index), so a line is read from LDS once
-// per pass instead of once per output node; the 1D tables are read with uniform (scalar) loads.
-// The element statistics of the raw stage (always formed before this map) give the element
-// averages: the OE map keeps each element's mean, the (0, 0) Legendre mode.
-template <int P, int BS>
+// Tile of the hydro OE sensor: TX x TY elements and the ring around them, one thread per component and
+// face.  The tile's (TX + 1) TY x faces run on the block's first half, its TX (TY + 1) y faces on the second
+// (120 and 125 of 128 threads), so that a wave has one direction.
+template <int P>
+struct HS {
+  static constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1;  // odd element stride in LDS: no bank conflicts
+  static constexpr int TX = 5, TY = 4, TE = TX * TY, BS = 256;
+  static constexpr int NX = (TX + 1) * TY, NY = TX * (TY + 1);  // faces
+  static constexpr int NS = TE + 2 * (TX + TY);                 // staged elements: the tile's, then the ring's
+};
+
+// squared, weighted jumps of the derivatives of order r (eq. euler-oe-jump) across a face between the
+// elements at m (minus side) and q (plus side), normal direction D, as square roots.  On the symmetric GLL
+// nodes d^r l_k (+1) = (-1)^r d^r l_{p-k} (-1), which the tables hold bit for bit, so the jump of order r is one
+// sum over the differences (r even) or sums (r odd) of mirrored values.
+template <int P, int D>
+__device__ __forceinline__ void face_jumps(const double* m, const double* q, const HydroTab* __restrict__ T, double J[]) {
+  constexpr int NP = P + 1;
+#pragma unroll
+  for (int r = 0; r < NP; ++r) J[r] = 0.0;
+#pragma unroll
+  for (int l = 0; l < NP; ++l) {
+    double dif[NP], sum[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const double a = q[D ? k * NP + l : l * NP + k], b = m[D ? (P - k) * NP + l : l * NP + P - k];
+      dif[k] = a - b;
+      sum[k] = a + b;
+    }
+#pragma unroll
+    for (int r = 0; r < NP; ++r) {
+      double j = 0.0;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) j = fma(T->Dr0[r][k], r & 1 ? sum[k] : dif[k], j);
+      J[r] = fma(0.5 * T->w[l] * j, j, J[r]);
+    }
+    SCHED_FENCE();
+  }
+#pragma unroll
+  for (int r = 0; r < NP; ++r) J[r] = sqrt(J[r]);
+}
+
+// Hydro OE sensor (eq. euler-oe-amplitude .. eq. euler-oe-map): the shell damping factors D_l (l = 0..p) of every
+// element from the raw stage, Dfac[K][p+1].  Every face's jumps are formed once per tile, by a thread of
+// its own from LDS; only the squared sums are exchanged.  Bound by VALU issue (1.6e8 instructions at
+// 1024^2, N = 4) and its reads: 0.40 ms there (1.2 GB).
+template <int P>
+__device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust, const double* __restrict__ stats,
+                                                  const double* __restrict__ lines, const double* __restrict__ glob,
+                                                  double* __restrict__ Dfac, const int* __restrict__ flag,
+                                                  const HydroTab* __restrict__ T, MeshP mp, double tau, double sH,
+                                                  int blk) {
+  using C = HS<P>;
+  constexpr int NP = C::NP, NN = C::NN, ES = C::ES, TX = C::TX, TY = C::TY, TE = C::TE, BS = C::BS, NS = C::NS;
+  constexpr int NX = C::NX, NY = C::NY;
+  // su[c][staged element][ES]; then the faces' jumps sj[c][face][NP] (x faces first)
+  constexpr int NU = 5 * NS * ES, NJ = 5 * (NX + NY) * NP;
+  __shared__ double su[NU > NJ ? NU : NJ], ssg[TE][2 * NP], samp[2][TX], slam[2][TE];
+  __shared__ int sel[NS];
+  const int tid = threadIdx.x;
+  int ty0, tx0;
+  tile_of(blk, (mp.nx + TX - 1) / TX, (mp.ny + TY - 1) / TY, tx0, ty0);
+  tx0 *= TX; ty0 *= TY;
+  const int tw = mp.nx - tx0 < TX ? mp.nx - tx0 : TX, th = mp.ny - ty0 < TY ? mp.ny - ty0 : TY;  // tile in the mesh
+  const long KN = mp.K * NN;
+  const double g = mp.gamma;
+  // the staged elements (ring: left, right column, bottom, top row), -1 where the mesh ends the tile early
+  if (tid < NS) {
+    const int s = tid;
+    int x, y;
+    bool in;
+    if (s < TE) { y = s / TX; x = s - y * TX; in = x < tw && y < th; }
+    else if (s < TE + 2 * TY) { const int h = s - TE; x = h < TY ? -1 : tw; y = h < TY ? h : h - TY; in = y < th; }
+    else { const int h = s - TE - 2 * TY; y = h < TX ? -1 : th; x = h < TX ? h : h - TX; in = x < tw; }
+    sel[s] = in ? wrap32(ty0 + y, mp.ny) * mp.nx + wrap32(tx0 + x, mp.nx) : -1;
+  }
+  __syncthreads();
+  // their nodes, coalesced
+  constexpr int NR = (NS * NN + BS - 1) / BS;
+  double raw[NR][5];
+  int slot[NR];
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int n = tid + m * BS, s = n / NN, q = n - s * NN;
+    const int e = n < NS * NN ? sel[s] : -1;
+    slot[m] = e < 0 ? -1 : s * ES + q;
+    if (e >= 0)
+#pragma unroll
+      for (int d = 0; d < 5; ++d) raw[m][d] = bld(node_rsrc(Ust + d * KN, KN), ((unsigned)e * NN + q) * 8u);
+  }
+  if (flag && *flag) return;
+  // cross-line amplitudes shared by the components (eq. euler-oe-amplitude): rows, then columns
+  for (int t = tid; t < TY + TX; t += BS) {
+    const int D = t < TY ? 0 : 1, i = D ? t - TY : t;
+    if (i < (D ? tw : th)) {
+      const double* l = lines + (D ? mp.ny + tx0 + i : ty0 + i) * 15;
+      const double rn = D ? mp.r4ny : mp.r4nx;
+      double a = 0.0;
+#pragma unroll
+      for (int d = 0; d < 5; ++d) {
+        const double gm = glob[d * 3] * mp.r4K, m = l[d * 3] * rn;
+        const double dOm = fmax(glob[d * 3 + 2] - gm, gm - glob[d * 3 + 1]);
+        a = fmax(a, fmax(fmax(l[d * 3 + 2] - m, m - l[d * 3 + 1]), 1e-6 * dOm));
+      }
+      samp[D][i] = a;
+    }
+  }
+  // wave speeds of the damping rate (eq. euler-oe-rate) from the element averages
+  if (tid >= 64 && tid - 64 < TE) {
+    const int en = tid - 64, x = en % TX, y = en / TX;
+    if (x < tw && y < th) {
+      const double* st = stats + (long)((ty0 + y) * mp.nx + tx0 + x) * 15;
+      double a[5];
+#pragma unroll
+      for (int d = 0; d < 5; ++d) a[d] = 0.25 * st[3 * d];
+      const double ir0 = 1.0 / a[0];
+      const double pa = (g - 1.0) * (a[4] - 0.5 * (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) * ir0);
+      const double ck = sqrt(g * pa * ir0);
+      slam[0][en] = (2.0 * P + 1.0) * (fabs(a[1] * ir0) + ck) * mp.rhx;
+      slam[1][en] = (2.0 * P + 1.0) * (fabs(a[2] * ir0) + ck) * mp.rhy;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < NR; ++m)
+    if (slot[m] >= 0)
+#pragma unroll
+      for (int d = 0; d < 5; ++d) su[d * NS * ES + slot[m]] = raw[m][d];
+  __syncthreads();
+  // the thread's face (x faces: fx counts the TX + 1 faces of a row) and component
+  const int D = __builtin_amdgcn_readfirstlane(tid >= BS / 2 ? 1 : 0);
+  const int t = tid - D * (BS / 2), nf = D ? NY : NX, c = t / nf, f = t - c * nf;
+  const int fx = D ? f % TX : f % (TX + 1), fy = D ? f / TX : f / (TX + 1);
+  const bool act = c < 5 && (D ? fx < tw && fy <= th : fx <= tw && fy < th);
+  double J[NP];
+  if (act) {
+    const double* S = su + c * NS * ES;
+    if (D == 0)
+      face_jumps<P, 0>(S + (fx == 0 ? TE + fy : fy * TX + fx - 1) * ES, S + (fx == tw ? TE + TY + fy : fy * TX + fx) * ES, T, J);
+    else
+      face_jumps<P, 1>(S + (fy == 0 ? TE + 2 * TY + fx : (fy - 1) * TX + fx) * ES,
+                       S + (fy == th ? TE + 2 * TY + TX + fx : fy * TX + fx) * ES, T, J);
+  }
+  __syncthreads();
+  if (act) {
+    // a component that is constant to roundoff (its nodal values agree to 2^10 ulps of its size, an exact
+    // test) does not count
+    const double gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
+    const bool cst = gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn));
+    double* o = su + (c * (NX + NY) + (D ? NX + f : f)) * NP;
+#pragma unroll
+    for (int r = 0; r < NP; ++r) o[r] = cst ? 0.0 : J[r];
+  }
+  __syncthreads();
+  // sigma (eq. euler-oe-sigma): the two faces' jumps, maximum over the components, against the shared amplitude
+  for (int k = tid; k < TE * 2 * NP; k += BS) {
+    const int r = k % NP, d = (k / NP) & 1, en = k / (2 * NP), x = en % TX, y = en / TX;
+    if (x < tw && y < th) {
+      const int f0 = d ? NX + y * TX + x : y * (TX + 1) + x, f1 = f0 + (d ? TX : 1);
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 5; ++q)
+        s = fmax(s, su[(q * (NX + NY) + f0) * NP + r] + su[(q * (NX + NY) + f1) * NP + r]);
+      const double A = samp[d][d ? x : y];
+      ssg[en][d * NP + r] = A > 0.0 ? T->fr[r] * s / A : 0.0;
+    }
+  }
+  __syncthreads();
+  // D_l = exp(-s tau (lx sum_{r<=l} sigma_x,r + ly sum_{r<=l} sigma_y,r))
+  for (int k = tid; k < TE * NP; k += BS) {
+    const int l = k % NP, en = k / NP, x = en % TX, y = en / TX;
+    if (x < tw && y < th) {
+      double sx = 0.0, sy = 0.0;
+      for (int r = 0; r <= l; ++r) { sx += ssg[en][r]; sy += ssg[en][NP + r]; }
+      Dfac[(long)((ty0 + y) * mp.nx + tx0 + x) * NP + l] = l == 0 ? 1.0 : exp(-sH * tau * (slam[0][en] * sx + slam[1][en] * sy));
+    }
+  }
+}
+
+template <int P>
+__global__ __launch_bounds__(HS<P>::BS) void k_hydro_sensor(const double* __restrict__ Ust, const double* __restrict__ stats,
+                                                  const double* __restrict__ lines, const double* __restrict__ glob,
+                                                  double* __restrict__ Dfac, const int* __restrict__ flag,
+                                                  const HydroTab* __restrict__ T, MeshP mp, double tau, double sH) {
+  hydro_sensor_body<P>(Ust, stats, lines, glob, Dfac, flag, T, mp, tau, sH, (int)xcd_block());
+}
+
+struct hydro_sensor_args {
+  const double* Ust;
+  const double* stats;
+  const double* lines;
+  const double* glob;
+  double* Dfac;
+  const int* flag;
+  const HydroTab* T;
+  MeshP mp;
+  double tau;
+  double sH;
+};
+
+template <int P>
+__global__ __launch_bounds__(HS<P>::BS) void k_hydro_sensor_rt(const hydro_sensor_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+  const int r = rt_run(boff, nr);
+  const hydro_sensor_args& a = A[r];
+  hydro_sensor_body<P>(gl(a.Ust), gl(a.stats), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.flag), gl(a.T), a.mp, a.tau, a.sH, (int)blockIdx.x - boff[r]);
+}
+
+// Discrete Legendre transform of a grid line and its inverse.  On the symmetric GLL nodes
+// Tf[a][k] = (-1)^a Tf[a][p-k] and V[k][a] = (-1)^a V[p-k][a], bit for bit in the tables, so the line's even
+// and odd parts are transformed.
+template <int P>
+__device__ __forceinline__ void legendre_fwd(const double* v, double* m, const HydroTab* __restrict__ T) {
+  constexpr int NP = P + 1, H = NP / 2;
+  double e[H + 1], o[H + 1];
+#pragma unroll
+  for (int k = 0; k < H; ++k) { e[k] = v[k] + v[P - k]; o[k] = v[k] - v[P - k]; }
+  if (NP % 2) e[H] = v[H];
+#pragma unroll
+  for (int a = 0; a < NP; ++a) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < (a % 2 ? H : NP - H); ++k) s = fma(T->Tf[a][k], a % 2 ? o[k] : e[k], s);
+    m[a] = s;
+  }
+}
+template <int P>
+__device__ __forceinline__ void legendre_inv(const double* m, double* v, const HydroTab* __restrict__ T) {
+  constexpr int NP = P + 1, H = NP / 2;
+#pragma unroll
+  for (int k = 0; k < NP - H; ++k) {
+    double e = 0.0, o = 0.0;
+#pragma unroll
+    for (int a = 0; a < NP; a += 2) e = fma(T->V[k][a], m[a], e);
+    if (k < H)
+#pragma unroll
+      for (int a = 1; a < NP; a += 2) o = fma(T->V[k][a], m[a], o);
+    v[k] = e + o;
+    if (k < H) v[P - k] = e - o;
+  }
+}
+
+// Block of the stage map: EB consecutive elements, one thread per (component, element).
+template <int P>
+struct OM {
+  static constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1;  // odd element stride in LDS: no bank conflicts
+  static constexpr int EB = 24, BS = 128;                      // 120 of 128 threads
+};
+
+// P = P_PP o P_OE on a raw stage (eq. euler-oe-map, eq. euler-pp-density, eq. euler-pp-pressure) with the damping
+// factors Dfac of the sensor.  A thread holds one component of an element in registers: the modal transforms
+// and the damping are straight-line code with the 1D tables as scalars.  The
+// element statistics of the raw stage (always formed before this map) give the element averages: the map
+// keeps each element's mean, the (0, 0) Legendre mode.  Bound by HBM: 2.4 GB in 0.46 ms at 1024^2, N = 4.
+//
+// One kernel for sensor and map, with a thread per element line and component that formed its neighbours'
+// traces too, was bound by VALU issue and LDS alike (4.5e8 VALU instructions, 4.5e8 LDS cycles): 1.23 ms at
+// 1024^2, N = 4 against 0.86 for the two, 0.324 against 0.152 ms at 512^2, N = 3 (20 line tasks on an element's
+// 16 threads), 38 against 27 us at 256^2, N = 2, 70 against 57 us at 241 x 137, N = 5.  One kernel with a thread
+// per component and element that exchanges its traces through LDS took 1.18 ms: its 16 barriers and 160
+// registers leave two blocks on a CU.
+template <int P>
 __device__ __forceinline__ void hydro_oe_pp_body(const double* __restrict__ Ust, double* __restrict__ Uout,
-                                                     const double* __restrict__ stats, const double* __restrict__ lines,
-                                                     const double* __restrict__ glob, uint8_t* __restrict__ flags,
+                                                     const double* __restrict__ stats, const double* __restrict__ Dfac,
+                                                     uint8_t* __restrict__ flags,
                                                      unsigned long long* __restrict__ counts,
                                                      const int* __restrict__ flag, const HydroTab* __restrict__ T,
-                                                     MeshP mp, double tau, double sH, int do_oe, int do_pp,
+                                                     MeshP mp, int do_oe, int do_pp,
                                                      double* __restrict__ rho_o, double* __restrict__ e_o,
                                                      double* __restrict__ u_o, long blk) {
-  using C = Cfg<P, BS>;
-  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, NL = 5 * NP;
-  __shared__ double su[5][EB * NN];
-  __shared__ double st[10][EB * NN];
-  __shared__ double ssig0[EB][NP], ssig1[EB][NP], ssg[EB][5][NP];
-  __shared__ double sD[EB][NP], samp[EB][2][5], srow[EB][3][NP];
-  __shared__ int scst[EB][5];
-  if (flag && *flag) return;
-  const int tid = threadIdx.x;
-  const int el = tid / NN, q = tid - el * NN;
-  const long e = blk * EB + el;
-  const bool act = tid < C::NT && e < mp.K;
+  using C = OM<P>;
+  constexpr int NP = C::NP, NN = C::NN, ES = C::ES, EB = C::EB, BS = C::BS;
+  __shared__ double su[5][EB * ES];
+  __shared__ double sa[5][EB], sred[2][5][EB], sth[2][EB], srmin[EB];
+  const int tid = threadIdx.x, c = tid / EB, el = tid - c * EB;
+  const int e0 = (int)(blk * EB);
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;
+  const bool act = c < 5 && el < nel;
   const long KN = mp.K * NN;
-  const unsigned no = ((unsigned)e * NN + q) * 8u;  // the node's byte offset in a component array
+  const int e = e0 + el;
   const double g = mp.gamma;
-  int ex, ey;
-  elem_xy32(mp, act ? (int)e : 0, ex, ey);
-  // grid line ln of direction D (D = 0: row, index along x; D = 1: column), position k on it
-  auto nodeof = [](int D, int ln, int k) { return D == 0 ? ln * NP + k : k * NP + ln; };
-  double U[5], a[5];
-  // the four neighbours' nodes (x minus, x plus, y minus, y plus) are loaded into registers up
-  // front with the element's own, so that their latency overlaps the amplitude and x phases; they
-  // go to LDS when their direction comes
-  double nb[4][5];
-  if (act && do_oe) {
-    const int nbe[4] = {ey * mp.nx + wrap32(ex - 1, mp.nx), ey * mp.nx + wrap32(ex + 1, mp.nx),
-                        wrap32(ey - 1, mp.ny) * mp.nx + ex, wrap32(ey + 1, mp.ny) * mp.nx + ex};
+  constexpr int NR = (EB * NN + BS - 1) / BS;
+  {
+    double raw[NR][5];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const unsigned on = ((unsigned)nbe[s] * NN + q) * 8u;
+    for (int m = 0; m < NR; ++m) {
+      const int n = tid + m * BS;
+      if (n < nel * NN)
 #pragma unroll
-      for (int c = 0; c < 5; ++c) nb[s][c] = bld(node_rsrc(Ust + c * KN, KN), on);
+        for (int d = 0; d < 5; ++d) raw[m][d] = bld(node_rsrc(Ust + d * KN, KN), ((unsigned)e0 * NN + n) * 8u);
+    }
+    if (flag && *flag) return;
+    if (act) {
+      sa[c][el] = 0.25 * stats[((long)e * 5 + c) * 3];
+      if (c == 0 && !do_oe) srmin[el] = stats[(long)e * 15 + 1];  // raw-stage density minimum
+    }
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const int n = tid + m * BS;
+      if (n < nel * NN)
+#pragma unroll
+        for (int d = 0; d < 5; ++d) su[d][n / NN * ES + n % NN] = raw[m][d];
     }
   }
-  if (act) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) { U[c] = bld(node_rsrc(Ust + c * KN, KN), no); su[c][tid] = U[c]; }
-#pragma unroll
-    for (int c = 0; c < 5; ++c) a[c] = 0.25 * stats[(e * 5 + c) * 3];
-  }
-  double rmin = act ? stats[(e * 5) * 3 + 1] : DBL_MAX;  // raw-stage density minimum (no OE)
   __syncthreads();
   if (do_oe) {
-    // global and cross-line amplitudes (eq. euler-oe-amplitude), one task per component
-    for (int c = q; act && c < 5; c += NN) {
-      const double gs = glob[c * 3 + 0], gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
-      const double gm = gs * mp.r4K;
-      const double dOm = fmax(gmx - gm, gm - gmn);
-      // constant to roundoff: the nodal values agree to 2^10 ulps of the field's size (exact test)
-      scst[el][c] = gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn)) ? 1 : 0;
-      const double* rl = lines + (ey * 5 + c) * 3;
-      const double* cl = lines + ((mp.ny + ex) * 5 + c) * 3;
-      const double rm = rl[0] * mp.r4nx, cm = cl[0] * mp.r4ny;
-      samp[el][0][c] = fmax(fmax(rl[2] - rm, rm - rl[1]), 1e-6 * dOm);
-      samp[el][1][c] = fmax(fmax(cl[2] - cm, cm - cl[1]), 1e-6 * dOm);
-    }
+    if (act) {
+      double* const mine = su[c] + el * ES;
+      double f[NP];
 #pragma unroll
-    for (int D = 0; D < 2; ++D) {
-      // neighbours across the two faces normal to direction D, staged in st rows 0..9
-      // (row c: minus-side neighbour, row 5 + c: plus-side neighbour)
-      if (act) {
+      for (int l = 0; l < NP; ++l) f[l] = Dfac[(long)e * NP + l];
+      double w[NP][NP];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) {
-          st[c][tid] = nb[2 * D][c];
-          st[5 + c][tid] = nb[2 * D + 1][c];
-        }
-      }
-      if (D == 1 && act && q < NP) {  // direction-0 sigma: maximum over the components
-        double sg = 0.0;
+      for (int j = 0; j < NP; ++j) {
+        double v[NP];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) sg = fmax(sg, ssg[el][c][q]);
-        ssig0[el][q] = sg;
-      }
-      __syncthreads();
-      // normal-jump contributions (eq. euler-oe-jump) of line ln of component c: the r-th
-      // derivatives at both faces of the element and of its neighbours.  The squared, weighted
-      // jumps of derivative order r overwrite the task's own staged slots (position r on the line)
-      for (int t = q; act && t < NL; t += NN) {
-        const int ln = t / 5, c = t - ln * 5;  // component fastest (fewer LDS bank conflicts)
-        double own[NP], mn[NP], pl[NP];
-#pragma unroll
-        for (int k = 0; k < NP; ++k) {
-          const int n = el * NN + nodeof(D, ln, k);
-          own[k] = su[c][n]; mn[k] = st[c][n]; pl[k] = st[5 + c][n];
-        }
-        const double wl = 0.5 * T->w[ln];
-#pragma unroll
-        for (int r = 0; r < NP; ++r) {
-          double ja = 0.0, jd = 0.0, jb = 0.0, jc = 0.0;
-#pragma unroll
-          for (int k = 0; k < NP; ++k) {
-            // the +1 row from the -1 row: on the symmetric GLL nodes d^r l_k (+1) = (-1)^r d^r l_{p-k} (-1),
-            // which the tables hold bit for bit, so one table stays in scalar registers instead of two
-            const double d0 = T->Dr0[r][k], dp = (r & 1) ? -T->Dr0[r][P - k] : T->Dr0[r][P - k];
-            ja += d0 * own[k];
-            jd += dp * own[k];
-            jb += dp * mn[k];
-            jc += d0 * pl[k];
-          }
-          const double jm = ja - jb, jp = jc - jd;
-          const int n = el * NN + nodeof(D, ln, r);
-          st[c][n] = wl * jm * jm;
-          st[5 + c][n] = wl * jp * jp;
-        }
-      }
-      __syncthreads();
-      // sigma (eq. euler-oe-sigma): task (r, c) sums its squared jumps over the lines
-      {
-        double Dsh = 0.0;
-#pragma unroll
-        for (int c = 0; c < 5; ++c) Dsh = act ? fmax(Dsh, samp[el][D][c]) : 0.0;
-        for (int t = q; act && t < 5 * NP; t += NN) {
-          const int rr = t / 5, c = t - rr * 5;
-          double v = 0.0;
-          if (Dsh > 0.0 && !scst[el][c]) {
-            double sm = 0.0, spp = 0.0;
-            for (int l = 0; l < NP; ++l) {
-              const int n = el * NN + nodeof(D, l, rr);
-              sm += st[c][n];
-              spp += st[5 + c][n];
-            }
-            v = T->fr[rr] * (sqrt(sm) + sqrt(spp)) / Dsh;
-          }
-          ssg[el][c][rr] = v;  // direction 0's values are reduced before direction 1 writes
-        }
-      }
-      __syncthreads();
-    }
-    // modal damping with line tasks: x transform of each row, then per column the y transform,
-    // the shell factors and the inverse y transform, then the inverse x transform of each row.
-    // On the symmetric GLL nodes Tf[a][k] = (-1)^a Tf[a][p-k] and V[k][a] = (-1)^a V[p-k][a], bit for
-    // bit in the tables, so only the entries with k <= p/2 are read (fewer scalar registers).
-    auto tf = [&](int a, int k) {
-      return k <= P / 2 ? T->Tf[a][k] : ((a & 1) ? -T->Tf[a][P - k] : T->Tf[a][P - k]);
-    };
-    auto vt = [&](int k, int a) {
-      return k <= P / 2 ? T->V[k][a] : ((a & 1) ? -T->V[P - k][a] : T->V[P - k][a]);
-    };
-    for (int t = q; act && t < NL; t += NN) {
-      const int ln = t / 5, c = t - ln * 5;  // component fastest (fewer LDS bank conflicts)
-      double v[NP];
-#pragma unroll
-      for (int k = 0; k < NP; ++k) v[k] = su[c][el * NN + ln * NP + k];
-#pragma unroll
-      for (int aa = 0; aa < NP; ++aa) {
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < NP; ++k) s += tf(aa, k) * v[k];
-        st[c][el * NN + ln * NP + aa] = s;  // [row][x mode]
-      }
-    }
-    if (act && q < NP) {  // direction-1 sigma: maximum over the components
-      double sg = 0.0;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sg = fmax(sg, ssg[el][c][q]);
-      ssig1[el][q] = sg;
-    }
-    __syncthreads();
-    // shell damping factors (eq. euler-oe-map): D_l = exp(-s tau (lx sum_{r<=l} sigma_x,r + ...)),
-    // with one reciprocal of the mean density
-    if (act && q <= P) {
-      if (q == 0) {
-        sD[el][0] = 1.0;
-      } else {
-        const double ir0 = 1.0 / a[0];
-        const double pa = (g - 1.0) * (a[4] - 0.5 * (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) * ir0);
-        const double ck = sqrt(g * pa * ir0);
-        const double lx = (2.0 * P + 1.0) * (fabs(a[1] * ir0) + ck) * mp.rhx;
-        const double ly = (2.0 * P + 1.0) * (fabs(a[2] * ir0) + ck) * mp.rhy;
-        double sx = 0.0, sy = 0.0;
-        for (int r = 0; r <= q; ++r) { sx += ssig0[el][r]; sy += ssig1[el][r]; }
-        sD[el][q] = exp(-sH * tau * (lx * sx + ly * sy));
-      }
-    }
-    __syncthreads();
-    for (int t = q; act && t < NL; t += NN) {
-      const int aa = t / 5, c = t - aa * 5;
-      double v[NP], cb[NP];
-#pragma unroll
-      for (int k = 0; k < NP; ++k) v[k] = st[c][el * NN + k * NP + aa];
-#pragma unroll
-      for (int b = 0; b < NP; ++b) {
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < NP; ++k) s += tf(b, k) * v[k];
-        cb[b] = sD[el][aa > b ? aa : b] * s;  // coefficient (x mode aa, y mode b), damped
+        for (int i = 0; i < NP; ++i) v[i] = mine[j * NP + i];
+        legendre_fwd<P>(v, w[j], T);
       }
 #pragma unroll
-      for (int jj = 0; jj < NP; ++jj) {
-        double s = 0.0;
+      for (int a = 0; a < NP; ++a) {
+        double col[NP], m[NP];
 #pragma unroll
-        for (int b = 0; b < NP; ++b) s += vt(jj, b) * cb[b];
-        st[c][el * NN + jj * NP + aa] = s;  // [row][x mode]
+        for (int j = 0; j < NP; ++j) col[j] = w[j][a];
+        legendre_fwd<P>(col, m, T);
+#pragma unroll
+        for (int b = 0; b < NP; ++b) m[b] *= f[a > b ? a : b];
+        legendre_inv<P>(m, col, T);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) w[j][a] = col[j];
       }
-    }
-    __syncthreads();
-    for (int t = q; act && t < NL; t += NN) {
-      const int ln = t / 5, c = t - ln * 5;  // component fastest (fewer LDS bank conflicts)
-      double v[NP];
-#pragma unroll
-      for (int k = 0; k < NP; ++k) v[k] = st[c][el * NN + ln * NP + k];
       double mn = DBL_MAX;
 #pragma unroll
-      for (int ii = 0; ii < NP; ++ii) {
-        double s = 0.0;
+      for (int j = 0; j < NP; ++j) {
+        double o[NP];
+        legendre_inv<P>(w[j], o, T);
 #pragma unroll
-        for (int k = 0; k < NP; ++k) s += vt(ii, k) * v[k];
-        su[c][el * NN + ln * NP + ii] = s;
-        mn = fmin(mn, s);
+        for (int i = 0; i < NP; ++i) {
+          mine[j * NP + i] = o[i];
+          mn = fmin(mn, o[i]);
+        }
       }
-      if (c == 0) srow[el][0][ln] = mn;  // row minimum of the damped density
+      if (c == 0) srmin[el] = mn;
     }
     __syncthreads();
-    if (act) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) U[c] = su[c][tid];
-      rmin = DBL_MAX;
-#pragma unroll
-      for (int l = 0; l < NP; ++l) rmin = fmin(rmin, srow[el][0][l]);
-    }
   }
-  uint8_t f = 0;
+  // positivity scaling: S_p and the pressure minimum over the nodes by the element's five threads, the
+  // two factors by one of them, applied as the nodes are written
+  const double eps_r = 64.0 * EPSM;
   if (do_pp) {
-    // positivity scaling: the S_p and pressure extrema are reduced per row (NP tasks per
-    // element), then over the rows by every thread
-    const double eps_r = 64.0 * EPSM;
-    const bool collapse_r = !(a[0] > eps_r);
-    double thr = 1.0;
-    if (act && !collapse_r && rmin < eps_r) {
-      thr = fmin(1.0, fmax(0.0, (a[0] - eps_r) / (a[0] - rmin)));
-      f |= 1;
-      U[0] = a[0] + thr * (U[0] - a[0]);  // density-limited state of this node
-    }
+    double a0 = 0.0, thr = 1.0;
+    bool collapse = false;
     if (act) {
-      st[0][tid] = Sp(U, eps_r);
-      st[1][tid] = pres(U, g);
-    }
-    __syncthreads();
-    for (int t = q; act && t < NP; t += NN) {
+      a0 = sa[0][el];
+      collapse = !(a0 > eps_r);
+      const double rmin = srmin[el];
+      if (!collapse && rmin < eps_r) thr = fmin(1.0, fmax(0.0, (a0 - eps_r) / (a0 - rmin)));
       double S = 0.0, pm = DBL_MAX;
 #pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        S = fmax(S, st[0][el * NN + t * NP + k]);
-        pm = fmin(pm, st[1][el * NN + t * NP + k]);
+      for (int k = 0; k < (NN + 4) / 5; ++k) {
+        const int q = c + 5 * k;
+        if (q < NN) {
+          double U[5];
+#pragma unroll
+          for (int d = 0; d < 5; ++d) U[d] = su[d][el * ES + q];
+          if (thr != 1.0) U[0] = a0 + thr * (U[0] - a0);
+          S = fmax(S, Sp(U, eps_r));
+          pm = fmin(pm, pres(U, g));
+        }
       }
-      srow[el][1][t] = S;
-      srow[el][2][t] = pm;
+      sred[0][c][el] = S;
+      sred[1][c][el] = pm;
     }
     __syncthreads();
-    if (act && !collapse_r) {
-      double S = Sp(a, eps_r), pmin = DBL_MAX;
+    if (act && c == 0) {
+      double a[5], thp = 1.0;
+      int f = 0;
 #pragma unroll
-      for (int l = 0; l < NP; ++l) { S = fmax(S, srow[el][1][l]); pmin = fmin(pmin, srow[el][2][l]); }
-      const double eps_p = fmax(64.0 * EPSM, 8192.0 * EPSM * S);
-      const double pb = pres(a, g);
-      if (pb <= eps_p) {
-        f |= 4;
+      for (int d = 0; d < 5; ++d) a[d] = sa[d][el];
+      if (collapse) {
+        f = 4;
+      } else {
+        f = srmin[el] < eps_r ? 1 : 0;
+        double S = Sp(a, eps_r), pmin = DBL_MAX;
 #pragma unroll
-        for (int c = 0; c < 5; ++c) U[c] = a[c];
-      } else if (pmin < eps_p) {
-        const double thp = fmin(1.0, fmax(0.0, (pb - eps_p) / (pb - pmin)));
-        f |= 2;
-#pragma unroll
-        for (int c = 0; c < 5; ++c) U[c] = a[c] + thp * (U[c] - a[c]);
+        for (int d = 0; d < 5; ++d) { S = fmax(S, sred[0][d][el]); pmin = fmin(pmin, sred[1][d][el]); }
+        const double eps_p = fmax(64.0 * EPSM, 8192.0 * EPSM * S);
+        const double pb = pres(a, g);
+        if (pb <= eps_p) {
+          f |= 4;
+        } else if (pmin < eps_p) {
+          thp = fmin(1.0, fmax(0.0, (pb - eps_p) / (pb - pmin)));
+          f |= 2;
+        }
       }
-    } else if (act && collapse_r) {
-      f = 4;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) U[c] = a[c];
-    }
-  }
-  if (act) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) bst(node_rsrc(Uout + c * KN, KN), no, U[c]);
-    if (rho_o) {  // primitive copy for the magnetic substep (the conversion's arithmetic)
-      const double r = U[0], ux = U[1] / r, uy = U[2] / r, uz = U[3] / r;
-      bst(node_rsrc(rho_o, KN), no, r);
-      bst(node_rsrc(u_o, KN), no, ux); bst(node_rsrc(u_o + KN, KN), no, uy); bst(node_rsrc(u_o + 2 * KN, KN), no, uz);
-      bst(node_rsrc(e_o, KN), no, (U[4] - 0.5 * r * (ux * ux + uy * uy + uz * uz)) / r);
-    }
-    if (q == 0) {
-      if (flags) flags[e] = f;
+      sth[0][el] = thr;
+      sth[1][el] = (f & 4) ? -1.0 : thp;  // -1: collapsed to the average
+      if (flags) flags[e] = (uint8_t)f;
       if (counts && f) {
         if (f & 1) atomicAdd(&counts[0], 1ull);
         if (f & 2) atomicAdd(&counts[1], 1ull);
         if (f & 4) atomicAdd(&counts[2], 1ull);
       }
     }
+    __syncthreads();
+  } else if (act && c == 0 && flags) {
+    flags[e] = 0;
+  }
+#pragma unroll
+  for (int m = 0; m < NR; ++m) {
+    const int n = tid + m * BS;
+    if (n >= nel * NN) continue;
+    const unsigned no = ((unsigned)e0 * NN + n) * 8u;
+    const int en = n / NN, k = en * ES + n % NN;
+    double U[5];
+#pragma unroll
+    for (int d = 0; d < 5; ++d) U[d] = su[d][k];
+    if (do_pp) {
+      const double thr = sth[0][en], thp = sth[1][en];
+      if (thr != 1.0) U[0] = sa[0][en] + thr * (U[0] - sa[0][en]);
+      if (thp != 1.0) {
+#pragma unroll
+        for (int d = 0; d < 5; ++d) U[d] = thp < 0.0 ? sa[d][en] : sa[d][en] + thp * (U[d] - sa[d][en]);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 5; ++d) bst(node_rsrc(Uout + d * KN, KN), no, U[d]);
+    if (rho_o) {  // primitive copy for the magnetic substep (the conversion's arithmetic)
+      const double r = U[0], ux = U[1] / r, uy = U[2] / r, uz = U[3] / r;
+      bst(node_rsrc(rho_o, KN), no, r);
+      bst(node_rsrc(u_o, KN), no, ux); bst(node_rsrc(u_o + KN, KN), no, uy); bst(node_rsrc(u_o + 2 * KN, KN), no, uz);
+      bst(node_rsrc(e_o, KN), no, (U[4] - 0.5 * r * (ux * ux + uy * uy + uz * uz)) / r);
+    }
   }
 }
 
-template <int P, int BS>
-__global__ __launch_bounds__(BS) void k_hydro_oe_pp(const double* __restrict__ Ust, double* __restrict__ Uout,
-                                                     const double* __restrict__ stats, const double* __restrict__ lines,
-                                                     const double* __restrict__ glob, uint8_t* __restrict__ flags,
+template <int P>
+__global__ __launch_bounds__(OM<P>::BS) void k_hydro_oe_pp(const double* __restrict__ Ust, double* __restrict__ Uout,
+                                                     const double* __restrict__ stats, const double* __restrict__ Dfac,
+                                                     uint8_t* __restrict__ flags,
                                                      unsigned long long* __restrict__ counts,
                                                      const int* __restrict__ flag, const HydroTab* __restrict__ T,
-                                                     MeshP mp, double tau, double sH, int do_oe, int do_pp,
+                                                     MeshP mp, int do_oe, int do_pp,
                                                      double* __restrict__ rho_o, double* __restrict__ e_o,
                                                      double* __restrict__ u_o) {
-  hydro_oe_pp_body<P, BS>(Ust, Uout, stats, lines, glob, flags, counts, flag, T, mp, tau, sH, do_oe, do_pp, rho_o, e_o, u_o, xcd_block());
+  hydro_oe_pp_body<P>(Ust, Uout, stats, Dfac, flags, counts, flag, T, mp, do_oe, do_pp, rho_o, e_o, u_o, xcd_block());
 }
 
 struct hydro_oe_pp_args {
   const double* Ust;
   double* Uout;
   const double* stats;
-  const double* lines;
-  const double* glob;
+  const double* Dfac;
   uint8_t* flags;
   unsigned long long* counts;
   const int* flag;
   const HydroTab* T;
   MeshP mp;
-  double tau;
-  double sH;
   int do_oe;
   int do_pp;
   double* rho_o;
@@ -842,11 +967,11 @@ struct hydro_oe_pp_args {
   double* u_o;
 };
 
-template <int P, int BS>
-__global__ __launch_bounds__(BS) void k_hydro_oe_pp_rt(const hydro_oe_pp_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int P>
+__global__ __launch_bounds__(OM<P>::BS) void k_hydro_oe_pp_rt(const hydro_oe_pp_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const hydro_oe_pp_args& a = A[r];
-  hydro_oe_pp_body<P, BS>(gl(a.Ust), gl(a.Uout), gl(a.stats), gl(a.lines), gl(a.glob), gl(a.flags), gl(a.counts), gl(a.flag), gl(a.T), a.mp, a.tau, a.sH, a.do_oe, a.do_pp, gl(a.rho_o), gl(a.e_o), gl(a.u_o), (long)blockIdx.x - boff[r]);
+  hydro_oe_pp_body<P>(gl(a.Ust), gl(a.Uout), gl(a.stats), gl(a.Dfac), gl(a.flags), gl(a.counts), gl(a.flag), gl(a.T), a.mp, a.do_oe, a.do_pp, gl(a.rho_o), gl(a.e_o), gl(a.u_o), (long)blockIdx.x - boff[r]);
 }
 
 // Connectivity export: nbr[K][4] (left, right, bottom, top neighbour) and the face map
@@ -1178,30 +1303,32 @@ int hydro_stats_only(mhd25_ctx* c, const double* U, int* flag) {
   return check(c, hipGetLastError(), "stats launch");
 }
 
-// threads per block of the OE/PP map: its LDS use (about 35 KB at N = 4 with 256 threads) caps a CU
-// at 4 such blocks, 4 waves per SIMD; with 128 threads the registers allow 5 waves per SIMD, which
-// measured 10 % faster on the 1024^2, N = 4 workload
-#ifndef MHD_OE_BS
-#define MHD_OE_BS 128
-#endif
-
+// The stage map: the OE sensor (damping factors, into the context's dfac), then the map itself.
 // rho_o, e_o, u_o: optional primitive outputs (all null or all set)
 int hydro_stage_b(mhd25_ctx* c, const double* Ust, double* Uout, double tau, const int* flag, double* rho_o,
                   double* e_o, double* u_o) {
-  constexpr int BS = MHD_OE_BS;
-  const int eb = BS / ((c->p + 1) * (c->p + 1));
-  const long blocks = (c->mp.K + eb - 1) / eb;
+  const long sblocks = (long)((c->mp.nx + HS<1>::TX - 1) / HS<1>::TX) * ((c->mp.ny + HS<1>::TY - 1) / HS<1>::TY);
+  const long blocks = (c->mp.K + OM<1>::EB - 1) / OM<1>::EB;
   if (c->rec) {
+    if (c->opt.oe_hydro)
+      rt_record(c, RT_HYDRO_SENSOR, c->p, sblocks,
+                hydro_sensor_args{Ust, c->stats, c->lines, c->glob, c->dfac, flag, c->d_ht, c->mp, tau, c->opt.s_H});
     rt_record(c, RT_OE_PP, c->p, blocks,
-              hydro_oe_pp_args{Ust, Uout, c->stats, c->lines, c->glob, c->d_flags, c->d_counts, flag, c->d_ht, c->mp,
-                               tau, c->opt.s_H, c->opt.oe_hydro, c->opt.pp, rho_o, e_o, u_o});
+              hydro_oe_pp_args{Ust, Uout, c->stats, c->dfac, c->d_flags, c->d_counts, flag, c->d_ht, c->mp,
+                               c->opt.oe_hydro, c->opt.pp, rho_o, e_o, u_o});
     return 0;
   }
   hipEvent_t* ev = c->timing ? timing_slot(c, 1) : nullptr;
   if (ev) hipEventRecord(ev[0], c->stream);
-#define LB(P) hipLaunchKernelGGL((k_hydro_oe_pp<P, BS>), dim3(blocks), dim3(BS), 0, c->stream, Ust, Uout, c->stats, \
-                                 c->lines, c->glob, c->d_flags, c->d_counts, flag, c->d_ht, c->mp, tau, c->opt.s_H, \
-                                 c->opt.oe_hydro, c->opt.pp, rho_o, e_o, u_o)
+  if (c->opt.oe_hydro) {
+#define LS(P) hipLaunchKernelGGL((k_hydro_sensor<P>), dim3(sblocks), dim3(HS<P>::BS), 0, c->stream, Ust, c->stats, c->lines, \
+                                 c->glob, c->dfac, flag, c->d_ht, c->mp, tau, c->opt.s_H)
+    DISPATCH_P(c->p, LS);
+#undef LS
+  }
+#define LB(P) hipLaunchKernelGGL((k_hydro_oe_pp<P>), dim3(blocks), dim3(OM<P>::BS), 0, c->stream, Ust, Uout, c->stats, \
+                                 c->dfac, c->d_flags, c->d_counts, flag, c->d_ht, c->mp, c->opt.oe_hydro, c->opt.pp, rho_o, \
+                                 e_o, u_o)
   DISPATCH_P(c->p, LB);
 #undef LB
   if (ev) hipEventRecord(ev[1], c->stream);
@@ -1312,9 +1439,16 @@ int hydro_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int 
 #undef RS
       break;
     }
+    case RT_HYDRO_SENSOR: {
+      const hydro_sensor_args* A = (const hydro_sensor_args*)dargs;
+#define RV(P_) hipLaunchKernelGGL((k_hydro_sensor_rt<P_>), g, dim3(HS<P_>::BS), 0, s, A, dboff, nr)
+      DISPATCH_P(h.key, RV);
+#undef RV
+      break;
+    }
     case RT_OE_PP: {
       const hydro_oe_pp_args* A = (const hydro_oe_pp_args*)dargs;
-#define RO(P_) hipLaunchKernelGGL((k_hydro_oe_pp_rt<P_, MHD_OE_BS>), g, dim3(MHD_OE_BS), 0, s, A, dboff, nr)
+#define RO(P_) hipLaunchKernelGGL((k_hydro_oe_pp_rt<P_>), g, dim3(OM<P_>::BS), 0, s, A, dboff, nr)
       DISPATCH_P(h.key, RO);
 #undef RO
       break;

@@ -13,6 +13,17 @@ __device__ __forceinline__ long xcd_block() {
   return x * q + (x < r ? x : r) + (b >> 3);
 }
 
+// Tile (tx, ty) of block b of an ntx x nty grid of tiles: the blocks walk strips of TILE_STRIP tile columns,
+// row by row, so that a tile's lower neighbour ran TILE_STRIP blocks before it and its border is still in the
+// L2 (at 1024 x 1024 elements, N = 4, a whole row of 5 x 4 tiles is 4 MB, an L2's size).
+constexpr int TILE_STRIP = 16;
+__device__ __forceinline__ void tile_of(int b, int ntx, int nty, int& tx, int& ty) {
+  const int s = b / (TILE_STRIP * nty), r = b - s * (TILE_STRIP * nty);
+  const int w = ntx - s * TILE_STRIP < TILE_STRIP ? ntx - s * TILE_STRIP : TILE_STRIP;
+  ty = r / w;
+  tx = s * TILE_STRIP + (r - ty * w);
+}
+
 // Run-table launches: one launch covers several independent runs, whose blocks are consecutive
 // ranges; boff[r] is the first block of run r and boff[nr] the grid size.  Returns the run of the
 // calling block (the same for all its threads) by bisection.  The result is declared wave-uniform

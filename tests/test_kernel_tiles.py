@@ -92,7 +92,25 @@ def check_hydro_substep(run, p, m, nx, ny):
         close(out[0][c], want[c], "component %d" % c)
 
 
-CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep]
+def check_stage_map(run, p, m, nx, ny):
+    """The OE sensor's tiles and the map's blocks, with OE alone, PP alone, both and neither, on states whose
+    limiter acts (decisions bit for bit)."""
+    import paper_2609_10849_amd as pk
+    from tests.test_gpu_hydro import stressed_state
+    L, U = stressed_state(nx, ny, p, seed=30 + p)
+    L.m = m  # (stressed_state's own choice is of no use here)
+    L.M1 = m + 1
+    M = omesh(L)
+    for oe, pp in ((1, 0), (0, 1), (1, 1), (0, 0)):
+        tau = 0.013 if not oe else 1e-7
+        want, flags, _, _ = O.hydro_stage_map(M, O.Options(oe_hydro=oe, pp=pp), U, tau)
+        out = run(L, pk.Options.make(oe_hydro=oe, pp=pp), "mhd25_hydro_stage_map", [U, tau, np.zeros(L.K, np.uint8)])
+        assert (out[2] == flags).all()
+        for c in range(5):
+            close(out[0][c], want[c], "component %d, oe %d, pp %d" % (c, oe, pp))
+
+
+CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep, check_stage_map]
 
 
 @pytest.mark.parametrize("nx,ny", SMALL)
