@@ -38,9 +38,8 @@ def kernel_table(N, k):
     averages over the launches of a step (see stage_bytes, oe_pp_bytes)."""
     NP, nn = N + 1, (N + 1) ** 2
     A, B = k + 2, k + 1
-    psi = nn * (N * N + (N * N) % 2) * 8  # the basis table: N^2 modes at each node
+    psi = nn * (nn + (nn % 2)) * 8  # the basis values of all (N+1)^2 modes (the kernels hold the N^2 below the last shell)
     grid3 = 3 * B * B * 8
-    loads = (2 * A * B + A * A) * 8
     y = 4 * nn * 8 + grid3  # (e, u, B) of one element
     blk = lambda bs, nt: (bs // nt) * nt / bs
     nt = max(nn, A * A)
@@ -55,10 +54,9 @@ def kernel_table(N, k):
          psi + 3 * nn * 8 + 2 * nn * 8 + NP * 8 + 4 * nn * 8, None, blk(128, nn)),
         (4, "velocity-OE preparation (Gram, Cholesky, basis)", "k_vel_prep<", "magnetic.hip",
          nn * 8 + psi, None, blk(256, nn)),
-        (5, "E loads", "k_E_loads<", "magnetic.hip", 3 * nn * 8 + 2 * grid3 + 8 + loads, None, blk(128, nt)),
+        (5, "E reconstruction", "k_E<", "magnetic.hip", 3 * nn * 8 + 3 * grid3 + 8, None, 1.0),
         (6, "velocity-OE sensor", "k_vel_sensor<", "magnetic.hip", 4 * nn * 8 + grid3 + NP * 8, None, blk(256, nn)),
-        (7, "J loads", "k_J_loads<", "magnetic.hip", grid3 + loads, None, blk(256, nt)),
-        (8, "gathers of shared DOFs", "k_gather<", "magnetic.hip", loads + grid3, None, 1.0),
+        (7, "J reconstruction", "k_J<", "magnetic.hip", 2 * grid3, None, 1.0),
         (9, "A.R. traces", "k_ar_traces<", "magnetic.hip", 4 * nn * 8 + grid3 + (8 * A + 2) * 8, None, blk(256, nn)),
     ]
 

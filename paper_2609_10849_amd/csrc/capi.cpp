@@ -117,7 +117,7 @@ void mhd25_destroy(mhd25_ctx* c) {
   if (!c) return;
   void* ptrs[] = {c->d_ht, c->d_mt, c->Un, c->S1, c->S2, c->Ust, c->stats, c->lines, c->glob, c->d_flag,
                   c->d_counts, c->d_flags, c->rho, c->e, c->u, c->eta, c->Y1, c->Y2, c->JE,
-                  c->loads, c->saveU, c->saveB, c->red, c->snapU, c->vjp_scratch, c->psi, c->artr, c->dfac};
+                  c->saveU, c->saveB, c->red, c->snapU, c->vjp_scratch, c->psi, c->artr, c->dfac};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->h_pinned) (void)hipHostFree(c->h_pinned);
@@ -156,21 +156,7 @@ int mhd25_init(const mhd25_mesh_desc* mesh, const mhd25_options* opt, void* stre
   c->G = (long)d.nx * d.ny * c->M1 * c->M1;
   build_hydro_tables(c->p, &c->h_ht);
   build_mag_tables(c->p, c->m, &c->h_mt);
-  {  // reciprocal lumped weights of the gathered nodes (a shared node adds its neighbours' weights)
-    const int A = c->m + 2, B = c->m + 1;
-    const MagTab& t = c->h_mt;
-    for (int j = 0; j < B; ++j)
-      for (int i = 0; i < B; ++i) {
-        const long double wx = (long double)t.ww[i] + (i == 0 ? t.ww[A - 1] : 0.0L);
-        const long double wy = (long double)t.ww[j] + (j == 0 ? t.ww[A - 1] : 0.0L);
-        const long double J = c->mp.J;
-        c->h_mt.rjw[0][j][i] = (double)(1.0L / (J * wx * wy));               // W: GLL in x and y
-        c->h_mt.rjw[1][j][i] = (double)(1.0L / (J * (long double)t.wg[i] * wy));  // N_x: Gauss in x
-        c->h_mt.rjw[2][j][i] = (double)(1.0L / (J * wx * (long double)t.wg[j]));  // N_y: Gauss in y
-      }
-  }
   const long K = c->mp.K, KN = K * c->nn, n5 = 5 * KN, G = c->G;
-  const int a = c->m + 2, b = c->m + 1;
   const long ny_ = d.ny, nx_ = d.nx;
   auto alloc = [&](void** p, size_t bytes) -> int {
     hipError_t e = hipMalloc(p, bytes ? bytes : 8);
@@ -198,7 +184,6 @@ int mhd25_init(const mhd25_mesh_desc* mesh, const mhd25_options* opt, void* stre
   r = r ? r : alloc((void**)&c->Y1, ny * 8);
   r = r ? r : alloc((void**)&c->Y2, ny * 8);
   r = r ? r : alloc((void**)&c->JE, 6 * G * 8);
-  r = r ? r : alloc((void**)&c->loads, K * (2 * a * b + a * a) * 8);
   r = r ? r : alloc((void**)&c->saveU, n5 * 8);
   r = r ? r : alloc((void**)&c->saveB, 3 * G * 8);
   r = r ? r : alloc((void**)&c->snapU, n5 * 8);

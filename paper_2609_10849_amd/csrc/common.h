@@ -46,10 +46,11 @@ struct MagTab {
   double D_W_V[MHD_MAXN][MHD_MAXN], I_G_V[MHD_MAXN][MHD_MAXN];
   double I_G_E[2][MHD_MAXN], I_V_E[2][MHD_MAXN];   // basis values at -1 and +1
   double I_V_Q[MHD_MAXN][MHD_MAXN];
-  // 1 / (|J_K| w) of a gathered node, per local position [j][i] < m+1 of its owning element: the
-  // lumped weight w sums the contributions of every element sharing the node (W, N_x, N_y nodes).
-  // Mesh dependent: set by mhd25_init.
-  double rjw[3][MHD_MAXN][MHD_MAXN];
+  // Operators of the J and E reconstruction, row i divided by the assembled 1D weight of node i (GLL_{m+1}
+  // end nodes are shared by two elements): the exact mass matrix of W, the weak derivative of W against
+  // Gauss_m and GLL_m nodal fields, and the mass matrices of W and Gauss_m by the GLL_p rule.
+  double RWQ[MHD_MAXN][MHD_MAXN], RDG[MHD_MAXN][MHD_MAXN], RDV[MHD_MAXN][MHD_MAXN];
+  double RWP[MHD_MAXN][MHD_MAXN], RGP[MHD_MAXN][MHD_MAXN];
 };
 
 // velocity-OE basis table per element of degree p: (p+1)^2 rows (one per node) of the p^2 modes of the
@@ -141,7 +142,7 @@ struct MagIO {
 // instead of launching; a plan zips the records of all runs into run-table launches.
 enum RtKind {
   RT_HYDRO_STAGE, RT_OE_PP, RT_LINE_REDUCE, RT_GLOBAL_REDUCE, RT_RESET, RT_COPY, RT_SNAP_U, RT_COPY_CHECK,
-  RT_TO_PRIM, RT_TO_CONS, RT_J_LOADS, RT_E_LOADS, RT_GATHER, RT_MAG_UPDATE, RT_VEL_PREP, RT_VEL_SENSOR,
+  RT_TO_PRIM, RT_TO_CONS, RT_J, RT_E, RT_MAG_UPDATE, RT_VEL_PREP, RT_VEL_SENSOR,
   RT_VEL_PROJ, RT_B_STATS, RT_AR_TRACES, RT_AR_ETA, RT_MAX, RT_BATCH_ZERO, RT_BATCH_FOLD, RT_HYDRO_SENSOR, RT_NKIND
 };
 struct RtRecord {
@@ -168,7 +169,7 @@ struct mhd25_ctx {
   unsigned long long* d_counts;  // [3] per attempt
   uint8_t* d_flags;
   // magnetic workspace
-  double *rho, *e, *u, *eta, *Y1, *Y2, *Ys, *JE, *loads, *bstat;
+  double *rho, *e, *u, *eta, *Y1, *Y2, *Ys, *JE, *bstat;
   double *saveU, *saveB, *snapU;
   double* red;  // scratch for small reductions
   double* vjp_scratch;  // allocated on the first magnetic VJP

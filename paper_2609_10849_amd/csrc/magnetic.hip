@@ -1,10 +1,9 @@
 // Magnetic-velocity subflow kernels for gfx950 (section "Magnetic--velocity subflow:
 // compatible finite elements").
 //
-// Element-local kernels use one block per tile of EB elements and NT = max((p+1)^2,(m+2)^2)
-// threads per element; element data are staged in LDS.  Loads of shared degrees of freedom
-// are written per element and summed by a per-node gather in a fixed order (no floating-point
-// atomics), then divided by the lumped weights (eq. quad-hcurl-element, eq. quad-cg-element).
+// Element-local kernels use one block per tile of EB elements; element data are staged in LDS.  Shared
+// degrees of freedom are assembled by the tile that owns them, in a fixed order (no floating-point
+// atomics), with the lumped weights of eq. quad-hcurl-element and eq. quad-cg-element.
 #include <cfloat>
 #include <mutex>
 #include <string>
@@ -51,340 +50,508 @@ __device__ __forceinline__ void load_B(double* bx, double* by, double* bz, const
 }
 
 // ---------------------------------------------------------------------------------------------
-// Current loads (eq. mag-current-proj): W part int B_x d_y phi - B_y d_x phi with the (m+2)-point
-// Gauss rule; N parts int B_z (-d_y psi) and int B_z d_x psi with the (m+1)-point rule.
+// Reconstruction of J (eq. mag-current-proj) and E (eq. mag-electric-proj) on the auxiliary grids.
+//
+// Both are assembled on tiles of TX x TY elements: a task forms one grid row of an element (row tasks of
+// the W rows, for the x and z components, on the block's first waves; of the Gauss rows, for the y
+// component, on the others).  At the shared node of a row it adds the left element's contribution, whose
+// operands it reads too; row A-1 of the element below a tile element is a task of the tile, added to that
+// element's row 0 through LDS.  So every node is written once, by its owner, and no per-element loads pass
+// through memory: with a load kernel and a gather per field these moved 1 040 B more per element and
+// field at k = 3.  The 1D operators along x are scalars (compile-time indices), those along y are the
+// task's own row of the table.
+//
+// Lumped weights: with W_i the assembled 1D weight of node i, the tables RWQ.. hold the 1D operators with
+// row i divided by W_i (|J_K| cancels).
 // ---------------------------------------------------------------------------------------------
-template <int P, int M, int BS, bool R2>
-__device__ __forceinline__ void J_loads_body(const double* __restrict__ Bx, const double* __restrict__ By,
-                                                 const double* __restrict__ Bz, double* __restrict__ Lx,
-                                                 double* __restrict__ Ly, double* __restrict__ Lz,
-                                                 const MagTab* __restrict__ T, MeshP mp, long blk) {
-  using C = MC<P, M, BS>;
-  constexpr int A = C::A, B = C::B, AA = C::AA, AB = C::AB, BB = C::BB, EB = C::EB, NT = C::NT;
-  __shared__ double sbx[EB][AB], sby[EB][AB], sbz[EB][BB], swx[EB][AA], swy[EB][AA], szg[EB][BB];
-  __shared__ double sh[EB][2][AA];  // first half of the sum factorisation of the W loads
-  __shared__ double tWQ[A][A], tGQ[A][B], tDWQ[A][A], tVG[B][B], tDWG[B][A], twq[A], twg[B];
-  const int tid = threadIdx.x, el = tid / NT, t = tid - el * NT;
-  const long e = blk * EB + el;
-  const bool act = el < EB && e < mp.K;
-  long ex, ey;
-  elem_xy(mp, act ? e : 0, ex, ey);
-  for (int k = tid; k < A * A; k += BS) {
-    tWQ[k / A][k % A] = T->I_W_Q[k / A][k % A];
-    tDWQ[k / A][k % A] = T->D_W_Q[k / A][k % A];
+template <int M, bool R2>
+struct RT {
+  static constexpr int A = M + 2, B = M + 1;
+  // tile sizes that fill the row tasks' waves: A TE of the W rows, B TE of the Gauss rows
+  static constexpr int TX = M == 2 || M >= 5 ? 4 : 5, TY = M == 3 ? 5 : 4, TE = TX * TY;
+  static constexpr int WW = (A * TE + 63) / 64 * 64;  // threads of the W rows (whole waves)
+  static constexpr int BS = R2 ? WW : WW + (B * TE + 63) / 64 * 64;
+};
+
+// A patch of NR x NC nodes of a periodic magnetic grid on its way to LDS: the loads of several patches
+// are issued before the first is waited for.  In LDS node (row y B + j, column x B + i) lies at
+// y RS + j PITCH + i W + x with RS = TX (mod 16), so that 16 lanes of neighbouring elements, TX to a row, read
+// 16 neighbouring doubles, all banks (in the grid's own order their stride of B doubles conflicts).
+template <int NR, int NC, int B, int TX, int BS>
+struct Patch {
+  static constexpr int N = NR * NC, R = (N + BS - 1) / BS, W = (NC + B - 1) / B, PITCH = W * B;
+  static constexpr int RS = B * PITCH + (TX - B * PITCH % 16 + 16) % 16, SIZE = (NR + B - 1) / B * RS;
+  // offset of node (i, j) from its element's (x, y) (i = B or j = B: the next element's first node)
+  static __device__ __forceinline__ constexpr int at(int i, int j = 0) { return (i < B ? i * W : 1) + (j < B ? j * PITCH : RS); }
+  double v[R];
+  // nodes (gy0 + r, gx0 + c), r < nr, c < nc (at most one period away from the grid)
+  __device__ __forceinline__ void load(const double* __restrict__ f, const MeshP& mp, int gx0, int gy0, int nc, int nr) {
+    const int NXg = mp.nx * B, NYg = mp.ny * B;
+    const auto rs = node_rsrc(f, (long)NXg * NYg);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int n = threadIdx.x + k * BS, r = n / NC, c = n - r * NC;
+      v[k] = 0.0;
+      if (r < nr && c < nc) v[k] = bld(rs, (unsigned)(wrap32(gy0 + r, NYg) * NXg + wrap32(gx0 + c, NXg)) * 8u);
+    }
   }
-  for (int k = tid; k < A * B; k += BS) tGQ[k / B][k % B] = T->I_G_Q[k / B][k % B];
-  for (int k = tid; k < B * B; k += BS) tVG[k / B][k % B] = T->I_V_G[k / B][k % B];
-  for (int k = tid; k < B * A; k += BS) tDWG[k / A][k % A] = T->D_W_G[k / A][k % A];
-  if (tid < A) twq[tid] = T->wq[tid];
-  if (tid < B) twg[tid] = T->wg[tid];
-  if (act) load_B<P, M, R2>(sbx[el], sby[el], sbz[el], Bx, By, Bz, mp, ex, ey, t);
+  __device__ __forceinline__ void store(double* s) const {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int n = threadIdx.x + k * BS, r = n / NC, c = n - r * NC;
+      if (n < N) s[r / B * RS + r % B * PITCH + c % B * W + c / B] = v[k];
+    }
+  }
+};
+
+// sum_k t[k] f[k * step] of an N-term row
+template <int N>
+__device__ __forceinline__ double dot_col(const double* t, const double* f, int step) {
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) s = fma(t[k], f[k * step], s);
+  return s;
+}
+
+// the same down N nodes of column i of an element at f in a patch
+template <class Q, int N>
+__device__ __forceinline__ double dot_patch(const double* t, const double* f, int i) {
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) s = fma(t[k], f[Q::at(i, k)], s);
+  return s;
+}
+
+// The thread's row task: W row j (or Gauss row j) of tile element (lx, ly); ye is the element row it reads,
+// ly, or ly - 1 for the row A-1 of the element below.
+template <int M, bool R2>
+struct RowTask {
+  bool w, act, below;
+  int j, lx, ly, ye, el;
+  __device__ __forceinline__ RowTask(int tw, int th) {
+    using C = RT<M, R2>;
+    w = R2 || __builtin_amdgcn_readfirstlane(threadIdx.x < C::WW ? 1 : 0);
+    const int t = threadIdx.x - (w ? 0 : C::WW);
+    j = t / C::TE; el = t - j * C::TE;
+    ly = el / C::TX; lx = el - ly * C::TX;
+    act = j < (w ? C::A : C::B) && lx < tw && ly < th;
+    below = w && j == C::A - 1;
+    ye = below ? ly - 1 : ly;
+  }
+};
+
+// J: int B_x d_y phi - B_y d_x phi with the (m+2)-point Gauss rule (z), int B_z (-d_y psi) and int B_z d_x psi
+// with the (m+1)-point rule (x, y), each as one operator per direction.
+// Measured: 1024^2, N = 4, k = 3: 0.66 (load kernel and gather) -> 0.29 ms; 128^2, N = k = 4: 28 -> 13 us.  Bound by the
+// latency of its staging loads and barriers (1.3 GB moved).
+template <int P, int M, bool R2>
+__device__ __forceinline__ void J_body(const double* __restrict__ Bx, const double* __restrict__ By,
+                                       const double* __restrict__ Bz, double* __restrict__ Jx, double* __restrict__ Jy,
+                                       double* __restrict__ Jz, const MagTab* __restrict__ T, const MeshP& mp, int blk) {
+  using C = RT<M, R2>;
+  constexpr int A = C::A, B = C::B, TX = C::TX, TY = C::TY, TE = C::TE, BS = C::BS;
+  // the tile's elements, the column left of it and the row below
+  using PX = Patch<(TY + 1) * B, (TX + 1) * B + 1, B, TX, BS>;
+  using PY = Patch<(TY + 1) * B + 1, (TX + 1) * B, B, TX, BS>;
+  using PZ = Patch<(TY + 1) * B, (TX + 1) * B, B, TX, BS>;
+  __shared__ double sx[PX::SIZE], sy[PY::SIZE], sz[R2 ? 1 : PZ::SIZE], sbel[2][TE][B];
+  int tx0, ty0;
+  tile_of(blk, (mp.nx + TX - 1) / TX, (mp.ny + TY - 1) / TY, tx0, ty0);
+  tx0 *= TX; ty0 *= TY;
+  const int tw = mp.nx - tx0 < TX ? mp.nx - tx0 : TX, th = mp.ny - ty0 < TY ? mp.ny - ty0 : TY;
+  {
+    PX px;
+    PY py;
+    const int gx0 = (tx0 - 1) * B, gy0 = (ty0 - 1) * B;
+    px.load(Bx, mp, gx0, gy0, (tw + 1) * B + 1, (th + 1) * B);
+    py.load(By, mp, gx0, gy0, (tw + 1) * B, (th + 1) * B + 1);
+    if constexpr (!R2) {
+      PZ pz;
+      pz.load(Bz, mp, gx0, gy0, (tw + 1) * B, (th + 1) * B);
+      pz.store(sz);
+    }
+    px.store(sx);
+    py.store(sy);
+  }
+  const RowTask<M, R2> k(tw, th);
+  const int gx = (tx0 + k.lx) * B, gy = (ty0 + k.ly) * B + k.j, NXg = mp.nx * B;
+  double tq[A], td[B], tv[B];  // rows j of the tables along y
+  if (k.act) {
+#pragma unroll
+    for (int i = 0; i < A; ++i) tq[i] = k.w ? T->RWQ[k.j][i] : 0.0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) { td[i] = k.w ? T->RDG[k.j][i] : 0.0; tv[i] = k.w ? T->RDV[k.j][i] : T->I_V_G[k.j][i]; }
+  }
   __syncthreads();
-  if (act && t < AA) {
-    const int qx = t % A, qy = t / A;
-    double bxq = 0.0, byq = 0.0;
+  // the task's element in the patches
+  const double* const xe = sx + (k.ye + 1) * PX::RS + k.lx + 1;
+  const double* const yq = sy + (k.ye + 1) * PY::RS + k.lx + 1;
+  const double* const ze = sz + (k.ye + 1) * PZ::RS + k.lx + 1;
+  const double sX = 2.0 * mp.rhx, sY = 2.0 * mp.rhy;
+  double z[B], x[B];
+  if (k.act && k.w) {
+    double c[A], cl[B];  // Bx summed along y; cl: the left element's (its last node is this one's first)
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-      double s = 0.0;
+    for (int i = 0; i < A; ++i) c[i] = dot_patch<PX, B>(td, xe, i);
 #pragma unroll
-      for (int i = 0; i < A; ++i) s += tWQ[qx][i] * sbx[el][j * A + i];
-      bxq += tGQ[qy][j] * s;
+    for (int i = 0; i < B; ++i) cl[i] = dot_patch<PX, B>(td, xe - 1, i);
+    double d[B], dl[B];  // By
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      d[i] = dot_patch<PY, A>(tq, yq, i);
+      dl[i] = dot_patch<PY, A>(tq, yq - 1, i);
     }
 #pragma unroll
-    for (int j = 0; j < A; ++j) {
-      double s = 0.0;
+    for (int i = 0; i < B; ++i) {
+      double s = 0.0, t = 0.0;
 #pragma unroll
-      for (int i = 0; i < B; ++i) s += tGQ[qx][i] * sby[el][j * B + i];
-      byq += tWQ[qy][j] * s;
+      for (int q = 0; q < A; ++q) s = fma(T->RWQ[i][(i + q) % A], c[(i + q) % A], s);  // the diagonal, its largest term, first
+#pragma unroll
+      for (int q = 0; q < B; ++q) t = fma(T->RDG[i][q], d[q], t);
+      if (i == 0) {
+        s = fma(T->RWQ[A - 1][A - 1], c[0], s);
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+          s = fma(T->RWQ[A - 1][q], cl[q], s);
+          t = fma(T->RDG[A - 1][q], dl[q], t);
+        }
+      }
+      z[i] = sY * s - sX * t;
     }
-    const double wgt = mp.J * twq[qx] * twq[qy];
-    swx[el][t] = wgt * bxq;
-    swy[el][t] = wgt * byq;
+    if constexpr (!R2) {
+      double f[B];
+#pragma unroll
+      for (int i = 0; i < B; ++i) f[i] = dot_patch<PZ, B>(tv, ze, i);
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < B; ++q) s = fma(T->I_V_G[i][q], f[q], s);
+        x[i] = -sY * s;
+      }
+    }
+    if (k.below)
+#pragma unroll
+      for (int i = 0; i < B; ++i) { sbel[0][k.el][i] = z[i]; sbel[1][k.el][i] = R2 ? 0.0 : x[i]; }
   }
-  if (!R2 && act && t < BB) {  // B_z at the Gauss nodes (the N loads; none in the 2D2V system)
-    const int gx = t % B, gy = t / B;
-    double v = 0.0;
+  if constexpr (!R2) {
+    if (k.act && !k.w) {
+      double f[B], fl[B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-      double s = 0.0;
+      for (int i = 0; i < B; ++i) {
+        f[i] = dot_patch<PZ, B>(tv, ze, i);
+        fl[i] = dot_patch<PZ, B>(tv, ze - 1, i);
+      }
 #pragma unroll
-      for (int i = 0; i < B; ++i) s += tVG[gx][i] * sbz[el][j * B + i];
-      v += tVG[gy][j] * s;
+      for (int i = 0; i < B; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < B; ++q) s = fma(T->RDV[i][q], f[q], s);
+        if (i == 0)
+#pragma unroll
+          for (int q = 0; q < B; ++q) s = fma(T->RDV[A - 1][q], fl[q], s);
+        Jy[(long)gy * NXg + gx + i] = sX * s;
+      }
     }
-    szg[el][t] = v;
   }
   __syncthreads();
-  // W loads, factorised: sh[0][qy][i] = sum_qx I_W_Q[qx][i] swx[qy][qx], sh[1][qy][i] = sum_qx D_W_Q[qx][i] swy[qy][qx]
-  if (act && t < AA) {
-    const int i = t % A, qy = t / A;
-    double a0 = 0.0, a1 = 0.0;
+  if (k.act && k.w && !k.below) {
 #pragma unroll
-    for (int qx = 0; qx < A; ++qx) {
-      a0 += tWQ[qx][i] * swx[el][qy * A + qx];
-      a1 += tDWQ[qx][i] * swy[el][qy * A + qx];
-    }
-    sh[el][0][t] = a0;
-    sh[el][1][t] = a1;
-  }
-  __syncthreads();
-  if (!act) return;
-  if (t < AA) {
-    const int i = t % A, j = t / A;
-    double sx = 0.0, sy = 0.0;
-#pragma unroll
-    for (int qy = 0; qy < A; ++qy) {
-      sx += tDWQ[qy][j] * sh[el][0][qy * A + i];
-      sy += tWQ[qy][j] * sh[el][1][qy * A + i];
-    }
-    Lz[e * AA + t] = (2.0 * mp.rhy) * sx - (2.0 * mp.rhx) * sy;
-  }
-  if (!R2 && t < AB) {
-    {  // N_x node: i Gauss (B), j GLL (A); index j*B + i
-      const int i = t % B, j = t / B;
-      double s = 0.0;
-#pragma unroll
-      for (int qy = 0; qy < B; ++qy) s += twg[qy] * szg[el][qy * B + i] * tDWG[qy][j];
-      Lx[e * AB + t] = -(2.0 * mp.rhy) * mp.J * twg[i] * s;
-    }
-    {  // N_y node: i GLL (A), j Gauss (B); index j*A + i
-      const int i = t % A, j = t / A;
-      double s = 0.0;
-#pragma unroll
-      for (int qx = 0; qx < B; ++qx) s += twg[qx] * szg[el][j * B + qx] * tDWG[qx][i];
-      Ly[e * AB + t] = (2.0 * mp.rhx) * mp.J * twg[j] * s;
+    for (int i = 0; i < B; ++i) {
+      const long g = (long)gy * NXg + gx + i;
+      Jz[g] = k.j == 0 ? z[i] + sbel[0][k.el][i] : z[i];
+      if (!R2) Jx[g] = k.j == 0 ? x[i] + sbel[1][k.el][i] : x[i];
     }
   }
 }
 
-template <int P, int M, int BS, bool R2>
-__global__ __launch_bounds__(BS) void k_J_loads(const double* __restrict__ Bx, const double* __restrict__ By,
-                                                 const double* __restrict__ Bz, double* __restrict__ Lx,
-                                                 double* __restrict__ Ly, double* __restrict__ Lz,
+// E: -u x B at the nodes, averaged over the elements that share the node (their lumped weights are equal),
+// plus eta_K sum_q M_q J(x_q) . phi_a(x_q) by the degree-p GLL rule, i.e. the 1D operators RWP / RGP applied
+// to J; blocks whose elements all have eta = 0 skip that term.
+// Measured: 1024^2, N = 4, k = 3, with resistivity: 1.08 (load kernel and gather) -> 0.55 ms; 128^2, N = k = 4, without:
+// 36 -> 17.5 us.  Bound by LDS reads and latency (2.0 GB moved).
+template <int P, int M, bool R2>
+__device__ __forceinline__ void E_body(const double* __restrict__ u, const double* __restrict__ Bx,
+                                       const double* __restrict__ By, const double* __restrict__ Bz,
+                                       const double* __restrict__ Jx, const double* __restrict__ Jy,
+                                       const double* __restrict__ Jz, const double* __restrict__ eta,
+                                       double* __restrict__ Ex, double* __restrict__ Ey, double* __restrict__ Ez,
+                                       const MagTab* __restrict__ T, const MeshP& mp, int blk) {
+  using C = RT<M, R2>;
+  constexpr int A = C::A, B = C::B, TX = C::TX, TY = C::TY, TE = C::TE, BS = C::BS;
+  constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1, NU = R2 ? 2 : 3;
+  constexpr int NE = (TX + 1) * (TY + 1);  // staged elements: the tile's, the column left of it, the row below
+  using PX = Patch<(TY + 1) * B, TX * B, B, TX, BS>;  // B_x: the row below
+  using PY = Patch<TY * B, (TX + 1) * B, B, TX, BS>;  // B_y: the column left
+  using PZ = Patch<(TY + 1) * B, (TX + 1) * B, B, TX, BS>;
+  using QX = Patch<(TY + 1) * B + 1, TX * B, B, TX, BS>;  // J_x, J_y, J_z: the shared nodes of the last elements too
+  using QY = Patch<TY * B, (TX + 1) * B + 1, B, TX, BS>;
+  using QZ = Patch<(TY + 1) * B + 1, (TX + 1) * B + 1, B, TX, BS>;
+  __shared__ double su[NU * NE * ES], sx[PX::SIZE], sy[PY::SIZE], sz[R2 ? 1 : PZ::SIZE], sbel[2][TE][B];
+  __shared__ double jx[R2 ? 1 : QX::SIZE], jy[R2 ? 1 : QY::SIZE], jz[QZ::SIZE];
+  int tx0, ty0;
+  tile_of(blk, (mp.nx + TX - 1) / TX, (mp.ny + TY - 1) / TY, tx0, ty0);
+  tx0 *= TX; ty0 *= TY;
+  const int tw = mp.nx - tx0 < TX ? mp.nx - tx0 : TX, th = mp.ny - ty0 < TY ? mp.ny - ty0 : TY;
+  const long KN = mp.K * NN;
+  const int bx0 = tx0 * B, by0 = ty0 * B;
+  const RowTask<M, R2> k(tw, th);
+  // resistivity of the task's element and of the one left of it
+  double et = 0.0, etl = 0.0;
+  if (eta && k.act) {
+    const int row = wrap32(ty0 + k.ye, mp.ny) * mp.nx;
+    et = eta[row + tx0 + k.lx];
+    etl = eta[row + wrap32(tx0 + k.lx - 1, mp.nx)];
+  }
+  {
+    constexpr int NR = (NE * NN + BS - 1) / BS;
+    double v[NR][NU];
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const int n = threadIdx.x + m * BS, s = n / NN, q = n - s * NN, y = s / (TX + 1), x = s - y * (TX + 1);
+      if (s < NE && x <= tw && y <= th) {
+        const unsigned o = ((unsigned)(wrap32(ty0 + y - 1, mp.ny) * mp.nx + wrap32(tx0 + x - 1, mp.nx)) * NN + q) * 8u;
+#pragma unroll
+        for (int d = 0; d < NU; ++d) v[m][d] = bld(node_rsrc(u + d * KN, KN), o);
+      }
+    }
+    PX px;
+    PY py;
+    px.load(Bx, mp, bx0, by0 - B, tw * B, (th + 1) * B);
+    py.load(By, mp, bx0 - B, by0, (tw + 1) * B, th * B);
+    if constexpr (!R2) {
+      PZ pz;
+      pz.load(Bz, mp, bx0 - B, by0 - B, (tw + 1) * B, (th + 1) * B);
+      pz.store(sz);
+    }
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      const int n = threadIdx.x + m * BS, s = n / NN, q = n - s * NN;
+      if (s < NE)
+#pragma unroll
+        for (int d = 0; d < NU; ++d) su[(d * NE + s) * ES + q] = v[m][d];
+    }
+    px.store(sx);
+    py.store(sy);
+  }
+  bool res = false;
+  if (eta) {
+    res = __syncthreads_or(et != 0.0 || etl != 0.0);
+    if (res) {
+      QZ pz;
+      pz.load(Jz, mp, bx0 - B, by0 - B, (tw + 1) * B + 1, (th + 1) * B + 1);
+      if constexpr (!R2) {
+        QX px;
+        QY py;
+        px.load(Jx, mp, bx0, by0 - B, tw * B, (th + 1) * B + 1);
+        py.load(Jy, mp, bx0 - B, by0, (tw + 1) * B + 1, th * B);
+        px.store(jx);
+        py.store(jy);
+      }
+      pz.store(jz);
+    }
+  }
+  double tp[NP], tg[B], tv[B];  // rows j of the interpolations along y: of u, of B_x (W rows), of B_z
+  if (k.act) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) tp[q] = k.w ? T->I_P_W[k.j][q] : T->I_P_G[k.j][q];
+#pragma unroll
+    for (int q = 0; q < B; ++q) { tg[q] = k.w ? T->I_G_W[k.j][q] : 0.0; tv[q] = k.w ? T->I_V_W[k.j][q] : T->I_V_G[k.j][q]; }
+  }
+  __syncthreads();
+  const int gx = (tx0 + k.lx) * B, gy = (ty0 + k.ly) * B + k.j, NXg = mp.nx * B;
+  // the task's element and the one left of it in su (row 0 of the staged elements is the row below the tile)
+  const double* ue = su + ((k.ye + 1) * (TX + 1) + k.lx + 1) * ES;
+  const double* ul = ue - ES;
+  const double* const ze = sz + (k.ye + 1) * PZ::RS + k.lx + 1;  // B_z of the element
+  double z[B], x[B];
+  if (k.act && k.w) {
+    const double cj = k.j == 0 || k.j == A - 1 ? 0.5 : 1.0;
+    double u0[NP], u1[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      u0[q] = dot_col<NP>(tp, ue + q, NP);
+      u1[q] = dot_col<NP>(tp, ue + NE * ES + q, NP);
+    }
+    const double l0 = dot_col<NP>(tp, ul + P, NP), l1 = dot_col<NP>(tp, ul + NE * ES + P, NP);  // left, at x = +1
+    double b1[B], bl = 0.0;  // B_y of the row at the Gauss nodes; the left element's at x = +1
+    const double* yr = sy + k.ly * PY::RS + (k.below ? 0 : k.j) * PY::PITCH + k.lx + 1;
+#pragma unroll
+    for (int q = 0; q < B; ++q) {
+      b1[q] = yr[PY::at(q)];
+      bl = fma(T->I_G_W[A - 1][q], yr[PY::at(q) - 1], bl);
+    }
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const double bx = dot_patch<PX, B>(tg, sx + (k.ye + 1) * PX::RS + k.lx, i);
+      double ux = 0.0, uy = 0.0, by = 0.0;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) { ux = fma(T->I_P_W[i][q], u0[q], ux); uy = fma(T->I_P_W[i][q], u1[q], uy); }
+#pragma unroll
+      for (int q = 0; q < B; ++q) by = fma(T->I_G_W[i][q], b1[q], by);
+      z[i] = -(ux * by - uy * bx);
+      if (i == 0) z[i] = 0.5 * (z[i] - (l0 * bl - l1 * bx));
+      z[i] *= cj;
+    }
+    if constexpr (!R2) {
+      double u2[NP], bz[B];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) u2[q] = dot_col<NP>(tp, ue + 2 * NE * ES + q, NP);
+#pragma unroll
+      for (int q = 0; q < B; ++q) bz[q] = dot_patch<PZ, B>(tv, ze, q);
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double uy = 0.0, uz = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) { uy = fma(T->I_P_G[i][q], u1[q], uy); uz = fma(T->I_P_G[i][q], u2[q], uz); }
+#pragma unroll
+        for (int q = 0; q < B; ++q) b = fma(T->I_V_G[i][q], bz[q], b);
+        x[i] = -cj * (uy * b - uz * b1[i]);
+      }
+    }
+    if (res) {
+      double tw_[A];
+#pragma unroll
+      for (int q = 0; q < A; ++q) tw_[q] = T->RWP[k.j][q];
+      const double* r = jz + (k.ye + 1) * QZ::RS + k.lx + 1;
+      double c[A], cl[B];
+#pragma unroll
+      for (int q = 0; q < A; ++q) c[q] = dot_patch<QZ, A>(tw_, r, q);
+#pragma unroll
+      for (int q = 0; q < B; ++q) cl[q] = dot_patch<QZ, A>(tw_, r - 1, q);
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < A; ++q) s = fma(T->RWP[i][q], c[q], s);
+        z[i] = fma(et, s, z[i]);
+        if (i == 0) {
+          double t = T->RWP[A - 1][A - 1] * c[0];
+#pragma unroll
+          for (int q = 0; q < B; ++q) t = fma(T->RWP[A - 1][q], cl[q], t);
+          z[i] = fma(etl, t, z[i]);
+        }
+      }
+      if constexpr (!R2) {
+        double f[B];
+        const double* rx = jx + (k.ye + 1) * QX::RS + k.lx;
+#pragma unroll
+        for (int q = 0; q < B; ++q) f[q] = dot_patch<QX, A>(tw_, rx, q);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          double s = 0.0;
+#pragma unroll
+          for (int q = 0; q < B; ++q) s = fma(T->RGP[i][q], f[q], s);
+          x[i] = fma(et, s, x[i]);
+        }
+      }
+    }
+    if (k.below)
+#pragma unroll
+      for (int i = 0; i < B; ++i) { sbel[0][k.el][i] = z[i]; sbel[1][k.el][i] = R2 ? 0.0 : x[i]; }
+  }
+  if constexpr (!R2) {
+    if (k.act && !k.w) {
+      double u0[NP], u2[NP], bz[B], y[B];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        u0[q] = dot_col<NP>(tp, ue + q, NP);
+        u2[q] = dot_col<NP>(tp, ue + 2 * NE * ES + q, NP);
+      }
+      const double l0 = dot_col<NP>(tp, ul + P, NP), l2 = dot_col<NP>(tp, ul + 2 * NE * ES + P, NP);
+      double bzl = 0.0;  // the left element's B_z at x = +1
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        bz[q] = dot_patch<PZ, B>(tv, ze, q);
+        bzl = fma(T->I_V_W[A - 1][q], dot_patch<PZ, B>(tv, ze - 1, q), bzl);
+      }
+      const double* xr = sx + (k.ly + 1) * PX::RS + k.j * PX::PITCH + k.lx;
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        double ux = 0.0, uz = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) { ux = fma(T->I_P_W[i][q], u0[q], ux); uz = fma(T->I_P_W[i][q], u2[q], uz); }
+#pragma unroll
+        for (int q = 0; q < B; ++q) b = fma(T->I_V_W[i][q], bz[q], b);
+        y[i] = -(uz * xr[PX::at(i)] - ux * b);
+        if (i == 0) y[i] = 0.5 * (y[i] - (l2 * xr[PX::at(i)] - l0 * bzl));
+      }
+      if (res) {
+        double tw_[B];
+#pragma unroll
+        for (int q = 0; q < B; ++q) tw_[q] = T->RGP[k.j][q];
+        const double* r = jy + k.ly * QY::RS + k.lx + 1;
+        double c[A], cl[B];
+#pragma unroll
+        for (int q = 0; q < A; ++q) c[q] = dot_patch<QY, B>(tw_, r, q);
+#pragma unroll
+        for (int q = 0; q < B; ++q) cl[q] = dot_patch<QY, B>(tw_, r - 1, q);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          double s = 0.0;
+#pragma unroll
+          for (int q = 0; q < A; ++q) s = fma(T->RWP[i][q], c[q], s);
+          y[i] = fma(et, s, y[i]);
+          if (i == 0) {
+            double t = T->RWP[A - 1][A - 1] * c[0];
+#pragma unroll
+            for (int q = 0; q < B; ++q) t = fma(T->RWP[A - 1][q], cl[q], t);
+            y[i] = fma(etl, t, y[i]);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < B; ++i) Ey[(long)gy * NXg + gx + i] = y[i];
+    }
+  }
+  __syncthreads();
+  if (k.act && k.w && !k.below) {
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      const long g = (long)gy * NXg + gx + i;
+      Ez[g] = k.j == 0 ? z[i] + sbel[0][k.el][i] : z[i];
+      if (!R2) Ex[g] = k.j == 0 ? x[i] + sbel[1][k.el][i] : x[i];
+    }
+  }
+}
+
+template <int P, int M, bool R2>
+__global__ __launch_bounds__((RT<M, R2>::BS)) void k_J(const double* __restrict__ Bx, const double* __restrict__ By,
+                                                 const double* __restrict__ Bz, double* __restrict__ Jx,
+                                                 double* __restrict__ Jy, double* __restrict__ Jz,
                                                  const MagTab* __restrict__ T, MeshP mp) {
-  J_loads_body<P, M, BS, R2>(Bx, By, Bz, Lx, Ly, Lz, T, mp, xcd_block());
+  J_body<P, M, R2>(Bx, By, Bz, Jx, Jy, Jz, T, mp, (int)xcd_block());
 }
 
-struct J_loads_args {
+struct J_args {
   const double* Bx;
   const double* By;
   const double* Bz;
-  double* Lx;
-  double* Ly;
-  double* Lz;
+  double* Jx;
+  double* Jy;
+  double* Jz;
   const MagTab* T;
   MeshP mp;
 };
 
-template <int P, int M, int BS, bool R2>
-__global__ __launch_bounds__(BS) void k_J_loads_rt(const J_loads_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int P, int M, bool R2>
+__global__ __launch_bounds__((RT<M, R2>::BS)) void k_J_rt(const J_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
-  const J_loads_args& a = A[r];
-  J_loads_body<P, M, BS, R2>(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Lx), gl(a.Ly), gl(a.Lz), gl(a.T), a.mp, (long)blockIdx.x - boff[r]);
+  const J_args& a = A[r];
+  J_body<P, M, R2>(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Electric-field loads (eq. mag-electric-proj): w_a (-u x B)|_K at the element's own auxiliary
-// nodes, plus eta_K sum_q M_q J(x_q) . phi_a(x_q) by the degree-p GLL rule.
-// ---------------------------------------------------------------------------------------------
-template <int P, int M, int BS, bool R2>
-__device__ __forceinline__ void E_loads_body(const double* __restrict__ u, const double* __restrict__ Bx,
+template <int P, int M, bool R2>
+__global__ __launch_bounds__((RT<M, R2>::BS)) void k_E(const double* __restrict__ u, const double* __restrict__ Bx,
                                                  const double* __restrict__ By, const double* __restrict__ Bz,
                                                  const double* __restrict__ Jx, const double* __restrict__ Jy,
                                                  const double* __restrict__ Jz, const double* __restrict__ eta,
-                                                 double* __restrict__ Lx, double* __restrict__ Ly,
-                                                 double* __restrict__ Lz, const MagTab* __restrict__ T, MeshP mp, long blk) {
-  using C = MC<P, M, BS>;
-  constexpr int NP = C::NP, NN = C::NN, A = C::A, B = C::B, AA = C::AA, AB = C::AB, BB = C::BB, EB = C::EB,
-                NT = C::NT;
-  // J on the auxiliary grids (sjx, sjy, sjz), and later the x sums of the eta term (sxj)
-  constexpr int NJ = 2 * AB + AA, NXJ = NP * (B + 2 * A), NJB = NJ > NXJ ? NJ : NXJ;
-  __shared__ double su[EB][3][NN], sbx[EB][AB], sby[EB][AB], sbz[EB][BB];
-  __shared__ double sjb[EB][NJB];
-  // the eta-weighted J values at the GLL_p nodes reuse su once the x interpolation has read it
-  // (with 96 VGPRs and 14.8 KB of LDS per 128-thread block at N = 4: 5 waves per SIMD)
-  double(*const swj)[3][NN] = su;
-  __shared__ double sux[EB][3][NP][A + B];  // velocity interpolated in x: [d][qj][W nodes | Gauss nodes]
-  __shared__ double tGP[NP][B], tWP[NP][A], tPW[A][NP], tPG[B][NP], tGW[A][B], tVG[B][B], tVW[A][B];
-  __shared__ double twp[NP], tww[A], twg[B];
-  const int tid = threadIdx.x, el = tid / NT, t = tid - el * NT;
-  const long e = blk * EB + el;
-  const bool act = el < EB && e < mp.K;
-  double* const sjx = sjb[el < EB ? el : 0];  // [j < A][i < B]
-  double* const sjy = sjx + AB;                // [j < B][i < A]
-  double* const sjz = sjx + 2 * AB;            // [j < A][i < A]
-  long ex, ey;
-  elem_xy(mp, act ? e : 0, ex, ey);
-  const long KN = mp.K * NN;
-  const double et = (act && eta) ? eta[e] : 0.0;
-  for (int k = tid; k < NP * B; k += BS) tGP[k / B][k % B] = T->I_G_P[k / B][k % B];
-  for (int k = tid; k < NP * A; k += BS) {
-    tWP[k / A][k % A] = T->I_W_P[k / A][k % A];
-    tPW[k / NP][k % NP] = T->I_P_W[k / NP][k % NP];
-  }
-  for (int k = tid; k < B * NP; k += BS) tPG[k / NP][k % NP] = T->I_P_G[k / NP][k % NP];
-  for (int k = tid; k < A * B; k += BS) {
-    tGW[k / B][k % B] = T->I_G_W[k / B][k % B];
-    tVW[k / B][k % B] = T->I_V_W[k / B][k % B];
-  }
-  for (int k = tid; k < B * B; k += BS) tVG[k / B][k % B] = T->I_V_G[k / B][k % B];
-  if (tid < NP) twp[tid] = T->wp[tid];
-  if (tid < A) tww[tid] = T->ww[tid];
-  if (tid < B) twg[tid] = T->wg[tid];
-  constexpr int NU = R2 ? 2 : 3;  // velocity components carried (u_z = 0 in the 2D2V system)
-  if (act) {
-    for (int k = t; k < NN; k += NT)
-      for (int d = 0; d < NU; ++d) su[el][d][k] = u[d * KN + e * NN + k];
-    load_B<P, M, R2>(sbx[el], sby[el], sbz[el], Bx, By, Bz, mp, ex, ey, t);
-    if (et != 0.0) {
-      if constexpr (!R2)
-        for (int k = t; k < AB; k += NT) {
-          sjx[k] = Jx[gix(mp, B, ex, ey, k % B, k / B)];
-          sjy[k] = Jy[gix(mp, B, ex, ey, k % A, k / A)];
-        }
-      for (int k = t; k < AA; k += NT) sjz[k] = Jz[gix(mp, B, ex, ey, k % A, k / A)];
-    }
-  }
-  __syncthreads();
-  if (act) {
-    // first half of the sum factorisation of u at the auxiliary nodes: interpolate in x
-    // (the 2D2V system needs u_x, u_y at the W nodes only: x < A)
-    constexpr int NX = R2 ? A : A + B;
-    for (int tk = t; tk < NU * NP * NX; tk += NT) {
-      const int d = tk / (NP * NX), rem = tk - d * NP * NX, qj = rem / NX, x = rem - qj * NX;
-      const double* I = x < A ? tPW[x] : tPG[x - A];
-      double v = 0.0;
-#pragma unroll
-      for (int qi = 0; qi < NP; ++qi) v += I[qi] * su[el][d][qj * NP + qi];
-      sux[el][d][qj][x] = v;
-    }
-  }
-  const bool jnode = act && et != 0.0 && t < NN;
-  double jw[3] = {0.0, 0.0, 0.0};
-  if (jnode) {
-    const int qi = t % NP, qj = t / NP;
-    double jx = 0.0, jy = 0.0, jz = 0.0;
-    if constexpr (!R2) {
-#pragma unroll
-      for (int j = 0; j < A; ++j) {
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < B; ++i) s += tGP[qi][i] * sjx[j * B + i];
-        jx += tWP[qj][j] * s;
-      }
-#pragma unroll
-      for (int j = 0; j < B; ++j) {
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < A; ++i) s += tWP[qi][i] * sjy[j * A + i];
-        jy += tGP[qj][j] * s;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < A; ++j) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < A; ++i) s += tWP[qi][i] * sjz[j * A + i];
-      jz += tWP[qj][j] * s;
-    }
-    const double w = et * mp.J * twp[qi] * twp[qj];
-    jw[0] = w * jx; jw[1] = w * jy; jw[2] = w * jz;
-  }
-  __syncthreads();  // every lane has finished reading su and the J grids
-  if (jnode) { swj[el][0][t] = jw[0]; swj[el][1][t] = jw[1]; swj[el][2][t] = jw[2]; }
-  __syncthreads();
-  // the eta term sum_q M_q (eta J)(x_q) phi_a(x_q) by sum factorisation: x sums first, into the
-  // J-grid space, xs0[qj][i < B] (G in x, for E_x), xs1[qj][i < A] and xs2[qj][i < A] (W in x)
-  double* const xs0 = sjx;
-  double* const xs1 = xs0 + NP * B;
-  double* const xs2 = xs1 + NP * A;
-  if (act && et != 0.0) {
-    for (int tk = t; tk < NXJ; tk += NT) {
-      int c, qj, i;
-      if (tk < NP * B) { c = 0; qj = tk / B; i = tk - qj * B; }
-      else { const int r = (tk - NP * B) % (NP * A); c = 1 + (tk - NP * B) / (NP * A); qj = r / A; i = r - qj * A; }
-      if (R2 && c < 2) continue;
-      double v = 0.0;
-#pragma unroll
-      for (int qi = 0; qi < NP; ++qi) v += (c == 0 ? tGP[qi][i] : tWP[qi][i]) * swj[el][c][qj * NP + qi];
-      xs0[tk] = v;
-    }
-  }
-  __syncthreads();
-  if (!act) return;
-  // second half: interpolate in y (Iy = I_P_W or I_P_G row aj; x column xc of sux)
-  auto u_at = [&](int d, const double* Iy, int xc) {
-    double v = 0.0;
-#pragma unroll
-    for (int qj = 0; qj < NP; ++qj) v += Iy[qj] * sux[el][d][qj][xc];
-    return v;
-  };
-  // y sums of the eta term: xs[qj * nx + ai] against the y basis column aj
-  auto eta_term = [&](const double* xs, int nx, int ai, bool ygauss, int aj) {
-    double v = 0.0;
-#pragma unroll
-    for (int qj = 0; qj < NP; ++qj) v += (ygauss ? tGP[qj][aj] : tWP[qj][aj]) * xs[qj * nx + ai];
-    return v;
-  };
-  if (t < AA) {  // W node (xw[i], xw[j]): z-component
-    const int i = t % A, j = t / A;
-    const double ux = u_at(0, tPW[j], i), uy = u_at(1, tPW[j], i);
-    double bxv = 0.0, byv = 0.0;
-#pragma unroll
-    for (int k = 0; k < B; ++k) {
-      bxv += tGW[j][k] * sbx[el][k * A + i];
-      byv += tGW[i][k] * sby[el][j * B + k];
-    }
-    double s = mp.J * tww[i] * tww[j] * (-(ux * byv - uy * bxv));
-    if (et != 0.0) s += eta_term(xs2, A, i, false, j);
-    Lz[e * AA + t] = s;
-  }
-  if (!R2 && t < AB) {
-    {  // N_x node (xg[i], xw[j]): x-component; B_y lives on these nodes
-      const int i = t % B, j = t / B;
-      const double uy = u_at(1, tPW[j], A + i), uz = u_at(2, tPW[j], A + i);
-      const double byv = sby[el][t];
-      double bzv = 0.0;
-#pragma unroll
-      for (int jj = 0; jj < B; ++jj) {
-        double s = 0.0;
-#pragma unroll
-        for (int ii = 0; ii < B; ++ii) s += tVG[i][ii] * sbz[el][jj * B + ii];
-        bzv += tVW[j][jj] * s;
-      }
-      double s = mp.J * twg[i] * tww[j] * (-(uy * bzv - uz * byv));
-      if (et != 0.0) s += eta_term(xs0, B, i, false, j);
-      Lx[e * AB + t] = s;
-    }
-    {  // N_y node (xw[i], xg[j]): y-component; B_x lives on these nodes
-      const int i = t % A, j = t / A;
-      const double ux = u_at(0, tPG[j], i), uz = u_at(2, tPG[j], i);
-      const double bxv = sbx[el][t];
-      double bzv = 0.0;
-#pragma unroll
-      for (int jj = 0; jj < B; ++jj) {
-        double s = 0.0;
-#pragma unroll
-        for (int ii = 0; ii < B; ++ii) s += tVW[i][ii] * sbz[el][jj * B + ii];
-        bzv += tVG[j][jj] * s;
-      }
-      double s = mp.J * tww[i] * twg[j] * (-(uz * bxv - ux * bzv));
-      if (et != 0.0) s += eta_term(xs1, A, i, true, j);
-      Ly[e * AB + t] = s;
-    }
-  }
+                                                 double* __restrict__ Ex, double* __restrict__ Ey,
+                                                 double* __restrict__ Ez, const MagTab* __restrict__ T, MeshP mp) {
+  E_body<P, M, R2>(u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, T, mp, (int)xcd_block());
 }
 
-template <int P, int M, int BS, bool R2>
-__global__ __launch_bounds__(BS, (!R2 && P <= 5) ? 5 : 1) void k_E_loads(const double* __restrict__ u, const double* __restrict__ Bx,
-                                                 const double* __restrict__ By, const double* __restrict__ Bz,
-                                                 const double* __restrict__ Jx, const double* __restrict__ Jy,
-                                                 const double* __restrict__ Jz, const double* __restrict__ eta,
-                                                 double* __restrict__ Lx, double* __restrict__ Ly,
-                                                 double* __restrict__ Lz, const MagTab* __restrict__ T, MeshP mp) {
-  E_loads_body<P, M, BS, R2>(u, Bx, By, Bz, Jx, Jy, Jz, eta, Lx, Ly, Lz, T, mp, xcd_block());
-}
-
-struct E_loads_args {
+struct E_args {
   const double* u;
   const double* Bx;
   const double* By;
@@ -393,18 +560,18 @@ struct E_loads_args {
   const double* Jy;
   const double* Jz;
   const double* eta;
-  double* Lx;
-  double* Ly;
-  double* Lz;
+  double* Ex;
+  double* Ey;
+  double* Ez;
   const MagTab* T;
   MeshP mp;
 };
 
-template <int P, int M, int BS, bool R2>
-__global__ __launch_bounds__(BS, (!R2 && P <= 5) ? 5 : 1) void k_E_loads_rt(const E_loads_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int P, int M, bool R2>
+__global__ __launch_bounds__((RT<M, R2>::BS)) void k_E_rt(const E_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
-  const E_loads_args& a = A[r];
-  E_loads_body<P, M, BS, R2>(gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.eta), gl(a.Lx), gl(a.Ly), gl(a.Lz), gl(a.T), a.mp, (long)blockIdx.x - boff[r]);
+  const E_args& a = A[r];
+  E_body<P, M, R2>(gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.eta), gl(a.Ex), gl(a.Ey), gl(a.Ez), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1590,69 +1757,6 @@ __global__ __launch_bounds__(256) void k_B_stats_rt(const B_stats_args* __restri
 
 }  // namespace
 
-// gather of per-element loads at shared nodes and division by the lumped weights
-template <int M, bool R2>
-__device__ __forceinline__ void gather_body(const double* __restrict__ Lx, const double* __restrict__ Ly,
-                                                const double* __restrict__ Lz, double* __restrict__ Ox,
-                                                double* __restrict__ Oy, double* __restrict__ Oz,
-                                                const MagTab* __restrict__ T, MeshP mp, long blk) {
-  constexpr int A = M + 2, B = M + 1, AA = A * A, AB = A * B;
-  const int NX = mp.nx * B;
-  const long G = (long)NX * mp.ny * B;  // below 2^29 (mhd25_init)
-  const long g = blk * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  const int gy = (int)row_of(mp, g / B), gx = (int)g - gy * NX;  // g / (nx B) = (g / B) / nx
-  const int ex = gx / B, ey = gy / B;
-  const int i = gx - ex * B, j = gy - ey * B;
-  const long e = (long)ey * mp.nx + ex;
-  const long eL = (long)ey * mp.nx + wrap32(ex - 1, mp.nx), eD = (long)wrap32(ey - 1, mp.ny) * mp.nx + ex;
-  const long eLD = (long)wrap32(ey - 1, mp.ny) * mp.nx + wrap32(ex - 1, mp.nx);
-  {  // W node
-    double s = Lz[e * AA + j * A + i];
-    if (i == 0) s += Lz[eL * AA + j * A + (A - 1)];
-    if (j == 0) s += Lz[eD * AA + (A - 1) * A + i];
-    if (i == 0 && j == 0) s += Lz[eLD * AA + (A - 1) * A + (A - 1)];
-    Oz[g] = s * T->rjw[0][j][i];
-  }
-  if (R2) return;  // the 2D2V system has no in-plane J or E
-  {  // N_x node: Gauss in x (i), GLL in y (j); local index j*B + i
-    double s = Lx[e * AB + j * B + i];
-    if (j == 0) s += Lx[eD * AB + (A - 1) * B + i];
-    Ox[g] = s * T->rjw[1][j][i];
-  }
-  {  // N_y node: GLL in x (i), Gauss in y (j); local index j*A + i
-    double s = Ly[e * AB + j * A + i];
-    if (i == 0) s += Ly[eL * AB + j * A + (A - 1)];
-    Oy[g] = s * T->rjw[2][j][i];
-  }
-}
-
-template <int M, bool R2>
-__global__ __launch_bounds__(256) void k_gather(const double* __restrict__ Lx, const double* __restrict__ Ly,
-                                                const double* __restrict__ Lz, double* __restrict__ Ox,
-                                                double* __restrict__ Oy, double* __restrict__ Oz,
-                                                const MagTab* __restrict__ T, MeshP mp) {
-  gather_body<M, R2>(Lx, Ly, Lz, Ox, Oy, Oz, T, mp, (long)blockIdx.x);
-}
-
-struct gather_args {
-  const double* Lx;
-  const double* Ly;
-  const double* Lz;
-  double* Ox;
-  double* Oy;
-  double* Oz;
-  const MagTab* T;
-  MeshP mp;
-};
-
-template <int M, bool R2>
-__global__ __launch_bounds__(256) void k_gather_rt(const gather_args* __restrict__ A, const int* __restrict__ boff, int nr) {
-  const int r = rt_run(boff, nr);
-  const gather_args& a = A[r];
-  gather_body<M, R2>(gl(a.Lx), gl(a.Ly), gl(a.Lz), gl(a.Ox), gl(a.Oy), gl(a.Oz), gl(a.T), a.mp, (long)blockIdx.x - boff[r]);
-}
-
 // Local-to-global maps of the six magnetic node sets of each element (B_x, B_y, B_z, W, N_x, N_y;
 // local order [j][i], i fastest), formed with the kernels' own grid index gix.  One thread per element.
 template <int M>
@@ -1781,15 +1885,7 @@ static long mblocks(int p, int m, long K, int bs = 256) {
   return (K + eb - 1) / eb;
 }
 
-// threads per block of the element-load and update kernels (measured on the 1024^2, N = 4, k = 3
-// workload: 128-thread blocks make the E loads 6 % faster, being limited by their LDS use at 256;
-// the J loads and the update run slightly slower with 128)
-#ifndef MHD_JL_BS
-#define MHD_JL_BS 256
-#endif
-#ifndef MHD_EL_BS
-#define MHD_EL_BS 128
-#endif
+// threads per block of the update kernel
 #ifndef MHD_MU_BS
 #define MHD_MU_BS 256
 #endif
@@ -1799,76 +1895,49 @@ static long mblocks(int p, int m, long K, int bs = 256) {
 #define MHD_VP_BS 128
 #endif
 
+template <int M>
+static long tiles(const MeshP& mp) {
+  return (long)((mp.nx + RT<M, false>::TX - 1) / RT<M, false>::TX) * ((mp.ny + RT<M, false>::TY - 1) / RT<M, false>::TY);
+}
+
 // r2: the 2D2V reduced system (only J_z and E_z are formed; the in-plane grids are not written)
-// loads: the per-element load workspace, K (2 (m+2)(m+1) + (m+2)^2) doubles
-static int reconstruct_JE_ws(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
-                             const double* eta, double* JE, bool r2, double* loads) {
-  const long K = c->mp.K, G = c->G;
-  const int a = c->m + 2, b = c->m + 1;
-  double* Lx = loads;
-  double* Ly = Lx + K * a * b;
-  double* Lz = Ly + K * a * b;
-  const long nbj = mblocks(c->p, c->m, K, MHD_JL_BS), nbe = mblocks(c->p, c->m, K, MHD_EL_BS);
-  const long gb = (G + 255) / 256;
+int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
+                       const double* eta, double* JE, bool r2) {
+  const long G = c->G;
+  double *Jx = JE, *Jy = JE + G, *Jz = JE + 2 * G, *Ex = JE + 3 * G, *Ey = JE + 4 * G, *Ez = JE + 5 * G;
+  long nb = 0;
+#define NB(M) nb = tiles<M>(c->mp)
+  DISPATCH_M(c->m, NB);
+#undef NB
   if (c->rec) {
     const int k = mkey(c->p, c->m, r2);
-    rt_record(c, RT_J_LOADS, k, nbj, J_loads_args{Bx, By, Bz, Lx, Ly, Lz, c->d_mt, c->mp});
-    rt_record(c, RT_GATHER, k, gb, gather_args{Lx, Ly, Lz, JE, JE + G, JE + 2 * G, c->d_mt, c->mp});
-    rt_record(c, RT_E_LOADS, k, nbe,
-              E_loads_args{u, Bx, By, Bz, JE, JE + G, JE + 2 * G, eta, Lx, Ly, Lz, c->d_mt, c->mp});
-    rt_record(c, RT_GATHER, k, gb, gather_args{Lx, Ly, Lz, JE + 3 * G, JE + 4 * G, JE + 5 * G, c->d_mt, c->mp});
+    rt_record(c, RT_J, k, nb, J_args{Bx, By, Bz, Jx, Jy, Jz, c->d_mt, c->mp});
+    rt_record(c, RT_E, k, nb, E_args{u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp});
     return 0;
   }
 #define LJ(P, M)                                                                                                    \
-  if (r2) hipLaunchKernelGGL((k_J_loads<P, M, MHD_JL_BS, true>), dim3(nbj), dim3(MHD_JL_BS), 0, c->stream, Bx, By, \
-                             Bz, Lx, Ly, Lz, c->d_mt, c->mp);                                                       \
-  else hipLaunchKernelGGL((k_J_loads<P, M, MHD_JL_BS, false>), dim3(nbj), dim3(MHD_JL_BS), 0, c->stream, Bx, By, Bz, \
-                          Lx, Ly, Lz, c->d_mt, c->mp)
+  if (r2) hipLaunchKernelGGL((k_J<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, Bx, By, Bz, Jx, Jy, \
+                             Jz, c->d_mt, c->mp);                                                                   \
+  else hipLaunchKernelGGL((k_J<P, M, false>), dim3(nb), dim3(RT<M, false>::BS), 0, c->stream, Bx, By, Bz, Jx, Jy,  \
+                          Jz, c->d_mt, c->mp)
   {
     T_BEGIN(7);
     DISPATCH_PM(c->p, c->m, LJ);
     T_END();
   }
 #undef LJ
-#define GJ(M)                                                                                                       \
-  if (r2) hipLaunchKernelGGL((k_gather<M, true>), dim3(gb), dim3(256), 0, c->stream, Lx, Ly, Lz, JE, JE + G,       \
-                             JE + 2 * G, c->d_mt, c->mp);                                                           \
-  else hipLaunchKernelGGL((k_gather<M, false>), dim3(gb), dim3(256), 0, c->stream, Lx, Ly, Lz, JE, JE + G,         \
-                          JE + 2 * G, c->d_mt, c->mp)
-  {
-    T_BEGIN(8);
-    DISPATCH_M(c->m, GJ);
-    T_END();
-  }
-#undef GJ
 #define LE(P, M)                                                                                                    \
-  if (r2) hipLaunchKernelGGL((k_E_loads<P, M, MHD_EL_BS, true>), dim3(nbe), dim3(MHD_EL_BS), 0, c->stream, u, Bx,  \
-                             By, Bz, JE, JE + G, JE + 2 * G, eta, Lx, Ly, Lz, c->d_mt, c->mp);                      \
-  else hipLaunchKernelGGL((k_E_loads<P, M, MHD_EL_BS, false>), dim3(nbe), dim3(MHD_EL_BS), 0, c->stream, u, Bx, By, \
-                          Bz, JE, JE + G, JE + 2 * G, eta, Lx, Ly, Lz, c->d_mt, c->mp)
+  if (r2) hipLaunchKernelGGL((k_E<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, u, Bx, By, Bz, Jx,  \
+                             Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp);                                              \
+  else hipLaunchKernelGGL((k_E<P, M, false>), dim3(nb), dim3(RT<M, false>::BS), 0, c->stream, u, Bx, By, Bz, Jx,   \
+                          Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp)
   {
     T_BEGIN(5);
     DISPATCH_PM(c->p, c->m, LE);
     T_END();
   }
 #undef LE
-#define GE(M)                                                                                                       \
-  if (r2) hipLaunchKernelGGL((k_gather<M, true>), dim3(gb), dim3(256), 0, c->stream, Lx, Ly, Lz, JE + 3 * G,       \
-                             JE + 4 * G, JE + 5 * G, c->d_mt, c->mp);                                               \
-  else hipLaunchKernelGGL((k_gather<M, false>), dim3(gb), dim3(256), 0, c->stream, Lx, Ly, Lz, JE + 3 * G,         \
-                          JE + 4 * G, JE + 5 * G, c->d_mt, c->mp)
-  {
-    T_BEGIN(8);
-    DISPATCH_M(c->m, GE);
-    T_END();
-  }
-#undef GE
   return chk(c, "reconstruct launch");
-}
-
-int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
-                       const double* eta, double* JE, bool r2) {
-  return reconstruct_JE_ws(c, u, Bx, By, Bz, eta, JE, r2, c->loads);
 }
 
 int mag_update(mhd25_ctx* c, const MagIO& io, int mode) {
@@ -2089,30 +2158,21 @@ int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, i
   const int p = h.key / 1000, m = (h.key / 100) % 10, mode = h.key % 10;
   const bool r2 = (h.key / 10) % 10 != 0;
   switch (h.kind) {
-    case RT_J_LOADS: {
-      const J_loads_args* A = (const J_loads_args*)dargs;
+    case RT_J: {
+      const J_args* A = (const J_args*)dargs;
 #define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_J_loads_rt<P, M, MHD_JL_BS, true>), g, dim3(MHD_JL_BS), 0, s, A, dboff, nr);       \
-  else hipLaunchKernelGGL((k_J_loads_rt<P, M, MHD_JL_BS, false>), g, dim3(MHD_JL_BS), 0, s, A, dboff, nr)
+  if (r2) hipLaunchKernelGGL((k_J_rt<P, M, true>), g, dim3(RT<M, true>::BS), 0, s, A, dboff, nr);                   \
+  else hipLaunchKernelGGL((k_J_rt<P, M, false>), g, dim3(RT<M, false>::BS), 0, s, A, dboff, nr)
       DISPATCH_PM(p, m, F);
 #undef F
       break;
     }
-    case RT_E_LOADS: {
-      const E_loads_args* A = (const E_loads_args*)dargs;
+    case RT_E: {
+      const E_args* A = (const E_args*)dargs;
 #define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_E_loads_rt<P, M, MHD_EL_BS, true>), g, dim3(MHD_EL_BS), 0, s, A, dboff, nr);       \
-  else hipLaunchKernelGGL((k_E_loads_rt<P, M, MHD_EL_BS, false>), g, dim3(MHD_EL_BS), 0, s, A, dboff, nr)
+  if (r2) hipLaunchKernelGGL((k_E_rt<P, M, true>), g, dim3(RT<M, true>::BS), 0, s, A, dboff, nr);                   \
+  else hipLaunchKernelGGL((k_E_rt<P, M, false>), g, dim3(RT<M, false>::BS), 0, s, A, dboff, nr)
       DISPATCH_PM(p, m, F);
-#undef F
-      break;
-    }
-    case RT_GATHER: {
-      const gather_args* A = (const gather_args*)dargs;
-#define F(M)                                                                                                        \
-  if (r2) hipLaunchKernelGGL((k_gather_rt<M, true>), g, dim3(256), 0, s, A, dboff, nr);                             \
-  else hipLaunchKernelGGL((k_gather_rt<M, false>), g, dim3(256), 0, s, A, dboff, nr)
-      DISPATCH_M(m, F);
 #undef F
       break;
     }
@@ -2242,9 +2302,7 @@ extern "C" int mhd25_rhs_magnetic_noalloc(mhd25_ctx* c, const double* rho, const
     return -2;
   }
   double* JE = ws;            // six grids: J_x, J_y, J_z, E_x, E_y, E_z
-  double* loads = ws + 6 * G;  // every entry is written by the load kernels before the gathers read it
-  const bool r2 = c->opt.reduced_2d2v != 0;
-  if (const int r = reconstruct_JE_ws(c, u, Bx, By, Bz, eta, JE, r2, loads)) return r;
+  if (const int r = mag_reconstruct_JE(c, u, Bx, By, Bz, eta, JE, c->opt.reduced_2d2v != 0)) return r;
   MagIO io{};
   io.rho = rho; io.us = u; io.bxs = Bx; io.bys = By; io.bzs = Bz;
   io.jx = JE; io.jy = JE + G; io.jz = JE + 2 * G;

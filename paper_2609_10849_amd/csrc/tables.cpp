@@ -150,6 +150,33 @@ void build_mag_tables(int p, int m, MagTab* T) {
   fill(T->I_G_P, xg, xp, false); fill(T->I_W_P, xw, xp, false); fill(T->I_V_P, xv, xp, false);
   fill(T->D_W_V, xw, xv, true); fill(T->I_G_V, xg, xv, false);
   fill(T->I_V_Q, xv, xq, false);
+  {
+    const int A = m + 2, B = m + 1;
+    auto L = [&](const std::vector<ld>& s, int k, ld x) { return lag_val(s, k, x); };
+    for (int i = 0; i < A; ++i) {
+      const ld W = ww[i] + (i == 0 || i == A - 1 ? ww[A - 1 - i] : 0);
+      for (int j = 0; j < A; ++j) {
+        ld q = 0, r = 0;
+        for (size_t k = 0; k < xq.size(); ++k) q += wq[k] * L(xw, i, xq[k]) * L(xw, j, xq[k]);
+        for (size_t k = 0; k < xp.size(); ++k) r += wp[k] * L(xw, i, xp[k]) * L(xw, j, xp[k]);
+        T->RWQ[i][j] = (double)(q / W);
+        T->RWP[i][j] = (double)(r / W);
+      }
+      for (int j = 0; j < B; ++j) {
+        ld q = 0, r = 0;
+        for (size_t k = 0; k < xq.size(); ++k) q += wq[k] * lag_der(xw, i, xq[k]) * L(xg, j, xq[k]);
+        for (size_t k = 0; k < xg.size(); ++k) r += wg[k] * lag_der(xw, i, xg[k]) * L(xv, j, xg[k]);
+        T->RDG[i][j] = (double)(q / W);
+        T->RDV[i][j] = (double)(r / W);
+      }
+    }
+    for (int i = 0; i < B; ++i)
+      for (int j = 0; j < B; ++j) {
+        ld r = 0;
+        for (size_t k = 0; k < xp.size(); ++k) r += wp[k] * L(xg, i, xp[k]) * L(xg, j, xp[k]);
+        T->RGP[i][j] = (double)(r / wg[i]);
+      }
+  }
   std::vector<ld> ends = {-1, 1};
   for (int s = 0; s < 2; ++s) {
     for (size_t k = 0; k < xg.size(); ++k) T->I_G_E[s][k] = (double)lag_val(xg, (int)k, ends[s]);

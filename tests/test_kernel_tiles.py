@@ -110,7 +110,21 @@ def check_stage_map(run, p, m, nx, ny):
             close(out[0][c], want[c], "component %d, oe %d, pp %d" % (c, oe, pp))
 
 
-CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep, check_stage_map]
+def check_reconstruction(run, p, m, nx, ny):
+    """J and E without resistivity, with it everywhere, and with it in one element (tiles of both kinds)."""
+    import paper_2609_10849_amd as pk
+    L, M, rho, e, u, _, Bx, By, Bz = state(p, m, nx, ny)
+    eta = np.random.default_rng(5).uniform(0.01, 0.05, M.K)
+    one = np.where(np.arange(M.K) == M.K // 2, eta, 0.0)
+    for et in (None, eta, one):
+        want = O.reconstruct_JE(M, u, Bx, By, Bz, et)
+        out = run(L, pk.Options.make(), "mhd25_reconstruct_JE", [u, Bx, By, Bz, et, np.zeros((6,) + Bx.shape)])
+        for k in range(6):
+            # a one-element mesh's derivatives cancel across its own faces
+            close(out[5][k], want[k], "grid %d" % k, np.abs(Bx).max() / max(M.hx, M.hy))
+
+
+CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep, check_stage_map, check_reconstruction]
 
 
 @pytest.mark.parametrize("nx,ny", SMALL)
