@@ -11,6 +11,7 @@
 #include "common.h"
 #include "xcd.h"
 #include "ec_log.h"
+#include "jumps.h"
 #include "rsqrt.h"
 
 namespace {
@@ -514,37 +515,6 @@ struct HS {
   static constexpr int NX = (TX + 1) * TY, NY = TX * (TY + 1);  // faces
   static constexpr int NS = TE + 2 * (TX + TY);                 // staged elements: the tile's, then the ring's
 };
-
-// squared, weighted jumps of the derivatives of order r (eq. euler-oe-jump) across a face between the
-// elements at m (minus side) and q (plus side), normal direction D, as square roots.  On the symmetric GLL
-// nodes d^r l_k (+1) = (-1)^r d^r l_{p-k} (-1), which the tables hold bit for bit, so the jump of order r is one
-// sum over the differences (r even) or sums (r odd) of mirrored values.
-template <int P, int D>
-__device__ __forceinline__ void face_jumps(const double* m, const double* q, const HydroTab* __restrict__ T, double J[]) {
-  constexpr int NP = P + 1;
-#pragma unroll
-  for (int r = 0; r < NP; ++r) J[r] = 0.0;
-#pragma unroll
-  for (int l = 0; l < NP; ++l) {
-    double dif[NP], sum[NP];
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const double a = q[D ? k * NP + l : l * NP + k], b = m[D ? (P - k) * NP + l : l * NP + P - k];
-      dif[k] = a - b;
-      sum[k] = a + b;
-    }
-#pragma unroll
-    for (int r = 0; r < NP; ++r) {
-      double j = 0.0;
-#pragma unroll
-      for (int k = 0; k < NP; ++k) j = fma(T->Dr0[r][k], r & 1 ? sum[k] : dif[k], j);
-      J[r] = fma(0.5 * T->w[l] * j, j, J[r]);
-    }
-    SCHED_FENCE();
-  }
-#pragma unroll
-  for (int r = 0; r < NP; ++r) J[r] = sqrt(J[r]);
-}
 
 // Hydro OE sensor (eq. euler-oe-amplitude .. eq. euler-oe-map): the shell damping factors D_l (l = 0..p) of every
 // element from the raw stage, Dfac[K][p+1].  Every face's jumps are formed once per tile, by a thread of

@@ -10,6 +10,7 @@
 
 #include "common.h"
 #include "xcd.h"
+#include "jumps.h"
 #include "rsqrt.h"
 
 namespace {
@@ -1101,226 +1102,233 @@ __global__ __launch_bounds__(MHD_PREP_BS) void k_vel_prep_rt(const vel_prep_args
   vel_prep_body<P>(gl(a.rho), gl(a.Psi), gl(a.H), a.mp, (long)blockIdx.x - boff[r]);
 }
 
-template <int P, int M>
+// Tile of the velocity-OE sensor: TX x TY elements and the ring around them.  One thread per component and
+// face, the tile's (TX + 1) TY x faces on the block's first half, its TX (TY + 1) y faces on the second, so that
+// a wave has one direction.  The wave speeds are row tasks, one GLL row of an element each.  5 x 5 elements
+// leave three blocks per CU at N = 4; 6 x 6 fill more lanes but leave two (0.56 against 0.52 ms at 1024^2).
+template <int P, int M, bool R2>
 struct VS {
-  static constexpr int NP = P + 1, NN = NP * NP, EB = 256 / NN;
-  static constexpr int A = M + 2, B = M + 1, AB = A * B, BB = B * B;
+  static constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1;  // odd element stride in LDS: no bank conflicts
+  static constexpr int A = M + 2, B = M + 1, BS = 256, NU = R2 ? 2 : 3;  // u_z = 0 in the 2D2V system
+  static constexpr int TX = 5, TY = P < 6 ? 5 : 4, TE = TX * TY;
+  static constexpr int NX = (TX + 1) * TY, NY = TX * (TY + 1);  // faces
+  static constexpr int NS = TE + 2 * (TX + TY);                 // staged elements: the tile's, then the ring's
 };
 
-// Velocity-OE sensor (eq. magnetic-oe-sensor, eq. magnetic-oe-rate, eq. magnetic-oe-factor): one
-// thread per GLL_p node, EB elements per block; writes the element's damping factors D_l
-// (l = 0..p) to Dfac[K][p+1].  Neighbour velocities are staged per direction in LDS with coalesced
-// loads.  u is only read here (the projection kernel that updates it runs afterwards).
-// (at N = 4, k = 3 the kernel fits 80 VGPRs and 27 KB of LDS without spills: 6 waves per SIMD)
+// Velocity-OE sensor (eq. magnetic-oe-sensor, eq. magnetic-oe-rate, eq. magnetic-oe-factor): the element's
+// damping factors D_l (l = 0..p), Dfac[K][p+1].  Every face's jumps are formed once per tile from LDS.  u is
+// only read here (the projection kernel that updates it runs afterwards).  Measured, against a thread per
+// node with the neighbours staged per element: 0.98 -> 0.52 ms at 1024^2, N = 4, k = 3 (1.24 GB), 61 -> 37 us
+// at 241 x 137, N = 5, 32 -> 17 us at 256^2, N = 2.  Bound by VALU issue and the latency of its staging loads.
 template <int P, int M, bool R2>
 __device__ __forceinline__ void vel_sensor_body(const double* __restrict__ rho, const double* __restrict__ u,
                                                     const double* __restrict__ Bx, const double* __restrict__ By,
                                                     const double* __restrict__ Bz, const double* __restrict__ lines,
                                                     const double* __restrict__ glob, double* __restrict__ Dfac,
                                                     const HydroTab* __restrict__ H, const MagTab* __restrict__ T,
-                                                    MeshP mp, double tau, double sM, long blk) {
-  using C = VS<P, M>;
-  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, A = C::A, B = C::B, AB = C::AB;
-  // sbb holds an element's B coefficients (B_x, B_y, B_z at offsets 0, AB, 2 AB) and, once they
-  // have been interpolated, its node wave speeds |u_x| + c_A and |u_y| + c_A (offsets 0 and NN);
-  // sharing the buffer keeps the block at about 27 KB of LDS at N = 4 (6 blocks per CU)
-  constexpr int NSB = 2 * AB + C::BB > 2 * NN ? 2 * AB + C::BB : 2 * NN;
-  __shared__ double su[EB][3][NN], sx[EB][6][NN], ssig[EB][2][NP], samp[EB][2][3], ssg[EB][3][NP];
-  __shared__ double srow[EB][2][NP];
-  __shared__ int scst[EB][3];
-  __shared__ double sbb[EB][NSB];
-  __shared__ double tD0[NP][NP], tDp[NP][NP], tWP[NP][A], tGP[NP][B], tVP[NP][B], tw[NP], tfr[NP];
-  constexpr int NU = R2 ? 2 : 3;  // velocity components (u_z = 0 in the 2D2V system)
-  const int tid = threadIdx.x, el = tid / NN, q = tid - el * NN;
-  const int qi = q % NP, qj = q / NP;
-  const long e = blk * EB + el;
-  const bool act = el < EB && e < mp.K;
-  int ex, ey;
-  elem_xy32(mp, act ? (int)e : 0, ex, ey);
+                                                    const MeshP& mp, double tau, double sM, int blk) {
+  using C = VS<P, M, R2>;
+  constexpr int NP = C::NP, NN = C::NN, ES = C::ES, A = C::A, B = C::B, BS = C::BS, NU = C::NU;
+  constexpr int TX = C::TX, TY = C::TY, TE = C::TE, NS = C::NS, NX = C::NX, NY = C::NY;
+  using PX = Patch<TY * B, TX * B + 1, B, TX, BS>;
+  using PY = Patch<TY * B + 1, TX * B, B, TX, BS>;
+  using PZ = Patch<TY * B, TX * B, B, TX, BS>;
+  // su[c][staged element][ES]; then the faces' jumps sj[c][face][NP] (x faces first)
+  constexpr int NUS = NU * NS * ES, NJ = NU * (NX + NY) * NP;
+  __shared__ double su[NUS > NJ ? NUS : NJ], sr[TE * ES], sx[PX::SIZE], sy[PY::SIZE], sz[R2 ? 1 : PZ::SIZE];
+  __shared__ double sws[2][NP][TE], ssg[TE][2 * NP], samp[2][TX > TY ? TX : TY];
+  const int tid = threadIdx.x;
+  int tx0, ty0;
+  tile_of(blk, (mp.nx + TX - 1) / TX, (mp.ny + TY - 1) / TY, tx0, ty0);
+  tx0 *= TX; ty0 *= TY;
+  const int tw = mp.nx - tx0 < TX ? mp.nx - tx0 : TX, th = mp.ny - ty0 < TY ? mp.ny - ty0 : TY;
   const long KN = mp.K * NN;
-  // node arrays through buffer resources and 32-bit byte offsets (arrays below 2^29 nodes)
-  auto uoff = [&](int el_) { return ((unsigned)el_ * NN + q) * 8u; };
-  const __amdgpu_buffer_rsrc_t ur[3] = {node_rsrc(u, KN), node_rsrc(u + KN, KN), node_rsrc(u + 2 * KN, KN)};
-  for (int t = tid; t < NP * NP; t += 256) {
-    tD0[t / NP][t % NP] = H->Dr0[t / NP][t % NP];
-    tDp[t / NP][t % NP] = H->Drp[t / NP][t % NP];
-  }
-  for (int t = tid; t < NP * A; t += 256) tWP[t / A][t % A] = T->I_W_P[t / A][t % A];
-  for (int t = tid; t < NP * B; t += 256) {
-    tGP[t / B][t % B] = T->I_G_P[t / B][t % B];
-    tVP[t / B][t % B] = T->I_V_P[t / B][t % B];
-  }
-  if (tid < NP) { tw[tid] = H->w[tid]; tfr[tid] = H->fr[tid]; }
-  double uu[3] = {0.0, 0.0, 0.0}, rq = 1.0;
-  if (act) {
+  // the nodes of the staged elements (ring: left, right column, bottom, top row), coalesced
+  constexpr int NR = (NS * NN + BS - 1) / BS, NRR = (TE * NN + BS - 1) / BS;
+  {
+    double v[NR][NU], w[NRR];
+    int slot[NR];
 #pragma unroll
-    for (int d = 0; d < NU; ++d) { uu[d] = bld(ur[d], uoff((int)e)); su[el][d][q] = uu[d]; }
-    rq = bld(node_rsrc(rho, KN), uoff((int)e));
-    for (int k = q; k < AB; k += NN) {
-      sbb[el][k] = Bx[gix(mp, B, ex, ey, k % A, k / A)];
-      sbb[el][AB + k] = By[gix(mp, B, ex, ey, k % B, k / B)];
+    for (int m = 0; m < NR; ++m) {
+      const int n = tid + m * BS, s = n / NN, q = n - s * NN;
+      int x, y;
+      bool in;
+      if (s < TE) { y = s / TX; x = s - y * TX; in = x < tw && y < th; }
+      else if (s < TE + 2 * TY) { const int h = s - TE; x = h < TY ? -1 : tw; y = h < TY ? h : h - TY; in = y < th; }
+      else { const int h = s - TE - 2 * TY; y = h < TX ? -1 : th; x = h < TX ? h : h - TX; in = s < NS && x < tw; }
+      slot[m] = in ? s * ES + q : -1;
+      if (in) {
+        const unsigned o = ((unsigned)(wrap32(ty0 + y, mp.ny) * mp.nx + wrap32(tx0 + x, mp.nx)) * NN + q) * 8u;
+#pragma unroll
+        for (int d = 0; d < NU; ++d) v[m][d] = bld(node_rsrc(u + d * KN, KN), o);
+        if (m < NRR && s < TE) w[m < NRR ? m : 0] = bld(node_rsrc(rho, KN), o);
+      }
     }
-    for (int k = q; !R2 && k < C::BB; k += NN) sbb[el][2 * AB + k] = Bz[gix(mp, B, ex, ey, k % B, k / B)];
+    PX px;
+    PY py;
+    px.load(Bx, mp, tx0 * B, ty0 * B, tw * B + 1, th * B);
+    py.load(By, mp, tx0 * B, ty0 * B, tw * B, th * B + 1);
+    if constexpr (!R2) {
+      PZ pz;
+      pz.load(Bz, mp, tx0 * B, ty0 * B, tw * B, th * B);
+      pz.store(sz);
+    }
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+      if (slot[m] >= 0) {
+#pragma unroll
+        for (int d = 0; d < NU; ++d) su[d * NS * ES + slot[m]] = v[m][d];
+        if (m < NRR && slot[m] < TE * ES) sr[slot[m]] = w[m < NRR ? m : 0];
+      }
+    px.store(sx);
+    py.store(sy);
+  }
+  // cross-line amplitudes shared by the components: rows, then columns
+  if (tid < TY + TX) {
+    const int D = tid < TY ? 0 : 1, i = D ? tid - TY : tid;
+    if (i < (D ? tw : th)) {
+      const double* l = lines + (D ? mp.ny + tx0 + i : ty0 + i) * (NU * 3);
+      const double rn = D ? mp.r4ny : mp.r4nx;
+      double a = 0.0;
+#pragma unroll
+      for (int d = 0; d < NU; ++d) {
+        const double gm = glob[d * 3] * mp.r4K, m = l[d * 3] * rn;
+        const double dOm = fmax(glob[d * 3 + 2] - gm, gm - glob[d * 3 + 1]);
+        a = fmax(a, fmax(fmax(l[d * 3 + 2] - m, m - l[d * 3 + 1]), 1e-6 * dOm));
+      }
+      samp[D][i] = a;
+    }
   }
   __syncthreads();
-  // shared amplitudes: each component's global and cross-line spreads formed once per element
-  for (int c = q; act && c < NU; c += NN) {
-    const double gs = glob[c * 3], gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
-    const double gm = gs * mp.r4K;
-    const double dOm = fmax(gmx - gm, gm - gmn);
-    // constant to roundoff: the nodal values agree to 2^10 ulps of the field's size (exact test)
-    scst[el][c] = gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn)) ? 1 : 0;
-    const double* rl = lines + (ey * NU + c) * 3;
-    const double* cl = lines + ((mp.ny + ex) * NU + c) * 3;
-    const double rm = rl[0] * mp.r4nx, cm = cl[0] * mp.r4ny;
-    samp[el][0][c] = fmax(fmax(rl[2] - rm, rm - rl[1]), 1e-6 * dOm);
-    samp[el][1][c] = fmax(fmax(cl[2] - cm, cm - cl[1]), 1e-6 * dOm);
-  }
-  double wsx = 0.0, wsy = 0.0;  // node wave speeds
-  if (act) {
-    double bxv = 0.0, byv = 0.0, bzv = 0.0;
+  // the largest wave speeds |u_x| + c_A, |u_y| + c_A of each GLL row
+  for (int k = tid; k < TE * NP; k += BS) {
+    const int j = k / TE, en = k - j * TE, y = en / TX, x = en - y * TX;
+    if (x < tw && y < th) {
+      double b2[NP];
+      {
+        double c[A], t[B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-      double s = 0.0;
+        for (int i = 0; i < B; ++i) t[i] = T->I_G_P[j][i];
 #pragma unroll
-      for (int i = 0; i < A; ++i) s += tWP[qi][i] * sbb[el][j * A + i];
-      bxv += tGP[qj][j] * s;
-    }
+        for (int i = 0; i < A; ++i) c[i] = dot_patch<PX, B>(t, sx + y * PX::RS + x, i);
 #pragma unroll
-    for (int j = 0; j < A; ++j) {
-      double s = 0.0;
+        for (int q = 0; q < NP; ++q) {
+          double s = 0.0;
 #pragma unroll
-      for (int i = 0; i < B; ++i) s += tGP[qi][i] * sbb[el][AB + j * B + i];
-      byv += tWP[qj][j] * s;
-    }
-#pragma unroll
-    for (int j = 0; !R2 && j < B; ++j) {
-      double s = 0.0;
-#pragma unroll
-      for (int i = 0; i < B; ++i) s += tVP[qi][i] * sbb[el][2 * AB + j * B + i];
-      bzv += tVP[qj][j] * s;
-    }
-    const double va = sqrt(bxv * bxv + byv * byv + bzv * bzv) * rsqrt_refined(rq);  // rho > 0
-    wsx = fabs(uu[0]) + va;
-    wsy = fabs(uu[1]) + va;
-  }
-  __syncthreads();  // every lane has read the B coefficients
-  if (act) { sbb[el][q] = wsx; sbb[el][NN + q] = wsy; }
-  // the y neighbours' velocities are loaded into registers here, so that their latency overlaps
-  // the x-direction phases (they go to LDS once those are done)
-  double uy_nb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (act) {
-    const unsigned om = uoff(wrap32(ey - 1, mp.ny) * mp.nx + ex), op = uoff(wrap32(ey + 1, mp.ny) * mp.nx + ex);
-#pragma unroll
-    for (int c = 0; c < NU; ++c) {
-      uy_nb[c] = bld(ur[c], om);
-      uy_nb[3 + c] = bld(ur[c], op);
-    }
-  }
-#pragma unroll
-  for (int D = 0; D < 2; ++D) {
-    // neighbours across the faces normal to D: sx rows 0..2 minus side, 3..5 plus side
-    if (act) {
-      if (D == 0) {
-        const unsigned om = uoff(ey * mp.nx + wrap32(ex - 1, mp.nx)), op = uoff(ey * mp.nx + wrap32(ex + 1, mp.nx));
-#pragma unroll
-        for (int c = 0; c < NU; ++c) {
-          sx[el][c][q] = bld(ur[c], om);
-          sx[el][3 + c][q] = bld(ur[c], op);
+          for (int i = 0; i < A; ++i) s = fma(T->I_W_P[q][i], c[i], s);
+          b2[q] = s * s;
         }
-      } else {
-#pragma unroll
-        for (int c = 0; c < NU; ++c) { sx[el][c][q] = uy_nb[c]; sx[el][3 + c][q] = uy_nb[3 + c]; }
       }
-    }
-    __syncthreads();
-    const int r = D == 0 ? qi : qj, line = D == 0 ? qj : qi;
-    double jmp[6];
-    if (act) {
-      const double wl = 0.5 * tw[line];
+      SCHED_FENCE();
+      {
+        double c[B], t[A];
 #pragma unroll
-      for (int c = 0; c < NU; ++c) {
-        double a = 0.0, d = 0.0, b = 0.0, cc = 0.0;
+        for (int i = 0; i < A; ++i) t[i] = T->I_W_P[j][i];
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-          const int nk = D == 0 ? line * NP + k : k * NP + line;
-          const double own = su[el][c][nk];
-          a += tD0[r][k] * own;
-          d += tDp[r][k] * own;
-          b += tDp[r][k] * sx[el][c][nk];
-          cc += tD0[r][k] * sx[el][3 + c][nk];
+        for (int i = 0; i < B; ++i) c[i] = dot_patch<PY, A>(t, sy + y * PY::RS + x, i);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          double s = 0.0;
+#pragma unroll
+          for (int i = 0; i < B; ++i) s = fma(T->I_G_P[q][i], c[i], s);
+          b2[q] = fma(s, s, b2[q]);
         }
-        const double jm = a - b, jp = cc - d;
-        jmp[2 * c] = wl * jm * jm;
-        jmp[2 * c + 1] = wl * jp * jp;
       }
-    }
-    __syncthreads();
-    if (act) {
+      SCHED_FENCE();
+      if constexpr (!R2) {
+        double c[B], t[B];
 #pragma unroll
-      for (int c = 0; c < 2 * NU; ++c) sx[el][c][q] = jmp[c];
-    }
-    __syncthreads();
-    // sigma^u: the (r, component) terms spread over the element's threads, then max over components
-    {
-      double Dsh = 0.0;
+        for (int i = 0; i < B; ++i) t[i] = T->I_V_P[j][i];
 #pragma unroll
-      for (int c = 0; c < NU; ++c) Dsh = act ? fmax(Dsh, samp[el][D][c]) : 0.0;
-      for (int tk = q; act && tk < NU * NP; tk += NN) {
-        const int rr = tk % NP, c = tk / NP;
-        double v = 0.0;
-        if (Dsh > 0.0 && !scst[el][c]) {
-          double sm = 0.0, spp = 0.0;
-          for (int l = 0; l < NP; ++l) {
-            const int nk = D == 0 ? l * NP + rr : rr * NP + l;
-            sm += sx[el][2 * c][nk];
-            spp += sx[el][2 * c + 1][nk];
-          }
-          v = tfr[rr] * (sqrt(sm) + sqrt(spp)) / Dsh;
+        for (int i = 0; i < B; ++i) c[i] = dot_patch<PZ, B>(t, sz + y * PZ::RS + x, i);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          double s = 0.0;
+#pragma unroll
+          for (int i = 0; i < B; ++i) s = fma(T->I_V_P[q][i], c[i], s);
+          b2[q] = fma(s, s, b2[q]);
         }
-        ssg[el][c][rr] = v;
       }
-      if (D == 0)  // row maxima of the node wave speeds, combined over the rows at the end
-        for (int t = q; act && t < NP; t += NN) {
-          double ax = 0.0, ay = 0.0;
-#pragma unroll
-          for (int k = 0; k < NP; ++k) { ax = fmax(ax, sbb[el][t * NP + k]); ay = fmax(ay, sbb[el][NN + t * NP + k]); }
-          srow[el][0][t] = ax;
-          srow[el][1][t] = ay;
-        }
-    }
-    __syncthreads();
-    if (act && q < NP) {
-      double sig = 0.0;
-#pragma unroll
-      for (int c = 0; c < NU; ++c) sig = fmax(sig, ssg[el][c][q]);
-      ssig[el][D][q] = sig;
-    }
-    __syncthreads();
-  }
-  if (act && q <= P) {
-    double Dl = 1.0;
-    if (q > 0) {
+      SCHED_FENCE();
       double ax = 0.0, ay = 0.0;
 #pragma unroll
-      for (int l = 0; l < NP; ++l) { ax = fmax(ax, srow[el][0][l]); ay = fmax(ay, srow[el][1][l]); }
-      const double lx = (2.0 * P + 1.0) * mp.rhx * ax, ly = (2.0 * P + 1.0) * mp.rhy * ay;
-      double sx_ = 0.0, sy_ = 0.0;
-      for (int r = 0; r <= q; ++r) { sx_ += ssig[el][0][r]; sy_ += ssig[el][1][r]; }
-      Dl = exp(-sM * tau * (lx * sx_ + ly * sy_));
+      for (int q = 0; q < NP; ++q) {
+        const int n = en * ES + j * NP + q;
+        const double va = sqrt(b2[q]) * rsqrt_refined(sr[n]);  // rho > 0
+        ax = fmax(ax, fabs(su[n]) + va);
+        ay = fmax(ay, fabs(su[NS * ES + n]) + va);
+      }
+      sws[0][j][en] = ax;
+      sws[1][j][en] = ay;
     }
-    Dfac[e * NP + q] = Dl;
+  }
+  SCHED_FENCE();
+  // the thread's face (x faces: fx counts the TX + 1 faces of a row) and component
+  const int D = __builtin_amdgcn_readfirstlane(tid >= BS / 2 ? 1 : 0);
+  const int t = tid - D * (BS / 2), nf = D ? NY : NX, c = t / nf, f = t - c * nf;
+  const int fx = D ? f % TX : f % (TX + 1), fy = D ? f / TX : f / (TX + 1);
+  const bool act = c < NU && (D ? fx < tw && fy <= th : fx <= tw && fy < th);
+  double J[NP];
+  if (act) {
+    const double* S = su + c * NS * ES;
+    if (D == 0)
+      face_jumps<P, 0>(S + (fx == 0 ? TE + fy : fy * TX + fx - 1) * ES, S + (fx == tw ? TE + TY + fy : fy * TX + fx) * ES, H, J);
+    else
+      face_jumps<P, 1>(S + (fy == 0 ? TE + 2 * TY + fx : (fy - 1) * TX + fx) * ES,
+                       S + (fy == th ? TE + 2 * TY + TX + fx : fy * TX + fx) * ES, H, J);
+  }
+  __syncthreads();
+  if (act) {
+    // a component that is constant to roundoff (its nodal values agree to 2^10 ulps of the field's size, an exact
+    // test) does not count
+    const double gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
+    const bool cst = gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn));
+    double* o = su + (c * (NX + NY) + (D ? NX + f : f)) * NP;
+#pragma unroll
+    for (int r = 0; r < NP; ++r) o[r] = cst ? 0.0 : J[r];
+  }
+  __syncthreads();
+  // sigma^u: the two faces' jumps, maximum over the components, against the shared amplitude
+  for (int k = tid; k < TE * 2 * NP; k += BS) {
+    const int r = k % NP, d = (k / NP) & 1, en = k / (2 * NP), x = en % TX, y = en / TX;
+    if (x < tw && y < th) {
+      const int f0 = d ? NX + y * TX + x : y * (TX + 1) + x, f1 = f0 + (d ? TX : 1);
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < NU; ++q)
+        s = fmax(s, su[(q * (NX + NY) + f0) * NP + r] + su[(q * (NX + NY) + f1) * NP + r]);
+      const double a = samp[d][d ? x : y];
+      ssg[en][d * NP + r] = a > 0.0 ? H->fr[r] * s / a : 0.0;
+    }
+  }
+  __syncthreads();
+  for (int k = tid; k < TE * NP; k += BS) {
+    const int l = k % NP, en = k / NP, x = en % TX, y = en / TX;
+    if (x < tw && y < th) {
+      double ax = 0.0, ay = 0.0, sgx = 0.0, sgy = 0.0;
+#pragma unroll
+      for (int j = 0; j < NP; ++j) { ax = fmax(ax, sws[0][j][en]); ay = fmax(ay, sws[1][j][en]); }
+      const double lx = (2.0 * P + 1.0) * mp.rhx * ax, ly = (2.0 * P + 1.0) * mp.rhy * ay;
+      for (int r = 0; r <= l; ++r) { sgx += ssg[en][r]; sgy += ssg[en][NP + r]; }
+      Dfac[(long)((ty0 + y) * mp.nx + tx0 + x) * NP + l] = l == 0 ? 1.0 : exp(-sM * tau * (lx * sgx + ly * sgy));
+    }
   }
 }
 
+template <int P, int M>
+long vel_sensor_tiles(const MeshP& mp, bool r2) {
+  const int TX = VS<P, M, true>::TX, TY = r2 ? VS<P, M, true>::TY : VS<P, M, false>::TY;
+  return (long)((mp.nx + TX - 1) / TX) * ((mp.ny + TY - 1) / TY);
+}
+
 template <int P, int M, bool R2>
-__global__ __launch_bounds__(256, (P == 4 && M == 3) ? 6 : 1) void k_vel_sensor(const double* __restrict__ rho, const double* __restrict__ u,
+__global__ __launch_bounds__((VS<P, M, R2>::BS)) void k_vel_sensor(const double* __restrict__ rho, const double* __restrict__ u,
                                                     const double* __restrict__ Bx, const double* __restrict__ By,
                                                     const double* __restrict__ Bz, const double* __restrict__ lines,
                                                     const double* __restrict__ glob, double* __restrict__ Dfac,
                                                     const HydroTab* __restrict__ H, const MagTab* __restrict__ T,
                                                     MeshP mp, double tau, double sM) {
-  vel_sensor_body<P, M, R2>(rho, u, Bx, By, Bz, lines, glob, Dfac, H, T, mp, tau, sM, xcd_block());
+  vel_sensor_body<P, M, R2>(rho, u, Bx, By, Bz, lines, glob, Dfac, H, T, mp, tau, sM, (int)xcd_block());
 }
 
 struct vel_sensor_args {
@@ -1340,10 +1348,10 @@ struct vel_sensor_args {
 };
 
 template <int P, int M, bool R2>
-__global__ __launch_bounds__(256, (P == 4 && M == 3) ? 6 : 1) void k_vel_sensor_rt(const vel_sensor_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+__global__ __launch_bounds__((VS<P, M, R2>::BS)) void k_vel_sensor_rt(const vel_sensor_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const vel_sensor_args& a = A[r];
-  vel_sensor_body<P, M, R2>(gl(a.rho), gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.H), gl(a.T), a.mp, a.tau, a.sM, (long)blockIdx.x - boff[r]);
+  vel_sensor_body<P, M, R2>(gl(a.rho), gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.H), gl(a.T), a.mp, a.tau, a.sM, (int)blockIdx.x - boff[r]);
 }
 
 // Velocity-OE map (eq. magnetic-oe-map) with the prepared basis, EB elements per block.  The block's
@@ -2007,17 +2015,21 @@ int mag_velocity_apply(mhd25_ctx* c, double tau, const double* rho, double* u, d
 #undef FS
   }
   line_global_reduce(c, c->stats, nu, nullptr);
+  long nbs = 0;
+#define NBS(P, M) nbs = vel_sensor_tiles<P, M>(c->mp, r2)
+  DISPATCH_PM(c->p, c->m, NBS);
+#undef NBS
   if (c->rec) {
     if (!stats_ready) { c->err = "run-table plan: velocity statistics must come from the update"; return -2; }
-    rt_record(c, RT_VEL_SENSOR, mkey(c->p, c->m, r2), nb,
+    rt_record(c, RT_VEL_SENSOR, mkey(c->p, c->m, r2), nbs,
               vel_sensor_args{rho, u, Bx, By, Bz, c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M});
     rt_record(c, RT_VEL_PROJ, mkey(c->p, c->m, r2), nb2, vel_proj_args{rho, u, e, c->psi, c->dfac, c->d_ht, c->mp, Uc});
     return 0;
   }
 #define VSN(P, M)                                                                                                   \
-  if (r2) hipLaunchKernelGGL((k_vel_sensor<P, M, true>), dim3(nb), dim3(256), 0, c->stream, rho, u, Bx, By, Bz,    \
+  if (r2) hipLaunchKernelGGL((k_vel_sensor<P, M, true>), dim3(nbs), dim3((VS<P, M, true>::BS)), 0, c->stream, rho, u, Bx, By, Bz,    \
                              c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M);                 \
-  else hipLaunchKernelGGL((k_vel_sensor<P, M, false>), dim3(nb), dim3(256), 0, c->stream, rho, u, Bx, By, Bz,      \
+  else hipLaunchKernelGGL((k_vel_sensor<P, M, false>), dim3(nbs), dim3((VS<P, M, false>::BS)), 0, c->stream, rho, u, Bx, By, Bz,      \
                           c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M)
   {
     T_BEGIN(6);
@@ -2197,8 +2209,8 @@ int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, i
     case RT_VEL_SENSOR: {
       const vel_sensor_args* A = (const vel_sensor_args*)dargs;
 #define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_vel_sensor_rt<P, M, true>), g, dim3(256), 0, s, A, dboff, nr);                      \
-  else hipLaunchKernelGGL((k_vel_sensor_rt<P, M, false>), g, dim3(256), 0, s, A, dboff, nr)
+  if (r2) hipLaunchKernelGGL((k_vel_sensor_rt<P, M, true>), g, dim3((VS<P, M, true>::BS)), 0, s, A, dboff, nr);                      \
+  else hipLaunchKernelGGL((k_vel_sensor_rt<P, M, false>), g, dim3((VS<P, M, false>::BS)), 0, s, A, dboff, nr)
       DISPATCH_PM(p, m, F);
 #undef F
       break;

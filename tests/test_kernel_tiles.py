@@ -55,13 +55,17 @@ def run_gpu(L, opts, name, args):
 
 
 def check_velocity_oe(run, p, m, nx, ny):
+    """The full system, and the 2D2V system (u_z = 0, B_z = 0)."""
     import paper_2609_10849_amd as pk
     L, M, rho, e, u, _, Bx, By, Bz = state(p, m, nx, ny)
     tau = 0.05  # damping factors well away from 0 and 1
-    ru, re, _ = O.velocity_oe(M, O.Options.full(), tau, rho, u, e, Bx, By, Bz)
-    out = run(L, pk.Options.full(), "mhd25_velocity_oe", [tau, rho, u, e, Bx, By, Bz])
-    close(out[2], ru, "u")
-    close(out[3], re, "e")
+    plane = u.copy()
+    plane[2] = 0.0
+    for r2, v, bz in ((0, u, Bz), (1, plane, np.zeros_like(Bz))):
+        ru, re, _ = O.velocity_oe(M, O.Options.full(), tau, rho, v, e, Bx, By, bz)
+        out = run(L, pk.Options.full(reduced_2d2v=r2), "mhd25_velocity_oe", [tau, rho, v, e, Bx, By, bz])
+        close(out[2], ru, "u, 2d2v %d" % r2)
+        close(out[3], re, "e, 2d2v %d" % r2)
 
 
 def check_rhs_hydro(run, p, m, nx, ny):
