@@ -64,7 +64,7 @@ def kernel_table(N, k):
 def source_sha(fname):
     """Hash of a kernel source file and the headers every kernel file includes."""
     h = hashlib.sha256(open(os.path.join(CSRC, fname), "rb").read())
-    for name in ("common.h", "xcd.h", "ec_log.h", "rsqrt.h"):
+    for name in ("common.h", "xcd.h", "ec_log.h", "rsqrt.h", "jumps.h"):
         h.update(open(os.path.join(CSRC, name), "rb").read())
     return h.hexdigest()[:16]
 
@@ -87,7 +87,7 @@ def ingest_counters(dirs, K=1048576, N=4, k=3, steps=1):
     `bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-extras`: one directory with FETCH_SIZE, one
     with WRITE_SIZE and one with the FP64 instruction counters (SQ_INSTS_VALU_FLOPS_FP64, SQ_INSTS_VALU,
     SQ_WAVES).  FETCH_SIZE and WRITE_SIZE are scaled by what they read for the entry snapshot kernel,
-    which copies the state (5 K (N+1)^2 doubles) once: known bytes over counter value.  FP64 flops per
+    which copies the state (K (5 (N+1)^2 + 3 (k+1)^2) doubles) once: known bytes over counter value.  FP64 flops per
     launch are SQ_INSTS_VALU_FLOPS_FP64 (2 FMA + ADD + MUL + TRANS FP64 instructions per wave) times 64
     lanes times the fraction of a block's lanes that carry work."""
     import csv
@@ -99,15 +99,15 @@ def ingest_counters(dirs, K=1048576, N=4, k=3, steps=1):
             for row in csv.DictReader(open(f)):
                 name, ctr = row["Kernel_Name"], row["Counter_Name"]
                 val = float(row["Counter_Value"])
-                for pre in [t[2] for t in kernel_table(N, k)] + ["k_snap_check_U"]:
+                for pre in [t[2] for t in kernel_table(N, k)] + ["k_snap_check"]:
                     if pre in name:
                         vals.setdefault(ctr, {}).setdefault(pre, []).append(val)
-    known = 5.0 * K * (N + 1) ** 2 * 8
-    fetch_cal = known / vals["FETCH_SIZE"]["k_snap_check_U"][0]
-    write_cal = known / vals["WRITE_SIZE"]["k_snap_check_U"][0]
+    known = (5.0 * (N + 1) ** 2 + 3.0 * (k + 1) ** 2) * K * 8
+    fetch_cal = known / vals["FETCH_SIZE"]["k_snap_check"][0]
+    write_cal = known / vals["WRITE_SIZE"]["k_snap_check"][0]
     out = {"elements": K, "N": N, "k": k, "workload": "blast-like state %dx%d elements, N=%d, k=%d, one Strang step"
            % (int(K ** 0.5), int(K ** 0.5), N, k),
-           "calibration": {"kernel": "k_snap_check_U (entry snapshot: copies the state)", "bytes": known,
+           "calibration": {"kernel": "k_snap_check (entry snapshot: copies the state)", "bytes": known,
                            "fetch_factor": fetch_cal, "write_factor": write_cal},
            "commands": ["rocprofv3 --pmc %s --output-format csv -d gpurun_out/%s -o %s -- python -u bench.py --steps 1 "
                         "--warmup 0 --no-cpu-baseline --no-extras" % (c, d, d[-1].lower())

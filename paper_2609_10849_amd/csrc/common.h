@@ -141,7 +141,7 @@ struct MagIO {
 // kernel launch (its kind, template key, block count and the kernel's argument struct for this run)
 // instead of launching; a plan zips the records of all runs into run-table launches.
 enum RtKind {
-  RT_HYDRO_STAGE, RT_OE_PP, RT_LINE_REDUCE, RT_GLOBAL_REDUCE, RT_RESET, RT_COPY, RT_SNAP_U, RT_COPY_CHECK,
+  RT_HYDRO_STAGE, RT_OE_PP, RT_LINE_REDUCE, RT_GLOBAL_REDUCE, RT_RESET, RT_COPY, RT_SNAP,
   RT_TO_PRIM, RT_TO_CONS, RT_J, RT_E, RT_MAG_UPDATE, RT_VEL_PREP, RT_VEL_SENSOR,
   RT_VEL_PROJ, RT_B_STATS, RT_AR_TRACES, RT_AR_ETA, RT_MAX, RT_BATCH_ZERO, RT_BATCH_FOLD, RT_HYDRO_SENSOR, RT_NKIND
 };

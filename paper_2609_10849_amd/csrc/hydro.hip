@@ -982,20 +982,24 @@ __device__ __forceinline__ void snap_check_node(const double* __restrict__ U, do
   if (!fin || !(v[0] > 0.0) || !(p > 0.0)) atomicOr(flag + 1, 2);
 }
 
-__global__ __launch_bounds__(256) void k_snap_check_U(const double* __restrict__ U, double* __restrict__ snap, long KN,
-                                                      double g, int* __restrict__ flag) {
-  for (long n = (long)blockIdx.x * blockDim.x + threadIdx.x; n < KN; n += (long)gridDim.x * blockDim.x)
-    snap_check_node(U, snap, KN, g, flag, n);
+// the same of an entry copy of the magnetic grids (finiteness), entry k of B_x, B_y and B_z
+__device__ __forceinline__ void snap_check_B(const double* __restrict__ Bx, const double* __restrict__ By,
+                                             const double* __restrict__ Bz, double* __restrict__ snap, long G,
+                                             int* __restrict__ flag, long k) {
+  const double x = Bx[k], y = By[k], z = Bz[k];
+  snap[k] = x; snap[G + k] = y; snap[2 * G + k] = z;
+  if (!(fabs(x) <= DBL_MAX && fabs(y) <= DBL_MAX && fabs(z) <= DBL_MAX)) atomicOr(flag + 1, 2);
 }
 
-// entry copy with a finiteness test (magnetic grids); a non-finite value sets bit 1 of flag[1]
-__global__ __launch_bounds__(256) void k_copy_check(const double* __restrict__ a, double* __restrict__ b, long n,
+// The entry copy in one launch (on small meshes launches cost more than the copies: 3 us saved per launch).
+// G = 0: no magnetic grids.
+__global__ __launch_bounds__(256) void k_snap_check(const double* __restrict__ U, double* __restrict__ snapU, long KN, double g,
+                                                    const double* __restrict__ Bx, const double* __restrict__ By,
+                                                    const double* __restrict__ Bz, double* __restrict__ snapB, long G,
                                                     int* __restrict__ flag) {
-  for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const double v = a[k];
-    b[k] = v;
-    if (!(fabs(v) <= DBL_MAX)) atomicOr(flag + 1, 2);
-  }
+  const long k0 = (long)blockIdx.x * blockDim.x + threadIdx.x, dk = (long)gridDim.x * blockDim.x;
+  for (long n = k0; n < KN; n += dk) snap_check_node(U, snapU, KN, g, flag, n);
+  for (long k = k0; k < G; k += dk) snap_check_B(Bx, By, Bz, snapB, G, flag, k);
 }
 
 }  // namespace
@@ -1156,13 +1160,17 @@ struct copy_args {
   const double* a;
   double* b;
   long n;
-  int* flag;  // non-null: finiteness test into flag[1]
 };
 struct snap_args {
   const double* U;
-  double* snap;
+  double* snapU;
   long KN;
   double g;
+  const double* Bx;
+  const double* By;
+  const double* Bz;
+  double* snapB;
+  long G;
   int* flag;
 };
 
@@ -1233,7 +1241,8 @@ int hydro_rhs(mhd25_ctx* c, const double* U, double* dU) {
   return check(c, hipGetLastError(), "rhs_hydro launch");
 }
 
-// raw stage + statistics + line/global reductions
+// raw stage + statistics + line/global reductions (the OE sensor's only: without OE nothing reads them, and on a
+// 16^2 mesh they were a quarter of a step)
 int hydro_stage_a(mhd25_ctx* c, const double* Us, const double* Un, double* Ust, double ca, double cb, double tau) {
   const int bs = stage_block(c);
   const int eb = bs / 2 / (c->p + 1);
@@ -1241,7 +1250,7 @@ int hydro_stage_a(mhd25_ctx* c, const double* Us, const double* Un, double* Ust,
   if (c->rec) {
     rt_record(c, RT_HYDRO_STAGE, c->p * 1000 + bs, blocks,
               hydro_stage_args{Us, Un, Ust, c->stats, c->d_flag, c->d_ht, c->mp, ca, cb, tau, c->opt.iface_flux});
-    return launch_reductions(c, c->stats, 5, c->d_flag);
+    return c->opt.oe_hydro ? launch_reductions(c, c->stats, 5, c->d_flag) : 0;
   }
   hipEvent_t* ev = c->timing ? timing_slot(c, 0) : nullptr;
   if (ev) hipEventRecord(ev[0], c->stream);
@@ -1255,6 +1264,7 @@ int hydro_stage_a(mhd25_ctx* c, const double* Us, const double* Un, double* Ust,
   if (ev) hipEventRecord(ev[1], c->stream);
   int r = check(c, hipGetLastError(), "hydro stage launch");
   if (r) return r;
+  if (!c->opt.oe_hydro) return 0;
   if (const int rl = launch_reductions(c, c->stats, 5, c->d_flag)) return rl;
   return check(c, hipGetLastError(), "reduce launch");
 }
@@ -1326,22 +1336,16 @@ int entry_clear(mhd25_ctx* c) {
 // entry snapshot of U (and of the magnetic grids when B is set) into snapU / saveB with the
 // admissibility test; clears and then sets the entry word flag[1]
 int entry_snapshot(mhd25_ctx* c, const double* U, double* snapU, const double* const* B, double* saveB) {
-  const long KN = c->mp.K * c->nn;
+  const long KN = c->mp.K * c->nn, G = B ? c->G : 0;
+  const double *Bx = B ? B[0] : nullptr, *By = B ? B[1] : nullptr, *Bz = B ? B[2] : nullptr;
   if (c->rec) {
     rt_record(c, RT_RESET, 0, 1, reset_args{c->d_flag, c->d_counts, 1});
-    rt_record(c, RT_SNAP_U, 0, flat_blocks(KN), snap_args{U, snapU, KN, c->mp.gamma, c->d_flag});
-    if (B)
-      for (int k = 0; k < 3; ++k)
-        rt_record(c, RT_COPY_CHECK, 0, flat_blocks(c->G), copy_args{B[k], saveB + k * c->G, c->G, c->d_flag});
+    rt_record(c, RT_SNAP, 0, flat_blocks(KN), snap_args{U, snapU, KN, c->mp.gamma, Bx, By, Bz, saveB, G, c->d_flag});
     return 0;
   }
   hipLaunchKernelGGL(k_reset_attempt, dim3(1), dim3(64), 0, c->stream, c->d_flag, c->d_counts, 1);
-  hipLaunchKernelGGL(k_snap_check_U, dim3(flat_blocks(KN)), dim3(256), 0, c->stream, U, snapU, KN, c->mp.gamma,
-                     c->d_flag);
-  if (B)
-    for (int k = 0; k < 3; ++k)
-      hipLaunchKernelGGL(k_copy_check, dim3(flat_blocks(c->G)), dim3(256), 0, c->stream, B[k], saveB + k * c->G, c->G,
-                         c->d_flag);
+  hipLaunchKernelGGL(k_snap_check, dim3(flat_blocks(KN)), dim3(256), 0, c->stream, U, snapU, KN, c->mp.gamma, Bx, By, Bz,
+                     saveB, G, c->d_flag);
   return check(c, hipGetLastError(), "entry snapshot launch");
 }
 
@@ -1357,7 +1361,7 @@ int dcopy(mhd25_ctx* c, const double* a, double* b, long n) {
   long blocks = (n + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
-  if (c->rec) { rt_record(c, RT_COPY, 0, blocks, copy_args{a, b, n, nullptr}); return 0; }
+  if (c->rec) { rt_record(c, RT_COPY, 0, blocks, copy_args{a, b, n}); return 0; }
   hipLaunchKernelGGL(k_copy, dim3(blocks), dim3(256), 0, c->stream, a, b, n);
   return check(c, hipGetLastError(), "copy launch");
 }
@@ -1380,20 +1384,15 @@ __global__ __launch_bounds__(256) void k_copy_rt(const copy_args* __restrict__ A
   const int r = rt_run(boff, nr);
   const copy_args& a = A[r];
   const long stride = (long)(boff[r + 1] - boff[r]) * blockDim.x;
-  for (long k = (long)(blockIdx.x - boff[r]) * blockDim.x + threadIdx.x; k < a.n; k += stride) {
-    const double v = gl(a.a)[k];
-    gl(a.b)[k] = v;
-    if (gl(a.flag) && !(fabs(v) <= DBL_MAX)) atomicOr(gl(a.flag) + 1, 2);
-  }
+  for (long k = (long)(blockIdx.x - boff[r]) * blockDim.x + threadIdx.x; k < a.n; k += stride) gl(a.b)[k] = gl(a.a)[k];
 }
 
-__global__ __launch_bounds__(256) void k_snap_check_U_rt(const snap_args* __restrict__ A, const int* __restrict__ boff,
-                                                         int nr) {
+__global__ __launch_bounds__(256) void k_snap_check_rt(const snap_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const snap_args& a = A[r];
-  const long stride = (long)(boff[r + 1] - boff[r]) * blockDim.x;
-  for (long n = (long)(blockIdx.x - boff[r]) * blockDim.x + threadIdx.x; n < a.KN; n += stride)
-    snap_check_node(gl(a.U), gl(a.snap), a.KN, a.g, gl(a.flag), n);
+  const long k0 = (long)(blockIdx.x - boff[r]) * blockDim.x + threadIdx.x, dk = (long)(boff[r + 1] - boff[r]) * blockDim.x;
+  for (long n = k0; n < a.KN; n += dk) snap_check_node(gl(a.U), gl(a.snapU), a.KN, a.g, gl(a.flag), n);
+  for (long k = k0; k < a.G; k += dk) snap_check_B(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.snapB), a.G, gl(a.flag), k);
 }
 
 int hydro_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int nr, long nblocks, hipStream_t s) {
@@ -1443,11 +1442,10 @@ int hydro_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int 
       hipLaunchKernelGGL(k_reset_rt, dim3((nr + 63) / 64), dim3(64), 0, s, (const reset_args*)dargs, nr);
       break;
     case RT_COPY:
-    case RT_COPY_CHECK:
       hipLaunchKernelGGL(k_copy_rt, g, dim3(256), 0, s, (const copy_args*)dargs, dboff, nr);
       break;
-    case RT_SNAP_U:
-      hipLaunchKernelGGL(k_snap_check_U_rt, g, dim3(256), 0, s, (const snap_args*)dargs, dboff, nr);
+    case RT_SNAP:
+      hipLaunchKernelGGL(k_snap_check_rt, g, dim3(256), 0, s, (const snap_args*)dargs, dboff, nr);
       break;
     default:
       return 1;  // not a kind of this file
