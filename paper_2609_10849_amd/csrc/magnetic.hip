@@ -1908,21 +1908,14 @@ static long tiles(const MeshP& mp) {
   return (long)((mp.nx + RT<M, false>::TX - 1) / RT<M, false>::TX) * ((mp.ny + RT<M, false>::TY - 1) / RT<M, false>::TY);
 }
 
-// r2: the 2D2V reduced system (only J_z and E_z are formed; the in-plane grids are not written)
-int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
-                       const double* eta, double* JE, bool r2) {
-  const long G = c->G;
-  double *Jx = JE, *Jy = JE + G, *Jz = JE + 2 * G, *Ex = JE + 3 * G, *Ey = JE + 4 * G, *Ez = JE + 5 * G;
+// J alone (three grids).  r2: the 2D2V reduced system (only J_z and E_z are formed; the in-plane grids are not written)
+int mag_reconstruct_J(mhd25_ctx* c, const double* Bx, const double* By, const double* Bz, double* J, bool r2) {
+  double *Jx = J, *Jy = J + c->G, *Jz = J + 2 * c->G;
   long nb = 0;
 #define NB(M) nb = tiles<M>(c->mp)
   DISPATCH_M(c->m, NB);
 #undef NB
-  if (c->rec) {
-    const int k = mkey(c->p, c->m, r2);
-    rt_record(c, RT_J, k, nb, J_args{Bx, By, Bz, Jx, Jy, Jz, c->d_mt, c->mp});
-    rt_record(c, RT_E, k, nb, E_args{u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp});
-    return 0;
-  }
+  if (c->rec) { rt_record(c, RT_J, mkey(c->p, c->m, r2), nb, J_args{Bx, By, Bz, Jx, Jy, Jz, c->d_mt, c->mp}); return 0; }
 #define LJ(P, M)                                                                                                    \
   if (r2) hipLaunchKernelGGL((k_J<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, Bx, By, Bz, Jx, Jy, \
                              Jz, c->d_mt, c->mp);                                                                   \
@@ -1934,6 +1927,22 @@ int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const do
     T_END();
   }
 #undef LJ
+  return chk(c, "J reconstruction launch");
+}
+
+int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
+                       const double* eta, double* JE, bool r2) {
+  const long G = c->G;
+  double *Jx = JE, *Jy = JE + G, *Jz = JE + 2 * G, *Ex = JE + 3 * G, *Ey = JE + 4 * G, *Ez = JE + 5 * G;
+  if (const int r = mag_reconstruct_J(c, Bx, By, Bz, JE, r2)) return r;
+  long nb = 0;
+#define NB(M) nb = tiles<M>(c->mp)
+  DISPATCH_M(c->m, NB);
+#undef NB
+  if (c->rec) {
+    rt_record(c, RT_E, mkey(c->p, c->m, r2), nb, E_args{u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp});
+    return 0;
+  }
 #define LE(P, M)                                                                                                    \
   if (r2) hipLaunchKernelGGL((k_E<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, u, Bx, By, Bz, Jx,  \
                              Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp);                                              \

@@ -299,9 +299,152 @@ __device__ __forceinline__ long gix(const MeshP& mp, int B, long ex, long ey, in
   return gy * NX + gx;
 }
 
+// 1D tables in LDS, rows at an odd stride (16 lanes that read 16 rows then read 16 banks)
+using Tab = double[MHD_MAXN][MHD_MAXN + 1];
+__device__ __forceinline__ void tab(Tab d, const double (&s)[MHD_MAXN][MHD_MAXN], int tid) {
+  for (int k = tid; k < MHD_MAXN * MHD_MAXN; k += 256) d[k / MHD_MAXN][k % MHD_MAXN] = s[k / MHD_MAXN][k % MHD_MAXN];
+}
+
+// Both kernels of the reverse run a thread per node and EB elements per block, and form every 2D operator as two
+// 1D ones with the intermediate line sums in LDS (tasks spread over the element's threads).  As double sums over
+// the nodes, with the tables at a stride of 8, they took 2.77 (update) and 2.60 ms (E) at 1024^2, N = 4,
+// k = 3, now 1.81 and 2.10 ms; at 128^2, N = 3 both forms take 21 to 24 us.  Bound by LDS reads and index
+// arithmetic.
+//
+// x halves of the interpolation of NC nodal fields f[c][qj][qi] at the columns of the W and Gauss nodes:
+// h[c][qj][x] (x < A: W, else Gauss)
+template <class C, int NC>
+__device__ __forceinline__ void x_nodes(double* h, const double* f, const Tab& tPW, const Tab& tPG, int t) {
+  constexpr int NP = C::NP, A = C::A, X = C::A + C::B;
+  for (int k = t; k < NC * NP * X; k += C::NT) {
+    const int r = k / X, x = k - r * X;
+    const double* I = x < A ? tPW[x] : tPG[x - A];
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v = fma(I[q], f[r * NP + q], v);
+    h[k] = v;
+  }
+}
+
+// their value at a node: column x, row j of Iy
+template <class C>
+__device__ __forceinline__ double y_node(const double* h, int c, int x, const double* Iy) {
+  constexpr int NP = C::NP, X = C::A + C::B;
+  double v = 0.0;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) v = fma(Iy[q], h[(c * NP + q) * X + x], v);
+  return v;
+}
+
+// x halves of B_z at the columns of the W and Gauss nodes, z[jj][x], and its value at a node
+template <class C>
+__device__ __forceinline__ void x_bz(double* z, const double* bz, const Tab& tVW, const Tab& tVG, int t) {
+  constexpr int A = C::A, B = C::B, X = A + B;
+  for (int k = t; k < B * X; k += C::NT) {
+    const int jj = k / X, x = k - jj * X;
+    const double* I = x < A ? tVW[x] : tVG[x - A];
+    double v = 0.0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) v = fma(I[i], bz[jj * B + i], v);
+    z[k] = v;
+  }
+}
+template <class C>
+__device__ __forceinline__ double y_bz(const double* z, int x, const double* Iy) {
+  constexpr int B = C::B, X = C::A + B;
+  double v = 0.0;
+#pragma unroll
+  for (int jj = 0; jj < B; ++jj) v = fma(Iy[jj], z[jj * X + x], v);
+  return v;
+}
+
+// transpose of the B_z interpolation: x halves z[row][ii] of the values fx at the N_x nodes (rows 0..A-1) and fy at
+// the N_y nodes (rows A..), then the coefficient (ii, jj)
+template <class C>
+__device__ __forceinline__ void x_bzt(double* z, const double* fx, const double* fy, const Tab& tVW, const Tab& tVG, int t) {
+  constexpr int A = C::A, B = C::B;
+  for (int k = t; k < (A + B) * B; k += C::NT) {
+    const int j = k / B, ii = k - j * B;
+    double v = 0.0;
+    if (j < A) {
+#pragma unroll
+      for (int i = 0; i < B; ++i) v = fma(tVG[i][ii], fx[j * B + i], v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < A; ++i) v = fma(tVW[i][ii], fy[(j - A) * A + i], v);
+    }
+    z[k] = v;
+  }
+}
+template <class C>
+__device__ __forceinline__ double y_bzt(const double* z, int ii, int jj, const Tab& tVW, const Tab& tVG) {
+  constexpr int A = C::A, B = C::B;
+  double v = 0.0;
+#pragma unroll
+  for (int j = 0; j < A; ++j) v = fma(tVW[j][jj], z[j * B + ii], v);
+#pragma unroll
+  for (int j = 0; j < B; ++j) v = fma(tVG[j][jj], z[(A + j) * B + ii], v);
+  return v;
+}
+
+// J layouts (N_x, N_y, W nodes) to the GLL_p nodes: x halves h (N_x: [j < A][qi], N_y: [j < B][qi], W: [j < A][qi]),
+// then the three components at node (qi, qj)
+template <class C>
+__device__ __forceinline__ void x_toP(double* h, const double* fx, const double* fy, const double* fz, const Tab& tWP, const Tab& tGP, int t) {
+  constexpr int NP = C::NP, A = C::A, B = C::B;
+  for (int k = t; k < (2 * A + B) * NP; k += C::NT) {
+    const int r = k / NP, q = k - r * NP;
+    double v = 0.0;
+    if (r < A) {
+#pragma unroll
+      for (int i = 0; i < B; ++i) v = fma(tGP[q][i], fx[r * B + i], v);
+    } else {
+      const double* f = r < A + B ? fy + (r - A) * A : fz + (r - A - B) * A;
+#pragma unroll
+      for (int i = 0; i < A; ++i) v = fma(tWP[q][i], f[i], v);
+    }
+    h[k] = v;
+  }
+}
+template <class C>
+__device__ __forceinline__ void y_toP(double* v, const double* h, int qi, int qj, const Tab& tWP, const Tab& tGP) {
+  constexpr int NP = C::NP, A = C::A, B = C::B;
+  v[0] = v[1] = v[2] = 0.0;
+#pragma unroll
+  for (int j = 0; j < A; ++j) {
+    v[0] = fma(tWP[qj][j], h[j * NP + qi], v[0]);
+    v[2] = fma(tWP[qj][j], h[(A + B + j) * NP + qi], v[2]);
+  }
+#pragma unroll
+  for (int j = 0; j < B; ++j) v[1] = fma(tGP[qj][j], h[(A + j) * NP + qi], v[1]);
+}
+
+// its transpose: x halves of f[c][qj][qi], h[qj][x] (x < B: N_x, then A of N_y, then A of W), then one node
+template <class C>
+__device__ __forceinline__ void x_fromP(double* h, const double* f, const Tab& tWP, const Tab& tGP, int t) {
+  constexpr int NP = C::NP, NN = C::NN, A = C::A, B = C::B, X = 2 * A + B;
+  for (int k = t; k < NP * X; k += C::NT) {
+    const int qj = k / X, x = k - qj * X, c = x < B ? 0 : (x < A + B ? 1 : 2);
+    const double(*I)[MHD_MAXN + 1] = x < B ? tGP : tWP;
+    const int i = x < B ? x : (x < A + B ? x - B : x - A - B);
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v = fma(I[q][i], f[c * NN + qj * NP + q], v);
+    h[k] = v;
+  }
+}
+template <class C>
+__device__ __forceinline__ double y_fromP(const double* h, int x, const Tab& ty, int j) {
+  constexpr int NP = C::NP, X = 2 * C::A + C::B;
+  double v = 0.0;
+#pragma unroll
+  for (int q = 0; q < NP; ++q) v = fma(ty[q][j], h[q * X + x], v);
+  return v;
+}
+
 // Reverse of the update (curl, Lorentz, Ohm).  Writes per-element locals:
 //   EL: E-bar in (Nx, Ny, W) layouts; JL: J-bar (Lorentz + Ohm) in (Nx, Ny, W);
-//   BL: B-bar of the element's B locals: [bx: Ny layout (AB) | by: Nx layout (AB) | bz (BB)] (accumulated).
+//   BL: B-bar of the element's B locals: [bx: Ny layout (AB) | by: Nx layout (AB) | bz (BB)].
 template <int P, int M>
 __global__ __launch_bounds__(256) void k_vjp_update(const double* __restrict__ rho, const double* __restrict__ Bx,
                                                     const double* __restrict__ By, const double* __restrict__ Bz,
@@ -313,32 +456,26 @@ __global__ __launch_bounds__(256) void k_vjp_update(const double* __restrict__ r
                                                     const MagTab* __restrict__ T, MeshP mp, long G) {
   using C = MV<P, M>;
   constexpr int NP = C::NP, NN = C::NN, A = C::A, B = C::B, AA = C::AA, AB = C::AB, BB = C::BB, EB = C::EB,
-                NT = C::NT, LOC = C::LOC;
-  __shared__ double sbx[EB][AB], sby[EB][AB], sbz[EB][BB], sjx[EB][AB], sjy[EB][AB], sjz[EB][AA];
-  __shared__ double scx[EB][BB], scy[EB][BB], scz[EB][BB];  // cotangents at owned B nodes
-  __shared__ double sup[EB][3][NN];                         // du_cot / (rho M)
-  __shared__ double sjq[EB][3][NN];                         // J-bar at GLL_p nodes (Ohm)
-  __shared__ double sfb[EB][3][AA + 2 * AB];                // B-bar at aux nodes: W (AA), Nx (AB), Ny (AB)
-  // the interpolation and derivative tables, staged in LDS (lane-dependent indexes into the
-  // device table would each be a vector memory load)
-  __shared__ double tDWG[MHD_MAXN][MHD_MAXN], tDWV[MHD_MAXN][MHD_MAXN], tIGP[MHD_MAXN][MHD_MAXN], tIGV[MHD_MAXN][MHD_MAXN], tIGW[MHD_MAXN][MHD_MAXN], tIVG[MHD_MAXN][MHD_MAXN], tIVW[MHD_MAXN][MHD_MAXN], tIWP[MHD_MAXN][MHD_MAXN], tIPW[MHD_MAXN][MHD_MAXN], tIPG[MHD_MAXN][MHD_MAXN];
+                NT = C::NT, LOC = C::LOC, X = A + B;
+  constexpr int NHP = (2 * A + B) * NP, NH = 3 * NP * X > NHP ? 3 * NP * X : NHP;
+  __shared__ double sbx[EB][AB], sby[EB][AB], sjx[EB][AB], sjy[EB][AB], sjz[EB][AA];
+  __shared__ double sbz[EB][BB], scx[EB][BB], scy[EB][BB], scz[EB][BB];  // cotangents at owned B nodes
+  __shared__ double sup[EB][3 * NN];  // du_cot / (rho M)
+  __shared__ double sh[EB][NH];       // x halves
+  __shared__ double szh[EB][X * B];   // x halves of B_z and of its transpose
+  __shared__ double sch[EB][B * X];   // x halves of the curl's transpose of the B_z cotangents
+  // J-bar at the GLL_p nodes (Ohm); then B-bar at the W (x, y), N_x and N_y (z) nodes
+  constexpr int NQ = 3 * NN > 2 * (AA + AB) ? 3 * NN : 2 * (AA + AB);
+  __shared__ double sq[EB][NQ];
+  double* const sjq = sq[threadIdx.x / NT < EB ? threadIdx.x / NT : 0];
+  double *const swx = sjq, *const swy = sjq + AA, *const szx = sjq + 2 * AA, *const szy = szx + AB;
+  __shared__ Tab tDWG, tDWV, tIGP, tIGV, tIGW, tIVG, tIVW, tIWP, tIPW, tIPG;
   __shared__ double tww[MHD_MAXN], twg[MHD_MAXN], twp[MHD_MAXN];
   const int tid = threadIdx.x, el = tid / NT, t = tid - el * NT;
-  for (int k = threadIdx.x; k < MHD_MAXN * MHD_MAXN; k += 256) {
-    const int r = k / MHD_MAXN, c = k % MHD_MAXN;
-    tDWG[r][c] = T->D_W_G[r][c];
-    tDWV[r][c] = T->D_W_V[r][c];
-    tIGP[r][c] = T->I_G_P[r][c];
-    tIGV[r][c] = T->I_G_V[r][c];
-    tIGW[r][c] = T->I_G_W[r][c];
-    tIVG[r][c] = T->I_V_G[r][c];
-    tIVW[r][c] = T->I_V_W[r][c];
-    tIWP[r][c] = T->I_W_P[r][c];
-    tIPW[r][c] = T->I_P_W[r][c];
-    tIPG[r][c] = T->I_P_G[r][c];
-  }
-  if (threadIdx.x < MHD_MAXN) { tww[threadIdx.x] = T->ww[threadIdx.x]; twg[threadIdx.x] = T->wg[threadIdx.x]; twp[threadIdx.x] = T->wp[threadIdx.x]; }
-  __syncthreads();  // the load phase below already reads the tables
+  tab(tDWG, T->D_W_G, tid); tab(tDWV, T->D_W_V, tid); tab(tIGP, T->I_G_P, tid); tab(tIGV, T->I_G_V, tid);
+  tab(tIGW, T->I_G_W, tid); tab(tIVG, T->I_V_G, tid); tab(tIVW, T->I_V_W, tid); tab(tIWP, T->I_W_P, tid);
+  tab(tIPW, T->I_P_W, tid); tab(tIPG, T->I_P_G, tid);
+  if (tid < MHD_MAXN) { tww[tid] = T->ww[tid]; twg[tid] = T->wg[tid]; twp[tid] = T->wp[tid]; }
   const long e = (long)blockIdx.x * EB + el;
   const bool act = el < EB && e < mp.K;
   long ex, ey;
@@ -346,7 +483,14 @@ __global__ __launch_bounds__(256) void k_vjp_update(const double* __restrict__ r
   const long KN = mp.K * NN;
   const double et = (act && eta) ? eta[e] : 0.0;
   const double* Jx = JE; const double* Jy = JE + G; const double* Jz = JE + 2 * G;
+  double rq = 1.0, dec = 0.0, du[3] = {0.0, 0.0, 0.0};
   if (act) {
+    if (t < NN) {
+      const long n = e * NN + t;
+      rq = rho[n];
+      for (int d = 0; d < 3; ++d) du[d] = du_c[d * KN + n];
+      if (et != 0.0) dec = de_c[n];
+    }
     for (int k = t; k < AB; k += NT) {
       sbx[el][k] = Bx[gix(mp, B, ex, ey, k % A, k / A)];
       sby[el][k] = By[gix(mp, B, ex, ey, k % B, k / B)];
@@ -359,38 +503,53 @@ __global__ __launch_bounds__(256) void k_vjp_update(const double* __restrict__ r
       sbz[el][k] = Bz[g];
       scx[el][k] = dBx_c[g]; scy[el][k] = dBy_c[g]; scz[el][k] = dBz_c[g];
     }
-    if (t < NN) {
-      const int qi = t % NP, qj = t / NP;
-      const long n = e * NN + t;
-      const double w = 1.0 / (rho[n] * mp.J * twp[qi] * twp[qj]);
-      for (int d = 0; d < 3; ++d) sup[el][d][t] = du_c[d * KN + n] * w;
-      // Ohm: de = eta |J(x_q)|^2 / rho  ->  J-bar(x_q) = de_c * 2 eta J / rho
-      double jx = 0.0, jy = 0.0, jz = 0.0;
-      if (et != 0.0) {
-        for (int jj = 0; jj < A; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < B; ++ii) s += tIGP[qi][ii] * Jx[gix(mp, B, ex, ey, ii, jj)];
-          jx += tIWP[qj][jj] * s;
-        }
-        for (int jj = 0; jj < B; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < A; ++ii) s += tIWP[qi][ii] * Jy[gix(mp, B, ex, ey, ii, jj)];
-          jy += tIGP[qj][jj] * s;
-        }
-        for (int jj = 0; jj < A; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < A; ++ii) s += tIWP[qi][ii] * Jz[gix(mp, B, ex, ey, ii, jj)];
-          jz += tIWP[qj][jj] * s;
-        }
-      }
-      const double f = et != 0.0 ? de_c[n] * 2.0 * et / rho[n] : 0.0;
-      sjq[el][0][t] = f * jx; sjq[el][1][t] = f * jy; sjq[el][2][t] = f * jz;
+  }
+  __syncthreads();
+  const int qi = t % NP, qj = t / NP;
+  if (act && t < NN) {
+    const double w = 1.0 / (rq * mp.J * twp[qi] * twp[qj]);
+    for (int d = 0; d < 3; ++d) sup[el][d * NN + t] = du[d] * w;
+  }
+  const int any_eta = __syncthreads_or(act && et != 0.0);
+  if (any_eta) {
+    // Ohm: de = eta |J(x_q)|^2 / rho  ->  J-bar(x_q) = de_c * 2 eta J / rho
+    if (act && et != 0.0) x_toP<C>(sh[el], sjx[el], sjy[el], sjz[el], tIWP, tIGP, t);
+    __syncthreads();
+    if (act && et != 0.0 && t < NN) {
+      double j[3];
+      y_toP<C>(j, sh[el], qi, qj, tIWP, tIGP);
+      const double f = dec * 2.0 * et / rq;
+      for (int d = 0; d < 3; ++d) sjq[d * NN + t] = f * j[d];
+    }
+    __syncthreads();
+    if (act && et != 0.0) x_fromP<C>(sh[el], sjq, tIWP, tIGP, t);
+    __syncthreads();
+  }
+  // the Ohm part of J-bar at the thread's nodes
+  double oz = 0.0, ox = 0.0, oy = 0.0;
+  if (act && et != 0.0) {
+    if (t < AA) oz = y_fromP<C>(sh[el], A + B + t % A, tIWP, t / A);
+    if (t < AB) {
+      ox = y_fromP<C>(sh[el], t % B, tIWP, t / B);
+      oy = y_fromP<C>(sh[el], B + t % A, tIGP, t / A);
+    }
+  }
+  if (any_eta) __syncthreads();
+  if (act) {
+    x_nodes<C, 3>(sh[el], sup[el], tIPW, tIPG, t);
+    x_bz<C>(szh[el], sbz[el], tIVW, tIVG, t);
+    for (int k = t; k < B * X; k += NT) {  // [jj][x < A: D_W_V, else I_G_V]
+      const int jj = k / X, x = k - jj * X;
+      double v = 0.0;
+      for (int ii = 0; ii < B; ++ii) v = fma(x < A ? tDWV[ii][x] : tIGV[ii][x - A], scz[el][jj * B + ii], v);
+      sch[el][k] = v;
     }
   }
   __syncthreads();
   double* ELe = EL + e * LOC;
   double* JLe = JL + e * LOC;
   double* BLe = BL + e * (2 * AB + BB);
+  double bx0 = 0.0, by0 = 0.0;  // B-bar of B_x at its N_y node and of B_y at its N_x node
   if (act) {
     // E-bar from the curl (owned B nodes only; E nodes of the element's last GLL row/column belong to
     // neighbours' B nodes and receive nothing from this element)
@@ -407,108 +566,68 @@ __global__ __launch_bounds__(256) void k_vjp_update(const double* __restrict__ r
       {  // E_y local: Ny layout (i < A GLL x, l < B Gauss y); dBz = -(2/hx) sum I_G_V[j][l] D_W_V[i'][i] E_y
         const int i = t % A, l = t / A;
         double s = 0.0;
-        for (int jj = 0; jj < B; ++jj)
-          for (int ii = 0; ii < B; ++ii) s += tIGV[jj][l] * tDWV[ii][i] * scz[el][jj * B + ii];
+        for (int jj = 0; jj < B; ++jj) s = fma(tIGV[jj][l], sch[el][jj * X + i], s);
         ELe[AB + t] = -(2.0 / mp.hx) * s;
       }
       {  // E_x local: Nx layout (k < B Gauss x, l < A GLL y); dBz += (2/hy) sum D_W_V[j][l] I_G_V[i][k] E_x
         const int k = t % B, l = t / B;
         double s = 0.0;
-        for (int jj = 0; jj < B; ++jj)
-          for (int ii = 0; ii < B; ++ii) s += tDWV[jj][l] * tIGV[ii][k] * scz[el][jj * B + ii];
+        for (int jj = 0; jj < B; ++jj) s = fma(tDWV[jj][l], sch[el][jj * X + A + k], s);
         ELe[t] = (2.0 / mp.hy) * s;
       }
     }
     // Lorentz reverse at aux nodes: f-bar_a = w_a sum_q I_{a,q} u'_q
-    auto fbar = [&](int d, const double (*Ix)[MHD_MAXN], int ai, const double (*Iy)[MHD_MAXN], int aj) {
-      double v = 0.0;
-      for (int qj = 0; qj < NP; ++qj) {
-        double s = 0.0;
-        for (int qi = 0; qi < NP; ++qi) s += Ix[ai][qi] * sup[el][d][qj * NP + qi];
-        v += Iy[aj][qj] * s;
-      }
-      return v;
-    };
-    // Ohm reverse J-bar at aux node a of one layout: sum_q phi_a(x_q) Jbar(x_q)
-    auto ohm = [&](int c, const double (*Px)[MHD_MAXN], int ai, const double (*Py)[MHD_MAXN], int aj) {
-      double v = 0.0;
-      for (int qj = 0; qj < NP; ++qj)
-        for (int qi = 0; qi < NP; ++qi) v += sjq[el][c][qj * NP + qi] * (Px[qi][ai] * Py[qj][aj]);
-      return v;
-    };
     if (t < AA) {  // W node: f = (-B_y J_z, B_x J_z, 0)
       const int i = t % A, j = t / A;
       const double w = mp.J * tww[i] * tww[j];
-      const double fx = w * fbar(0, tIPW, i, tIPW, j), fy = w * fbar(1, tIPW, i, tIPW, j);
+      const double fx = w * y_node<C>(sh[el], 0, i, tIPW[j]), fy = w * y_node<C>(sh[el], 1, i, tIPW[j]);
       double bxv = 0.0, byv = 0.0;
       for (int k = 0; k < B; ++k) { bxv += tIGW[j][k] * sbx[el][k * A + i]; byv += tIGW[i][k] * sby[el][j * B + k]; }
       const double jz = sjz[el][t];
-      JLe[2 * AB + t] = -fx * byv + fy * bxv + (et != 0.0 ? ohm(2, tIWP, i, tIWP, j) : 0.0);
-      sfb[el][0][t] = fy * jz;   // B_x bar at W node
-      sfb[el][1][t] = -fx * jz;  // B_y bar
-      sfb[el][2][t] = 0.0;
+      JLe[2 * AB + t] = -fx * byv + fy * bxv + oz;
+      swx[t] = fy * jz;   // B_x bar at W node
+      swy[t] = -fx * jz;  // B_y bar
     }
     if (t < AB) {
       {  // N_x node (i < B, j < A): f = (0, -B_z J_x, B_y J_x)
         const int i = t % B, j = t / B;
         const double w = mp.J * twg[i] * tww[j];
-        const double fy = w * fbar(1, tIPG, i, tIPW, j), fz = w * fbar(2, tIPG, i, tIPW, j);
-        double bzv = 0.0;
-        for (int jj = 0; jj < B; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < B; ++ii) s += tIVG[i][ii] * sbz[el][jj * B + ii];
-          bzv += tIVW[j][jj] * s;
-        }
-        const double jx = sjx[el][t];
-        JLe[t] = -fy * bzv + fz * sby[el][t] + (et != 0.0 ? ohm(0, tIGP, i, tIWP, j) : 0.0);
-        sfb[el][0][AA + t] = 0.0;
-        sfb[el][1][AA + t] = fz * jx;   // B_y bar (B_y lives on these nodes)
-        sfb[el][2][AA + t] = -fy * jx;  // B_z bar at the node
+        const double fy = w * y_node<C>(sh[el], 1, A + i, tIPW[j]), fz = w * y_node<C>(sh[el], 2, A + i, tIPW[j]);
+        const double bzv = y_bz<C>(szh[el], A + i, tIVW[j]), jx = sjx[el][t];
+        JLe[t] = -fy * bzv + fz * sby[el][t] + ox;
+        by0 = fz * jx;            // B_y bar (B_y lives on these nodes)
+        szx[t] = -fy * jx;  // B_z bar at the node
       }
       {  // N_y node (i < A, j < B): f = (B_z J_y, 0, -B_x J_y)
         const int i = t % A, j = t / A;
         const double w = mp.J * tww[i] * twg[j];
-        const double fx = w * fbar(0, tIPW, i, tIPG, j), fz = w * fbar(2, tIPW, i, tIPG, j);
-        double bzv = 0.0;
-        for (int jj = 0; jj < B; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < B; ++ii) s += tIVW[i][ii] * sbz[el][jj * B + ii];
-          bzv += tIVG[j][jj] * s;
-        }
-        const double jy = sjy[el][t];
-        JLe[AB + t] = fx * bzv - fz * sbx[el][t] + (et != 0.0 ? ohm(1, tIWP, i, tIGP, j) : 0.0);
-        sfb[el][0][AA + AB + t] = -fz * jy;  // B_x bar (B_x lives on these nodes)
-        sfb[el][1][AA + AB + t] = 0.0;
-        sfb[el][2][AA + AB + t] = fx * jy;   // B_z bar
+        const double fx = w * y_node<C>(sh[el], 0, i, tIPG[j]), fz = w * y_node<C>(sh[el], 2, i, tIPG[j]);
+        const double bzv = y_bz<C>(szh[el], i, tIVG[j]), jy = sjy[el][t];
+        JLe[AB + t] = fx * bzv - fz * sbx[el][t] + oy;
+        bx0 = -fz * jy;          // B_x bar (B_x lives on these nodes)
+        szy[t] = fx * jy;  // B_z bar
       }
     }
   }
   __syncthreads();
-  if (!act) return;
   // transpose-interpolate aux-node B-bar to the element's B locals
-  if (t < AB) {
+  if (act) x_bzt<C>(szh[el], szx, szy, tIVW, tIVG, t);
+  if (act && t < AB) {
     {  // B_x local (i < A, k < B): from W nodes (i, j) via I_G_W[j][k] and from N_y node t directly
       const int i = t % A, k = t / A;
-      double s = sfb[el][0][AA + AB + t];
-      for (int j = 0; j < A; ++j) s += tIGW[j][k] * sfb[el][0][j * A + i];
+      double s = bx0;
+      for (int j = 0; j < A; ++j) s += tIGW[j][k] * swx[j * A + i];
       BLe[t] = s;
     }
     {  // B_y local (k < B, j < A): from W nodes (i, j) via I_G_W[i][k] and from N_x node t directly
       const int k = t % B, j = t / B;
-      double s = sfb[el][1][AA + t];
-      for (int i = 0; i < A; ++i) s += tIGW[i][k] * sfb[el][1][j * A + i];
+      double s = by0;
+      for (int i = 0; i < A; ++i) s += tIGW[i][k] * swy[j * A + i];
       BLe[AB + t] = s;
     }
   }
-  if (t < BB) {  // B_z local (ii, jj): from N_x (I_V_G x, I_V_W y) and N_y (I_V_W x, I_V_G y)
-    const int ii = t % B, jj = t / B;
-    double s = 0.0;
-    for (int j = 0; j < A; ++j)
-      for (int i = 0; i < B; ++i) s += tIVG[i][ii] * tIVW[j][jj] * sfb[el][2][AA + j * B + i];
-    for (int j = 0; j < B; ++j)
-      for (int i = 0; i < A; ++i) s += tIVW[i][ii] * tIVG[j][jj] * sfb[el][2][AA + AB + j * A + i];
-    BLe[2 * AB + t] = s;
-  }
+  __syncthreads();
+  if (act && t < BB) BLe[2 * AB + t] = y_bzt<C>(szh[el], t % B, t / B, tIVW, tIVG);
 }
 
 // Reverse of the E reconstruction: given E-bar (grids), produce u-bar (direct), and add
@@ -522,29 +641,22 @@ __global__ __launch_bounds__(256) void k_vjp_E(const double* __restrict__ u, con
                                                long G) {
   using C = MV<P, M>;
   constexpr int NP = C::NP, NN = C::NN, A = C::A, B = C::B, AA = C::AA, AB = C::AB, BB = C::BB, EB = C::EB,
-                NT = C::NT, LOC = C::LOC;
-  __shared__ double su[EB][3][NN], sbx[EB][AB], sby[EB][AB], sbz[EB][BB];
-  __shared__ double sl[EB][AA + 2 * AB];          // load-bar = E-bar / m at the element's aux nodes (W, Nx, Ny)
-  __shared__ double sub[EB][3][AA + 2 * AB];      // u-bar at aux nodes
-  __shared__ double sbb[EB][3][AA + 2 * AB];      // B-bar at aux nodes
-  __shared__ double tWP[NP][A], tGP[NP][B];         // W and Gauss bases at the GLL_p nodes (eta term)
-  // the interpolation tables, staged in LDS (lane-dependent indexes into the device table would
-  // each be a vector memory load)
-  __shared__ double tIGW[MHD_MAXN][MHD_MAXN], tIPG[MHD_MAXN][MHD_MAXN], tIPW[MHD_MAXN][MHD_MAXN], tIVG[MHD_MAXN][MHD_MAXN], tIVW[MHD_MAXN][MHD_MAXN];
+                NT = C::NT, LOC = C::LOC, X = A + B;
+  constexpr int NHP = (2 * A + B) * NP, NH = 3 * NP * X > NHP ? 3 * NP * X : NHP;
+  __shared__ double su[EB][3 * NN];  // u; then J-bar at the GLL_p nodes (eta term)
+  __shared__ double sbx[EB][AB], sby[EB][AB], sbz[EB][BB];
+  __shared__ double slz[EB][AA], slx[EB][AB], sly[EB][AB];  // load-bar = E-bar / m at the element's W, N_x, N_y nodes
+  __shared__ double sh[EB][NH];                              // x halves
+  __shared__ double szh[EB][X * B];                          // x halves of B_z and of its transpose
+  // u-bar at the W (x, y), N_x (y, z) and N_y (x, z) nodes; B-bar at W (x, y), N_x (z) and N_y (z)
+  __shared__ double swx[EB][AA], swy[EB][AA], snx[EB][2][AB], sny[EB][2][AB];
+  __shared__ double sbwx[EB][AA], sbwy[EB][AA], szx[EB][AB], szy[EB][AB];
+  __shared__ Tab tWP, tGP, tIGW, tIPG, tIPW, tIVG, tIVW;
   __shared__ double tww[MHD_MAXN], twg[MHD_MAXN], twp[MHD_MAXN];
   const int tid = threadIdx.x, el = tid / NT, t = tid - el * NT;
-  for (int k = tid; k < NP * A; k += 256) tWP[k / A][k % A] = T->I_W_P[k / A][k % A];
-  for (int k = tid; k < NP * B; k += 256) tGP[k / B][k % B] = T->I_G_P[k / B][k % B];
-  for (int k = tid; k < MHD_MAXN * MHD_MAXN; k += 256) {
-    const int r = k / MHD_MAXN, c = k % MHD_MAXN;
-    tIGW[r][c] = T->I_G_W[r][c];
-    tIPG[r][c] = T->I_P_G[r][c];
-    tIPW[r][c] = T->I_P_W[r][c];
-    tIVG[r][c] = T->I_V_G[r][c];
-    tIVW[r][c] = T->I_V_W[r][c];
-  }
+  tab(tWP, T->I_W_P, tid); tab(tGP, T->I_G_P, tid); tab(tIGW, T->I_G_W, tid); tab(tIPG, T->I_P_G, tid);
+  tab(tIPW, T->I_P_W, tid); tab(tIVG, T->I_V_G, tid); tab(tIVW, T->I_V_W, tid);
   if (tid < MHD_MAXN) { tww[tid] = T->ww[tid]; twg[tid] = T->wg[tid]; twp[tid] = T->wp[tid]; }
-  __syncthreads();  // the load phase below already reads the tables
   const long e = (long)blockIdx.x * EB + el;
   const bool act = el < EB && e < mp.K;
   long ex, ey;
@@ -552,169 +664,141 @@ __global__ __launch_bounds__(256) void k_vjp_E(const double* __restrict__ u, con
   const long KN = mp.K * NN;
   const double et = (act && eta) ? eta[e] : 0.0;
   const double* Exb = Ebar; const double* Eyb = Ebar + G; const double* Ezb = Ebar + 2 * G;
+  double ez = 0.0, ex_ = 0.0, ey_ = 0.0;  // E-bar at the thread's W, N_x and N_y nodes
   if (act) {
+    if (t < AA) ez = Ezb[gix(mp, B, ex, ey, t % A, t / A)];
+    if (t < AB) {
+      ex_ = Exb[gix(mp, B, ex, ey, t % B, t / B)];
+      ey_ = Eyb[gix(mp, B, ex, ey, t % A, t / A)];
+      sbx[el][t] = Bx[gix(mp, B, ex, ey, t % A, t / A)];
+      sby[el][t] = By[gix(mp, B, ex, ey, t % B, t / B)];
+    }
     for (int k = t; k < NN; k += NT)
-      for (int d = 0; d < 3; ++d) su[el][d][k] = u[d * KN + e * NN + k];
-    for (int k = t; k < AB; k += NT) {
-      sbx[el][k] = Bx[gix(mp, B, ex, ey, k % A, k / A)];
-      sby[el][k] = By[gix(mp, B, ex, ey, k % B, k / B)];
-    }
+      for (int d = 0; d < 3; ++d) su[el][d * NN + k] = u[d * KN + e * NN + k];
     for (int k = t; k < BB; k += NT) sbz[el][k] = Bz[gix(mp, B, ex, ey, k % B, k / B)];
-    // load-bar = E-bar / (assembled lumped weight); weights are sums over the sharing elements
-    for (int k = t; k < AA; k += NT) {
-      const int i = k % A, j = k / A;
-      const double wx = (i == 0 || i == A - 1) ? tww[0] + tww[A - 1] : tww[i];
-      const double wy = (j == 0 || j == A - 1) ? tww[0] + tww[A - 1] : tww[j];
-      sl[el][k] = Ezb[gix(mp, B, ex, ey, i, j)] / (mp.J * wx * wy);
-    }
-    for (int k = t; k < AB; k += NT) {
-      {
-        const int i = k % B, j = k / B;  // Nx
-        const double wy = (j == 0 || j == A - 1) ? tww[0] + tww[A - 1] : tww[j];
-        sl[el][AA + k] = Exb[gix(mp, B, ex, ey, i, j)] / (mp.J * twg[i] * wy);
-      }
-      {
-        const int i = k % A, j = k / A;  // Ny
-        const double wx = (i == 0 || i == A - 1) ? tww[0] + tww[A - 1] : tww[i];
-        sl[el][AA + AB + k] = Eyb[gix(mp, B, ex, ey, i, j)] / (mp.J * wx * twg[j]);
-      }
-    }
   }
   __syncthreads();
-  auto u_at = [&](int d, const double (*Ix)[MHD_MAXN], int ai, const double (*Iy)[MHD_MAXN], int aj) {
-    double v = 0.0;
-    for (int qj = 0; qj < NP; ++qj) {
-      double s = 0.0;
-      for (int qi = 0; qi < NP; ++qi) s += Ix[ai][qi] * su[el][d][qj * NP + qi];
-      v += Iy[aj][qj] * s;
+  if (act) {
+    // load-bar = E-bar / (assembled lumped weight); weights are sums over the sharing elements
+    auto W = [&](int i) { return (i == 0 || i == A - 1) ? tww[0] + tww[A - 1] : tww[i]; };
+    if (t < AA) slz[el][t] = ez / (mp.J * W(t % A) * W(t / A));
+    if (t < AB) {
+      slx[el][t] = ex_ / (mp.J * twg[t % B] * W(t / B));
+      sly[el][t] = ey_ / (mp.J * W(t % A) * twg[t / A]);
     }
-    return v;
-  };
+    x_nodes<C, 3>(sh[el], su[el], tIPW, tIPG, t);
+    x_bz<C>(szh[el], sbz[el], tIVW, tIVG, t);
+  }
+  __syncthreads();
+  double bx0 = 0.0, by0 = 0.0;  // B-bar of B_x at its N_y node and of B_y at its N_x node
   if (act) {
     if (t < AA) {  // W node: X_z = -(u_x B_y - u_y B_x)
       const int i = t % A, j = t / A;
-      const double ux = u_at(0, tIPW, i, tIPW, j), uy = u_at(1, tIPW, i, tIPW, j);
+      const double ux = y_node<C>(sh[el], 0, i, tIPW[j]), uy = y_node<C>(sh[el], 1, i, tIPW[j]);
       double bxv = 0.0, byv = 0.0;
       for (int k = 0; k < B; ++k) { bxv += tIGW[j][k] * sbx[el][k * A + i]; byv += tIGW[i][k] * sby[el][j * B + k]; }
-      const double s = mp.J * tww[i] * tww[j] * sl[el][t];
-      sub[el][0][t] = -s * byv; sub[el][1][t] = s * bxv; sub[el][2][t] = 0.0;
-      sbb[el][0][t] = s * uy; sbb[el][1][t] = -s * ux; sbb[el][2][t] = 0.0;
+      const double s = mp.J * tww[i] * tww[j] * slz[el][t];
+      swx[el][t] = -s * byv; swy[el][t] = s * bxv;
+      sbwx[el][t] = s * uy; sbwy[el][t] = -s * ux;
     }
     if (t < AB) {
       {  // N_x node: X_x = -(u_y B_z - u_z B_y)
         const int i = t % B, j = t / B;
-        const double uy = u_at(1, tIPG, i, tIPW, j), uz = u_at(2, tIPG, i, tIPW, j);
-        const double byv = sby[el][t];
-        double bzv = 0.0;
-        for (int jj = 0; jj < B; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < B; ++ii) s += tIVG[i][ii] * sbz[el][jj * B + ii];
-          bzv += tIVW[j][jj] * s;
-        }
-        const double s = mp.J * twg[i] * tww[j] * sl[el][AA + t];
-        sub[el][0][AA + t] = 0.0; sub[el][1][AA + t] = -s * bzv; sub[el][2][AA + t] = s * byv;
-        sbb[el][0][AA + t] = 0.0; sbb[el][1][AA + t] = s * uz; sbb[el][2][AA + t] = -s * uy;
+        const double uy = y_node<C>(sh[el], 1, A + i, tIPW[j]), uz = y_node<C>(sh[el], 2, A + i, tIPW[j]);
+        const double bzv = y_bz<C>(szh[el], A + i, tIVW[j]);
+        const double s = mp.J * twg[i] * tww[j] * slx[el][t];
+        snx[el][0][t] = -s * bzv; snx[el][1][t] = s * sby[el][t];
+        by0 = s * uz; szx[el][t] = -s * uy;
       }
       {  // N_y node: X_y = -(u_z B_x - u_x B_z)
         const int i = t % A, j = t / A;
-        const double ux = u_at(0, tIPW, i, tIPG, j), uz = u_at(2, tIPW, i, tIPG, j);
-        const double bxv = sbx[el][t];
-        double bzv = 0.0;
-        for (int jj = 0; jj < B; ++jj) {
-          double s = 0.0;
-          for (int ii = 0; ii < B; ++ii) s += tIVW[i][ii] * sbz[el][jj * B + ii];
-          bzv += tIVG[j][jj] * s;
-        }
-        const double s = mp.J * tww[i] * twg[j] * sl[el][AA + AB + t];
-        sub[el][0][AA + AB + t] = s * bzv; sub[el][1][AA + AB + t] = 0.0; sub[el][2][AA + AB + t] = -s * bxv;
-        sbb[el][0][AA + AB + t] = -s * uz; sbb[el][1][AA + AB + t] = 0.0; sbb[el][2][AA + AB + t] = s * ux;
+        const double ux = y_node<C>(sh[el], 0, i, tIPG[j]), uz = y_node<C>(sh[el], 2, i, tIPG[j]);
+        const double bzv = y_bz<C>(szh[el], i, tIVG[j]);
+        const double s = mp.J * tww[i] * twg[j] * sly[el][t];
+        sny[el][0][t] = s * bzv; sny[el][1][t] = -s * sbx[el][t];
+        bx0 = -s * uz; szy[el][t] = s * ux;
       }
     }
   }
+  double* JLe = JL + e * LOC;
+  double* BLe = BL + e * (2 * AB + BB);
   // eta term: load_a += eta sum_q M_q J_c(x_q) phi_a(x_q), so J-bar_c(x_q) = eta M_q sum_a phi_a(x_q)
   // lbar_a; it is formed once per GLL_p node (into su, whose last reads precede this barrier) and
   // then moved to the J-bar locals by the transpose of the J interpolation to GLL_p
   const int any_eta = __syncthreads_or(act && et != 0.0);
   if (any_eta) {
+    if (act && et != 0.0) x_toP<C>(sh[el], slx[el], sly[el], slz[el], tWP, tGP, t);
+    __syncthreads();
     if (act && et != 0.0 && t < NN) {
-      const int qi = t % NP, qj = t / NP;
-      double vz = 0.0, vx = 0.0, vy = 0.0;
-      for (int j = 0; j < A; ++j)
-        for (int i = 0; i < A; ++i) vz += tWP[qi][i] * tWP[qj][j] * sl[el][j * A + i];
-      for (int j = 0; j < A; ++j)
-        for (int i = 0; i < B; ++i) vx += tGP[qi][i] * tWP[qj][j] * sl[el][AA + j * B + i];
-      for (int j = 0; j < B; ++j)
-        for (int i = 0; i < A; ++i) vy += tWP[qi][i] * tGP[qj][j] * sl[el][AA + AB + j * A + i];
-      const double wq = et * mp.J * twp[qi] * twp[qj];
-      su[el][0][t] = wq * vx; su[el][1][t] = wq * vy; su[el][2][t] = wq * vz;
+      double v[3];
+      y_toP<C>(v, sh[el], t % NP, t / NP, tWP, tGP);
+      const double wq = et * mp.J * twp[t % NP] * twp[t / NP];
+      for (int d = 0; d < 3; ++d) su[el][d * NN + t] = wq * v[d];
+    }
+    __syncthreads();
+    if (act && et != 0.0) x_fromP<C>(sh[el], su[el], tWP, tGP, t);
+    __syncthreads();
+    if (act && et != 0.0) {
+      if (t < AA) JLe[2 * AB + t] += y_fromP<C>(sh[el], A + B + t % A, tWP, t / A);
+      if (t < AB) {
+        JLe[t] += y_fromP<C>(sh[el], t % B, tWP, t / B);
+        JLe[AB + t] += y_fromP<C>(sh[el], B + t % A, tGP, t / A);
+      }
     }
     __syncthreads();
   }
+  if (act) {
+    // u-bar: x halves of the transpose of the three interpolations, sh[d][row][qi] (A W rows, then B Gauss rows)
+    for (int k = t; k < 3 * X * NP; k += NT) {
+      const int r = k / NP, q = k - r * NP, d = r / X, j = r - d * X;
+      double v = 0.0;
+      if (j < A) {
+        if (d < 2) {
+          const double* f = d == 0 ? swx[el] : swy[el];
+#pragma unroll
+          for (int i = 0; i < A; ++i) v = fma(tIPW[i][q], f[j * A + i], v);
+        }
+        if (d > 0)
+#pragma unroll
+          for (int i = 0; i < B; ++i) v = fma(tIPG[i][q], snx[el][d - 1][j * B + i], v);
+      } else if (d != 1) {
+#pragma unroll
+        for (int i = 0; i < A; ++i) v = fma(tIPW[i][q], sny[el][d / 2][(j - A) * A + i], v);
+      }
+      sh[el][k] = v;
+    }
+    x_bzt<C>(szh[el], szx[el], szy[el], tIVW, tIVG, t);
+    if (t < AB) {
+      {  // B_x local (i < A, k < B)
+        const int i = t % A, k = t / A;
+        double s = bx0;
+        for (int j = 0; j < A; ++j) s += tIGW[j][k] * sbwx[el][j * A + i];
+        BLe[t] += s;
+      }
+      {  // B_y local (k < B, j < A)
+        const int k = t % B, j = t / B;
+        double s = by0;
+        for (int i = 0; i < A; ++i) s += tIGW[i][k] * sbwy[el][j * A + i];
+        BLe[AB + t] += s;
+      }
+    }
+  }
+  __syncthreads();
   if (!act) return;
-  double* JLe = JL + e * LOC;
-  double* BLe = BL + e * (2 * AB + BB);
-  if (t < NN) {  // u-bar at GLL_p node q: transpose of the three interpolations
+  if (t < NN) {
     const int qi = t % NP, qj = t / NP;
     for (int d = 0; d < 3; ++d) {
+      const double* h = sh[el] + d * X * NP + qi;
       double s = 0.0;
-      for (int j = 0; j < A; ++j)
-        for (int i = 0; i < A; ++i) s += tIPW[i][qi] * tIPW[j][qj] * sub[el][d][j * A + i];
-      for (int j = 0; j < A; ++j)
-        for (int i = 0; i < B; ++i) s += tIPG[i][qi] * tIPW[j][qj] * sub[el][d][AA + j * B + i];
-      for (int j = 0; j < B; ++j)
-        for (int i = 0; i < A; ++i) s += tIPW[i][qi] * tIPG[j][qj] * sub[el][d][AA + AB + j * A + i];
+#pragma unroll
+      for (int j = 0; j < A; ++j) s = fma(tIPW[j][qj], h[j * NP], s);
+      if (d != 1)
+#pragma unroll
+        for (int j = 0; j < B; ++j) s = fma(tIPG[j][qj], h[(A + j) * NP], s);
       ubar[d * KN + e * NN + t] = s;
     }
   }
-  if (t < AB) {
-    {  // B_x local (i < A, k < B)
-      const int i = t % A, k = t / A;
-      double s = sbb[el][0][AA + AB + t];
-      for (int j = 0; j < A; ++j) s += tIGW[j][k] * sbb[el][0][j * A + i];
-      BLe[t] += s;
-    }
-    {  // B_y local (k < B, j < A)
-      const int k = t % B, j = t / B;
-      double s = sbb[el][1][AA + t];
-      for (int i = 0; i < A; ++i) s += tIGW[i][k] * sbb[el][1][j * A + i];
-      BLe[AB + t] += s;
-    }
-  }
-  if (t < BB) {
-    const int ii = t % B, jj = t / B;
-    double s = 0.0;
-    for (int j = 0; j < A; ++j)
-      for (int i = 0; i < B; ++i) s += tIVG[i][ii] * tIVW[j][jj] * sbb[el][2][AA + j * B + i];
-    for (int j = 0; j < B; ++j)
-      for (int i = 0; i < A; ++i) s += tIVW[i][ii] * tIVG[j][jj] * sbb[el][2][AA + AB + j * A + i];
-    BLe[2 * AB + t] += s;
-  }
-  if (et != 0.0) {
-    const double(*jq)[NN] = su[el];  // J-bar_x, J-bar_y, J-bar_z at the GLL_p nodes
-    if (t < AA) {
-      const int i = t % A, j = t / A;
-      double s = 0.0;
-      for (int qj = 0; qj < NP; ++qj)
-        for (int qi = 0; qi < NP; ++qi) s += tWP[qi][i] * tWP[qj][j] * jq[2][qj * NP + qi];
-      JLe[2 * AB + t] += s;
-    }
-    if (t < AB) {
-      {
-        const int i = t % B, j = t / B;
-        double s = 0.0;
-        for (int qj = 0; qj < NP; ++qj)
-          for (int qi = 0; qi < NP; ++qi) s += tGP[qi][i] * tWP[qj][j] * jq[0][qj * NP + qi];
-        JLe[t] += s;
-      }
-      {
-        const int i = t % A, j = t / A;
-        double s = 0.0;
-        for (int qj = 0; qj < NP; ++qj)
-          for (int qi = 0; qi < NP; ++qi) s += tWP[qi][i] * tGP[qj][j] * jq[1][qj * NP + qi];
-        JLe[AB + t] += s;
-      }
-    }
-  }
+  if (t < BB) BLe[2 * AB + t] += y_bzt<C>(szh[el], t % B, t / B, tIVW, tIVG);
 }
 
 // Reverse of the J reconstruction: given J-bar (grids) add the B-bar locals of the weak curl.
@@ -882,8 +966,7 @@ __global__ void k_scatter_bz(const double* __restrict__ BL, long stride, long of
   switch (m) { case 0: F(0); break; case 1: F(1); break; case 2: F(2); break; case 3: F(3); break; \
                case 4: F(4); break; case 5: F(5); break; case 6: F(6); break; default: return -4; }
 
-int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
-                       const double* eta, double* JE, bool r2);
+int mag_reconstruct_J(mhd25_ctx* c, const double* Bx, const double* By, const double* Bz, double* J, bool r2);
 
 static int vchk(mhd25_ctx* c, const char* what) {
   hipError_t e = hipGetLastError();
@@ -921,8 +1004,8 @@ extern "C" int mhd25_rhs_magnetic_vjp(mhd25_ctx* c, const double* rho, const dou
   double* BL = JL + K * loc;
   double* Ebar = BL + K * bloc;  // 3G
   double* Jbar = Ebar + 3 * G;   // 3G
-  // forward recomputation of J and E
-  int r = mag_reconstruct_JE(c, u, Bx, By, Bz, eta, c->JE, false);  // the VJP reads every grid
+  // forward recomputation of J (E enters linearly: the reverse does not read it)
+  int r = mag_reconstruct_J(c, Bx, By, Bz, c->JE, false);  // the VJP reads every grid
   if (r) return r;
   int nn = (c->p + 1) * (c->p + 1), aa = a * a;
   const int eb = 256 / (nn > aa ? nn : aa);
