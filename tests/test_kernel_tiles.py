@@ -128,7 +128,35 @@ def check_reconstruction(run, p, m, nx, ny):
             close(out[5][k], want[k], "grid %d" % k, np.abs(Bx).max() / max(M.hx, M.hy))
 
 
-CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep, check_stage_map, check_reconstruction]
+def check_adjoint(run, p, m, nx, ny):
+    """Both VJPs against the oracle's JVP (dot products of random directions and cotangents, relative to the
+    sum of the terms' sizes, at least that of one derivative of B: a one-element mesh's cancel across its
+    own faces), the magnetic one without resistivity, with it, and with it in one element."""
+    import paper_2609_10849_amd as pk
+    L, M, rho, e, u, U, Bx, By, Bz = state(p, m, nx, ny)
+    rng = np.random.default_rng(7)
+
+    def dot_test(grads, dirs, cots, outs):
+        lhs = [(g * v).sum() for g, v in zip(grads, dirs)]
+        rhs = [(c * o).sum() for c, o in zip(cots, outs)]
+        size = max(sum(np.abs(g * v).sum() for g, v in zip(grads, dirs)), np.abs(Bx).max() / max(M.hx, M.hy))
+        assert abs(sum(lhs) - sum(rhs)) <= 1e-12 * size, (sum(lhs), sum(rhs), size)
+
+    eta = np.random.default_rng(5).uniform(0.01, 0.05, M.K)
+    for et in (None, eta, np.where(np.arange(M.K) == M.K // 2, eta, 0.0)):
+        ins = [u, Bx, By, Bz]
+        cots = [rng.standard_normal(a.shape) for a in [e] + ins]
+        dirs = [rng.standard_normal(a.shape) for a in ins]
+        out = run(L, pk.Options.make(), "mhd25_rhs_magnetic_vjp",
+                  [rho, u, Bx, By, Bz, et] + cots + [np.zeros_like(a) for a in ins])
+        dot_test(out[-4:], dirs, cots, O.rhs_magnetic_jvp(M, rho, u, Bx, By, Bz, et, *dirs))
+    for iface in (0, 1):
+        cot, V = rng.standard_normal(U.shape), rng.standard_normal(U.shape)
+        out = run(L, pk.Options.make(iface_flux=iface), "mhd25_rhs_hydro_vjp", [U, cot, np.zeros_like(U)])
+        dot_test([out[2]], [V], [cot], [O.rhs_hydro_jvp(M, U, V, iface)])
+
+
+CHECKS = [check_velocity_oe, check_rhs_hydro, check_hydro_substep, check_stage_map, check_reconstruction, check_adjoint]
 
 
 @pytest.mark.parametrize("nx,ny", SMALL)
