@@ -51,7 +51,33 @@ struct MagTab {
   // Gauss_m and GLL_m nodal fields, and the mass matrices of W and Gauss_m by the GLL_p rule.
   double RWQ[MHD_MAXN][MHD_MAXN], RDG[MHD_MAXN][MHD_MAXN], RDV[MHD_MAXN][MHD_MAXN];
   double RWP[MHD_MAXN][MHD_MAXN], RGP[MHD_MAXN][MHD_MAXN];
+  // The magnetic update's tables in the order and at the sizes of its LDS (see UpdTab), so that a block copies
+  // them with one load per thread in flight instead of waiting for one table after another.
+  double upd[10 * MHD_MAXN * MHD_MAXN];
 };
+
+// offsets of the magnetic update's tables, rows x columns in comments (A = m+2, B = m+1, NP = p+1)
+struct UpdTab {
+  int DWG, DWV, IGV, IGW, IVG, IVW, IPW, IPG, IGP, IWP, ww, wg, wp, n;
+  constexpr UpdTab(int p, int m) : DWG(0), DWV(0), IGV(0), IGW(0), IVG(0), IVW(0), IPW(0), IPG(0), IGP(0), IWP(0), ww(0), wg(0), wp(0), n(0) {
+    const int A = m + 2, B = m + 1, NP = p + 1;
+    DWG = 0;             // B x A
+    DWV = DWG + B * A;   // B x A
+    IGV = DWV + B * A;   // B x B
+    IGW = IGV + B * B;   // A x B
+    IVG = IGW + A * B;   // B x B
+    IVW = IVG + B * B;   // A x B
+    IPW = IVW + A * B;   // A x NP
+    IPG = IPW + A * NP;  // B x NP
+    IGP = IPG + B * NP;  // NP x B
+    IWP = IGP + NP * B;  // NP x A
+    ww = IWP + NP * A;
+    wg = ww + A;
+    wp = wg + B;
+    n = wp + NP;
+  }
+};
+static_assert(UpdTab(6, 6).n <= 10 * MHD_MAXN * MHD_MAXN, "the update's tables must fit");
 
 // velocity-OE basis table per element of degree p: (p+1)^2 rows (one per node) of the p^2 modes of the
 // shells below the last one (the last shell's part of a field is what the others leave of it), each

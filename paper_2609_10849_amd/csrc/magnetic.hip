@@ -580,6 +580,10 @@ __global__ __launch_bounds__((RT<M, R2>::BS)) void k_E_rt(const E_args* __restri
 // MODE 0: write L_M.  MODE 1: write the SSP stage (ca*Y^n + cb*Y_s) + cb*tau*L_M(Y_s).
 // ---------------------------------------------------------------------------------------------
 
+// One thread per node, EB elements per block.  Bound by the latency of its loads and barriers: the block's
+// tables and all node values are loaded before the first is stored to LDS (a table at a time and in loops per
+// array, each waited for its loads: 1.35 -> 1.06 ms at 1024^2, N = 4, k = 3 (4.8 GB); 44 -> 35 us at 256^2,
+// N = k = 2; 92 -> 81 us at 241 x 137, N = 5, k = 4; 200 -> 187 us at 512^2, N = 4, 2D2V).
 // (the 2D2V variants up to N = 4 fit 72 VGPRs, i.e. 7 waves per SIMD, without spills; the bound
 // keeps the compiler there)
 template <int P, int M, int MODE, int BS, bool R2>
@@ -597,8 +601,15 @@ __device__ __forceinline__ void mag_update_body(MagIO io, const MagTab* __restri
   constexpr int NF = 2 * AA + 4 * AB;
   static_assert(3 * NN <= NF, "the velocity buffer must fit in the Lorentz-load buffer");
   __shared__ double sf[EB][NF];
-  __shared__ double tDWG[B][A], tDWV[B][A], tIGV[B][B], tIGW[A][B], tIVG[B][B], tIVW[A][B], tIPW[A][NP], tIPG[B][NP], tIGP[NP][B], tIWP[NP][A];
-  __shared__ double tww[A], twg[B], twp[NP];
+  constexpr UpdTab o(P, M);
+  __shared__ double tb[o.n];
+  auto *const tDWG = (const double(*)[A])(tb + o.DWG), *const tDWV = (const double(*)[A])(tb + o.DWV);
+  auto *const tIGV = (const double(*)[B])(tb + o.IGV), *const tIGW = (const double(*)[B])(tb + o.IGW);
+  auto *const tIVG = (const double(*)[B])(tb + o.IVG), *const tIVW = (const double(*)[B])(tb + o.IVW);
+  auto *const tIPW = (const double(*)[NP])(tb + o.IPW), *const tIPG = (const double(*)[NP])(tb + o.IPG);
+  auto *const tIGP = (const double(*)[B])(tb + o.IGP);
+  auto *const tIWP = (const double(*)[A])(tb + o.IWP);
+  const double *const tww = tb + o.ww, *const twg = tb + o.wg, *const twp = tb + o.wp;
   const int tid = threadIdx.x, el = tid / NT, t = tid - el * NT;
   const long e = blk * EB + el;
   const bool act = el < EB && e < mp.K;
@@ -608,19 +619,10 @@ __device__ __forceinline__ void mag_update_body(MagIO io, const MagTab* __restri
   double* const fz = sf[act ? el : 0];
   double* const fx = fz + 2 * AA;
   double* const fy = fx + 2 * AB;
-  for (int k = tid; k < B * A; k += BS) tDWG[k / A][k % A] = T->D_W_G[k / A][k % A];
-  for (int k = tid; k < B * A; k += BS) tDWV[k / A][k % A] = T->D_W_V[k / A][k % A];
-  for (int k = tid; k < B * B; k += BS) tIGV[k / B][k % B] = T->I_G_V[k / B][k % B];
-  for (int k = tid; k < A * B; k += BS) tIGW[k / B][k % B] = T->I_G_W[k / B][k % B];
-  for (int k = tid; k < B * B; k += BS) tIVG[k / B][k % B] = T->I_V_G[k / B][k % B];
-  for (int k = tid; k < A * B; k += BS) tIVW[k / B][k % B] = T->I_V_W[k / B][k % B];
-  for (int k = tid; k < A * NP; k += BS) tIPW[k / NP][k % NP] = T->I_P_W[k / NP][k % NP];
-  for (int k = tid; k < B * NP; k += BS) tIPG[k / NP][k % NP] = T->I_P_G[k / NP][k % NP];
-  for (int k = tid; k < NP * B; k += BS) tIGP[k / B][k % B] = T->I_G_P[k / B][k % B];
-  for (int k = tid; k < NP * A; k += BS) tIWP[k / A][k % A] = T->I_W_P[k / A][k % A];
-  if (tid < A) tww[tid] = T->ww[tid];
-  if (tid < B) twg[tid] = T->wg[tid];
-  if (tid < NP) twp[tid] = T->wp[tid];
+  constexpr int NTB = (o.n + BS - 1) / BS;
+  double vt[NTB];
+#pragma unroll
+  for (int k = 0; k < NTB; ++k) vt[k] = tid + k * BS < o.n ? T->upd[tid + k * BS] : 0.0;
   // values used only at the end are loaded first, so that their latency overlaps the work
   // (MODE 1 keeps only y0 = ca*Y^n + cb*Y_s of every value and adds cb*tau*L_M at the end, so
   // that one register pair per value stays live across the kernel instead of two)
@@ -644,17 +646,41 @@ __device__ __forceinline__ void mag_update_body(MagIO io, const MagTab* __restri
       if (!R2) b0[2] = io.ca * io.bzn[gown] + io.cb * io.bzs[gown];
     }
   }
-  if (act) {
-    load_B<P, M, R2>(sbx[el], sby[el], sbz[el], io.bxs, io.bys, io.bzs, mp, ex, ey, t);
-    for (int k = t; !R2 && k < AB; k += NT) {  // in-plane E and J (none in the 2D2V system)
-      const long gN_x = gix(mp, B, ex, ey, k % B, k / B), gN_y = gix(mp, B, ex, ey, k % A, k / A);
-      sex[el][k] = io.ex[gN_x]; sjx[el][k] = io.jx[gN_x];
-      sey[el][k] = io.ey[gN_y]; sjy[el][k] = io.jy[gN_y];
+  // the element's B, E and J nodes (one of each kind per thread): all loads are issued before the first is stored
+  {
+    const long G = (long)mp.nx * B * mp.ny * B;
+    const int NXg = mp.nx * B, NYg = mp.ny * B, x0 = (int)ex * B, y0_ = (int)ey * B;
+    auto off = [&](int i, int j) {
+      const int gx = x0 + i, gy = y0_ + j;
+      return (unsigned)((gy >= NYg ? gy - NYg : gy) * NXg + (gx >= NXg ? gx - NXg : gx)) * 8u;
+    };
+    double vbx = 0.0, vby = 0.0, vbz = 0.0, vex = 0.0, vey = 0.0, vez = 0.0, vjx = 0.0, vjy = 0.0, vjz = 0.0;
+    if (act && t < AB) {
+      const unsigned nx_ = off(t % B, t / B), ny_ = off(t % A, t / A);  // N_x and N_y nodes
+      vbx = bld(node_rsrc(io.bxs, G), ny_);
+      vby = bld(node_rsrc(io.bys, G), nx_);
+      if (!R2) {  // in-plane E and J (none in the 2D2V system)
+        vex = bld(node_rsrc(io.ex, G), nx_);
+        vjx = bld(node_rsrc(io.jx, G), nx_);
+        vey = bld(node_rsrc(io.ey, G), ny_);
+        vjy = bld(node_rsrc(io.jy, G), ny_);
+      }
     }
-    for (int k = t; k < AA; k += NT) {
-      const long g = gix(mp, B, ex, ey, k % A, k / A);
-      sez[el][k] = io.ez[g]; sjz[el][k] = io.jz[g];
+    if (act && t < AA) {
+      const unsigned w = off(t % A, t / A);
+      vez = bld(node_rsrc(io.ez, G), w);
+      vjz = bld(node_rsrc(io.jz, G), w);
     }
+    if (!R2 && act && t < BB) vbz = bld(node_rsrc(io.bzs, G), (unsigned)gown * 8u);
+#pragma unroll
+    for (int k = 0; k < NTB; ++k)
+      if (tid + k * BS < o.n) tb[tid + k * BS] = vt[k];
+    if (act && t < AB) {
+      sbx[el][t] = vbx; sby[el][t] = vby;
+      if (!R2) { sex[el][t] = vex; sjx[el][t] = vjx; sey[el][t] = vey; sjy[el][t] = vjy; }
+    }
+    if (act && t < AA) { sez[el][t] = vez; sjz[el][t] = vjz; }
+    if (!R2 && act && t < BB) sbz[el][t] = vbz;
   }
   __syncthreads();
   if (act && t < BB) {  // strong curl at the element's owned B nodes

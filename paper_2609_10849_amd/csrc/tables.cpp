@@ -177,6 +177,20 @@ void build_mag_tables(int p, int m, MagTab* T) {
         T->RGP[i][j] = (double)(r / wg[i]);
       }
   }
+  {
+    const int A = m + 2, B = m + 1, NP = p + 1;
+    const UpdTab o(p, m);
+    auto put = [&](int at, const double (*src)[MHD_MAXN], int nr, int nc) {
+      for (int r = 0; r < nr; ++r)
+        for (int k = 0; k < nc; ++k) T->upd[at + r * nc + k] = src[r][k];
+    };
+    put(o.DWG, T->D_W_G, B, A); put(o.DWV, T->D_W_V, B, A); put(o.IGV, T->I_G_V, B, B); put(o.IGW, T->I_G_W, A, B);
+    put(o.IVG, T->I_V_G, B, B); put(o.IVW, T->I_V_W, A, B); put(o.IPW, T->I_P_W, A, NP); put(o.IPG, T->I_P_G, B, NP);
+    put(o.IGP, T->I_G_P, NP, B); put(o.IWP, T->I_W_P, NP, A);
+    for (int k = 0; k < A; ++k) T->upd[o.ww + k] = T->ww[k];
+    for (int k = 0; k < B; ++k) T->upd[o.wg + k] = T->wg[k];
+    for (int k = 0; k < NP; ++k) T->upd[o.wp + k] = T->wp[k];
+  }
   std::vector<ld> ends = {-1, 1};
   for (int s = 0; s < 2; ++s) {
     for (size_t k = 0; k < xg.size(); ++k) T->I_G_E[s][k] = (double)lag_val(xg, (int)k, ends[s]);
