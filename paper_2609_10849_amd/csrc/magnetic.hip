@@ -36,20 +36,6 @@ __device__ __forceinline__ long gix(const MeshP& mp, int B, long ex, long ey, in
   return (long)(gy * NX + gx);
 }
 
-// R2: the 2D2V reduced system (u_z = B_z = 0, in-plane E and J identically zero); B_z is not read
-template <int P, int M, bool R2 = false>
-__device__ __forceinline__ void load_B(double* bx, double* by, double* bz, const double* __restrict__ Bx,
-                                       const double* __restrict__ By, const double* __restrict__ Bz, const MeshP& mp,
-                                       long ex, long ey, int t) {
-  using C = MC<P, M>;
-  for (int k = t; k < C::AB; k += C::NT) {
-    bx[k] = Bx[gix(mp, C::B, ex, ey, k % C::A, k / C::A)];  // [j<B][i<A]
-    by[k] = By[gix(mp, C::B, ex, ey, k % C::B, k / C::B)];  // [j<A][i<B]
-  }
-  if constexpr (!R2)
-    for (int k = t; k < C::BB; k += C::NT) bz[k] = Bz[gix(mp, C::B, ex, ey, k % C::B, k / C::B)];
-}
-
 // ---------------------------------------------------------------------------------------------
 // Reconstruction of J (eq. mag-current-proj) and E (eq. mag-electric-proj) on the auxiliary grids.
 //
