@@ -54,9 +54,15 @@ struct Frac {
 __device__ __forceinline__ Frac lmean_frac(double aL, double aR, double lL, double lR) {
   const double d = aR - aL, s = aR + aL, dl = lR - lL;
   const double y = dl * dl;
-  const double pu = 2.0 + y * (1.0 / 6.0 - y * (1.0 / 360.0 - y * (1.0 / 15120.0)));
+  const double pu = fma(y, fma(-y, fma(-y, 1.0 / 15120.0, 1.0 / 360.0), 1.0 / 6.0), 2.0);
   const bool near = d * d < 1e-4 * (s * s);
   return Frac{near ? s : d, near ? pu : dl};
+}
+
+// a . b of two 3-vectors, its fused operations written out: left to the compiler, which of two products joins
+// the sum differs between instantiations of one kernel, and so would a run's last bits between its tiles
+__device__ __forceinline__ double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
+  return fma(a2, b2, fma(a1, b1, a0 * b0));
 }
 
 // Chandrashekar flux (eq. euler-chandrashekar-flux) in the line's frame (mass, normal, tangential and
@@ -67,7 +73,7 @@ __device__ __forceinline__ void ec_form(const Prim& L, const Prim& R, double rl,
                                         double F[5]) {
   const double un = L.hn + R.hn, ut = L.ht + R.ht, uz = L.hz + R.hz;
   const double f0 = rl * un;
-  const double dot = L.hn * R.hn + L.ht * R.ht + L.hz * R.hz;
+  const double dot = dot3(L.hn, L.ht, L.hz, R.hn, R.ht, R.hz);
   F[0] = f0;
   F[1] = fma(f0, un, ph);
   F[2] = f0 * ut;
@@ -97,7 +103,7 @@ __device__ __forceinline__ void ecflux_log(const Prim& L, double lrL, double lbL
 
 // pressure of a conserved state whose reciprocal density is ir
 __device__ __forceinline__ double pressure_of(const double U[5], double ir, double g) {
-  return (g - 1.0) * (U[4] - 0.5 * ir * (U[1] * U[1] + U[2] * U[2] + U[3] * U[3]));
+  return (g - 1.0) * fma(-0.5 * ir, dot3(U[1], U[2], U[3], U[1], U[2], U[3]), U[4]);
 }
 
 // One side of an LLF interface flux (eq. euler-lf-flux) in the line's frame from density, half
@@ -112,7 +118,7 @@ __device__ __forceinline__ FaceSide face_side(double r, double hn, double ht, do
   const double y = rsqrt_refined(x), c0 = x * y;
   const double c = fma(0.5 * y, fma(-c0, c0, x), c0);  // sqrt(x)
   a.U[0] = r; a.U[1] = r * un; a.U[2] = r * (ht + ht); a.U[3] = r * (hz + hz);
-  a.U[4] = fma(cg, p, 2.0 * r * (hn * hn + ht * ht + hz * hz));
+  a.U[4] = fma(cg, p, 2.0 * r * dot3(hn, ht, hz, hn, ht, hz));
   a.F[0] = a.U[1];
   a.F[1] = fma(a.U[1], un, p);
   a.F[2] = a.U[2] * un;
@@ -277,7 +283,9 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
     const int k = base + i * step;
     return Prim{sp[0][k], sp[rn][k], sp[rt][k], sp[3][k], sp[4][k]};
   };
-  // does any line of the block hold values too far apart for the series of the logarithmic mean?
+  // does the line hold values too far apart for the series of the logarithmic mean?  Each line answers for
+  // itself, so that a pair's arithmetic depends on its own line's values only, not on which elements
+  // share the block (its size differs between a batch's tunings, whose results are the same bit for bit)
   bool lfar = false;
   if (act) {
     double r0 = sp[0][base], r1 = r0, b0 = sp[4][base], b1 = b0;
@@ -289,8 +297,7 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
     }
     lfar = !(r1 - r0 <= LM_NEAR * (r1 + r0)) || !(b1 - b0 <= LM_NEAR * (b1 + b0));
   }
-  const bool far = __syncthreads_or(lfar);
-  if (far) {  // then every node's logarithms
+  if (__syncthreads_or(lfar)) {  // then the block's node logarithms, which its far lines read
     for (int n = tid; n < nel * NN; n += BS) {
       const int k = slot(n);
       sp[6][k] = log_ec(sp[0][k]);
@@ -320,7 +327,7 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
         for (int c = 0; c < 5; ++c) F[c] = fma(0.5, a.F[c] + b.F[c], hl * (b.U[c] - a.U[c]));
       }
 #pragma unroll
-      for (int c = 0; c < 5; ++c) acc[i][c] = side ? acc[i][c] + rw * F[c] : acc[i][c] - rw * F[c];
+      for (int c = 0; c < 5; ++c) acc[i][c] = fma(side ? rw : -rw, F[c], acc[i][c]);
     }
     // S_ir by its exact symmetry S_{p-i,p-r} = -S_ir (the tables hold it bit for bit), which halves the
     // scalars that the pairs keep
@@ -346,7 +353,7 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
         }
       }
     };
-    if (__builtin_expect(far, 0)) {
+    if (__builtin_expect(lfar, 0)) {
       pairs([&](int i, int r, double* F) {
         const int ki = base + i * step, kr = base + r * step;
         ecflux_log(node(i), sp[6][ki], sp[7][ki], node(r), sp[6][kr], sp[7][kr], cg, F);
