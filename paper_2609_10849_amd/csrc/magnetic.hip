@@ -252,6 +252,9 @@ __device__ __forceinline__ void J_body(const double* __restrict__ Bx, const doub
   }
 }
 
+// e + eta j; an element without resistivity is not touched by its J, also where that is infinite or NaN
+__device__ __forceinline__ double add_eta(double eta, double j, double e) { return eta != 0.0 ? fma(eta, j, e) : e; }
+
 // E: -u x B at the nodes, averaged over the elements that share the node (their lumped weights are equal),
 // plus eta_K sum_q M_q J(x_q) . phi_a(x_q) by the degree-p GLL rule, i.e. the 1D operators RWP / RGP applied
 // to J; blocks whose elements all have eta = 0 skip that term.
@@ -411,12 +414,12 @@ __device__ __forceinline__ void E_body(const double* __restrict__ u, const doubl
         double s = 0.0;
 #pragma unroll
         for (int q = 0; q < A; ++q) s = fma(T->RWP[i][q], c[q], s);
-        z[i] = fma(et, s, z[i]);
+        z[i] = add_eta(et, s, z[i]);
         if (i == 0) {
           double t = T->RWP[A - 1][A - 1] * c[0];
 #pragma unroll
           for (int q = 0; q < B; ++q) t = fma(T->RWP[A - 1][q], cl[q], t);
-          z[i] = fma(etl, t, z[i]);
+          z[i] = add_eta(etl, t, z[i]);
         }
       }
       if constexpr (!R2) {
@@ -429,7 +432,7 @@ __device__ __forceinline__ void E_body(const double* __restrict__ u, const doubl
           double s = 0.0;
 #pragma unroll
           for (int q = 0; q < B; ++q) s = fma(T->RGP[i][q], f[q], s);
-          x[i] = fma(et, s, x[i]);
+          x[i] = add_eta(et, s, x[i]);
         }
       }
     }
@@ -478,12 +481,12 @@ __device__ __forceinline__ void E_body(const double* __restrict__ u, const doubl
           double s = 0.0;
 #pragma unroll
           for (int q = 0; q < A; ++q) s = fma(T->RWP[i][q], c[q], s);
-          y[i] = fma(et, s, y[i]);
+          y[i] = add_eta(et, s, y[i]);
           if (i == 0) {
             double t = T->RWP[A - 1][A - 1] * c[0];
 #pragma unroll
             for (int q = 0; q < B; ++q) t = fma(T->RWP[A - 1][q], cl[q], t);
-            y[i] = fma(etl, t, y[i]);
+            y[i] = add_eta(etl, t, y[i]);
           }
         }
       }
