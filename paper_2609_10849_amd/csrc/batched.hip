@@ -286,6 +286,7 @@ static int build_plan(mhd25_batch* b, double* const* U, double* const* Bx, doubl
         boff.push_back((int)tot);
         ++L.nr;
       }
+      if (tot == 0) continue;  // a place in the sequence that these runs leave empty
       L.nblocks = tot;
       align();
       L.boff_off = host.size();
@@ -435,6 +436,10 @@ int mhd25_batch_create(const mhd25_mesh_desc* runs, int32_t nruns, const mhd25_o
     if (rc) { for (auto* x : b->ctx) mhd25_destroy(x); delete b; return rc; }
     b->ctx.push_back(c);
   }
+  // a degree group's launches cover all of its runs, so the group takes one form of each kernel
+  long elements[MHD_MAXP + 1] = {};
+  for (auto* c : b->ctx) elements[c->p] += c->mp.K;
+  for (auto* c : b->ctx) c->launch_elements = elements[c->p];
   if (hipMalloc((void**)&b->d_fail, nruns * sizeof(int)) != hipSuccess ||
       hipMalloc((void**)&b->d_acc, 3 * nruns * sizeof(long long)) != hipSuccess ||
       hipMalloc((void**)&b->d_eta, nruns * sizeof(double)) != hipSuccess ||

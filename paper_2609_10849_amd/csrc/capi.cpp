@@ -157,6 +157,7 @@ int mhd25_init(const mhd25_mesh_desc* mesh, const mhd25_options* opt, void* stre
   build_hydro_tables(c->p, &c->h_ht);
   build_mag_tables(c->p, c->m, &c->h_mt);
   const long K = c->mp.K, KN = K * c->nn, n5 = 5 * KN, G = c->G;
+  c->launch_elements = K;
   const long ny_ = d.ny, nx_ = d.nx;
   auto alloc = [&](void** p, size_t bytes) -> int {
     hipError_t e = hipMalloc(p, bytes ? bytes : 8);

@@ -206,6 +206,7 @@ struct mhd25_ctx {
   std::string err;
   // timing
   int timing;
+  long launch_elements;  // that a launch over this mesh covers: its own, or in a batch those of its degree group
   int hydro_bs;  // threads per block of the hydro stage kernel (128 or 256; tuned)
   std::vector<hipEvent_t> ev_pool;  // pairs (start, stop) of timed launches
   std::vector<int> ev_kid;          // kernel id of each pair (0 hydro stage, 1 stage map)

@@ -14,6 +14,11 @@
 #include "jumps.h"
 #include "rsqrt.h"
 
+// Every fused operation of this file is written out.  Left to the compiler, which product of a sum it fuses
+// differs between instantiations of one kernel; a run's results are the same bit for bit for every tile and
+// every form of a kernel that it can take, alone and in a batch.
+#pragma clang fp contract(off)
+
 namespace {
 
 constexpr double EPSM = 2.220446049250313e-16;  // 2^-52
@@ -57,12 +62,6 @@ __device__ __forceinline__ Frac lmean_frac(double aL, double aR, double lL, doub
   const double pu = fma(y, fma(-y, fma(-y, 1.0 / 15120.0, 1.0 / 360.0), 1.0 / 6.0), 2.0);
   const bool near = d * d < 1e-4 * (s * s);
   return Frac{near ? s : d, near ? pu : dl};
-}
-
-// a . b of two 3-vectors, its fused operations written out: left to the compiler, which of two products joins
-// the sum differs between instantiations of one kernel, and so would a run's last bits between its tiles
-__device__ __forceinline__ double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
-  return fma(a2, b2, fma(a1, b1, a0 * b0));
 }
 
 // Chandrashekar flux (eq. euler-chandrashekar-flux) in the line's frame (mass, normal, tangential and
@@ -128,6 +127,23 @@ __device__ __forceinline__ FaceSide face_side(double r, double hn, double ht, do
   return a;
 }
 
+// Interface flux of a line's end node q (pressure pq) with its neighbour's conserved values n, the minus side at -1
+// (side 0) and the plus side at +1: LLF, or (iface 1) the EC flux
+__device__ __forceinline__ void face_flux(const Prim& q, double pq, const double n[5], int D, int side, int iface, double g,
+                                          double cg, double F[5]) {
+  const double ir = rcp_refined(n[0]), hi = 0.5 * ir, pn = pressure_of(n, ir, g);
+  const double hn = (D ? n[2] : n[1]) * hi, ht = (D ? n[1] : n[2]) * hi, hz = n[3] * hi;
+  if (iface == 1) {
+    const Prim o{n[0], hn, ht, hz, n[0] * rcp_refined(pn)};
+    ecflux_log(q, log_ec(q.r), log_ec(q.b), o, log_ec(o.r), log_ec(o.b), cg, F);
+    return;
+  }
+  const FaceSide a = face_side(q.r, q.hn, q.ht, q.hz, pq, g, cg), b = face_side(n[0], hn, ht, hz, pn, g, cg);
+  const double hl = (side ? -0.5 : 0.5) * fmax(a.s, b.s);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) F[c] = fma(0.5, a.F[c] + b.F[c], hl * (b.U[c] - a.U[c]));
+}
+
 // Face f = 2 D + side of element (ex, ey) (D 0: the x-normal faces, D 1: the y-normal faces; side 0
 // is the face at -1) and the face node `line` on it: the neighbour element en across the face, the
 // element's own face node qo and the neighbour's node qn at the same point (periodic mesh).
@@ -141,50 +157,54 @@ __device__ __forceinline__ void face_match(const MeshP& mp, int ex, int ey, int 
   en = D == 0 ? ey * mp.nx + wrap32(ex + (side ? 1 : -1), mp.nx) : wrap32(ey + (side ? 1 : -1), mp.ny) * mp.nx + ex;
 }
 
-// Per-element sums (GLL weights, without |J_K|), minima and maxima of 5 fields held in LDS rows
-// 0..4 of svf, plus the raw-average admissibility test (NaN-safe) from the five sums.  Two fixed-
-// order levels: task (component, grid row) reduces its row into rs = sst + el * 15 NP (at least
-// 15 (p+1) values per element, free LDS), then task (component, kind) combines the rows.  Rows
-// 5..6 of svf (at least 5 values per element) take the sums; every thread of the block must call
-// this.
-template <class C>
-__device__ __forceinline__ void element_stats(double* svf, double* sst, bool act, int el, int q, long e,
-                                              double* __restrict__ stats, int* __restrict__ flag,
-                                              const HydroTab* __restrict__ T, double g) {
-  constexpr int NP = C::NP, NN = C::NN, S = C::EB * C::NN;
-  double* rs = sst + el * 15 * NP;  // [component][kind][row]
-  for (int t = q; act && t < 5 * NP; t += NN) {
-    const int c = t / NP, r = t - c * NP;
-    const double wr = T->w[r];
-    double s = 0.0, mn = DBL_MAX, mx = -DBL_MAX;
+// does a line (its nodes at r and b, step apart) hold values too far apart for the series of the logarithmic mean?
+template <int P>
+__device__ __forceinline__ bool line_far(const double* r, const double* b, int step) {
+  double r0 = r[0], r1 = r0, b0 = b[0], b1 = b0;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const double v = svf[c * S + el * NN + r * NP + i];
-      s += (T->w[i] * wr) * v;
-      mn = fmin(mn, v); mx = fmax(mx, v);
-    }
-    rs[(c * 3 + 0) * NP + r] = s;
-    rs[(c * 3 + 1) * NP + r] = mn;
-    rs[(c * 3 + 2) * NP + r] = mx;
+  for (int i = 1; i <= P; ++i) {
+    const double x = r[i * step], y = b[i * step];
+    r0 = x < r0 ? x : r0; r1 = x > r1 ? x : r1;
+    b0 = y < b0 ? y : b0; b1 = y > b1 ? y : b1;
   }
-  __syncthreads();
-  double* ssum = svf + 5 * S + el * 5;
-  for (int t = q; act && t < 15; t += NN) {
-    const int c = t / 3, kind = t - 3 * c;
-    const double* v = rs + t * NP;
-    double s = kind == 0 ? 0.0 : v[0];
+  return !(r1 - r0 <= LM_NEAR * (r1 + r0)) || !(b1 - b0 <= LM_NEAR * (b1 + b0));
+}
+
+// Element statistics of five fields in LDS (component c at v + c row, element el at el ES, node (i, j) at j RS + i):
+// weighted sum (without |J_K|), minimum and maximum of each component to stats, and the raw-average
+// admissibility (NaN-safe) to flag (may be null).  ssum: 5 nel free values.  All threads of the block must call this.
+template <int P, int BS, int RS, int ES>
+__device__ __forceinline__ void stage_stats(const double* v, int row, double* ssum, int e0, int nel,
+                                            double* __restrict__ stats, int* __restrict__ flag,
+                                            const HydroTab* __restrict__ T, double g) {
+  constexpr int NP = P + 1;
+  const int tid = threadIdx.x;
+  for (int t = tid; t < nel * 5; t += BS) {
+    const int es = t / 5, c = t - es * 5;
+    const double* f = v + c * row + es * ES;
+    double s = 0.0, mn = f[0], mx = f[0];
+#pragma unroll 1
+    for (int j = 0; j < NP; ++j) {
+      double sr = 0.0;
 #pragma unroll
-    for (int r = kind == 0 ? 0 : 1; r < NP; ++r) s = kind == 0 ? s + v[r] : (kind == 1 ? fmin(s, v[r]) : fmax(s, v[r]));
-    stats[(e * 5 + c) * 3 + kind] = s;
-    if (kind == 0) ssum[c] = s;
+      for (int i = 0; i < NP; ++i) {
+        const double x = f[j * RS + i];
+        sr = fma(T->w[i], x, sr);
+        mn = fmin(mn, x); mx = fmax(mx, x);
+      }
+      s = fma(T->w[j], sr, s);
+    }
+    double* o = stats + ((long)(e0 + es) * 5 + c) * 3;
+    o[0] = s; o[1] = mn; o[2] = mx;
+    ssum[t] = s;
   }
   if (!flag) return;
   __syncthreads();
-  if (act && q == 0) {
+  if (tid < nel) {
     double a[5];
 #pragma unroll
-    for (int c = 0; c < 5; ++c) a[c] = 0.25 * ssum[c];
-    const double pb = (g - 1.0) * (a[4] - (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * a[0]));
+    for (int c = 0; c < 5; ++c) a[c] = 0.25 * ssum[tid * 5 + c];
+    const double pb = (g - 1.0) * (a[4] - dot3(a[1], a[2], a[3], a[1], a[2], a[3]) / (2.0 * a[0]));
     if (!(a[0] > 0.0) || !(pb > 0.0)) atomicOr(flag, 1);
   }
 }
@@ -283,20 +303,9 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
     const int k = base + i * step;
     return Prim{sp[0][k], sp[rn][k], sp[rt][k], sp[3][k], sp[4][k]};
   };
-  // does the line hold values too far apart for the series of the logarithmic mean?  Each line answers for
-  // itself, so that a pair's arithmetic depends on its own line's values only, not on which elements
-  // share the block (its size differs between a batch's tunings, whose results are the same bit for bit)
-  bool lfar = false;
-  if (act) {
-    double r0 = sp[0][base], r1 = r0, b0 = sp[4][base], b1 = b0;
-#pragma unroll
-    for (int i = 1; i < NP; ++i) {
-      const double r = sp[0][base + i * step], b = sp[4][base + i * step];
-      r0 = r < r0 ? r : r0; r1 = r > r1 ? r : r1;
-      b0 = b < b0 ? b : b0; b1 = b > b1 ? b : b1;
-    }
-    lfar = !(r1 - r0 <= LM_NEAR * (r1 + r0)) || !(b1 - b0 <= LM_NEAR * (b1 + b0));
-  }
+  // Each line answers for itself whether its pairs take the series, so that a pair's arithmetic depends on its own
+  // line's values only, not on which elements share the block
+  const bool lfar = act && line_far<P>(sp[0] + base, sp[4] + base, step);
   if (__syncthreads_or(lfar)) {  // then the block's node logarithms, which its far lines read
     for (int n = tid; n < nel * NN; n += BS) {
       const int k = slot(n);
@@ -306,26 +315,13 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
     __syncthreads();
   }
   if (act) {
-    // interface fluxes: the neighbour is the minus side at -1 and the plus side at +1
+    // interface fluxes
     const double rw = rcp_refined(T->w[0]);
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
-      const double* n = nb[side];
       const int i = side ? P : 0;
-      const double ir = rcp_refined(n[0]), hi = 0.5 * ir, pn = pressure_of(n, ir, mp.gamma);
-      const double hn = (D ? n[2] : n[1]) * hi, ht = (D ? n[1] : n[2]) * hi, hz = n[3] * hi;
-      const Prim q = node(i);
       double F[5];
-      if (iface == 1) {
-        const Prim o{n[0], hn, ht, hz, n[0] * rcp_refined(pn)};
-        ecflux_log(q, log_ec(q.r), log_ec(q.b), o, log_ec(o.r), log_ec(o.b), cg, F);
-      } else {
-        const FaceSide a = face_side(q.r, q.hn, q.ht, q.hz, sp[5][base + i * step], mp.gamma, cg);
-        const FaceSide b = face_side(n[0], hn, ht, hz, pn, mp.gamma, cg);
-        const double hl = (side ? -0.5 : 0.5) * fmax(a.s, b.s);
-#pragma unroll
-        for (int c = 0; c < 5; ++c) F[c] = fma(0.5, a.F[c] + b.F[c], hl * (b.U[c] - a.U[c]));
-      }
+      face_flux(node(i), sp[5][base + i * step], nb[side], D, side, iface, mp.gamma, cg, F);
 #pragma unroll
       for (int c = 0; c < 5; ++c) acc[i][c] = fma(side ? rw : -rw, F[c], acc[i][c]);
     }
@@ -426,35 +422,7 @@ __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, 
   }
   if (MODE == 0) return;
   __syncthreads();
-  // element statistics: weighted sum (without |J_K|), minimum and maximum of each component
-  double* const ssum = sp[5];
-  for (int t = tid; t < nel * 5; t += BS) {
-    const int es = t / 5, c = t - es * 5;
-    const double* v = sp[c] + es * ES;
-    double s = 0.0, mn = v[0], mx = v[0];
-#pragma unroll 1
-    for (int j = 0; j < NP; ++j) {
-      double sr = 0.0;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        const double x = v[j * RS + i];
-        sr = fma(T->w[i], x, sr);
-        mn = fmin(mn, x); mx = fmax(mx, x);
-      }
-      s = fma(T->w[j], sr, s);
-    }
-    double* o = stats + ((long)(e0 + es) * 5 + c) * 3;
-    o[0] = s; o[1] = mn; o[2] = mx;
-    ssum[t] = s;
-  }
-  __syncthreads();
-  if (tid < nel) {  // raw-average admissibility (NaN-safe)
-    double a[5];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) a[c] = 0.25 * ssum[tid * 5 + c];
-    const double pb = (mp.gamma - 1.0) * (a[4] - (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * a[0]));
-    if (!(a[0] > 0.0) || !(pb > 0.0)) atomicOr(flag, 1);
-  }
+  stage_stats<P, BS, RS, ES>(sp[0], EB * ES, sp[5], e0, nel, stats, flag, T, mp.gamma);
 }
 
 template <int P, int MODE, int BS>
@@ -486,30 +454,227 @@ __global__ __launch_bounds__(BS, 4) void k_hydro_stage_rt(const hydro_stage_args
   hydro_stage_body<P, MODE, BS>(gl(a.Us), gl(a.Un), gl(a.out), gl(a.stats), gl(a.flag), gl(a.T), a.mp, a.ca, a.cb, a.tau, a.iface, (long)blockIdx.x - boff[r]);
 }
 
+// The stage on small meshes (see small_mesh): a thread per node, EB elements per block, the same arithmetic.  In the
+// form above a line's thread works through its p(p+1)/2 pairs one after another, and that is the time of a launch with
+// fewer blocks than the chip has places.  Here the pairs of all lines, then the face nodes, are tasks spread over the
+// element's threads, their fluxes go through LDS, and each node adds its own in the line's order.  At 16^2 elements it
+// takes 6.9 (N = 3), 7.3 (4), 7.9 (5), 8.8 us (6) where the form above takes 7.7, 9.8, 12.0, 13.2; at 48^2 8.6, 11.4,
+// 17.0, 19.8 against 8.1, 10.1, 12.4, 14.3.
+template <int P, int MODE, int BS>
+__device__ __forceinline__ void hydro_stage_node_body(const double* __restrict__ Us, const double* __restrict__ Un,
+                                                      double* __restrict__ out, double* __restrict__ stats,
+                                                      int* __restrict__ flag, const HydroTab* __restrict__ T, MeshP mp,
+                                                      double ca, double cb, double tau, int iface, long blk) {
+  constexpr int NP = P + 1, NN = NP * NP, EB = BS / (2 * NN), TPE = BS / EB, NPR = NP * P / 2, RS = NP, ES = NN;
+  __shared__ double sp[8][EB * ES];             // as above
+  __shared__ double sF[EB][2][NP][NPR][5];      // pair fluxes [direction][line][pair][component in the line's frame]
+  __shared__ double sG[EB][2][2][NP][5];        // interface fluxes [direction][side][line][component]
+  __shared__ unsigned char sfar[EB][2][NP], sa[NPR], sb[NPR];  // far lines; a pair's nodes
+  static_assert(NN + 4 * NP <= TPE, "the face nodes have threads of their own");
+  __shared__ int sflag;
+  auto pair = [](int i, int r) { return i * NP - i * (i + 1) / 2 + r - i - 1; };  // index of the pair i < r
+  const int tid = threadIdx.x, el = tid / TPE, q = tid - el * TPE;
+  const int e0 = (int)(blk * EB), e = e0 + el;
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;
+  const bool act = el < nel, own = act && q < NN;  // own: the thread has node q
+  const int k = el * NN + q;                          // its slot
+  const long KN = mp.K * NN;
+  const unsigned no = ((unsigned)e * NN + q) * 8u;  // the node's byte offset in a component array
+  const double cg = 2.0 * mp.gk;
+  // the thread's face node (direction, side, line) and its node's rows of S; with the node's own values and the
+  // neighbour's all global loads are issued before the first wait
+  const int fq0 = q - NN, fD = fq0 / (2 * NP), fside = fq0 / NP & 1, fln = fq0 % NP;
+  const bool face = act && fq0 >= 0 && fq0 < 4 * NP;
+  int fq = 0;
+  double Y[5], n[5], S[2][NP];
+  if (face) {
+    int ex, ey, en, qn;
+    elem_xy32(mp, e, ex, ey);
+    face_match<P>(mp, ex, ey, fD, fside, fln, en, fq, qn);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) n[c] = bld(node_rsrc(Us + c * KN, KN), ((unsigned)en * NN + qn) * 8u);
+  }
+  if (own) {
+    double U[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) U[c] = bld(node_rsrc(Us + c * KN, KN), no);
+#pragma unroll
+    for (int r = 0; r < NP; ++r) { S[0][r] = T->Shat[q % NP][r]; S[1][r] = T->Shat[q / NP][r]; }
+    if (MODE == 1) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) Y[c] = cb * U[c];
+      if (ca != 0.0) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) Y[c] = fma(ca, bld(node_rsrc(Un + c * KN, KN), no), Y[c]);
+      }
+    }
+    const double ir = rcp_refined(U[0]), hi = 0.5 * ir, p = pressure_of(U, ir, mp.gamma);
+    sp[0][k] = U[0]; sp[1][k] = U[1] * hi; sp[2][k] = U[2] * hi; sp[3][k] = U[3] * hi;
+    sp[4][k] = U[0] * rcp_refined(p); sp[5][k] = p;
+  }
+  if (tid < NN) {
+    const int i = tid / NP, r = tid - i * NP;
+    if (i < r) { sa[pair(i, r)] = i; sb[pair(i, r)] = r; }
+  }
+  if (MODE == 1 && tid == 0) sflag = __atomic_load_n(flag, __ATOMIC_RELAXED);
+  __syncthreads();
+  if (MODE == 1 && sflag) return;  // skip stages after a rejected one
+  // the far lines (task = element, direction, line)
+  bool lfar = false;
+  for (int t = tid; t < nel * 2 * NP; t += BS) {
+    const int es = t / (2 * NP), D = t / NP & 1, ln = t % NP, base = es * ES + (D ? ln : ln * RS);
+    const bool f = line_far<P>(sp[0] + base, sp[4] + base, D ? RS : 1);
+    sfar[es][D][ln] = f;
+    lfar = lfar || f;
+  }
+  if (__syncthreads_or(lfar)) {
+    if (own) {
+      sp[6][k] = log_ec(sp[0][k]);
+      sp[7][k] = log_ec(sp[4][k]);
+    }
+    __syncthreads();
+  }
+  auto node = [&](int k, int D) { return Prim{sp[0][k], sp[1 + D][k], sp[2 - D][k], sp[3][k], sp[4][k]}; };
+  if (act) {
+    for (int t = q; t < 2 * NP * NPR; t += TPE) {
+      const int D = t / (NP * NPR), ln = t / NPR % NP, pr = t % NPR, step = D ? RS : 1;
+      const int base = el * ES + (D ? ln : ln * RS), ki = base + sa[pr] * step, kr = base + sb[pr] * step;
+      double F[5];
+      if (sfar[el][D][ln]) ecflux_log(node(ki, D), sp[6][ki], sp[7][ki], node(kr, D), sp[6][kr], sp[7][kr], cg, F);
+      else ecflux_near(node(ki, D), node(kr, D), cg, T, F);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sF[el][D][ln][pr][c] = F[c];
+    }
+    if (face) {
+      double F[5];
+      face_flux(node(el * ES + fq, fD), sp[5][el * ES + fq], n, fD, fside, iface, mp.gamma, cg, F);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sG[el][fD][fside][fln][c] = F[c];
+    }
+  }
+  __syncthreads();
+  if (own) {
+    const double rw = rcp_refined(T->w[0]);
+    double acc[2][5];
+#pragma unroll
+    for (int D = 0; D < 2; ++D) {
+      const int pos = D ? q / NP : q % NP, ln = D ? q % NP : q / NP;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) acc[D][c] = 0.0;
+#pragma unroll
+      for (int side = 0; side < 2; ++side)
+        if (pos == (side ? P : 0)) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) acc[D][c] = fma(side ? rw : -rw, sG[el][D][side][ln][c], acc[D][c]);
+        }
+#pragma unroll
+      for (int r = 0; r < NP; ++r)
+        if (r != pos) {
+          const double* F = sF[el][D][ln][r < pos ? pair(r, pos) : pair(pos, r)];
+#pragma unroll
+          for (int c = 0; c < 5; ++c) acc[D][c] = fma(S[D][r], F[c], acc[D][c]);
+        }
+      const double sc = -2.0 * (D ? mp.rhy : mp.rhx);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) acc[D][c] *= sc;
+    }
+    const double L[5] = {acc[0][0] + acc[1][0], acc[0][1] + acc[1][2], acc[0][2] + acc[1][1], acc[0][3] + acc[1][3],
+                         acc[0][4] + acc[1][4]};
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      const double v = MODE == 0 ? L[c] : fma(cb * tau, L[c], Y[c]);
+      bst(node_rsrc(out + c * KN, KN), no, v);
+      sp[c][k] = v;
+    }
+  }
+  if (MODE == 0) return;
+  __syncthreads();
+  stage_stats<P, BS, RS, ES>(sp[0], EB * ES, sp[5], e0, nel, stats, flag, T, mp.gamma);
+}
+
+template <int P, int MODE, int BS>
+__global__ __launch_bounds__(BS) void k_hydro_stage_node(const double* __restrict__ Us, const double* __restrict__ Un,
+                                                    double* __restrict__ out, double* __restrict__ stats,
+                                                    int* __restrict__ flag, const HydroTab* __restrict__ T, MeshP mp,
+                                                    double ca, double cb, double tau, int iface) {
+  hydro_stage_node_body<P, MODE, BS>(Us, Un, out, stats, flag, T, mp, ca, cb, tau, iface, (long)blockIdx.x);
+}
+
+template <int P, int MODE, int BS>
+__global__ __launch_bounds__(BS) void k_hydro_stage_node_rt(const hydro_stage_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+  const int r = rt_run(boff, nr);
+  const hydro_stage_args& a = A[r];
+  hydro_stage_node_body<P, MODE, BS>(gl(a.Us), gl(a.Un), gl(a.out), gl(a.stats), gl(a.flag), gl(a.T), a.mp, a.ca, a.cb, a.tau, a.iface, (long)blockIdx.x - boff[r]);
+}
+
 template <int P>
 __global__ __launch_bounds__(256) void k_elem_stats(const double* __restrict__ Uin, double* __restrict__ stats,
                                                     int* __restrict__ flag, const HydroTab* __restrict__ T, MeshP mp) {
   using C = Cfg<P>;
-  constexpr int NN = C::NN, EB = C::EB;
-  __shared__ double sv[7][EB * NN];
-  __shared__ double sst[EB * 15 * C::NP];
-  const int tid = threadIdx.x;
-  const int el = tid / NN, q = tid - el * NN;
-  const long e = (long)blockIdx.x * EB + el;
-  const bool act = tid < C::NT && e < mp.K;
+  constexpr int NP = C::NP, NN = C::NN, EB = C::EB;
+  __shared__ double sv[7][EB * NN];  // rows 5 and 6: the sums
+  const int tid = threadIdx.x, e0 = (int)blockIdx.x * EB;
+  const int nel = mp.K - e0 < EB ? (int)(mp.K - e0) : EB;
   const long KN = mp.K * NN;
-  if (act)
-    for (int c = 0; c < 5; ++c) sv[c][tid] = Uin[c * KN + e * NN + q];
+  if (tid < nel * NN)
+    for (int c = 0; c < 5; ++c) sv[c][tid] = Uin[c * KN + (long)e0 * NN + tid];
   __syncthreads();
-  element_stats<Cfg<P>>(&sv[0][0], sst, act, el, q, e, stats, flag, T, mp.gamma);
+  stage_stats<P, 256, NP, NN>(sv[0], EB * NN, sv[5], e0, nel, stats, flag, T, mp.gamma);
 }
 
-// Element-average pressure helper
+// pressure of a conserved state, and the size S_p that the pressure floor scales with
 __device__ __forceinline__ double pres(const double* a, double g) {
-  return (g - 1.0) * (a[4] - (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * a[0]));
+  return (g - 1.0) * (a[4] - dot3(a[1], a[2], a[3], a[1], a[2], a[3]) / (2.0 * a[0]));
 }
 __device__ __forceinline__ double Sp(const double* a, double eps_r) {
-  return fabs(a[4]) + (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) / (2.0 * fmax(a[0], eps_r));
+  return fabs(a[4]) + dot3(a[1], a[2], a[3], a[1], a[2], a[3]) / (2.0 * fmax(a[0], eps_r));
+}
+
+// Pieces that the two forms of the stage map share.
+// Cross-line amplitude shared by the components (eq. euler-oe-amplitude) from the statistics l of a row or column,
+// rn its reciprocal weight sum
+__device__ __forceinline__ double cross_amp(const double* __restrict__ l, const double* __restrict__ glob, double rn, double r4K) {
+  double a = 0.0;
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    const double gm = glob[d * 3] * r4K, m = l[d * 3] * rn;
+    const double dOm = fmax(glob[d * 3 + 2] - gm, gm - glob[d * 3 + 1]);
+    a = fmax(a, fmax(fmax(l[d * 3 + 2] - m, m - l[d * 3 + 1]), 1e-6 * dOm));
+  }
+  return a;
+}
+// a component that is constant to roundoff (its nodal values agree to 2^10 ulps of its size, an exact test) does
+// not count
+__device__ __forceinline__ bool is_constant(const double* __restrict__ glob, int c) {
+  const double gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
+  return gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn));
+}
+// damping rates (eq. euler-oe-rate) of an element with the averages a
+template <int P>
+__device__ __forceinline__ void damping_rates(const double a[5], double g, const MeshP& mp, double& lx, double& ly) {
+  const double ir0 = 1.0 / a[0];
+  const double pa = (g - 1.0) * fma(-0.5 * ir0, dot3(a[1], a[2], a[3], a[1], a[2], a[3]), a[4]);
+  const double ck = sqrt(g * pa * ir0);
+  lx = (2.0 * P + 1.0) * (fabs(a[1] * ir0) + ck) * mp.rhx;
+  ly = (2.0 * P + 1.0) * (fabs(a[2] * ir0) + ck) * mp.rhy;
+}
+// D_l = exp(-s tau (lx sum_{r<=l} sigma_x,r + ly sum_{r<=l} sigma_y,r)) (eq. euler-oe-map)
+__device__ __forceinline__ double shell_damping(int l, const double* sigx, const double* sigy, double lx, double ly, double st) {
+  double sx = 0.0, sy = 0.0;
+  for (int r = 0; r <= l; ++r) { sx += sigx[r]; sy += sigy[r]; }
+  return l == 0 ? 1.0 : exp(-st * fma(lx, sx, ly * sy));
+}
+// the stage's node: conserved, and as the primitive copy for the magnetic substep (rho_o null: none)
+__device__ __forceinline__ void store_node(const double U[5], unsigned no, long KN, double* __restrict__ Uout,
+                                           double* __restrict__ rho_o, double* __restrict__ e_o, double* __restrict__ u_o) {
+#pragma unroll
+  for (int d = 0; d < 5; ++d) bst(node_rsrc(Uout + d * KN, KN), no, U[d]);
+  if (rho_o) {
+    const double r = U[0], ux = U[1] / r, uy = U[2] / r, uz = U[3] / r;
+    bst(node_rsrc(rho_o, KN), no, r);
+    bst(node_rsrc(u_o, KN), no, ux); bst(node_rsrc(u_o + KN, KN), no, uy); bst(node_rsrc(u_o + 2 * KN, KN), no, uz);
+    bst(node_rsrc(e_o, KN), no, internal_energy(U[4], r, ux, uy, uz));
+  }
 }
 
 // Tile of the hydro OE sensor: TX x TY elements and the ring around them, one thread per component and
@@ -576,16 +741,7 @@ __device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust
   for (int t = tid; t < TY + TX; t += BS) {
     const int D = t < TY ? 0 : 1, i = D ? t - TY : t;
     if (i < (D ? tw : th)) {
-      const double* l = lines + (D ? mp.ny + tx0 + i : ty0 + i) * 15;
-      const double rn = D ? mp.r4ny : mp.r4nx;
-      double a = 0.0;
-#pragma unroll
-      for (int d = 0; d < 5; ++d) {
-        const double gm = glob[d * 3] * mp.r4K, m = l[d * 3] * rn;
-        const double dOm = fmax(glob[d * 3 + 2] - gm, gm - glob[d * 3 + 1]);
-        a = fmax(a, fmax(fmax(l[d * 3 + 2] - m, m - l[d * 3 + 1]), 1e-6 * dOm));
-      }
-      samp[D][i] = a;
+      samp[D][i] = cross_amp(lines + (D ? mp.ny + tx0 + i : ty0 + i) * 15, glob, D ? mp.r4ny : mp.r4nx, mp.r4K);
     }
   }
   // wave speeds of the damping rate (eq. euler-oe-rate) from the element averages
@@ -596,11 +752,7 @@ __device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust
       double a[5];
 #pragma unroll
       for (int d = 0; d < 5; ++d) a[d] = 0.25 * st[3 * d];
-      const double ir0 = 1.0 / a[0];
-      const double pa = (g - 1.0) * (a[4] - 0.5 * (a[1] * a[1] + a[2] * a[2] + a[3] * a[3]) * ir0);
-      const double ck = sqrt(g * pa * ir0);
-      slam[0][en] = (2.0 * P + 1.0) * (fabs(a[1] * ir0) + ck) * mp.rhx;
-      slam[1][en] = (2.0 * P + 1.0) * (fabs(a[2] * ir0) + ck) * mp.rhy;
+      damping_rates<P>(a, g, mp, slam[0][en], slam[1][en]);
     }
   }
 #pragma unroll
@@ -625,10 +777,7 @@ __device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust
   }
   __syncthreads();
   if (act) {
-    // a component that is constant to roundoff (its nodal values agree to 2^10 ulps of its size, an exact
-    // test) does not count
-    const double gmn = glob[c * 3 + 1], gmx = glob[c * 3 + 2];
-    const bool cst = gmx - gmn <= 1024.0 * EPSM * fmax(fabs(gmx), fabs(gmn));
+    const bool cst = is_constant(glob, c);
     double* o = su + (c * (NX + NY) + (D ? NX + f : f)) * NP;
 #pragma unroll
     for (int r = 0; r < NP; ++r) o[r] = cst ? 0.0 : J[r];
@@ -648,14 +797,11 @@ __device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust
     }
   }
   __syncthreads();
-  // D_l = exp(-s tau (lx sum_{r<=l} sigma_x,r + ly sum_{r<=l} sigma_y,r))
   for (int k = tid; k < TE * NP; k += BS) {
     const int l = k % NP, en = k / NP, x = en % TX, y = en / TX;
-    if (x < tw && y < th) {
-      double sx = 0.0, sy = 0.0;
-      for (int r = 0; r <= l; ++r) { sx += ssg[en][r]; sy += ssg[en][NP + r]; }
-      Dfac[(long)((ty0 + y) * mp.nx + tx0 + x) * NP + l] = l == 0 ? 1.0 : exp(-sH * tau * (slam[0][en] * sx + slam[1][en] * sy));
-    }
+    if (x < tw && y < th)
+      Dfac[(long)((ty0 + y) * mp.nx + tx0 + x) * NP + l] =
+          shell_damping(l, ssg[en], ssg[en] + NP, slam[0][en], slam[1][en], sH * tau);
   }
 }
 
@@ -904,14 +1050,7 @@ __device__ __forceinline__ void hydro_oe_pp_body(const double* __restrict__ Ust,
         for (int d = 0; d < 5; ++d) U[d] = thp < 0.0 ? sa[d][en] : sa[d][en] + thp * (U[d] - sa[d][en]);
       }
     }
-#pragma unroll
-    for (int d = 0; d < 5; ++d) bst(node_rsrc(Uout + d * KN, KN), no, U[d]);
-    if (rho_o) {  // primitive copy for the magnetic substep (the conversion's arithmetic)
-      const double r = U[0], ux = U[1] / r, uy = U[2] / r, uz = U[3] / r;
-      bst(node_rsrc(rho_o, KN), no, r);
-      bst(node_rsrc(u_o, KN), no, ux); bst(node_rsrc(u_o + KN, KN), no, uy); bst(node_rsrc(u_o + 2 * KN, KN), no, uz);
-      bst(node_rsrc(e_o, KN), no, (U[4] - 0.5 * r * (ux * ux + uy * uy + uz * uz)) / r);
-    }
+    store_node(U, no, KN, Uout, rho_o, e_o, u_o);
   }
 }
 
@@ -949,6 +1088,267 @@ __global__ __launch_bounds__(OM<P>::BS) void k_hydro_oe_pp_rt(const hydro_oe_pp_
   const int r = rt_run(boff, nr);
   const hydro_oe_pp_args& a = A[r];
   hydro_oe_pp_body<P>(gl(a.Ust), gl(a.Uout), gl(a.stats), gl(a.Dfac), gl(a.flags), gl(a.counts), gl(a.flag), gl(a.T), a.mp, a.do_oe, a.do_pp, gl(a.rho_o), gl(a.e_o), gl(a.u_o), (long)blockIdx.x - boff[r]);
+}
+
+// The whole stage map in one launch, for small and for one element wide meshes (see one_launch_map): the derivative jumps
+// and the modal transforms run as line tasks, task (c, line) holding one grid line of component c in registers (five
+// tasks per line index, EB elements per block); an element forms its neighbours' traces again.  Same arithmetic
+// as the two kernels above, whose threads work through an element and whose launch of its own counts here: at 24^2, N = 4
+// 8.9 against 6.6 + 6.6 us, N = 6 12.2 against 9.8 + 11 us.
+constexpr int ML_BS = 128;
+template <int P>
+__device__ __forceinline__ void hydro_map_lines_body(const double* __restrict__ Ust, double* __restrict__ Uout,
+                                                     const double* __restrict__ stats, const double* __restrict__ lines,
+                                                     const double* __restrict__ glob, uint8_t* __restrict__ flags,
+                                                     unsigned long long* __restrict__ counts,
+                                                     const int* __restrict__ flag, const HydroTab* __restrict__ T,
+                                                     MeshP mp, double tau, double sH, int do_pp,
+                                                     double* __restrict__ rho_o, double* __restrict__ e_o,
+                                                     double* __restrict__ u_o, long blk) {
+  using C = Cfg<P, ML_BS>;
+  constexpr int NP = C::NP, NN = C::NN, EB = C::EB, NL = 5 * NP;
+  __shared__ double su[5][EB * NN], st[10][EB * NN];
+  __shared__ double ssig[EB][2][NP], ssg[EB][5][NP], sD[EB][NP], samp[EB][2], srow[EB][3][NP];
+  if (flag && *flag) return;
+  const int tid = threadIdx.x;
+  const int el = tid / NN, q = tid - el * NN;
+  const long e = blk * EB + el;
+  const bool act = tid < C::NT && e < mp.K;
+  const long KN = mp.K * NN;
+  const unsigned no = ((unsigned)e * NN + q) * 8u;  // the node's byte offset in a component array
+  const double g = mp.gamma;
+  int ex, ey;
+  elem_xy32(mp, act ? (int)e : 0, ex, ey);
+  // grid line ln of direction D (D = 0: row, index along x; D = 1: column), position k on it
+  auto nodeof = [](int D, int ln, int k) { return D == 0 ? ln * NP + k : k * NP + ln; };
+  double U[5], a[5], rmin = 1.0;
+  // the four neighbours' nodes (x minus, x plus, y minus, y plus) are loaded into registers up
+  // front with the element's own, so that their latency overlaps the amplitude and x phases; they
+  // go to LDS when their direction comes
+  double nb[4][5];
+  if (act) {
+    const int nbe[4] = {ey * mp.nx + wrap32(ex - 1, mp.nx), ey * mp.nx + wrap32(ex + 1, mp.nx),
+                        wrap32(ey - 1, mp.ny) * mp.nx + ex, wrap32(ey + 1, mp.ny) * mp.nx + ex};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const unsigned on = ((unsigned)nbe[s] * NN + q) * 8u;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) nb[s][c] = bld(node_rsrc(Ust + c * KN, KN), on);
+    }
+  }
+  if (act) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) { U[c] = bld(node_rsrc(Ust + c * KN, KN), no); su[c][tid] = U[c]; }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) a[c] = 0.25 * stats[(e * 5 + c) * 3];
+  }
+  __syncthreads();
+  if (act && q < 2) samp[el][q] = cross_amp(lines + (q ? mp.ny + ex : ey) * 15, glob, q ? mp.r4ny : mp.r4nx, mp.r4K);
+#pragma unroll
+  for (int D = 0; D < 2; ++D) {
+    // neighbours across the two faces normal to direction D, staged in st rows 0..9
+    // (row c: minus-side neighbour, row 5 + c: plus-side neighbour)
+    if (act) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        st[c][tid] = nb[2 * D][c];
+        st[5 + c][tid] = nb[2 * D + 1][c];
+      }
+    }
+    __syncthreads();
+    // jumps of the derivatives (see face_jumps) of line ln of component c at the element's two faces, into the
+    // task's own staged slots (order r at position r of the line)
+    for (int t = q; act && t < NL; t += NN) {
+      const int ln = t / 5, c = t - ln * 5;  // component fastest (fewer LDS bank conflicts)
+      double own[NP], mn[NP], pl[NP];
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        const int n = el * NN + nodeof(D, ln, k);
+        own[k] = su[c][n]; mn[k] = st[c][n]; pl[k] = st[5 + c][n];
+      }
+#pragma unroll
+      for (int r = 0; r < NP; ++r) {
+        const int n = el * NN + nodeof(D, ln, r);
+        st[c][n] = line_jump<P>(mn, own, r, T);
+        st[5 + c][n] = line_jump<P>(own, pl, r, T);
+      }
+    }
+    __syncthreads();
+    // their norms over the lines, both faces together: task (r, c)
+    for (int t = q; act && t < NL; t += NN) {
+      const int r = t / 5, c = t - r * 5;
+      double Jm = 0.0, Jp = 0.0;
+#pragma unroll
+      for (int l = 0; l < NP; ++l) {
+        const int n = el * NN + nodeof(D, l, r);
+        Jm = fma(0.5 * T->w[l] * st[c][n], st[c][n], Jm);
+        Jp = fma(0.5 * T->w[l] * st[5 + c][n], st[5 + c][n], Jp);
+      }
+      ssg[el][c][r] = is_constant(glob, c) ? 0.0 : sqrt(Jm) + sqrt(Jp);
+    }
+    __syncthreads();
+    if (act && q < NP) {  // sigma (eq. euler-oe-sigma): maximum over the components, against the shared amplitude
+      double sg = 0.0;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sg = fmax(sg, ssg[el][c][q]);
+      const double A = samp[el][D];
+      ssig[el][D][q] = A > 0.0 ? T->fr[q] * sg / A : 0.0;
+    }
+  }
+  // modal damping with line tasks: x transform of each row, then per column the y transform,
+  // the shell factors and the inverse y transform, then the inverse x transform of each row
+  for (int t = q; act && t < NL; t += NN) {
+    const int ln = t / 5, c = t - ln * 5;  // component fastest (fewer LDS bank conflicts)
+    double v[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = su[c][el * NN + ln * NP + k];
+    double m[NP];
+    legendre_fwd<P>(v, m, T);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) st[c][el * NN + ln * NP + k] = m[k];  // [row][x mode]
+  }
+  __syncthreads();
+  if (act && q < NP) {
+    double lx, ly;
+    damping_rates<P>(a, g, mp, lx, ly);
+    sD[el][q] = shell_damping(q, ssig[el][0], ssig[el][1], lx, ly, sH * tau);
+  }
+  __syncthreads();
+  for (int t = q; act && t < NL; t += NN) {
+    const int aa = t / 5, c = t - aa * 5;
+    double v[NP], m[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) v[k] = st[c][el * NN + k * NP + aa];
+    legendre_fwd<P>(v, m, T);
+#pragma unroll
+    for (int b = 0; b < NP; ++b) m[b] *= sD[el][aa > b ? aa : b];
+    legendre_inv<P>(m, v, T);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) st[c][el * NN + k * NP + aa] = v[k];
+  }
+  __syncthreads();
+  for (int t = q; act && t < NL; t += NN) {
+    const int ln = t / 5, c = t - ln * 5;
+    double m[NP], v[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) m[k] = st[c][el * NN + ln * NP + k];
+    legendre_inv<P>(m, v, T);
+    double mn = DBL_MAX;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      su[c][el * NN + ln * NP + k] = v[k];
+      mn = fmin(mn, v[k]);
+    }
+    if (c == 0) srow[el][0][ln] = mn;  // row minimum of the damped density
+  }
+  __syncthreads();
+  if (act) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) U[c] = su[c][tid];
+    rmin = DBL_MAX;
+#pragma unroll
+    for (int l = 0; l < NP; ++l) rmin = fmin(rmin, srow[el][0][l]);
+  }
+  uint8_t f = 0;
+  if (do_pp) {
+    // positivity scaling: the S_p and pressure extrema are reduced per row (NP tasks per
+    // element), then over the rows by every thread
+    const double eps_r = 64.0 * EPSM;
+    const bool collapse_r = !(a[0] > eps_r);
+    double thr = 1.0;
+    if (act && !collapse_r && rmin < eps_r) {
+      thr = fmin(1.0, fmax(0.0, (a[0] - eps_r) / (a[0] - rmin)));
+      f |= 1;
+      if (thr != 1.0) U[0] = a[0] + thr * (U[0] - a[0]);  // density-limited state of this node
+    }
+    if (act) {
+      st[0][tid] = Sp(U, eps_r);
+      st[1][tid] = pres(U, g);
+    }
+    __syncthreads();
+    for (int t = q; act && t < NP; t += NN) {
+      double S = 0.0, pm = DBL_MAX;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        S = fmax(S, st[0][el * NN + t * NP + k]);
+        pm = fmin(pm, st[1][el * NN + t * NP + k]);
+      }
+      srow[el][1][t] = S;
+      srow[el][2][t] = pm;
+    }
+    __syncthreads();
+    if (act && !collapse_r) {
+      double S = Sp(a, eps_r), pmin = DBL_MAX;
+#pragma unroll
+      for (int l = 0; l < NP; ++l) { S = fmax(S, srow[el][1][l]); pmin = fmin(pmin, srow[el][2][l]); }
+      const double eps_p = fmax(64.0 * EPSM, 8192.0 * EPSM * S);
+      const double pb = pres(a, g);
+      if (pb <= eps_p) {
+        f |= 4;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) U[c] = a[c];
+      } else if (pmin < eps_p) {
+        const double thp = fmin(1.0, fmax(0.0, (pb - eps_p) / (pb - pmin)));
+        f |= 2;
+        if (thp != 1.0)
+#pragma unroll
+          for (int c = 0; c < 5; ++c) U[c] = a[c] + thp * (U[c] - a[c]);
+      }
+    } else if (act && collapse_r) {
+      f = 4;
+#pragma unroll
+      for (int c = 0; c < 5; ++c) U[c] = a[c];
+    }
+  }
+  if (act) {
+    store_node(U, no, KN, Uout, rho_o, e_o, u_o);
+    if (q == 0) {
+      if (flags) flags[e] = f;
+      if (counts && f) {
+        if (f & 1) atomicAdd(&counts[0], 1ull);
+        if (f & 2) atomicAdd(&counts[1], 1ull);
+        if (f & 4) atomicAdd(&counts[2], 1ull);
+      }
+    }
+  }
+}
+
+template <int P>
+__global__ __launch_bounds__(ML_BS) void k_hydro_map_lines(const double* __restrict__ Ust, double* __restrict__ Uout,
+                                                     const double* __restrict__ stats, const double* __restrict__ lines,
+                                                     const double* __restrict__ glob, uint8_t* __restrict__ flags,
+                                                     unsigned long long* __restrict__ counts,
+                                                     const int* __restrict__ flag, const HydroTab* __restrict__ T,
+                                                     MeshP mp, double tau, double sH, int do_pp,
+                                                     double* __restrict__ rho_o, double* __restrict__ e_o,
+                                                     double* __restrict__ u_o) {
+  hydro_map_lines_body<P>(Ust, Uout, stats, lines, glob, flags, counts, flag, T, mp, tau, sH, do_pp, rho_o, e_o, u_o, xcd_block());
+}
+
+struct hydro_map_lines_args {
+  const double* Ust;
+  double* Uout;
+  const double* stats;
+  const double* lines;
+  const double* glob;
+  uint8_t* flags;
+  unsigned long long* counts;
+  const int* flag;
+  const HydroTab* T;
+  MeshP mp;
+  double tau;
+  double sH;
+  int do_pp;
+  double* rho_o;
+  double* e_o;
+  double* u_o;
+};
+
+template <int P>
+__global__ __launch_bounds__(ML_BS) void k_hydro_map_lines_rt(const hydro_map_lines_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+  const int r = rt_run(boff, nr);
+  const hydro_map_lines_args& a = A[r];
+  hydro_map_lines_body<P>(gl(a.Ust), gl(a.Uout), gl(a.stats), gl(a.lines), gl(a.glob), gl(a.flags), gl(a.counts), gl(a.flag), gl(a.T), a.mp, a.tau, a.sH, a.do_pp, gl(a.rho_o), gl(a.e_o), gl(a.u_o), (long)blockIdx.x - boff[r]);
 }
 
 // Connectivity export: nbr[K][4] (left, right, bottom, top neighbour) and the face map
@@ -1206,9 +1606,46 @@ __global__ void k_copy(const double* __restrict__ a, double* __restrict__ b, lon
 
 hipEvent_t* timing_slot(mhd25_ctx* c, int kid);
 static int eb_of(int p) { return 256 / ((p + 1) * (p + 1)); }
-// threads per block of the hydro stage kernel: the tuned value if set, else 128 (the halves of a
-// 256-thread block wait for each other longer: 2 to 6 % more time for every degree)
+// Small meshes, by the elements of a launch (five for every compute unit).  The stage: at 32^2 elements the node form takes
+// 7.1 (N = 3), 8.7, 10.0, 11.2 us (6) and the line form 7.9, 9.7, 12.2, 17.6; at 40^2 they are 8.1, 9.8, 12.1, 14.6
+// against 8.0, 10.1, 11.7, 14.2, and beyond that the line form is ahead.  Below N = 3 it always is (5.5 us at 16^2, N = 1).
+// A batch's launches cover a whole degree group, whose form goes by their sum: all forms give the same bits.
+#ifndef MHD_SMALL_MESH
+#define MHD_SMALL_MESH 1280L
+#endif
+static bool node_stage(const mhd25_ctx* c) { return c->p >= 3 && c->launch_elements <= MHD_SMALL_MESH; }
+// The stage map in one launch.  N = 4 to 6: ahead up to about 56^2 (11.9, 15.0, 16.5 us at 48^2 against 13.7, 16.6, 22.2; 14.3,
+// 18.1, 21.6 at 64^2 against 14.0, 17.6, 23).  N = 2 and 3: 9.2 and 11.4 us against 9.6 and 11.0 in two launches up to
+// 32^2, 13.8 against 11.1 at 48^2 (N = 3).  On a mesh of one element's width a tile of the sensor is mostly outside
+// the mesh: 65536 x 1, N = 4 77 against 79 + 30 us, N = 6 240 against 204 + 71 us.
+static bool one_launch_map(const mhd25_ctx* c) {
+  const long most = c->p >= 4 ? 5 * MHD_SMALL_MESH / 2 : c->p >= 2 ? MHD_SMALL_MESH : 0;
+  return c->opt.oe_hydro && (c->launch_elements <= most || c->mp.nx == 1 || c->mp.ny == 1);
+}
+// threads per block of the hydro stage kernel: the tuned value if set, else 128.  256 take 906 against 885 us at 1024^2,
+// N = 4 (the halves of a block wait for each other longer), at 128^2 1 to 4 % less for N = 1 and 3 to 6 and 9 to 18 % more at
+// 24^2.
 static int stage_block(const mhd25_ctx* c) { return c->hydro_bs == 256 ? 256 : 128; }
+static long stage_blocks(const mhd25_ctx* c, int bs) {
+  const long eb = node_stage(c) ? bs / (2 * c->nn) : bs / 2 / c->np;
+  return (c->mp.K + eb - 1) / eb;
+}
+template <int P, int MODE>
+static void launch_stage(mhd25_ctx* c, const double* Us, const double* Un, double* out, double* stats, int* flag, double ca,
+                         double cb, double tau) {
+  const int bs = stage_block(c);
+  const dim3 grid(stage_blocks(c, bs));
+#define GO(K) hipLaunchKernelGGL(K, grid, dim3(bs), 0, c->stream, Us, Un, out, stats, flag, c->d_ht, c->mp, ca, cb, tau, c->opt.iface_flux)
+  if constexpr (P >= 3)
+    if (node_stage(c)) {
+      if (bs == 128) GO((k_hydro_stage_node<P, MODE, 128>));
+      else GO((k_hydro_stage_node<P, MODE, 256>));
+      return;
+    }
+  if (bs == 128) GO((k_hydro_stage<P, MODE, 128>));
+  else GO((k_hydro_stage<P, MODE, 256>));
+#undef GO
+}
 
 static int check(mhd25_ctx* c, hipError_t e, const char* what) {
   if (e != hipSuccess) { c->err = std::string(what) + ": " + hipGetErrorString(e); return -2; }
@@ -1235,14 +1672,7 @@ static int launch_reductions(mhd25_ctx* c, const double* stats, int nc, const in
 }
 
 int hydro_rhs(mhd25_ctx* c, const double* U, double* dU) {
-  const int bs = stage_block(c);
-  const int eb = bs / 2 / (c->p + 1);
-  const long blocks = (c->mp.K + eb - 1) / eb;
-#define L0(P)                                                                                                      \
-  if (bs == 128) hipLaunchKernelGGL((k_hydro_stage<P, 0, 128>), dim3(blocks), dim3(128), 0, c->stream, U, U, dU,  \
-                                    nullptr, nullptr, c->d_ht, c->mp, 0.0, 1.0, 0.0, c->opt.iface_flux);          \
-  else hipLaunchKernelGGL((k_hydro_stage<P, 0, 256>), dim3(blocks), dim3(256), 0, c->stream, U, U, dU, nullptr,    \
-                          nullptr, c->d_ht, c->mp, 0.0, 1.0, 0.0, c->opt.iface_flux)
+#define L0(P) launch_stage<P, 0>(c, U, U, dU, nullptr, nullptr, 0.0, 1.0, 0.0)
   DISPATCH_P(c->p, L0);
 #undef L0
   return check(c, hipGetLastError(), "rhs_hydro launch");
@@ -1251,21 +1681,15 @@ int hydro_rhs(mhd25_ctx* c, const double* U, double* dU) {
 // raw stage + statistics + line/global reductions (the OE sensor's only: without OE nothing reads them, and on a
 // 16^2 mesh they were a quarter of a step)
 int hydro_stage_a(mhd25_ctx* c, const double* Us, const double* Un, double* Ust, double ca, double cb, double tau) {
-  const int bs = stage_block(c);
-  const int eb = bs / 2 / (c->p + 1);
-  const long blocks = (c->mp.K + eb - 1) / eb;
   if (c->rec) {
-    rt_record(c, RT_HYDRO_STAGE, c->p * 1000 + bs, blocks,
+    const int bs = stage_block(c);
+    rt_record(c, RT_HYDRO_STAGE, (node_stage(c) ? 10000 : 0) + c->p * 1000 + bs, stage_blocks(c, bs),
               hydro_stage_args{Us, Un, Ust, c->stats, c->d_flag, c->d_ht, c->mp, ca, cb, tau, c->opt.iface_flux});
     return c->opt.oe_hydro ? launch_reductions(c, c->stats, 5, c->d_flag) : 0;
   }
   hipEvent_t* ev = c->timing ? timing_slot(c, 0) : nullptr;
   if (ev) hipEventRecord(ev[0], c->stream);
-#define L1(P)                                                                                                      \
-  if (bs == 128) hipLaunchKernelGGL((k_hydro_stage<P, 1, 128>), dim3(blocks), dim3(128), 0, c->stream, Us, Un, Ust, \
-                                    c->stats, c->d_flag, c->d_ht, c->mp, ca, cb, tau, c->opt.iface_flux);          \
-  else hipLaunchKernelGGL((k_hydro_stage<P, 1, 256>), dim3(blocks), dim3(256), 0, c->stream, Us, Un, Ust, c->stats, \
-                          c->d_flag, c->d_ht, c->mp, ca, cb, tau, c->opt.iface_flux)
+#define L1(P) launch_stage<P, 1>(c, Us, Un, Ust, c->stats, c->d_flag, ca, cb, tau)
   DISPATCH_P(c->p, L1);
 #undef L1
   if (ev) hipEventRecord(ev[1], c->stream);
@@ -1296,6 +1720,15 @@ int hydro_stage_b(mhd25_ctx* c, const double* Ust, double* Uout, double tau, con
                   double* e_o, double* u_o) {
   const long sblocks = (long)((c->mp.nx + HS<1>::TX - 1) / HS<1>::TX) * ((c->mp.ny + HS<1>::TY - 1) / HS<1>::TY);
   const long blocks = (c->mp.K + OM<1>::EB - 1) / OM<1>::EB;
+  const long lblocks = (c->mp.K + ML_BS / c->nn - 1) / (ML_BS / c->nn);
+  const bool one = one_launch_map(c);
+  if (c->rec && one) {  // (a plan's runs share one sequence of launches: the sensor's place is kept, with no block)
+    rt_record(c, RT_HYDRO_SENSOR, 0, 0, hydro_sensor_args{});
+    rt_record(c, RT_OE_PP, 10 + c->p, lblocks,
+              hydro_map_lines_args{Ust, Uout, c->stats, c->lines, c->glob, c->d_flags, c->d_counts, flag, c->d_ht, c->mp,
+                                   tau, c->opt.s_H, c->opt.pp, rho_o, e_o, u_o});
+    return 0;
+  }
   if (c->rec) {
     if (c->opt.oe_hydro)
       rt_record(c, RT_HYDRO_SENSOR, c->p, sblocks,
@@ -1307,6 +1740,15 @@ int hydro_stage_b(mhd25_ctx* c, const double* Ust, double* Uout, double tau, con
   }
   hipEvent_t* ev = c->timing ? timing_slot(c, 1) : nullptr;
   if (ev) hipEventRecord(ev[0], c->stream);
+  if (one) {
+#define LM(P) hipLaunchKernelGGL((k_hydro_map_lines<P>), dim3(lblocks), dim3(ML_BS), 0, c->stream, Ust, Uout, c->stats, \
+                                 c->lines, c->glob, c->d_flags, c->d_counts, flag, c->d_ht, c->mp, tau, c->opt.s_H, \
+                                 c->opt.pp, rho_o, e_o, u_o)
+    DISPATCH_P(c->p, LM);
+#undef LM
+    if (ev) hipEventRecord(ev[1], c->stream);
+    return check(c, hipGetLastError(), "stage map launch");
+  }
   if (c->opt.oe_hydro) {
 #define LS(P) hipLaunchKernelGGL((k_hydro_sensor<P>), dim3(sblocks), dim3(HS<P>::BS), 0, c->stream, Ust, c->stats, c->lines, \
                                  c->glob, c->dfac, flag, c->d_ht, c->mp, tau, c->opt.s_H)
@@ -1402,15 +1844,26 @@ __global__ __launch_bounds__(256) void k_snap_check_rt(const snap_args* __restri
   for (long k = k0; k < a.G; k += dk) snap_check_B(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.snapB), a.G, gl(a.flag), k);
 }
 
+template <int P>
+static void launch_stage_rt(bool node, int bs, dim3 g, hipStream_t s, const hydro_stage_args* A, const int* dboff, int nr) {
+  if constexpr (P >= 3)
+    if (node) {
+      if (bs == 128) hipLaunchKernelGGL((k_hydro_stage_node_rt<P, 1, 128>), g, dim3(128), 0, s, A, dboff, nr);
+      else hipLaunchKernelGGL((k_hydro_stage_node_rt<P, 1, 256>), g, dim3(256), 0, s, A, dboff, nr);
+      return;
+    }
+  if (bs == 128) hipLaunchKernelGGL((k_hydro_stage_rt<P, 1, 128>), g, dim3(128), 0, s, A, dboff, nr);
+  else hipLaunchKernelGGL((k_hydro_stage_rt<P, 1, 256>), g, dim3(256), 0, s, A, dboff, nr);
+}
+
 int hydro_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int nr, long nblocks, hipStream_t s) {
   const dim3 g((unsigned)nblocks);
   switch (h.kind) {
     case RT_HYDRO_STAGE: {
-      const int P = h.key / 1000, bs = h.key % 1000;
+      const int P = h.key / 1000 % 10, bs = h.key % 1000;
+      const bool node = h.key >= 10000;
       const hydro_stage_args* A = (const hydro_stage_args*)dargs;
-#define RS(P_)                                                                                                       \
-  if (bs == 128) hipLaunchKernelGGL((k_hydro_stage_rt<P_, 1, 128>), g, dim3(128), 0, s, A, dboff, nr);              \
-  else hipLaunchKernelGGL((k_hydro_stage_rt<P_, 1, 256>), g, dim3(256), 0, s, A, dboff, nr)
+#define RS(P_) launch_stage_rt<P_>(node, bs, g, s, A, dboff, nr)
       DISPATCH_P(P, RS);
 #undef RS
       break;
@@ -1423,6 +1876,13 @@ int hydro_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int 
       break;
     }
     case RT_OE_PP: {
+      if (h.key > 10) {
+        const hydro_map_lines_args* A = (const hydro_map_lines_args*)dargs;
+#define RM(P_) hipLaunchKernelGGL((k_hydro_map_lines_rt<P_>), g, dim3(ML_BS), 0, s, A, dboff, nr)
+        DISPATCH_P(h.key - 10, RM);
+#undef RM
+        break;
+      }
       const hydro_oe_pp_args* A = (const hydro_oe_pp_args*)dargs;
 #define RO(P_) hipLaunchKernelGGL((k_hydro_oe_pp_rt<P_>), g, dim3(OM<P_>::BS), 0, s, A, dboff, nr)
       DISPATCH_P(h.key, RO);

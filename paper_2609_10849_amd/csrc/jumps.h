@@ -3,6 +3,15 @@
 #include "common.h"
 #include "xcd.h"
 
+// jump of the derivative of order r across the face between the lines m (minus side) and q (plus side)
+template <int P>
+__device__ __forceinline__ double line_jump(const double* m, const double* q, int r, const HydroTab* __restrict__ T) {
+  double j = 0.0;
+#pragma unroll
+  for (int k = 0; k <= P; ++k) j = fma(T->Dr0[r][k], r & 1 ? q[k] + m[P - k] : q[k] - m[P - k], j);
+  return j;
+}
+
 // squared, weighted jumps of the derivatives of order r (eq. euler-oe-jump, eq. magnetic-oe-sensor) across a face between the
 // elements at m (minus side) and q (plus side), normal direction D, as square roots.  On the symmetric GLL
 // nodes d^r l_k (+1) = (-1)^r d^r l_{p-k} (-1), which the tables hold bit for bit, so the jump of order r is one

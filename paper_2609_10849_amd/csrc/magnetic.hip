@@ -1823,7 +1823,7 @@ __device__ __forceinline__ void to_primitive_node(const double* __restrict__ U, 
                                                   double* __restrict__ e, double* __restrict__ u, long n, long k) {
   const double r = U[k], ux = U[n + k] / r, uy = U[2 * n + k] / r, uz = U[3 * n + k] / r;
   rho[k] = r; u[k] = ux; u[n + k] = uy; u[2 * n + k] = uz;
-  e[k] = (U[4 * n + k] - 0.5 * r * (ux * ux + uy * uy + uz * uz)) / r;
+  e[k] = internal_energy(U[4 * n + k], r, ux, uy, uz);
 }
 
 __device__ __forceinline__ void to_conservative_node(const double* __restrict__ rho, const double* __restrict__ e,

@@ -1,4 +1,4 @@
-// Reciprocal and reciprocal square root from the hardware estimates.
+// Reciprocal and reciprocal square root from the hardware estimates, and sums in a fixed order.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -24,4 +24,14 @@ __device__ __forceinline__ double rcp_refined(double x) {
   y = fma(y, fma(-x, y, 1.0), y);
   y = fma(y, fma(-x, y, 1.0), y);
   return y;
+}
+
+// a . b of two 3-vectors, in a fixed order
+__device__ __forceinline__ double dot3(double a0, double a1, double a2, double b0, double b1, double b2) {
+  return fma(a2, b2, fma(a1, b1, a0 * b0));
+}
+
+// specific internal energy of a node from its total energy E, density and velocity (the exchange's arithmetic)
+__device__ __forceinline__ double internal_energy(double E, double r, double ux, double uy, double uz) {
+  return fma(-0.5 * r, dot3(ux, uy, uz, ux, uy, uz), E) / r;
 }

@@ -3,12 +3,15 @@ for every tile of the hydro stage kernel that a batch can be tuned to, and equal
 CPU emulation of the kernel sources and on the GPU.  An element without resistivity is not touched by J, whether or
 not its tile holds a resistive one."""
 import ctypes
+import os
+import subprocess
 
 import numpy as np
 import pytest
 
 from paper_2609_10849_amd import workloads as W
-from tests.test_hipemu_kernels import context, emu, ptr  # noqa: F401
+from tests.test_hipemu_kernels import FILES, HERE, SRC, context, emu, ptr  # noqa: F401
+from tests.test_kernel_tiles import check_hydro_substep, check_rhs_hydro, check_stage_map, run_emulated, run_gpu
 
 
 def rough_elements(nx, ny, p, m):
@@ -20,12 +23,37 @@ def rough_elements(nx, ny, p, m):
     return L, [U, Bx, By, Bz]
 
 
+@pytest.fixture(scope="module")
+def emu_large(tmp_path_factory):
+    """The emulated library with the forms of large meshes on every mesh (by default the meshes that the emulation
+    can afford take those of small ones)."""
+    import paper_2609_10849_amd as pk
+    d = tmp_path_factory.mktemp("hipemu_large")
+    procs = []
+    for f in FILES:
+        o = str(d / (os.path.splitext(f)[0] + ".o"))
+        procs.append((subprocess.Popen(["g++", "-std=c++20", "-O1", "-fPIC", "-ffp-contract=off", "-DMHD_SMALL_MESH=0L", "-I",
+                                        os.path.join(HERE, "hipemu"), "-x", "c++", "-c", os.path.join(SRC, f),
+                                        "-o", o], stderr=subprocess.PIPE), o))
+    for p, _ in procs:
+        _, err = p.communicate()
+        assert p.returncode == 0, err.decode()[-2000:]
+    so = str(d / "libmhd25_hipemu_large.so")
+    subprocess.check_call(["g++", "-shared", "-o", so] + [o for _, o in procs] + ["-pthread"])
+    lib = ctypes.CDLL(so)
+    for name, (res, args) in pk._SIGS.items():
+        fn = getattr(lib, name, None)
+        if fn is not None:
+            fn.restype, fn.argtypes = res, args
+    return lib, pk
+
+
 STEP = 1e-4
 
 
-@pytest.mark.parametrize("p,m", [(2, 1), (4, 3), (5, 5)])
-def test_emulated_step_is_the_same_for_every_tile(emu, p, m):  # noqa: F811
-    lib, pk = emu
+@pytest.mark.parametrize("form,p,m", [("emu_large", 2, 1), ("emu_large", 4, 3), ("emu_large", 5, 5), ("emu", 4, 3)])
+def test_emulated_step_is_the_same_for_every_tile(request, form, p, m):
+    lib, pk = request.getfixturevalue(form)
     L, st = rough_elements(8, 4, p, m)
     opts = pk.Options.full()
     one = [np.ascontiguousarray(a.copy()) for a in st]
@@ -97,3 +125,102 @@ def test_emulated_E_without_resistivity_ignores_J(emu, p, m, r2):  # noqa: F811
     for k in (2, 3, 4):  # dB_x, dB_y, dB_z
         a, b = grids(out[0][k])[far], grids(out[1][k])[far]
         assert np.array_equal(a, b, equal_nan=True), k
+
+
+HYDRO = [check_rhs_hydro, check_hydro_substep, check_stage_map]
+
+
+@pytest.mark.parametrize("nx,ny", [(3, 2), (5, 4), (6, 9)])
+@pytest.mark.parametrize("p,m", [(3, 2), (4, 3), (5, 5), (6, 5)])
+@pytest.mark.parametrize("check", HYDRO)
+def test_emulated_large_mesh_forms(emu_large, check, p, m, nx, ny):  # noqa: F811
+    """The hydro kernels that large meshes take, on the meshes of tests/test_kernel_tiles.py."""
+    check(lambda *a: run_emulated(emu_large, *a), p, m, nx, ny)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(130, 131), (1, 700), (900, 1)])
+@pytest.mark.parametrize("p,m", [(1, 0), (2, 2), (3, 2), (4, 3), (5, 5), (6, 5)])
+@pytest.mark.parametrize("check", HYDRO)
+def test_gpu_large_and_thin_mesh_forms(check, p, m, nx, ny):
+    """Meshes above the small ones' limit for every degree, and meshes of one element's width."""
+    from tests._gpu import announce
+    announce("%s p=%d m=%d %dx%d" % (check.__name__, p, m, nx, ny))
+    check(run_gpu, p, m, nx, ny)
+
+
+@pytest.mark.parametrize("nx,ny", [(5, 4), (1, 7), (6, 1)])
+@pytest.mark.parametrize("p", [3, 4, 5, 6])
+def test_emulated_forms_agree(emu, emu_large, p, nx, ny):  # noqa: F811
+    """The forms of small and of large meshes give the same bits: the right-hand side with both interface fluxes, the
+    substep, and the stage map on states whose limiter acts (decisions too), with and without OE and PP."""
+    from tests.test_gpu_hydro import stressed_state
+    pk = emu[1]
+    L, (U, *_) = rough_elements(nx, ny, p, p)
+    V = stressed_state(nx, ny, p, seed=30 + p)[1]
+    calls = [(pk.Options.make(iface_flux=i), "mhd25_rhs_hydro", [U, np.zeros_like(U)]) for i in (0, 1)]
+    calls.append((pk.Options.full(), "mhd25_hydro_substep", [U, STEP, None]))
+    for oe, pp in ((1, 0), (0, 1), (1, 1)):
+        calls.append((pk.Options.make(oe_hydro=oe, pp=pp), "mhd25_hydro_stage_map", [V, 1e-7, np.zeros(L.K, np.uint8)]))
+    for opts, name, args in calls:
+        a, b = (run_emulated(e, L, opts, name, args) for e in (emu, emu_large))
+        for x, y in zip(a, b):
+            assert not isinstance(x, np.ndarray) or np.array_equal(x, y), (name, opts.oe_hydro, opts.pp)
+
+
+def test_emulated_batch_of_runs_in_different_forms(emu):  # noqa: F811
+    """A batch whose degree groups take different forms (the stage map in one launch for N = 4, in two for N = 2; in one
+    on the narrow mesh) equals its runs stepped alone bit for bit."""
+    lib, pk = emu
+    runs = [rough_elements(nx, ny, p, p - 1) for nx, ny, p in ((6, 1, 2), (4, 3, 2), (3, 3, 4))]
+    n = len(runs)
+    opts = pk.Options.full()
+    descs = (pk.MeshDesc * n)(*[pk.MeshDesc(L.nx, L.ny, L.x0, L.x1, L.y0, L.y1, L.p, L.m, L.gamma) for L, _ in runs])
+    b = ctypes.c_void_p()
+    assert lib.mhd25_batch_create(descs, n, ctypes.byref(opts), None, ctypes.byref(b)) == 0
+    bat = [[np.ascontiguousarray(a.copy()) for a in st] for _, st in runs]
+    arr = [(ctypes.c_void_p * n)(*[x[i].ctypes.data for x in bat]) for i in range(4)]
+    dts = (ctypes.c_double * n)(STEP, 0.5 * STEP, STEP)
+    assert lib.mhd25_batch_autotune(b, *arr, dts, None, None) == 0
+    assert lib.mhd25_batch_strang_step(b, *arr, dts, None) == 0
+    lib.mhd25_batch_destroy(b)
+    for (L, st), got, dt in zip(runs, bat, dts):
+        one = [np.ascontiguousarray(a.copy()) for a in st]
+        h = context(lib, pk, L, opts)
+        assert lib.mhd25_strang_step(h, *[ptr(a) for a in one], dt, None) == 0
+        lib.mhd25_destroy(h)
+        for a, r in zip(got, one):
+            assert (a == r).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("p", [3, 4, 5, 6])
+def test_gpu_batch_of_small_and_large_runs(p):
+    """A batch whose runs together are above the small meshes' limit, each alone below or above it: the same bits in
+    either form, launched plainly, replayed and after the tile choice.  A
+    step that is refused alone (the narrow run's second one, as the oracle does) is refused in the batch."""
+    import paper_2609_10849_amd as pk
+    from tests._gpu import announce, dev, host
+    announce("batch of small and large runs p=%d" % p)
+    runs = [rough_elements(nx, ny, p, p - 1) for nx, ny in ((16, 20), (90, 81), (1, 300))]
+    opts = pk.Options.full()
+    dts = [STEP, 0.5 * STEP, 0.2 * STEP]
+    alone, status = [], []
+    for (L, st), dt in zip(runs, dts):
+        S = pk.Solver.from_layout(L, opts)
+        one = [dev(a) for a in st]
+        status.append([S.strang_step(*one, dt)[0] for _ in range(2)])
+        alone.append([host(a) for a in one])
+        S.close()
+    B = pk.Batch([L for L, _ in runs], opts)
+    for graph, tuned in ((False, False), (True, False), (False, True)):
+        B.graph(graph)
+        bat = [[dev(a) for a in st] for _, st in runs]
+        args = [[x[i] for x in bat] for i in range(4)]
+        if tuned:
+            B.autotune(*args, dts)
+        assert [B.strang_step(*args, dts)[0] for _ in range(2)] == [max(s[k] for s in status) for k in range(2)]
+        for got, want in zip(bat, alone):
+            for a, r in zip(got, want):
+                assert (host(a) == r).all(), (graph, tuned)
+    B.close()
