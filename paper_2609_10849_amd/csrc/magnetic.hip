@@ -51,11 +51,15 @@ __device__ __forceinline__ long gix(const MeshP& mp, int B, long ex, long ey, in
 // Lumped weights: with W_i the assembled 1D weight of node i, the tables RWQ.. hold the 1D operators with
 // row i divided by W_i (|J_K| cancels).
 // ---------------------------------------------------------------------------------------------
-template <int M, bool R2>
+// S: tile shape, 0 TX x TY; on meshes of one element's width, where such a tile is mostly outside the mesh, the same
+// number of elements in a row (1) or a column (2).  On 65536 x 1 elements with resistivity k_J takes 37 and k_E 79 us
+// (N = k = 4) where the 5 x 4 tiles took 68 and 221, at N = k = 6 88 and 230 against 167 and 702.
+template <int M, bool R2, int S>
 struct RT {
   static constexpr int A = M + 2, B = M + 1;
   // tile sizes that fill the row tasks' waves: A TE of the W rows, B TE of the Gauss rows
-  static constexpr int TX = M == 2 || M >= 5 ? 4 : 5, TY = M == 3 ? 5 : 4, TE = TX * TY;
+  static constexpr int SX = M == 2 || M >= 5 ? 4 : 5, SY = M == 3 ? 5 : 4, TE = SX * SY;
+  static constexpr int TX = S == 0 ? SX : (S == 1 ? TE : 1), TY = S == 0 ? SY : (S == 1 ? 1 : TE);
   static constexpr int WW = (A * TE + 63) / 64 * 64;  // threads of the W rows (whole waves)
   static constexpr int BS = R2 ? WW : WW + (B * TE + 63) / 64 * 64;
 };
@@ -111,12 +115,12 @@ __device__ __forceinline__ double dot_patch(const double* t, const double* f, in
 
 // The thread's row task: W row j (or Gauss row j) of tile element (lx, ly); ye is the element row it reads,
 // ly, or ly - 1 for the row A-1 of the element below.
-template <int M, bool R2>
+template <int M, bool R2, int S>
 struct RowTask {
   bool w, act, below;
   int j, lx, ly, ye, el;
   __device__ __forceinline__ RowTask(int tw, int th) {
-    using C = RT<M, R2>;
+    using C = RT<M, R2, S>;
     w = R2 || __builtin_amdgcn_readfirstlane(threadIdx.x < C::WW ? 1 : 0);
     const int t = threadIdx.x - (w ? 0 : C::WW);
     j = t / C::TE; el = t - j * C::TE;
@@ -131,11 +135,11 @@ struct RowTask {
 // with the (m+1)-point rule (x, y), each as one operator per direction.
 // Measured: 1024^2, N = 4, k = 3: 0.66 (load kernel and gather) -> 0.29 ms; 128^2, N = k = 4: 28 -> 13 us.  Bound by the
 // latency of its staging loads and barriers (1.3 GB moved).
-template <int P, int M, bool R2>
+template <int M, bool R2, int S>
 __device__ __forceinline__ void J_body(const double* __restrict__ Bx, const double* __restrict__ By,
                                        const double* __restrict__ Bz, double* __restrict__ Jx, double* __restrict__ Jy,
                                        double* __restrict__ Jz, const MagTab* __restrict__ T, const MeshP& mp, int blk) {
-  using C = RT<M, R2>;
+  using C = RT<M, R2, S>;
   constexpr int A = C::A, B = C::B, TX = C::TX, TY = C::TY, TE = C::TE, BS = C::BS;
   // the tile's elements, the column left of it and the row below
   using PX = Patch<(TY + 1) * B, (TX + 1) * B + 1, B, TX, BS>;
@@ -160,7 +164,7 @@ __device__ __forceinline__ void J_body(const double* __restrict__ Bx, const doub
     px.store(sx);
     py.store(sy);
   }
-  const RowTask<M, R2> k(tw, th);
+  const RowTask<M, R2, S> k(tw, th);
   const int gx = (tx0 + k.lx) * B, gy = (ty0 + k.ly) * B + k.j, NXg = mp.nx * B;
   double tq[A], td[B], tv[B];  // rows j of the tables along y
   if (k.act) {
@@ -260,14 +264,14 @@ __device__ __forceinline__ double add_eta(double eta, double j, double e) { retu
 // to J; blocks whose elements all have eta = 0 skip that term.
 // Measured: 1024^2, N = 4, k = 3, with resistivity: 1.08 (load kernel and gather) -> 0.55 ms; 128^2, N = k = 4, without:
 // 36 -> 17.5 us.  Bound by LDS reads and latency (2.0 GB moved).
-template <int P, int M, bool R2>
+template <int P, int M, bool R2, int S>
 __device__ __forceinline__ void E_body(const double* __restrict__ u, const double* __restrict__ Bx,
                                        const double* __restrict__ By, const double* __restrict__ Bz,
                                        const double* __restrict__ Jx, const double* __restrict__ Jy,
                                        const double* __restrict__ Jz, const double* __restrict__ eta,
                                        double* __restrict__ Ex, double* __restrict__ Ey, double* __restrict__ Ez,
                                        const MagTab* __restrict__ T, const MeshP& mp, int blk) {
-  using C = RT<M, R2>;
+  using C = RT<M, R2, S>;
   constexpr int A = C::A, B = C::B, TX = C::TX, TY = C::TY, TE = C::TE, BS = C::BS;
   constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1, NU = R2 ? 2 : 3;
   constexpr int NE = (TX + 1) * (TY + 1);  // staged elements: the tile's, the column left of it, the row below
@@ -285,7 +289,7 @@ __device__ __forceinline__ void E_body(const double* __restrict__ u, const doubl
   const int tw = mp.nx - tx0 < TX ? mp.nx - tx0 : TX, th = mp.ny - ty0 < TY ? mp.ny - ty0 : TY;
   const long KN = mp.K * NN;
   const int bx0 = tx0 * B, by0 = ty0 * B;
-  const RowTask<M, R2> k(tw, th);
+  const RowTask<M, R2, S> k(tw, th);
   // resistivity of the task's element and of the one left of it
   double et = 0.0, etl = 0.0;
   if (eta && k.act) {
@@ -505,12 +509,12 @@ __device__ __forceinline__ void E_body(const double* __restrict__ u, const doubl
   }
 }
 
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((RT<M, R2>::BS)) void k_J(const double* __restrict__ Bx, const double* __restrict__ By,
+template <int M, bool R2, int S>
+__global__ __launch_bounds__((RT<M, R2, S>::BS)) void k_J(const double* __restrict__ Bx, const double* __restrict__ By,
                                                  const double* __restrict__ Bz, double* __restrict__ Jx,
                                                  double* __restrict__ Jy, double* __restrict__ Jz,
                                                  const MagTab* __restrict__ T, MeshP mp) {
-  J_body<P, M, R2>(Bx, By, Bz, Jx, Jy, Jz, T, mp, (int)xcd_block());
+  J_body<M, R2, S>(Bx, By, Bz, Jx, Jy, Jz, T, mp, (int)xcd_block());
 }
 
 struct J_args {
@@ -524,21 +528,21 @@ struct J_args {
   MeshP mp;
 };
 
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((RT<M, R2>::BS)) void k_J_rt(const J_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int M, bool R2, int S>
+__global__ __launch_bounds__((RT<M, R2, S>::BS)) void k_J_rt(const J_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const J_args& a = A[r];
-  J_body<P, M, R2>(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
+  J_body<M, R2, S>(gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
 }
 
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((RT<M, R2>::BS)) void k_E(const double* __restrict__ u, const double* __restrict__ Bx,
+template <int P, int M, bool R2, int S>
+__global__ __launch_bounds__((RT<M, R2, S>::BS)) void k_E(const double* __restrict__ u, const double* __restrict__ Bx,
                                                  const double* __restrict__ By, const double* __restrict__ Bz,
                                                  const double* __restrict__ Jx, const double* __restrict__ Jy,
                                                  const double* __restrict__ Jz, const double* __restrict__ eta,
                                                  double* __restrict__ Ex, double* __restrict__ Ey,
                                                  double* __restrict__ Ez, const MagTab* __restrict__ T, MeshP mp) {
-  E_body<P, M, R2>(u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, T, mp, (int)xcd_block());
+  E_body<P, M, R2, S>(u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, T, mp, (int)xcd_block());
 }
 
 struct E_args {
@@ -557,11 +561,11 @@ struct E_args {
   MeshP mp;
 };
 
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((RT<M, R2>::BS)) void k_E_rt(const E_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int P, int M, bool R2, int S>
+__global__ __launch_bounds__((RT<M, R2, S>::BS)) void k_E_rt(const E_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const E_args& a = A[r];
-  E_body<P, M, R2>(gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.eta), gl(a.Ex), gl(a.Ey), gl(a.Ez), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
+  E_body<P, M, R2, S>(gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.Jx), gl(a.Jy), gl(a.Jz), gl(a.eta), gl(a.Ex), gl(a.Ey), gl(a.Ez), gl(a.T), a.mp, (int)blockIdx.x - boff[r]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1120,14 +1124,18 @@ __global__ __launch_bounds__(MHD_PREP_BS) void k_vel_prep_rt(const vel_prep_args
 // Tile of the velocity-OE sensor: TX x TY elements and the ring around them.  One thread per component and
 // face, the tile's (TX + 1) TY x faces on the block's first half, its TX (TY + 1) y faces on the second, so that
 // a wave has one direction.  The wave speeds are row tasks, one GLL row of an element each.  5 x 5 elements
-// leave three blocks per CU at N = 4; 6 x 6 fill more lanes but leave two (0.56 against 0.52 ms at 1024^2).
-template <int P, int M, bool R2>
+// leave three blocks per CU at N = 4; 6 x 6 fill more lanes but leave two (0.56 against 0.52 ms at 1024^2).  S: tile
+// shape as RT's, the row's and column's length for as many staged elements (65536 x 1: N = 4 56 us against 199, N = 6
+// 137 against 550).
+template <int P, int M, bool R2, int S>
 struct VS {
   static constexpr int NP = P + 1, NN = NP * NP, ES = NN | 1;  // odd element stride in LDS: no bank conflicts
   static constexpr int A = M + 2, B = M + 1, BS = 256, NU = R2 ? 2 : 3;  // u_z = 0 in the 2D2V system
-  static constexpr int TX = 5, TY = P < 6 ? 5 : 4, TE = TX * TY;
+  static constexpr int TL = P < 6 ? 15 : 12;
+  static constexpr int TX = S == 0 ? 5 : (S == 1 ? TL : 1), TY = S == 0 ? (P < 6 ? 5 : 4) : (S == 1 ? 1 : TL), TE = TX * TY;
   static constexpr int NX = (TX + 1) * TY, NY = TX * (TY + 1);  // faces
   static constexpr int NS = TE + 2 * (TX + TY);                 // staged elements: the tile's, then the ring's
+  static_assert(NU * NX <= BS / 2 && NU * NY <= BS / 2, "a thread per component and face");
 };
 
 // Velocity-OE sensor (eq. magnetic-oe-sensor, eq. magnetic-oe-rate, eq. magnetic-oe-factor): the element's
@@ -1135,14 +1143,14 @@ struct VS {
 // only read here (the projection kernel that updates it runs afterwards).  Measured, against a thread per
 // node with the neighbours staged per element: 0.98 -> 0.52 ms at 1024^2, N = 4, k = 3 (1.24 GB), 61 -> 37 us
 // at 241 x 137, N = 5, 32 -> 17 us at 256^2, N = 2.  Bound by VALU issue and the latency of its staging loads.
-template <int P, int M, bool R2>
+template <int P, int M, bool R2, int S>
 __device__ __forceinline__ void vel_sensor_body(const double* __restrict__ rho, const double* __restrict__ u,
                                                     const double* __restrict__ Bx, const double* __restrict__ By,
                                                     const double* __restrict__ Bz, const double* __restrict__ lines,
                                                     const double* __restrict__ glob, double* __restrict__ Dfac,
                                                     const HydroTab* __restrict__ H, const MagTab* __restrict__ T,
                                                     const MeshP& mp, double tau, double sM, int blk) {
-  using C = VS<P, M, R2>;
+  using C = VS<P, M, R2, S>;
   constexpr int NP = C::NP, NN = C::NN, ES = C::ES, A = C::A, B = C::B, BS = C::BS, NU = C::NU;
   constexpr int TX = C::TX, TY = C::TY, TE = C::TE, NS = C::NS, NX = C::NX, NY = C::NY;
   using PX = Patch<TY * B, TX * B + 1, B, TX, BS>;
@@ -1285,12 +1293,12 @@ __device__ __forceinline__ void vel_sensor_body(const double* __restrict__ rho, 
   const bool act = c < NU && (D ? fx < tw && fy <= th : fx <= tw && fy < th);
   double J[NP];
   if (act) {
-    const double* S = su + c * NS * ES;
+    const double* sv = su + c * NS * ES;
     if (D == 0)
-      face_jumps<P, 0>(S + (fx == 0 ? TE + fy : fy * TX + fx - 1) * ES, S + (fx == tw ? TE + TY + fy : fy * TX + fx) * ES, H, J);
+      face_jumps<P, 0>(sv + (fx == 0 ? TE + fy : fy * TX + fx - 1) * ES, sv + (fx == tw ? TE + TY + fy : fy * TX + fx) * ES, H, J);
     else
-      face_jumps<P, 1>(S + (fy == 0 ? TE + 2 * TY + fx : (fy - 1) * TX + fx) * ES,
-                       S + (fy == th ? TE + 2 * TY + TX + fx : fy * TX + fx) * ES, H, J);
+      face_jumps<P, 1>(sv + (fy == 0 ? TE + 2 * TY + fx : (fy - 1) * TX + fx) * ES,
+                       sv + (fy == th ? TE + 2 * TY + TX + fx : fy * TX + fx) * ES, H, J);
   }
   __syncthreads();
   if (act) {
@@ -1330,20 +1338,14 @@ __device__ __forceinline__ void vel_sensor_body(const double* __restrict__ rho, 
   }
 }
 
-template <int P, int M>
-long vel_sensor_tiles(const MeshP& mp, bool r2) {
-  const int TX = VS<P, M, true>::TX, TY = r2 ? VS<P, M, true>::TY : VS<P, M, false>::TY;
-  return (long)((mp.nx + TX - 1) / TX) * ((mp.ny + TY - 1) / TY);
-}
-
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((VS<P, M, R2>::BS)) void k_vel_sensor(const double* __restrict__ rho, const double* __restrict__ u,
+template <int P, int M, bool R2, int S>
+__global__ __launch_bounds__((VS<P, M, R2, S>::BS)) void k_vel_sensor(const double* __restrict__ rho, const double* __restrict__ u,
                                                     const double* __restrict__ Bx, const double* __restrict__ By,
                                                     const double* __restrict__ Bz, const double* __restrict__ lines,
                                                     const double* __restrict__ glob, double* __restrict__ Dfac,
                                                     const HydroTab* __restrict__ H, const MagTab* __restrict__ T,
                                                     MeshP mp, double tau, double sM) {
-  vel_sensor_body<P, M, R2>(rho, u, Bx, By, Bz, lines, glob, Dfac, H, T, mp, tau, sM, (int)xcd_block());
+  vel_sensor_body<P, M, R2, S>(rho, u, Bx, By, Bz, lines, glob, Dfac, H, T, mp, tau, sM, (int)xcd_block());
 }
 
 struct vel_sensor_args {
@@ -1362,11 +1364,11 @@ struct vel_sensor_args {
   double sM;
 };
 
-template <int P, int M, bool R2>
-__global__ __launch_bounds__((VS<P, M, R2>::BS)) void k_vel_sensor_rt(const vel_sensor_args* __restrict__ A, const int* __restrict__ boff, int nr) {
+template <int P, int M, bool R2, int S>
+__global__ __launch_bounds__((VS<P, M, R2, S>::BS)) void k_vel_sensor_rt(const vel_sensor_args* __restrict__ A, const int* __restrict__ boff, int nr) {
   const int r = rt_run(boff, nr);
   const vel_sensor_args& a = A[r];
-  vel_sensor_body<P, M, R2>(gl(a.rho), gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.H), gl(a.T), a.mp, a.tau, a.sM, (int)blockIdx.x - boff[r]);
+  vel_sensor_body<P, M, R2, S>(gl(a.rho), gl(a.u), gl(a.Bx), gl(a.By), gl(a.Bz), gl(a.lines), gl(a.glob), gl(a.Dfac), gl(a.H), gl(a.T), a.mp, a.tau, a.sM, (int)blockIdx.x - boff[r]);
 }
 
 // Velocity-OE map (eq. magnetic-oe-map) with the prepared basis, EB elements per block.  The block's
@@ -1918,27 +1920,57 @@ static long mblocks(int p, int m, long K, int bs = 256) {
 #define MHD_VP_BS 128
 #endif
 
+// tile shape of the tile kernels (see RT)
+static int mesh_shape(const MeshP& mp) { return mp.ny == 1 && mp.nx > 1 ? 1 : (mp.nx == 1 && mp.ny > 1 ? 2 : 0); }
+template <class C>
+static dim3 tiles(const MeshP& mp) {
+  return dim3((unsigned)((long)((mp.nx + C::TX - 1) / C::TX) * ((mp.ny + C::TY - 1) / C::TY)));
+}
+// F(R2, S) for the context's system and shape
+#define DISPATCH_RS(r2, sh, F)                                                                            \
+  if (sh == 0) { if (r2) { F(true, 0); } else { F(false, 0); } }                                          \
+  else if (sh == 1) { if (r2) { F(true, 1); } else { F(false, 1); } }                                     \
+  else { if (r2) { F(true, 2); } else { F(false, 2); } }
+
 template <int M>
-static long tiles(const MeshP& mp) {
-  return (long)((mp.nx + RT<M, false>::TX - 1) / RT<M, false>::TX) * ((mp.ny + RT<M, false>::TY - 1) / RT<M, false>::TY);
+static long recon_tiles(const mhd25_ctx* c, int sh) {
+  long nb = 0;
+#define NB(R2, S) nb = tiles<RT<M, R2, S>>(c->mp).x
+  DISPATCH_RS(false, sh, NB);
+#undef NB
+  return nb;
+}
+template <int M>
+static void launch_J(mhd25_ctx* c, const J_args& a, bool r2, int sh) {
+#define GO(R2, S) hipLaunchKernelGGL((k_J<M, R2, S>), (tiles<RT<M, R2, S>>(c->mp)), dim3(RT<M, R2, S>::BS), 0, c->stream, \
+                                     a.Bx, a.By, a.Bz, a.Jx, a.Jy, a.Jz, a.T, a.mp)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
+}
+template <int P, int M>
+static void launch_E(mhd25_ctx* c, const E_args& a, bool r2, int sh) {
+#define GO(R2, S) hipLaunchKernelGGL((k_E<P, M, R2, S>), (tiles<RT<M, R2, S>>(c->mp)), dim3(RT<M, R2, S>::BS), 0, c->stream, \
+                                     a.u, a.Bx, a.By, a.Bz, a.Jx, a.Jy, a.Jz, a.eta, a.Ex, a.Ey, a.Ez, a.T, a.mp)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
 }
 
 // J alone (three grids).  r2: the 2D2V reduced system (only J_z and E_z are formed; the in-plane grids are not written)
 int mag_reconstruct_J(mhd25_ctx* c, const double* Bx, const double* By, const double* Bz, double* J, bool r2) {
-  double *Jx = J, *Jy = J + c->G, *Jz = J + 2 * c->G;
-  long nb = 0;
-#define NB(M) nb = tiles<M>(c->mp)
-  DISPATCH_M(c->m, NB);
+  const J_args a{Bx, By, Bz, J, J + c->G, J + 2 * c->G, c->d_mt, c->mp};
+  const int sh = mesh_shape(c->mp);
+  if (c->rec) {
+    long nb = 0;
+#define NB(M) nb = recon_tiles<M>(c, sh)
+    DISPATCH_M(c->m, NB);
 #undef NB
-  if (c->rec) { rt_record(c, RT_J, mkey(c->p, c->m, r2), nb, J_args{Bx, By, Bz, Jx, Jy, Jz, c->d_mt, c->mp}); return 0; }
-#define LJ(P, M)                                                                                                    \
-  if (r2) hipLaunchKernelGGL((k_J<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, Bx, By, Bz, Jx, Jy, \
-                             Jz, c->d_mt, c->mp);                                                                   \
-  else hipLaunchKernelGGL((k_J<P, M, false>), dim3(nb), dim3(RT<M, false>::BS), 0, c->stream, Bx, By, Bz, Jx, Jy,  \
-                          Jz, c->d_mt, c->mp)
+    rt_record(c, RT_J, mkey(c->p, c->m, r2, sh), nb, a);
+    return 0;
+  }
+#define LJ(M) launch_J<M>(c, a, r2, sh)
   {
     T_BEGIN(7);
-    DISPATCH_PM(c->p, c->m, LJ);
+    DISPATCH_M(c->m, LJ);
     T_END();
   }
 #undef LJ
@@ -1948,21 +1980,18 @@ int mag_reconstruct_J(mhd25_ctx* c, const double* Bx, const double* By, const do
 int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const double* By, const double* Bz,
                        const double* eta, double* JE, bool r2) {
   const long G = c->G;
-  double *Jx = JE, *Jy = JE + G, *Jz = JE + 2 * G, *Ex = JE + 3 * G, *Ey = JE + 4 * G, *Ez = JE + 5 * G;
   if (const int r = mag_reconstruct_J(c, Bx, By, Bz, JE, r2)) return r;
-  long nb = 0;
-#define NB(M) nb = tiles<M>(c->mp)
-  DISPATCH_M(c->m, NB);
-#undef NB
+  const E_args a{u, Bx, By, Bz, JE, JE + G, JE + 2 * G, eta, JE + 3 * G, JE + 4 * G, JE + 5 * G, c->d_mt, c->mp};
+  const int sh = mesh_shape(c->mp);
   if (c->rec) {
-    rt_record(c, RT_E, mkey(c->p, c->m, r2), nb, E_args{u, Bx, By, Bz, Jx, Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp});
+    long nb = 0;
+#define NB(M) nb = recon_tiles<M>(c, sh)
+    DISPATCH_M(c->m, NB);
+#undef NB
+    rt_record(c, RT_E, mkey(c->p, c->m, r2, sh), nb, a);
     return 0;
   }
-#define LE(P, M)                                                                                                    \
-  if (r2) hipLaunchKernelGGL((k_E<P, M, true>), dim3(nb), dim3(RT<M, true>::BS), 0, c->stream, u, Bx, By, Bz, Jx,  \
-                             Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp);                                              \
-  else hipLaunchKernelGGL((k_E<P, M, false>), dim3(nb), dim3(RT<M, false>::BS), 0, c->stream, u, Bx, By, Bz, Jx,   \
-                          Jy, Jz, eta, Ex, Ey, Ez, c->d_mt, c->mp)
+#define LE(P, M) (launch_E<P, M>(c, a, r2, sh))
   {
     T_BEGIN(5);
     DISPATCH_PM(c->p, c->m, LE);
@@ -1970,6 +1999,22 @@ int mag_reconstruct_JE(mhd25_ctx* c, const double* u, const double* Bx, const do
   }
 #undef LE
   return chk(c, "reconstruct launch");
+}
+
+template <int P, int M>
+static long sensor_tiles(const mhd25_ctx* c, bool r2, int sh) {
+  long nb = 0;
+#define NB(R2, S) nb = tiles<VS<P, M, R2, S>>(c->mp).x
+  DISPATCH_RS(r2, sh, NB);
+#undef NB
+  return nb;
+}
+template <int P, int M>
+static void launch_vel_sensor(mhd25_ctx* c, const vel_sensor_args& a, bool r2, int sh) {
+#define GO(R2, S) hipLaunchKernelGGL((k_vel_sensor<P, M, R2, S>), (tiles<VS<P, M, R2, S>>(c->mp)), dim3((VS<P, M, R2, S>::BS)), 0, \
+                                     c->stream, a.rho, a.u, a.Bx, a.By, a.Bz, a.lines, a.glob, a.Dfac, a.H, a.T, a.mp, a.tau, a.sM)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
 }
 
 int mag_update(mhd25_ctx* c, const MagIO& io, int mode) {
@@ -2039,22 +2084,19 @@ int mag_velocity_apply(mhd25_ctx* c, double tau, const double* rho, double* u, d
 #undef FS
   }
   line_global_reduce(c, c->stats, nu, nullptr);
-  long nbs = 0;
-#define NBS(P, M) nbs = vel_sensor_tiles<P, M>(c->mp, r2)
-  DISPATCH_PM(c->p, c->m, NBS);
-#undef NBS
+  const vel_sensor_args sa{rho, u, Bx, By, Bz, c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M};
+  const int sh = mesh_shape(c->mp);
   if (c->rec) {
     if (!stats_ready) { c->err = "run-table plan: velocity statistics must come from the update"; return -2; }
-    rt_record(c, RT_VEL_SENSOR, mkey(c->p, c->m, r2), nbs,
-              vel_sensor_args{rho, u, Bx, By, Bz, c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M});
+    long nbs = 0;
+#define NBS(P, M) (nbs = sensor_tiles<P, M>(c, r2, sh))
+    DISPATCH_PM(c->p, c->m, NBS);
+#undef NBS
+    rt_record(c, RT_VEL_SENSOR, mkey(c->p, c->m, r2, sh), nbs, sa);
     rt_record(c, RT_VEL_PROJ, mkey(c->p, c->m, r2), nb2, vel_proj_args{rho, u, e, c->psi, c->dfac, c->d_ht, c->mp, Uc});
     return 0;
   }
-#define VSN(P, M)                                                                                                   \
-  if (r2) hipLaunchKernelGGL((k_vel_sensor<P, M, true>), dim3(nbs), dim3((VS<P, M, true>::BS)), 0, c->stream, rho, u, Bx, By, Bz,    \
-                             c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M);                 \
-  else hipLaunchKernelGGL((k_vel_sensor<P, M, false>), dim3(nbs), dim3((VS<P, M, false>::BS)), 0, c->stream, rho, u, Bx, By, Bz,      \
-                          c->lines, c->glob, c->dfac, c->d_ht, c->d_mt, c->mp, tau, c->opt.s_M)
+#define VSN(P, M) (launch_vel_sensor<P, M>(c, sa, r2, sh))
   {
     T_BEGIN(6);
     DISPATCH_PM(c->p, c->m, VSN);
@@ -2189,6 +2231,25 @@ __global__ __launch_bounds__(256) void k_to_conservative_rt(const prim_args* __r
     to_conservative_node(gl(a.rho), gl(a.e), gl(a.u), const_cast<double*>(gl(a.U)), a.n, k);
 }
 
+template <int M>
+static void launch_J_rt(bool r2, int sh, dim3 g, hipStream_t s, const J_args* A, const int* dboff, int nr) {
+#define GO(R2, S) hipLaunchKernelGGL((k_J_rt<M, R2, S>), g, dim3(RT<M, R2, S>::BS), 0, s, A, dboff, nr)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
+}
+template <int P, int M>
+static void launch_E_rt(bool r2, int sh, dim3 g, hipStream_t s, const E_args* A, const int* dboff, int nr) {
+#define GO(R2, S) hipLaunchKernelGGL((k_E_rt<P, M, R2, S>), g, dim3(RT<M, R2, S>::BS), 0, s, A, dboff, nr)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
+}
+template <int P, int M>
+static void launch_vel_sensor_rt(bool r2, int sh, dim3 g, hipStream_t s, const vel_sensor_args* A, const int* dboff, int nr) {
+#define GO(R2, S) hipLaunchKernelGGL((k_vel_sensor_rt<P, M, R2, S>), g, dim3((VS<P, M, R2, S>::BS)), 0, s, A, dboff, nr)
+  DISPATCH_RS(r2, sh, GO);
+#undef GO
+}
+
 int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, int nr, long nblocks, hipStream_t s) {
   const dim3 g((unsigned)nblocks);
   const int p = h.key / 1000, m = (h.key / 100) % 10, mode = h.key % 10;
@@ -2196,18 +2257,14 @@ int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, i
   switch (h.kind) {
     case RT_J: {
       const J_args* A = (const J_args*)dargs;
-#define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_J_rt<P, M, true>), g, dim3(RT<M, true>::BS), 0, s, A, dboff, nr);                   \
-  else hipLaunchKernelGGL((k_J_rt<P, M, false>), g, dim3(RT<M, false>::BS), 0, s, A, dboff, nr)
-      DISPATCH_PM(p, m, F);
+#define F(M) launch_J_rt<M>(r2, mode, g, s, A, dboff, nr)
+      DISPATCH_M(m, F);
 #undef F
       break;
     }
     case RT_E: {
       const E_args* A = (const E_args*)dargs;
-#define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_E_rt<P, M, true>), g, dim3(RT<M, true>::BS), 0, s, A, dboff, nr);                   \
-  else hipLaunchKernelGGL((k_E_rt<P, M, false>), g, dim3(RT<M, false>::BS), 0, s, A, dboff, nr)
+#define F(P, M) (launch_E_rt<P, M>(r2, mode, g, s, A, dboff, nr))
       DISPATCH_PM(p, m, F);
 #undef F
       break;
@@ -2232,9 +2289,7 @@ int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, i
     }
     case RT_VEL_SENSOR: {
       const vel_sensor_args* A = (const vel_sensor_args*)dargs;
-#define F(P, M)                                                                                                     \
-  if (r2) hipLaunchKernelGGL((k_vel_sensor_rt<P, M, true>), g, dim3((VS<P, M, true>::BS)), 0, s, A, dboff, nr);                      \
-  else hipLaunchKernelGGL((k_vel_sensor_rt<P, M, false>), g, dim3((VS<P, M, false>::BS)), 0, s, A, dboff, nr)
+#define F(P, M) (launch_vel_sensor_rt<P, M>(r2, mode, g, s, A, dboff, nr))
       DISPATCH_PM(p, m, F);
 #undef F
       break;

@@ -11,7 +11,8 @@ import pytest
 
 from paper_2609_10849_amd import workloads as W
 from tests.test_hipemu_kernels import FILES, HERE, SRC, context, emu, ptr  # noqa: F401
-from tests.test_kernel_tiles import check_hydro_substep, check_rhs_hydro, check_stage_map, run_emulated, run_gpu
+from tests.test_kernel_tiles import (check_adjoint, check_hydro_substep, check_reconstruction, check_rhs_hydro,
+                                     check_stage_map, check_velocity_oe, run_emulated, run_gpu)
 
 
 def rough_elements(nx, ny, p, m):
@@ -128,6 +129,7 @@ def test_emulated_E_without_resistivity_ignores_J(emu, p, m, r2):  # noqa: F811
 
 
 HYDRO = [check_rhs_hydro, check_hydro_substep, check_stage_map]
+MAGNETIC = [check_velocity_oe, check_reconstruction]
 
 
 @pytest.mark.parametrize("nx,ny", [(3, 2), (5, 4), (6, 9)])
@@ -138,10 +140,18 @@ def test_emulated_large_mesh_forms(emu_large, check, p, m, nx, ny):  # noqa: F81
     check(lambda *a: run_emulated(emu_large, *a), p, m, nx, ny)
 
 
+@pytest.mark.parametrize("nx,ny", [(27, 1), (1, 27)])
+@pytest.mark.parametrize("p,m", [(1, 0), (2, 2), (4, 3), (6, 5)])
+@pytest.mark.parametrize("check", MAGNETIC)
+def test_emulated_thin_tiles(emu, check, p, m, nx, ny):  # noqa: F811
+    """The row and column tiles of meshes of one element's width, with a last tile that the mesh ends early."""
+    check(lambda *a: run_emulated(emu, *a), p, m, nx, ny)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("nx,ny", [(130, 131), (1, 700), (900, 1)])
 @pytest.mark.parametrize("p,m", [(1, 0), (2, 2), (3, 2), (4, 3), (5, 5), (6, 5)])
-@pytest.mark.parametrize("check", HYDRO)
+@pytest.mark.parametrize("check", HYDRO + MAGNETIC + [check_adjoint])
 def test_gpu_large_and_thin_mesh_forms(check, p, m, nx, ny):
     """Meshes above the small ones' limit for every degree, and meshes of one element's width."""
     from tests._gpu import announce
