@@ -35,30 +35,47 @@ def kernel_table(N, k):
     algorithmic HBM bytes per element and launch, algorithmic FP64 flops per element and launch or
     None, fraction of a block's lanes that carry work).  Bytes count each array the kernel must
     touch once (neighbour data counted as cache hits); the stage kernel's and the map's are the
-    averages over the launches of a step (see stage_bytes, oe_pp_bytes)."""
+    averages over the launches of a step (see stage_bytes, oe_pp_bytes).  The velocity-OE rows count
+    a basis table of all (N+1)^2 modes; the kernels hold fewer, and kernel_bytes is what they must touch."""
     NP, nn = N + 1, (N + 1) ** 2
     A, B = k + 2, k + 1
-    psi = nn * (nn + (nn % 2)) * 8  # the basis values of all (N+1)^2 modes (the kernels hold the N^2 below the last shell)
+    psi = nn * (nn + (nn % 2)) * 8
     grid3 = 3 * B * B * 8
     y = 4 * nn * 8 + grid3  # (e, u, B) of one element
     blk = lambda bs, nt: (bs // nt) * nt / bs
     nt = max(nn, A * A)
+    # elements of a tile of the reconstructions, faces of one of the two sensors' tiles
+    te = (4 if k == 2 or k >= 5 else 5) * (5 if k == 3 else 4)
+    waves = lambda t: -(-t // 64) * 64
+    faces = lambda c, tx, ty: c * ((tx + 1) * ty + tx * (ty + 1)) / 256
     return [
         (0, "hydro stage (L_E + SSP combine + statistics)", "k_hydro_stage<", "hydro.hip",
-         (8.0 / 3.0) * 5 * nn * 8 + 15 * 8, stage_flops(1, NP), blk(128, nn)),
+         (8.0 / 3.0) * 5 * nn * 8 + 15 * 8, stage_flops(1, NP), blk(64, NP)),
         (1, "hydro stage map (OE + PP)", "k_hydro_oe_pp<", "hydro.hip",
-         2 * 5 * nn * 8 + 5 * nn * 8 / 6.0 + 49, oe_pp_flops(1, NP), blk(128, nn)),
+         2 * 5 * nn * 8 + 5 * nn * 8 / 6.0 + 49 + NP * 8, oe_pp_flops(1, NP) - sensor_flops(1, NP), 5 * 24 / 128),
+        (8, "hydro OE sensor", "k_hydro_sensor<", "hydro.hip",
+         5 * nn * 8 + 15 * 8 + NP * 8, sensor_flops(1, NP), faces(5, 5, 4)),
         (2, "magnetic update (curl, Lorentz, Ohm, SSP combine)", "k_mag_update<", "magnetic.hip",
          2 * grid3 + nn * 8 + 8 + y + (2.0 / 3.0) * y + y + 9 * 8, None, blk(256, nt)),
         (3, "velocity-OE projection", "k_vel_proj<", "magnetic.hip",
          psi + 3 * nn * 8 + 2 * nn * 8 + NP * 8 + 4 * nn * 8, None, blk(128, nn)),
         (4, "velocity-OE preparation (Gram, Cholesky, basis)", "k_vel_prep<", "magnetic.hip",
          nn * 8 + psi, None, blk(256, nn)),
-        (5, "E reconstruction", "k_E<", "magnetic.hip", 3 * nn * 8 + 3 * grid3 + 8, None, 1.0),
-        (6, "velocity-OE sensor", "k_vel_sensor<", "magnetic.hip", 4 * nn * 8 + grid3 + NP * 8, None, blk(256, nn)),
-        (7, "J reconstruction", "k_J<", "magnetic.hip", 2 * grid3, None, 1.0),
+        (5, "E reconstruction", "k_E<", "magnetic.hip", 3 * nn * 8 + 3 * grid3 + 8, None,
+         (A + B) * te / (waves(A * te) + waves(B * te))),
+        (6, "velocity-OE sensor", "k_vel_sensor<", "magnetic.hip", 4 * nn * 8 + grid3 + NP * 8, None,
+         faces(3, 5, 5 if N < 6 else 4)),
+        (7, "J reconstruction", "k_J<", "magnetic.hip", 2 * grid3, None, (A + B) * te / (waves(A * te) + waves(B * te))),
         (9, "A.R. traces", "k_ar_traces<", "magnetic.hip", 4 * nn * 8 + grid3 + (8 * A + 2) * 8, None, blk(256, nn)),
     ]
+
+
+def kernel_bytes(row, N):
+    """Bytes per element and launch that a kernel of kernel_table must touch.  The velocity-OE basis table holds the N^2
+    modes of the shells below the last one (rows padded to an even length), not all (N+1)^2."""
+    nn = (N + 1) ** 2
+    full, held = nn + nn % 2, N * N + (N * N) % 2
+    return row[4] - (nn * (full - held) * 8 if row[2] in ("k_vel_proj<", "k_vel_prep<") else 0)
 
 
 def source_sha(fname):
@@ -89,7 +106,7 @@ def ingest_counters(dirs, K=1048576, N=4, k=3, steps=1):
     SQ_WAVES).  FETCH_SIZE and WRITE_SIZE are scaled by what they read for the entry snapshot kernel,
     which copies the state (K (5 (N+1)^2 + 3 (k+1)^2) doubles) once: known bytes over counter value.  FP64 flops per
     launch are SQ_INSTS_VALU_FLOPS_FP64 (2 FMA + ADD + MUL + TRANS FP64 instructions per wave) times 64
-    lanes times the fraction of a block's lanes that carry work."""
+    lanes times the fraction of a block's lanes that carry work in its main phase."""
     import csv
     import glob
     vals = {}  # counter -> kernel prefix -> [values per dispatch]
@@ -114,7 +131,9 @@ def ingest_counters(dirs, K=1048576, N=4, k=3, steps=1):
                         for c, d in (("FETCH_SIZE", "pmcF"), ("WRITE_SIZE", "pmcW"),
                                      ("SQ_WAVES SQ_INSTS_VALU SQ_INSTS_VALU_FLOPS_FP64", "pmcV"))],
            "kernels": {}}
-    for kid, name, prefix, fname, bytes_el, flops_el, lanes in kernel_table(N, k):
+    for row in kernel_table(N, k):
+        kid, name, prefix, fname, _, flops_el, lanes = row
+        bytes_el = kernel_bytes(row, N)
         f = vals.get("FETCH_SIZE", {}).get(prefix)
         w = vals.get("WRITE_SIZE", {}).get(prefix)
         if not f or not w:
@@ -169,16 +188,19 @@ def stage_flops(K, NP):
     return K * (20 * nn + 74 * nn * (NP - 1) + 50 * 2 * NP + 15 * 4 * NP + 25 * nn + 20 * nn)
 
 
+def sensor_flops(K, NP):
+    """The hydro OE sensor's share of oe_pp_flops: the derivative traces and jumps, the sigma terms, the damping."""
+    return K * (10 * NP * (4 * NP * NP + 3 * NP) + 10 * NP * (NP + 4) + 4 * NP)
+
+
 def oe_pp_flops(K, NP):
-    """Algorithmic FP64 flops of one stage-map launch, per element: the derivative traces of
-    both sides of one face per direction, line and component (2 (N+1) dot products of length
+    """Algorithmic FP64 flops of the two launches of a stage map (OE sensor, then the map), per element: the derivative
+    traces of both sides of one face per direction, line and component (2 (N+1) dot products of length
     N+1) with the weighted squared jumps (3 per order); the per-order sums and sigma terms; the
     forward and inverse two-dimensional Legendre transforms (two passes each, 2 (N+1)^3 flops
     per pass and component); the shell damping; the positivity scaling, 30 per node."""
     nn = NP * NP
-    jumps = 10 * NP * (4 * NP * NP + 3 * NP)
-    sigma = 10 * NP * (NP + 4)
-    return K * (jumps + sigma + 40 * NP ** 3 + 5 * nn + 4 * NP + 30 * nn)
+    return sensor_flops(K, NP) + K * (40 * NP ** 3 + 5 * nn + 30 * nn)
 
 
 def valu_object(flops_alg, flops_ctr, avg_ms):
@@ -206,8 +228,8 @@ def traffic_rate(traffic, avg_ms):
 
 
 def oe_pp_bytes(K, nn):
-    """Algorithmic HBM bytes of one stage-map launch, averaged over the six launches of a Strang
-    step: the raw stage read and the limited stage written (one U each), the six element
+    """Algorithmic HBM bytes of one stage-map launch without the sensor's factors, averaged over the six launches of a
+    Strang step: the raw stage read and the limited stage written (one U each), the six element
     statistics it uses read and its decision flag written; the last launch of the first hydro
     half-step also writes the primitive copy (rho, e, u) for the magnetic substep."""
     u = 5 * K * nn * 8
@@ -552,10 +574,15 @@ def main():
     ms_per_step = 1e3 * t / args.steps
     value = K * nn * 9 / (t / args.steps)
     kernels = []
-    for kid, name, prefix, fname, bytes_el, flops_el, lanes in kernel_table(N, k):
-        launches, kms = S.timing_read(kid)
+    timed = {row[0]: S.timing_read(row[0]) for row in kernel_table(N, k)}
+    for row in kernel_table(N, k):
+        kid, name, prefix, fname, _, flops_el, lanes = row
+        launches, kms = timed[kid]
         if launches == 0:
             continue
+        if kid == 1:  # the stage map's time includes its sensor's, which has a row of its own
+            kms -= timed[8][1]
+        bytes_el = kernel_bytes(row, N)
         avg = kms / launches
         ach = K * bytes_el / (avg * 1e-3) / 1e9
         rec = counter_record(prefix, fname, K, N)

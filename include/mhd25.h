@@ -237,9 +237,9 @@ int mhd25_rhs_magnetic_vjp(mhd25_ctx* ctx, const double* rho, const double* u, c
 /* Kernel timing on the context stream with HIP events (off by default).  Kernel ids: 0 the hydro
  * stage kernel (L_E + SSP combine + statistics), 1 the hydro stage map (OE sensor, OE + PP), 2 the
  * magnetic update, 3 the velocity-OE projection, 4 the velocity-OE preparation, 5 the E
- * reconstruction, 6 the velocity-OE sensor, 7 the J reconstruction, 8 none (no launches), 9 the A.R.
- * traces.  mhd25_timing_read returns the launches and summed ms of one kernel since its last read
- * and resets them; another id or a NULL pointer returns -1. */
+ * reconstruction, 6 the velocity-OE sensor, 7 the J reconstruction, 8 the hydro OE sensor where it
+ * is a launch of its own (part of 1), 9 the A.R. traces.  mhd25_timing_read returns the launches and
+ * summed ms of one kernel since its last read and resets them; another id or a NULL pointer returns -1. */
 int mhd25_timing_enable(mhd25_ctx* ctx, int32_t on);
 int mhd25_timing_read(mhd25_ctx* ctx, int32_t kernel_id, int64_t* launches, double* total_ms);
 

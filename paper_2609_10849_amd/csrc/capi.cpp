@@ -59,9 +59,10 @@ static hipError_t timing_fold(mhd25_ctx* c) {
   return hipSuccess;
 }
 
-// next free (start, stop) event pair for a launch of kernel kid; a full pool is folded first
-hipEvent_t* timing_slot(mhd25_ctx* c, int kid) {
-  if ((size_t)(c->ev_used + 2) > c->ev_pool.size()) {
+// next free (start, stop) event pair for a launch of kernel kid; a pool without room for it and `inner` pairs that
+// open before its stop event is recorded is folded first
+hipEvent_t* timing_slot(mhd25_ctx* c, int kid, int inner) {
+  if ((size_t)(c->ev_used + 2 + 2 * inner) > c->ev_pool.size()) {
     (void)timing_fold(c);
     if (c->ev_pool.empty()) {
       c->ev_pool.resize(2048);

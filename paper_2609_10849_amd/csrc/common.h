@@ -209,7 +209,7 @@ struct mhd25_ctx {
   long launch_elements;  // that a launch over this mesh covers: its own, or in a batch those of its degree group
   int hydro_bs;  // threads per block of the hydro stage kernel (128 or 256; tuned)
   std::vector<hipEvent_t> ev_pool;  // pairs (start, stop) of timed launches
-  std::vector<int> ev_kid;          // kernel id of each pair (0 hydro stage, 1 stage map)
+  std::vector<int> ev_kid;          // kernel id of each pair (see mhd25_timing_read)
   int ev_used;
   long long t_launch[16];  // per timed kernel id (see mhd25_timing_read)
   double t_ms[16];

@@ -1604,7 +1604,7 @@ __global__ void k_copy(const double* __restrict__ a, double* __restrict__ b, lon
   switch (p) { case 1: F(1); break; case 2: F(2); break; case 3: F(3); break; \
                case 4: F(4); break; case 5: F(5); break; case 6: F(6); break; default: return -4; }
 
-hipEvent_t* timing_slot(mhd25_ctx* c, int kid);
+hipEvent_t* timing_slot(mhd25_ctx* c, int kid, int inner = 0);
 static int eb_of(int p) { return 256 / ((p + 1) * (p + 1)); }
 // Small meshes, by the elements of a launch (five for every compute unit).  The stage: at 32^2 elements the node form takes
 // 7.1 (N = 3), 8.7, 10.0, 11.2 us (6) and the line form 7.9, 9.7, 12.2, 17.6; at 40^2 they are 8.1, 9.8, 12.1, 14.6
@@ -1738,7 +1738,7 @@ int hydro_stage_b(mhd25_ctx* c, const double* Ust, double* Uout, double tau, con
                                c->opt.oe_hydro, c->opt.pp, rho_o, e_o, u_o});
     return 0;
   }
-  hipEvent_t* ev = c->timing ? timing_slot(c, 1) : nullptr;
+  hipEvent_t* ev = c->timing ? timing_slot(c, 1, 1) : nullptr;
   if (ev) hipEventRecord(ev[0], c->stream);
   if (one) {
 #define LM(P) hipLaunchKernelGGL((k_hydro_map_lines<P>), dim3(lblocks), dim3(ML_BS), 0, c->stream, Ust, Uout, c->stats, \
@@ -1750,10 +1750,13 @@ int hydro_stage_b(mhd25_ctx* c, const double* Ust, double* Uout, double tau, con
     return check(c, hipGetLastError(), "stage map launch");
   }
   if (c->opt.oe_hydro) {
+    hipEvent_t* sev = c->timing ? timing_slot(c, 8) : nullptr;
+    if (sev) hipEventRecord(sev[0], c->stream);
 #define LS(P) hipLaunchKernelGGL((k_hydro_sensor<P>), dim3(sblocks), dim3(HS<P>::BS), 0, c->stream, Ust, c->stats, c->lines, \
                                  c->glob, c->dfac, flag, c->d_ht, c->mp, tau, c->opt.s_H)
     DISPATCH_P(c->p, LS);
 #undef LS
+    if (sev) hipEventRecord(sev[1], c->stream);
   }
 #define LB(P) hipLaunchKernelGGL((k_hydro_oe_pp<P>), dim3(blocks), dim3(OM<P>::BS), 0, c->stream, Ust, Uout, c->stats, \
                                  c->dfac, c->d_flags, c->d_counts, flag, c->d_ht, c->mp, c->opt.oe_hydro, c->opt.pp, rho_o, \

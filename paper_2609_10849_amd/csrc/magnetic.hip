@@ -1880,7 +1880,7 @@ static int chk(mhd25_ctx* c, const char* what) {
   return 0;
 }
 
-hipEvent_t* timing_slot(mhd25_ctx* c, int kid);
+hipEvent_t* timing_slot(mhd25_ctx* c, int kid, int inner = 0);
 // HIP-event timing of one launch (kernel id kid) when the context's timing is on
 #define T_BEGIN(kid)                                                   \
   hipEvent_t* ev_ = c->timing ? timing_slot(c, kid) : nullptr;         \
