@@ -486,6 +486,14 @@ static bool batch_args_ok(const mhd25_batch* b, double* const* U, double* const*
   return true;
 }
 
+// while it lives a run of the batch is launched alone, in the forms that its own mesh takes
+struct Alone {
+  mhd25_ctx* c;
+  const long group;
+  explicit Alone(mhd25_ctx* ctx) : c(ctx), group(ctx->launch_elements) { c->launch_elements = c->mp.K; }
+  ~Alone() { c->launch_elements = group; }
+};
+
 // After the runs' deferred steps are on the caller's stream: one small copy returns every run's
 // failure word, limiter counters and A.R. maximum; a run that needed a halving is restored from
 // its entry snapshot and re-done with the ordinary reject-and-halve step.
@@ -506,6 +514,7 @@ static int finish_step(mhd25_batch* b, double* const* U, double* const* Bx, doub
       BTRY(dcopy(c, c->snapU, U[r], 5 * KN));
       BTRY(dcopy(c, c->saveB, Bx[r], G)); BTRY(dcopy(c, c->saveB + G, By[r], G));
       BTRY(dcopy(c, c->saveB + 2 * G, Bz[r], G));
+      const Alone alone(c);
       int s = mhd25_strang_step(c, U[r], Bx[r], By[r], Bz[r], dt[r], &one);
       if (s && !status) status = s;
     } else {
@@ -555,6 +564,7 @@ int mhd25_batch_strang_step_sequential(mhd25_batch* b, double* const* U, double*
   int status = 0;
   for (int r = 0; r < b->nruns; ++r) {
     mhd25_report one;
+    const Alone alone(b->ctx[r]);
     int s = mhd25_strang_step(b->ctx[r], U[r], Bx[r], By[r], Bz[r], dt[r], &one);
     if (s < 0) return s;
     if (s && !status) status = s;

@@ -233,4 +233,11 @@ def test_gpu_batch_of_small_and_large_runs(p):
         for got, want in zip(bat, alone):
             for a, r in zip(got, want):
                 assert (host(a) == r).all(), (graph, tuned)
+    bat = [[dev(a) for a in st] for _, st in runs]
+    args = [[x[i] for x in bat] for i in range(4)]
+    for k, how in enumerate(("sequential", "streams")):  # in the forms of each mesh, then of the group
+        assert B.strang_step(*args, dts, **{how: True})[0] == max(s[k] for s in status)
+    for got, want in zip(bat, alone):
+        for a, r in zip(got, want):
+            assert (host(a) == r).all()
     B.close()
