@@ -132,10 +132,11 @@ int mhd25_rhs_magnetic(mhd25_ctx* ctx, const double* rho, const double* u, const
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): mhd25_rhs_magnetic with the same arguments, kernels
- * and results, whose workspace (the six reconstructed J, E grids and the per-element loads) is a
+ * and results, whose workspace (the six reconstructed J, E grids) is in a
  * fixed file-scope device array of 32 MiB per device instead of the context's workspace.  The
- * call allocates nothing (its address is resolved once per device by mhd25_init).  The mesh must
- * need at most 32 MiB: 8 (6 G + K (2 (m+2)(m+1) + (m+2)^2)) bytes with G = K (m+1)^2 (up to
+ * call allocates nothing (its address is resolved once per device by mhd25_init).  The mesh may have
+ * 8 (6 G + K (2 (m+2)(m+1) + (m+2)^2)) <= 32 MiB with G = K (m+1)^2, the grids and as much as
+ * element loads of them would take (up to
  * 211 x 211 elements at m = 2, 161 x 161 at m = 3); larger meshes return -1 before any device
  * work.  Every call on a device shares that device's array: calls that overlap on one device
  * (different streams, threads or contexts) race and must be serialised by the caller.  No

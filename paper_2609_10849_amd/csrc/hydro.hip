@@ -25,7 +25,7 @@ constexpr double EPSM = 2.220446049250313e-16;  // 2^-52
 
 template <int P, int BS = 256>
 struct Cfg {
-  static constexpr int NP = P + 1, NN = NP * NP, EB = BS / NN, NT = EB * NN, ND = NP / 2;
+  static constexpr int NP = P + 1, NN = NP * NP, EB = BS / NN, NT = EB * NN;
 };
 
 // node values of the EC flux: density, half velocities (normal to the line's direction first) and the
@@ -38,8 +38,8 @@ struct Prim {
 // f = (aR - aL) / (aR + aL) and z = f^2 the mean is (aL + aR)/2 G(z), G(z) = f / atanh f, and its reciprocal
 // 2/(aL + aR) H(z), H(z) = atanh f / f = 1 + z/3 + z^2/5 + ...; G's coefficients are those of 1/H.  Both
 // series are summed to z^7: for |f| <= LM_NEAR = 0.1 (values within 22 % of each other) the first omitted
-// term is below 2e-18 relative.  The coefficients come from the tables, as scalars (as literals each
-// costs two register moves).
+// term is below 1.2e-18 (G) and 6e-18 (H) relative.  The coefficients come from the tables, as scalars (as
+// literals each costs two register moves).
 constexpr double LM_NEAR = 0.1;
 __device__ __forceinline__ double lm_series(const double* __restrict__ c, double z) {
   double s = c[LM_N - 1];
@@ -219,15 +219,17 @@ struct SC {
 
 // MODE 0: out = L_E(Us).  MODE 1: out = ca*Un + cb*(Us + tau*L_E(Us)) plus element statistics.
 //
-// Phases: (1) per node, the values of the EC flux into LDS, and whether the block needs logarithms; (2) per
+// Phases: (1) per node, the values of the EC flux into LDS, and which lines need logarithms; (2) per
 // line, its two interface fluxes and its p(p+1)/2 pair fluxes, the coefficients as scalars and the
 // residual of the line in registers; (3) the x lines' residuals into LDS over the node values, the y
 // lines' added; (4) per node, the SSP combine; (5) per element and component, the statistics.
 // A thread per node instead (each pair's second half through LDS, coefficients and partners by run-time
 // index, two logarithms per node) issued 4.3e8 VALU instructions a launch at 1024^2, N = 4 and was bound
 // by that: 1.02 ms.  This form issues 2.2e8, takes 0.82 ms and moves 4.1 GB (5 TB/s, a large copy's
-// rate); at 512^2, N = 3 0.160 -> 0.131 ms, at 256^2, N = 2 31.5 -> 21.8 us.  Four waves per SIMD: at three
-// it takes 0.87 ms.
+// rate), 1.4 times its arrays, the excess all reads (U_s is read twice, and its face nodes by the neighbours); at
+// 512^2, N = 3 0.160 -> 0.131 ms, at 256^2, N = 2 31.5 -> 21.8 us.  Four waves per SIMD: at three it takes 0.87 ms.
+// N = 4 fits 117 registers, with 36 bytes of scratch a lane and 6 spilled scalars; N = 5 and 6 need 133 and 145 (three
+// waves), the same scratch and 22 and 34 spilled scalars.
 template <int P, int MODE, int BS>
 __device__ __forceinline__ void hydro_stage_body(const double* __restrict__ Us, const double* __restrict__ Un,
                                                     double* __restrict__ out, double* __restrict__ stats,
@@ -879,6 +881,9 @@ struct OM {
 // and the damping are straight-line code with the 1D tables as scalars.  The
 // element statistics of the raw stage (always formed before this map) give the element averages: the map
 // keeps each element's mean, the (0, 0) Legendre mode.  Bound by HBM: 2.4 GB in 0.46 ms at 1024^2, N = 4.
+// All modes are transformed, also where nothing is damped: D_p U plus the others' (D_l - D_p) takes the same time, and with it
+// ||div B|| at the end of the rotor run, a quantity of round-off alone, comes out 20 % below the published value that
+// its test holds within 5 %.
 //
 // One kernel for sensor and map, with a thread per element line and component that formed its neighbours'
 // traces too, was bound by VALU issue and LDS alike (4.5e8 VALU instructions, 4.5e8 LDS cycles): 1.23 ms at

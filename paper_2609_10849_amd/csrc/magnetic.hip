@@ -133,6 +133,9 @@ struct RowTask {
 
 // J: int B_x d_y phi - B_y d_x phi with the (m+2)-point Gauss rule (z), int B_z (-d_y psi) and int B_z d_x psi
 // with the (m+1)-point rule (x, y), each as one operator per direction.
+// The mass matrix's rows are summed from the diagonal on.  The order is one of rounding, but J of a uniform field is
+// rounding alone, and so is ||div B|| at the end of the rotor run, which its test holds to the published 4.60e-12 within
+// 5 %: this order gives 0.96 and 0.97 of it (without and with A.R.), the plain one 0.94, the reversed 1.33, even then odd terms 1.43.
 // Measured: 1024^2, N = 4, k = 3: 0.66 (load kernel and gather) -> 0.29 ms; 128^2, N = k = 4: 28 -> 13 us.  Bound by the
 // latency of its staging loads and barriers (1.3 GB moved).
 template <int M, bool R2, int S>
@@ -196,7 +199,7 @@ __device__ __forceinline__ void J_body(const double* __restrict__ Bx, const doub
     for (int i = 0; i < B; ++i) {
       double s = 0.0, t = 0.0;
 #pragma unroll
-      for (int q = 0; q < A; ++q) s = fma(T->RWQ[i][(i + q) % A], c[(i + q) % A], s);  // the diagonal, its largest term, first
+      for (int q = 0; q < A; ++q) s = fma(T->RWQ[i][(i + q) % A], c[(i + q) % A], s);
 #pragma unroll
       for (int q = 0; q < B; ++q) t = fma(T->RDG[i][q], d[q], t);
       if (i == 0) {
@@ -2339,7 +2342,7 @@ int magnetic_rt_launch(const RtRecord& h, const void* dargs, const int* dboff, i
 
 // ---------------------------------------------------------------------------------------------
 // Allocation-free magnetic residual: the same kernels as mhd25_rhs_magnetic, with the
-// reconstructed J, E grids and the per-element loads in a fixed file-scope device array instead
+// reconstructed J, E grids in a fixed file-scope device array instead
 // of the context's workspace, for callers that cannot allocate device memory.
 // ---------------------------------------------------------------------------------------------
 namespace {
@@ -2375,6 +2378,8 @@ extern "C" int mhd25_rhs_magnetic_noalloc(mhd25_ctx* c, const double* rho, const
                                           double* du, double* dBx, double* dBy, double* dBz) {
   if (!c || !rho || !u || !Bx || !By || !Bz || !de || !du || !dBx || !dBy || !dBz) return -1;
   const long K = c->mp.K, G = c->G;
+  // the documented limit: the grids, and room for the element loads of W, N_x and N_y (no kernel writes those any
+  // more; the accepted meshes stay what they were)
   const long a = c->m + 2, b = c->m + 1;
   const long need = 6 * G + K * (2 * a * b + a * a);
   if (need > MHD_NOALLOC_DOUBLES) {

@@ -32,7 +32,9 @@ __device__ __forceinline__ Pr prim_of(const double U[5], double g) {
   return q;
 }
 
-// value and partial derivatives of the logarithmic mean (same branch rule as the forward)
+// Value and partial derivatives of the logarithmic mean: a series in f = (aR - aL) / (aR + aL) for |f| < 0.01, the
+// logarithms beyond.  The forward takes a longer series up to |f| = 0.1, line by line; on either side both are the
+// mean to rounding, so the reverse keeps its own rule.
 __device__ __forceinline__ void lmean_d(double aL, double aR, double lL, double lR, double& v, double& gL, double& gR) {
   const double d = aR - aL, s = aR + aL;
   if (d * d < 1e-4 * (s * s)) {

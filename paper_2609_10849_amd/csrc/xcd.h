@@ -28,8 +28,8 @@ __device__ __forceinline__ void tile_of(int b, int ntx, int nty, int& tx, int& t
 // ranges; boff[r] is the first block of run r and boff[nr] the grid size.  Returns the run of the
 // calling block (the same for all its threads) by bisection.  The result is declared wave-uniform
 // (readfirstlane), so that the run's argument struct is fetched with scalar loads into scalar
-// registers; otherwise its pointers and constants occupy vector registers in every lane (the OE/PP
-// map went from 95 to 177 VGPRs, 5 to 2 waves per SIMD).
+// registers; a compiler that did not find that by itself would keep its pointers and constants in vector
+// registers of every lane (ROCm 7.2's finds it for the kernels here: their registers are the same without).
 __device__ __forceinline__ int rt_run(const int* __restrict__ boff, int nr) {
   const int b = (int)blockIdx.x;
   int lo = 0, hi = nr;  // boff[lo] <= b < boff[hi]
@@ -44,8 +44,9 @@ __device__ __forceinline__ int rt_run(const int* __restrict__ boff, int nr) {
 // Run-table argument structs hold their array pointers as plain (generic) pointers.  Read through
 // gl() they are loaded as global-memory pointers, so that a kernel body inlined into a run-table
 // kernel addresses its arrays with global rather than flat memory instructions, as it does with
-// kernel arguments (with flat ones the OE/PP map needed 192 VGPRs instead of 107: 2 waves per
-// SIMD instead of 4).  Fields that are not pointers pass through unchanged.
+// kernel arguments (at N = 4, k = 3 with flat ones the J reconstruction needs 112 VGPRs instead of 80, 4 waves per SIMD
+// instead of 6, the line-task map 157 instead of 124, 3 instead of 4).  Fields that are not pointers pass through
+// unchanged.
 #ifndef MHD_GLOBAL_AS
 #define MHD_GLOBAL_AS __attribute__((address_space(1)))
 #endif
