@@ -225,7 +225,7 @@ struct SC {
 // lines' added; (4) per node, the SSP combine; (5) per element and component, the statistics.
 // A thread per node instead (each pair's second half through LDS, coefficients and partners by run-time
 // index, two logarithms per node) issued 4.3e8 VALU instructions a launch at 1024^2, N = 4 and was bound
-// by that: 1.02 ms.  This form issues 2.2e8, takes 0.82 ms and moves 4.1 GB (5 TB/s, a large copy's
+// by that: 1.02 ms.  This form issues 2.2e8, takes 0.82 ms and moves 4.2 GB (5 TB/s, a large copy's
 // rate), 1.4 times its arrays, the excess all reads (U_s is read twice, and its face nodes by the neighbours); at
 // 512^2, N = 3 0.160 -> 0.131 ms, at 256^2, N = 2 31.5 -> 21.8 us.  Four waves per SIMD: at three it takes 0.87 ms.
 // N = 4 fits 117 registers, with 36 bytes of scratch a lane and 6 spilled scalars; N = 5 and 6 need 133 and 145 (three
@@ -692,8 +692,8 @@ struct HS {
 
 // Hydro OE sensor (eq. euler-oe-amplitude .. eq. euler-oe-map): the shell damping factors D_l (l = 0..p) of every
 // element from the raw stage, Dfac[K][p+1].  Every face's jumps are formed once per tile, by a thread of
-// its own from LDS; only the squared sums are exchanged.  Bound by VALU issue (1.6e8 instructions at
-// 1024^2, N = 4) and its reads: 0.40 ms there (1.2 GB).
+// its own from LDS; only the squared sums are exchanged.  Bound by VALU issue (1.3e8 instructions at
+// 1024^2, N = 4) and its reads: 0.40 ms there (1.26 GB).
 template <int P>
 __device__ __forceinline__ void hydro_sensor_body(const double* __restrict__ Ust, const double* __restrict__ stats,
                                                   const double* __restrict__ lines, const double* __restrict__ glob,

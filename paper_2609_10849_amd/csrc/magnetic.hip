@@ -135,9 +135,10 @@ struct RowTask {
 // with the (m+1)-point rule (x, y), each as one operator per direction.
 // The mass matrix's rows are summed from the diagonal on.  The order is one of rounding, but J of a uniform field is
 // rounding alone, and so is ||div B|| at the end of the rotor run, which its test holds to the published 4.60e-12 within
-// 5 %: this order gives 0.96 and 0.97 of it (without and with A.R.), the plain one 0.94, the reversed 1.33, even then odd terms 1.43.
+// 5 %: this order gives 0.96 and 0.97 of it (without and with A.R.), the plain one 0.94, the reversed 1.33, even then
+// odd terms 1.43.
 // Measured: 1024^2, N = 4, k = 3: 0.66 (load kernel and gather) -> 0.29 ms; 128^2, N = k = 4: 28 -> 13 us.  Bound by the
-// latency of its staging loads and barriers (1.3 GB moved).
+// latency of its staging loads and barriers (0.84 GB moved).
 template <int M, bool R2, int S>
 __device__ __forceinline__ void J_body(const double* __restrict__ Bx, const double* __restrict__ By,
                                        const double* __restrict__ Bz, double* __restrict__ Jx, double* __restrict__ Jy,
@@ -266,7 +267,8 @@ __device__ __forceinline__ double add_eta(double eta, double j, double e) { retu
 // plus eta_K sum_q M_q J(x_q) . phi_a(x_q) by the degree-p GLL rule, i.e. the 1D operators RWP / RGP applied
 // to J; blocks whose elements all have eta = 0 skip that term.
 // Measured: 1024^2, N = 4, k = 3, with resistivity: 1.08 (load kernel and gather) -> 0.55 ms; 128^2, N = k = 4, without:
-// 36 -> 17.5 us.  Bound by LDS reads and latency (2.0 GB moved).
+// 36 -> 17.5 us.  Bound by LDS reads and latency (1.5 GB moved where few elements are
+// resistive).
 template <int P, int M, bool R2, int S>
 __device__ __forceinline__ void E_body(const double* __restrict__ u, const double* __restrict__ Bx,
                                        const double* __restrict__ By, const double* __restrict__ Bz,
@@ -578,7 +580,7 @@ __global__ __launch_bounds__((RT<M, R2, S>::BS)) void k_E_rt(const E_args* __res
 
 // One thread per node, EB elements per block.  Bound by the latency of its loads and barriers: the block's
 // tables and all node values are loaded before the first is stored to LDS (a table at a time and in loops per
-// array, each waited for its loads: 1.35 -> 1.06 ms at 1024^2, N = 4, k = 3 (4.8 GB); 44 -> 35 us at 256^2,
+// array, each waited for its loads: 1.35 -> 1.06 ms at 1024^2, N = 4, k = 3 (4.5 GB); 44 -> 35 us at 256^2,
 // N = k = 2; 92 -> 81 us at 241 x 137, N = 5, k = 4; 200 -> 187 us at 512^2, N = 4, 2D2V).
 // (the 2D2V variants up to N = 4 fit 72 VGPRs, i.e. 7 waves per SIMD, without spills; the bound
 // keeps the compiler there)
@@ -1144,7 +1146,7 @@ struct VS {
 // Velocity-OE sensor (eq. magnetic-oe-sensor, eq. magnetic-oe-rate, eq. magnetic-oe-factor): the element's
 // damping factors D_l (l = 0..p), Dfac[K][p+1].  Every face's jumps are formed once per tile from LDS.  u is
 // only read here (the projection kernel that updates it runs afterwards).  Measured, against a thread per
-// node with the neighbours staged per element: 0.98 -> 0.52 ms at 1024^2, N = 4, k = 3 (1.24 GB), 61 -> 37 us
+// node with the neighbours staged per element: 0.98 -> 0.52 ms at 1024^2, N = 4, k = 3 (1.31 GB), 61 -> 37 us
 // at 241 x 137, N = 5, 32 -> 17 us at 256^2, N = 2.  Bound by VALU issue and the latency of its staging loads.
 template <int P, int M, bool R2, int S>
 __device__ __forceinline__ void vel_sensor_body(const double* __restrict__ rho, const double* __restrict__ u,
@@ -1377,9 +1379,9 @@ __global__ __launch_bounds__((VS<P, M, R2, S>::BS)) void k_vel_sensor_rt(const v
 // Velocity-OE map (eq. magnetic-oe-map) with the prepared basis, EB elements per block.  The block's
 // basis tables (the p^2 modes of the shells 0..p-1) are copied to LDS first (all of a thread's 16-byte
 // loads are issued before the first store; rows keep an odd LDS stride), so the basis is read from
-// HBM once (5.1 GB at 1024^2, N = 4 in 0.985 ms: 5.2 TB/s, a large copy's rate).  Then the coefficients c_k = (u_d, psi_k)_rho (task = element and mode) and the shells'
-// parts at the nodes (thread = node) are formed, the last shell's part as what the others leave of
-// u, and u and e are updated in place.
+// HBM once (5.5 GB, 4.6 of them read, at 1024^2, N = 4 in 0.995 ms: 5.5 TB/s).  Then the coefficients
+// c_k = (u_d, psi_k)_rho (task = element and mode) and the shells' parts at the nodes (thread = node) are
+// formed, the last shell's part as what the others leave of u, and u and e are updated in place.
 template <int P, int BS>
 struct VPJ {
   static constexpr int NP = P + 1, NN = NP * NP, NK = psi_modes(P), EB = BS / NN, NKP = NK | 1;
